@@ -49,6 +49,16 @@ int launch_ffn_gemm(const void* x, int rows, int k, int H, int I, int P, const i
                     const int32_t* por, const void* w13, const void* w2, void* act, void* y, int32_t* plan, hipStream_t st);
 
 
+// ffn_f32.hip: the fp32 path (both products; S shared experts' slots behind the P routed ones, or none).
+int launch_ffn_f32(const void* x, int T, int k, int H, int I, int P, int S, const int32_t* counts, const int32_t* offsets,
+                   const int32_t* por, const void* w13, const void* w2, const void* w13_sh, const void* w2_sh, void* act, void* y,
+                   hipStream_t st);
+
+// ffn.hip: moe_grouped_ffn's fp32 path with shared experts, workspace checked as in the public calls.
+int grouped_ffn_f32(const void* x, int T, int k, int H, int I, int P, int S, const int32_t* counts, const int32_t* offsets,
+                    const int32_t* pair_of_row, const void* w13, const void* w2, const void* w13_shared, const void* w2_shared,
+                    void* y, void* ws, size_t ws_bytes, void* stream);
+
 // ffn_ws.hip: weight-stationary streaming path of moe_grouped_ffn (bf16; weights and gathered token
 // rows both reach LDS by LDS-direct loads, persistent workgroups pull items from per-XCD work
 // lists).  nf = 32-token fragments per row chunk (1, 2, 4 or 8).

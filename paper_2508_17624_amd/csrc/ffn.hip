@@ -177,50 +177,6 @@ __global__ __launch_bounds__(512) void k_ffn_stream(StreamArgs a) {
 }
 
 // ------------------------------------------------------------------------------------------
-// fp32 reference-precision path (tiny configurations): one thread per output element.
-__device__ __forceinline__ int slot_of_row(const int32_t* __restrict__ offsets, int P, int row) {
-  int lo = 0, hi = P;  // largest s with offsets[s] <= row and offsets[s+1] > row
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (offsets[mid] <= row) lo = mid; else hi = mid;
-  }
-  return lo;
-}
-
-__global__ __launch_bounds__(256) void k_ffn_f32_gateup(const float* __restrict__ x, const int32_t* __restrict__ offsets,
-                                                        const int32_t* __restrict__ por, const float* __restrict__ w13,
-                                                        int rows, int k, int H, int I, int P, float* __restrict__ act) {
-  const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (long long)rows * I) return;
-  const int row = (int)(idx / I), i = (int)(idx - (long long)row * I);
-  const int s = slot_of_row(offsets, P, row);
-  const int t = (por ? por[row] : row) / k;
-  const float* xr = x + (size_t)t * H;
-  const float* wg = w13 + ((size_t)s * 2 * I + i) * H;
-  const float* wu = wg + (size_t)I * H;
-  float g = 0.f, u = 0.f;
-  for (int h = 0; h < H; ++h) {
-    g = fmaf(xr[h], wg[h], g);
-    u = fmaf(xr[h], wu[h], u);
-  }
-  act[idx] = g / (1.f + expf(-g)) * u;
-}
-
-__global__ __launch_bounds__(256) void k_ffn_f32_down(const float* __restrict__ act, const int32_t* __restrict__ offsets,
-                                                      const float* __restrict__ w2, int rows, int H, int I, int P,
-                                                      float* __restrict__ y) {
-  const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (long long)rows * H) return;
-  const int row = (int)(idx / H), h = (int)(idx - (long long)row * H);
-  const int s = slot_of_row(offsets, P, row);
-  const float* ar = act + (size_t)row * I;
-  const float* wr = w2 + ((size_t)s * H + h) * I;
-  float acc = 0.f;
-  for (int i = 0; i < I; ++i) acc = fmaf(ar[i], wr[i], acc);
-  y[idx] = acc;
-}
-
-// ------------------------------------------------------------------------------------------
 // Tuning state (ew_tune_ffn); 0 = automatic everywhere except the wait, where negative = automatic.
 int g_path_override = 0;       // 1 = register-streaming kernel, 2 = tiled GEMM kernel, 3 = LDS-direct streaming kernel
 int g_nt_override = 0;         // register-streaming kernel: 16-token tiles per slot chunk (1 or 2)
@@ -327,16 +283,8 @@ int grouped_ffn(const char* who, bool plan_ready, const void* x, int dtype, int 
                              w2_shared, act, y_sorted, plan, wait_ticks, st);
   }
 
-  if (dtype == EW_F32) {
-    const long long n1 = (long long)rows * I, n2 = (long long)rows * H;
-    hipLaunchKernelGGL(k_ffn_f32_gateup, dim3((unsigned)((n1 + 255) / 256)), dim3(256), 0, st, (const float*)x, offsets,
-                       pair_of_row, (const float*)w13_base, rows, k, H, I, P, (float*)act);
-    EW_LAUNCH_CHECK("k_ffn_f32_gateup");
-    hipLaunchKernelGGL(k_ffn_f32_down, dim3((unsigned)((n2 + 255) / 256)), dim3(256), 0, st, (const float*)act, offsets,
-                       (const float*)w2_base, rows, H, I, P, (float*)y_sorted);
-    EW_LAUNCH_CHECK("k_ffn_f32_down");
-    return EW_OK;
-  }
+  if (dtype == EW_F32)
+    return ew::launch_ffn_f32(x, T, k, H, I, P, 0, counts, offsets, pair_of_row, w13_base, w2_base, nullptr, nullptr, act, y_sorted, st);
 
   if (H % 128 || I % 128) return fail(EW_ERR_UNSUPPORTED, "%s(bf16): H and I must be multiples of 128 (H=%d I=%d)", who, H, I);
   const int Kmax = H > I ? H : I;
@@ -384,6 +332,18 @@ int grouped_ffn(const char* who, bool plan_ready, const void* x, int dtype, int 
 }
 
 }  // namespace
+
+int ew::grouped_ffn_f32(const void* x, int T, int k, int H, int I, int P, int S, const int32_t* counts, const int32_t* offsets,
+                        const int32_t* pair_of_row, const void* w13, const void* w2, const void* w13_shared, const void* w2_shared,
+                        void* y, void* ws, size_t ws_bytes, void* stream) {
+  if (T == 0) return EW_OK;
+  if (!x || !counts || !offsets || !w13 || !w2 || !y || (S > 0 && (!w13_shared || !w2_shared)))
+    return fail(EW_ERR_INVALID_ARG, "grouped FFN (fp32): NULL device pointer");
+  const size_t need = moe_grouped_ffn_workspace_bytes(T, k + S, H, I, P + S, EW_F32);
+  if (!ws || ((uintptr_t)ws & 255) || ws_bytes < need)
+    return fail(EW_ERR_WORKSPACE, "grouped FFN (fp32): workspace needs %zu bytes aligned to 256 (got %zu at %p)", need, ws_bytes, ws);
+  return launch_ffn_f32(x, T, k, H, I, P, S, counts, offsets, pair_of_row, w13, w2, w13_shared, w2_shared, ws, y, (hipStream_t)stream);
+}
 
 extern "C" int moe_grouped_ffn(const void* x, int dtype, int T, int k, int H, int I, int P, const int32_t* counts,
                                const int32_t* offsets, const int32_t* pair_of_row, const void* w13_base,

@@ -564,3 +564,23 @@ def test_fused_entry_points_empty_batch_and_argument_errors(ew):
     assert lib.moe_unpermute_rmsnorm(dummy.data_ptr(), counts.data_ptr(), dummy.data_ptr(), None, 0, None, 1, k, H, B.EW_BF16,
                                      dummy.data_ptr(), 1e-6, dummy.data_ptr(), st) == -1   # normed_out must not be out
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("H,I", [(256, 128), (64, 48), (100, 36), (21, 7), (4, 1)], ids=["c0", "half-tile", "k-tail", "unaligned", "smallest"])
+def test_grouped_ffn_f32_tile_edges(ew, H, I):
+    """fp32 products at the edges of their 16-feature x 32-row tiles and 16-element steps: row counts around one and two
+    row tiles, empty slots between them, contractions that end inside a step, rows without 16-byte alignment."""
+    rng = np.random.default_rng(H * 10 + I)
+    counts = np.array([0, 1, 15, 16, 17, 0, 31, 32, 33, 64, 65, 200, 0], np.int32)
+    P, rows = len(counts), int(counts.sum())
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    por = rng.permutation(rows).astype(np.int32)
+    x = rng.standard_normal((rows, H), dtype=np.float32)
+    w13 = rng.standard_normal((P, 2 * I, H), dtype=np.float32) * np.float32(0.1)
+    w2 = rng.standard_normal((P, H, I), dtype=np.float32) * np.float32(0.1)
+    w13[counts == 0], w2[counts == 0] = np.nan, np.nan
+    dev = lambda a: torch.from_numpy(a).cuda()
+    got = to_f64(ew.moe_grouped_ffn(dev(x), 1, I, P, dev(counts), dev(offsets), dev(por), dev(w13), dev(w2), num_rows=rows))
+    for s in np.nonzero(counts)[0]:
+        r0, r1 = offsets[s], offsets[s + 1]
+        assert rel_l2(got[r0:r1], moe.expert_ffn(x[por[r0:r1]], w13[s], w2[s])) <= 1e-5, f"slot {s}"
