@@ -357,6 +357,46 @@ int moe_unpermute_rmsnorm(const void* y_sorted, const int32_t* row_of_pair, cons
                           const void* shared_out, int num_shared, const void* residual, int T, int k,
                           int H, int dtype, void* out, float eps, void* normed_out, void* stream);
 
+/* A whole layer pass in one call: moe_gate_logits (unless logits are given) ->
+ * moe_route_reroute_permute_plan -> moe_grouped_ffn_planned (routed and shared experts) ->
+ * moe_unpermute, or moe_unpermute_rmsnorm if normed_out is given; fp32 layers run the same steps
+ * with their own kernels.  Same results as those calls.  The struct only names dimensions and
+ * buffers; it is read during the call and may change between calls.
+ *   w13, w2         [dev] the pool's tensors (expert_pool_view); w13_shared / w2_shared [dev]
+ *                   [S, 2I, H] / [S, H, I], NULL if S = 0
+ *   Wg [dev] float32 [M, H]; bias [dev] float32 [N+1, M] or NULL; expert_map [dev] int32 [N+1, M]
+ *   logits .. row_of_pair [dev] the intermediates, sized for T_max tokens; y [T_max*(k+S), H]:
+ *                   the routed rows of the T tokens, then the shared experts' [S, T, H] outputs
+ *   ws_perm         moe_reroute_permute_workspace_bytes(T_max, k, P)
+ *   ws_ffn          moe_grouped_ffn_workspace_bytes(T_max, k + S, H, I, P + S, dtype)
+ * Errors: those of the calls; INVALID_ARG if T > T_max. */
+typedef struct ew_layer {
+  int dtype, H, I, M, k, N, P, S, renormalize, T_max;
+  const float* Wg;
+  const float* bias;
+  const int32_t* expert_map;
+  const void* w13;
+  const void* w2;
+  const void* w13_shared;
+  const void* w2_shared;
+  float* logits;
+  int32_t* ids;
+  float* w;
+  int32_t* slot;
+  int32_t* counts;
+  int32_t* offsets;
+  int32_t* pair_of_row;
+  int32_t* row_of_pair;
+  void* y;
+  void* ws_perm;
+  size_t ws_perm_bytes;
+  void* ws_ffn;
+  size_t ws_ffn_bytes;
+} ew_layer;
+int moe_layer_forward(const ew_layer* layer, const void* x, const int32_t* adapter_id, int T,
+                      const float* logits, const void* residual, void* out, void* normed_out,
+                      float eps, void* stream);
+
 /* ===================================================================================== *
  * Measurement aids (not on the hot path): what the GPU sustains, timed by the caller with events
  * in the same run as the hot path, for quoting roofline fractions against achievable peaks.

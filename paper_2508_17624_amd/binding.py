@@ -55,6 +55,7 @@ SIGNATURES = {
                                            _vp, _vp, _sz, _vp]),
     "moe_unpermute": (_int, [_vp, _vp, _vp, _vp, _int, _vp, _int, _int, _int, _int, _vp, _vp]),
     "moe_unpermute_rmsnorm": (_int, [_vp, _vp, _vp, _vp, _int, _vp, _int, _int, _int, _int, _vp, C.c_float, _vp, _vp]),
+    "moe_layer_forward": (_int, [_vp, _vp, _vp, _int, _vp, _vp, _vp, _vp, C.c_float, _vp]),
     "moe_gate_logits": (_int, [_vp, _int, _vp, _int, _int, _int, _vp, _vp, _vp, _vp]),
     "moe_rmsnorm": (_int, [_vp, _int, _int, _int, C.c_float, _vp, _vp]),
     "ew_probe_stream": (_int, [_vp, _vp, _sz, _int, _vp]),
@@ -71,6 +72,14 @@ class PoolStats(C.Structure):
 
     def as_dict(self):
         return {n: getattr(self, n) for n, _ in self._fields_}
+
+
+class LayerDesc(C.Structure):
+    """ew_layer: what moe_layer_forward has to know about a layer."""
+    _fields_ = [(n, _int) for n in ("dtype", "H", "I", "M", "k", "N", "P", "S", "renormalize", "T_max")] + \
+               [(n, _vp) for n in ("Wg", "bias", "expert_map", "w13", "w2", "w13_shared", "w2_shared", "logits", "ids", "w", "slot",
+                                   "counts", "offsets", "pair_of_row", "row_of_pair", "y", "ws_perm")] + \
+               [("ws_perm_bytes", _sz), ("ws_ffn", _vp), ("ws_ffn_bytes", _sz)]
 
 
 class EWError(RuntimeError):
@@ -111,7 +120,8 @@ def _ptr(t):
 
 
 def _stream():
-    return torch.cuda.current_stream().cuda_stream
+    # the raw handle: current_stream() builds a Stream object around it, five times the cost
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _dtype_code(t: torch.Tensor) -> int:

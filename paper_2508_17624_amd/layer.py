@@ -1,20 +1,26 @@
 """Sequencing of the library calls for adapter-aware MoE layers (paper Sec. 2.1 + Sec. 4).
 
 No arithmetic happens here: this module only owns device buffers (PyTorch tensors), loads a
-pool from per-class weight stacks, and issues the C-ABI calls in order on the current stream:
+pool from per-class weight stacks, and makes one C-ABI call per layer pass on the current stream,
+moe_layer_forward, which runs
 
     moe_gate_logits -> moe_route_reroute_permute_plan (also writes the FFN's work plan) ->
     moe_grouped_ffn_planned (routed experts on the pool's virtual weight tensors and the shared
     experts, one launch) -> moe_unpermute (+ residual; in a stack also the next layer's norm)
 
-fp32 layers (test-only kernels) call moe_route_reroute_permute and moe_grouped_ffn instead, the
-shared experts' call on a second stream.
+(fp32 layers the same steps with kernels of their own).
 """
 from __future__ import annotations
+
+import ctypes
 
 import torch
 
 from . import binding as B
+
+# attributes of a layer that its description for the library is made of
+_DESCRIBED = frozenset(("Wg", "bias", "renormalize", "shared_w13", "shared_w2", "w13_base", "w2_base", "emap", "buf", "dt", "H", "I", "M", "k",
+                        "N", "P", "S", "T_max"))
 
 
 def load_layer(pool: B.ExpertPool, layer: int, base, adapters, tuned):
@@ -43,30 +49,12 @@ class LayerBuffers:
         lib = B.lib()
         self.dt = B.EW_BF16 if dtype == torch.bfloat16 else B.EW_F32
         self.ws_perm = B._workspace(lib.moe_reroute_permute_workspace_bytes(T_max, k, P), device)
-        # one launch for routed and shared experts where the library supports it (bf16)
-        self.planned = dtype == torch.bfloat16 and H % 128 == 0 and I % 128 == 0
-        self.fused_shared = bool(S) and self.planned
-        Sf = S if self.fused_shared else 0
-        self.y = torch.empty((T_max * (k + Sf), H), dtype=dtype, device=device)
-        self.ws_ffn = B._workspace(lib.moe_grouped_ffn_workspace_bytes(T_max, k + Sf, H, I, P + Sf, self.dt), device)
-        if S and not self.fused_shared:
-            self.side = torch.cuda.Stream(device=device) if torch.device(device).type == "cuda" else None
-            self.ev_in, self.ev_out = torch.cuda.Event(), torch.cuda.Event()
-            self.y_sh = torch.empty((S * T_max, H), dtype=dtype, device=device)
-            self.ws_sh = B._workspace(lib.moe_grouped_ffn_workspace_bytes(S * T_max, 1, H, I, S, self.dt), device)
-            self.sh_counts = torch.empty(S, **i32)
-            self.sh_offsets = torch.empty(S + 1, **i32)
-            self.sh_por = torch.empty(S * T_max, **i32)
-            self._sh_T = -1
-
-    def shared_index(self, T: int):
-        """Row map of the shared experts (structure only): slab s holds tokens 0..T-1 in order."""
-        if self._sh_T != T:
-            S = self.S
-            self.sh_counts.fill_(T)
-            self.sh_offsets.copy_(torch.arange(S + 1, dtype=torch.int32) * T)
-            self.sh_por[:S * T].copy_(torch.arange(S * T, dtype=torch.int32) % T)
-            self._sh_T = T
+        # the permutation call of a bf16 layer also writes the grouped FFN's work plan
+        self.planned = dtype == torch.bfloat16
+        # routed and shared experts run in one launch
+        self.fused_shared = bool(S)
+        self.y = torch.empty((T_max * (k + S), H), dtype=dtype, device=device)
+        self.ws_ffn = B._workspace(lib.moe_grouped_ffn_workspace_bytes(T_max, k + S, H, I, P + S, self.dt), device)
 
 
 class MoELayer:
@@ -87,9 +75,25 @@ class MoELayer:
         b = self.buf
         assert (b.T_max, b.M, b.k, b.H, b.I, b.P, b.S, b.dtype) == (T_max, self.M, k, self.H, I, self.P, self.S, dtype)
         self.dt = b.dt
-        # Two-call layers only: the shared experts depend only on the layer input, so their call runs on a stream of its
-        # own (default priority) beside the router and the routed experts and is joined before the combine.
-        self.side = b.side if self.S and not b.fused_shared else None
+        self._desc = None
+
+    def __setattr__(self, name, value):
+        super().__setattr__(name, value)
+        if name in _DESCRIBED:
+            super().__setattr__("_desc", None)   # described again at the next pass
+
+    def _describe(self):
+        """The layer as moe_layer_forward reads it; kept until one of the attributes it is made of is set again."""
+        b, ptr = self.buf, B._ptr
+        d = B.LayerDesc(dtype=self.dt, H=self.H, I=self.I, M=self.M, k=self.k, N=self.N, P=self.P, S=self.S,
+                        renormalize=int(self.renormalize), T_max=self.T_max, Wg=ptr(self.Wg), bias=ptr(self.bias), expert_map=self.emap,
+                        w13=self.w13_base, w2=self.w2_base, w13_shared=ptr(self.shared_w13), w2_shared=ptr(self.shared_w2),
+                        logits=ptr(b.logits), ids=ptr(b.ids), w=ptr(b.w), slot=ptr(b.slot), counts=ptr(b.counts), offsets=ptr(b.offsets),
+                        pair_of_row=ptr(b.por), row_of_pair=ptr(b.rop), y=ptr(b.y), ws_perm=ptr(b.ws_perm),
+                        ws_perm_bytes=b.ws_perm.numel() if b.ws_perm is not None else 0, ws_ffn=ptr(b.ws_ffn), ws_ffn_bytes=b.ws_ffn.numel())
+        self._desc_struct = d
+        self._desc = ctypes.addressof(d)
+        return self._desc
 
     # intermediates of the last forward (views of the shared buffers)
     logits = property(lambda self: self.buf.logits)
@@ -101,8 +105,7 @@ class MoELayer:
     por = property(lambda self: self.buf.por)
     rop = property(lambda self: self.buf.rop)
     y = property(lambda self: self.buf.y[:self._T * self.k])                 # routed rows of the last forward
-    y_shared = property(lambda self: self.buf.y[self._T * self.k:self._T * (self.k + self.S)] if self.buf.fused_shared
-                        else self.buf.y_sh[:self.S * self._T])              # [S*T, H] shared-expert outputs of the last forward
+    y_shared = property(lambda self: self.buf.y[self._T * self.k:self._T * (self.k + self.S)])  # [S*T, H] shared-expert outputs
     out = property(lambda self: self.buf.out)
     ws_ffn = property(lambda self: self.buf.ws_ffn)
 
@@ -130,48 +133,16 @@ class MoELayer:
                 residual: torch.Tensor | None = None, out: torch.Tensor | None = None,
                 normed_out: torch.Tensor | None = None, eps: float = 0.0) -> torch.Tensor:
         """normed_out: if given, also receives the RMS-normalised result (the next layer's input in a stack)."""
-        lib, st, b = B.lib(), B._stream(), self.buf
-        T, H, k, P, I = x.shape[0], self.H, self.k, self.P, self.I
+        T = x.shape[0]
         assert T <= self.T_max and x.dtype == self.dtype and x.is_contiguous()
         self._T = T
-        sh_ptr = None
-        two_calls = self.S and not b.fused_shared
-        if two_calls:
-            b.shared_index(T)
-            main = torch.cuda.current_stream()
-            b.ev_in.record(main)                      # x (and the row map) are ready on the main stream
-            self.side.wait_event(b.ev_in)
-            B._check(lib.moe_grouped_ffn(x.data_ptr(), self.dt, self.S * T, 1, H, I, self.S, b.sh_counts.data_ptr(),
-                                         b.sh_offsets.data_ptr(), b.sh_por.data_ptr(), self.shared_w13.data_ptr(),
-                                         self.shared_w2.data_ptr(), b.y_sh.data_ptr(), b.ws_sh.data_ptr(),
-                                         b.ws_sh.numel(), self.side.cuda_stream))
-            b.ev_out.record(self.side)
-            sh_ptr = b.y_sh.data_ptr()
-        planned = b.planned                       # bf16 layers: the permutation call writes the FFN's work plan
-        self.route(x, aid, logits, plan=planned)
-        if planned:
-            fused = self.S and b.fused_shared
-            B._check(lib.moe_grouped_ffn_planned(x.data_ptr(), self.dt, T, k, H, I, P, self.S if fused else 0,
-                                                 b.counts.data_ptr(), b.offsets.data_ptr(), b.por.data_ptr(), self.w13_base,
-                                                 self.w2_base, self.shared_w13.data_ptr() if fused else None,
-                                                 self.shared_w2.data_ptr() if fused else None, b.y.data_ptr(),
-                                                 b.ws_ffn.data_ptr(), b.ws_ffn.numel(), st))
-            if fused:
-                sh_ptr = b.y.data_ptr() + T * k * H * b.y.element_size()
-        else:
-            B._check(lib.moe_grouped_ffn(x.data_ptr(), self.dt, T, k, H, I, P, b.counts.data_ptr(),
-                                         b.offsets.data_ptr(), b.por.data_ptr(), self.w13_base, self.w2_base,
-                                         b.y.data_ptr(), b.ws_ffn.data_ptr(), b.ws_ffn.numel(), st))
-        if two_calls:
-            torch.cuda.current_stream().wait_event(b.ev_out)
-        dst = b.out if out is None else out
-        res_ptr = residual.data_ptr() if residual is not None else None
-        if normed_out is not None:
-            B._check(lib.moe_unpermute_rmsnorm(b.y.data_ptr(), b.rop.data_ptr(), b.w.data_ptr(), sh_ptr, self.S, res_ptr, T, k, H,
-                                               self.dt, dst.data_ptr(), eps, normed_out.data_ptr(), st))
-        else:
-            B._check(lib.moe_unpermute(b.y.data_ptr(), b.rop.data_ptr(), b.w.data_ptr(), sh_ptr, self.S, res_ptr, T, k, H,
-                                       self.dt, dst.data_ptr(), st))
+        dst = self.buf.out if out is None else out
+        rc = B.lib().moe_layer_forward(self._desc or self._describe(), x.data_ptr(), aid.data_ptr(), T,
+                                       logits.data_ptr() if logits is not None else None,
+                                       residual.data_ptr() if residual is not None else None, dst.data_ptr(),
+                                       normed_out.data_ptr() if normed_out is not None else None, eps, B._stream())
+        if rc:
+            B._check(rc)
         return dst[:T]
 
 
