@@ -63,7 +63,7 @@ int grouped_ffn_f32(const void* x, int T, int k, int H, int I, int P, int S, con
 // rows both reach LDS by LDS-direct loads, persistent workgroups pull items from per-XCD work
 // lists).  nf = 32-token fragments per row chunk (1, 2, 4 or 8).
 int ffn_ws_frags(int max_rows_per_slot, int rows, int slots, int nf_override);
-size_t ffn_ws_plan_ints(int rows, int P, int nf);
+size_t ffn_ws_plan_ints(int T, int rows, int P);
 // Plan shape of a call with `rows` rows in all and `slots` slots (shared experts included).
 // merge: let the two products share a launch where the shape allows it.
 WsPlanShape ffn_ws_plan_shape(int rows, int slots, int nf, int chunk_frags, bool merge);
@@ -75,6 +75,14 @@ int launch_ffn_ws_plan(const int32_t* counts, const int32_t* offsets, int P, int
 int launch_ffn_ws(const void* x, int rows_routed, int k, int H, int I, int P, int S, const WsPlanShape& sh, bool plan_ready,
                   const int32_t* counts, const int32_t* offsets, const int32_t* por, const void* w13, const void* w2,
                   const void* w13_sh, const void* w2_sh, void* act, void* y, int32_t* plan, int wait_ticks, hipStream_t st);
+
+// ffn_dec.hip: the decode-sized calls of that path (sh.dec > 0), one continuous weight stream per workgroup.
+int launch_ffn_dec_plan(const int32_t* counts, const int32_t* offsets, int P, int S, int T, int rows_routed, const WsPlanShape& sh,
+                        int32_t* plan, hipStream_t st);
+int launch_ffn_dec(const void* x, int rows_routed, int k, int H, int I, int P, int S, const WsPlanShape& sh, const int32_t* por,
+                   const void* w13, const void* w2, const void* w13_sh, const void* w2_sh, void* act, void* y, int32_t* plan, int n_cu,
+                   hipStream_t st);
+WsPlanShape ffn_dec_plan_shape(int T, int rows, int slots, bool merge);
 
 // Whether moe_grouped_ffn / moe_grouped_ffn_with_shared with these dimensions runs the weight-stationary kernel, and
 // if so with which plan shape (defined beside the tuning state it depends on).

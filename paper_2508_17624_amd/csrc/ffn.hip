@@ -189,11 +189,11 @@ int g_ws_merge = 0;            // LDS-direct kernel, decode shapes: 1 = the two 
 // together already start together; waiting for the rest of the cohort measured the same or slower (0 / 1 / 2 / 4 us).
 constexpr int kWsWaitDefault = 0;
 
-size_t plan_bytes(int rows, int P) {
+size_t plan_bytes(int T, int rows, int P) {
   size_t ints = (size_t)P + 1;
   const size_t g = ew::ffn_gemm_plan_ints(rows, P);
   if (g > ints) ints = g;
-  const size_t w = ew::ffn_ws_plan_ints(rows, P, 1);
+  const size_t w = ew::ffn_ws_plan_ints(T, rows, P);
   if (w > ints) ints = w;
   return ew::align_up(ints * sizeof(int32_t), 256);
 }
@@ -233,7 +233,7 @@ extern "C" void ew_tune_ffn(int path, int stream_token_tiles, int stream_threads
 extern "C" size_t moe_grouped_ffn_workspace_bytes(int T, int k, int H, int I, int P, int dtype) {
   if (T <= 0 || k < 1 || H < 1 || I < 1 || P < 1) return 0;
   const size_t el = dtype == EW_BF16 ? 2 : 4;
-  return plan_bytes(T * k, P) + ew::align_up((size_t)T * k * I * el, 256);
+  return plan_bytes(T, T * k, P) + ew::align_up((size_t)T * k * I * el, 256);
 }
 
 namespace ew {
@@ -244,6 +244,13 @@ bool ffn_ws_shape_of_call(int dtype, int T, int k, int H, int I, int P, int S, W
   const long long rows = (long long)T * (k + S);
   const int slots = P + S, Kmax = H > I ? H : I;
   if (rows >= (1ll << 31) || slots > 2048 || (unsigned long long)rows * (unsigned long long)Kmax * 2ull >= (1ull << 32)) return false;
+  // The decode kernel streams weights best as long as slots are small: up to 512 tokens whatever the router does, beyond that
+  // while a slot has 64 rows on average (2000 tokens on 217 active slots: 328 -> 253 us; 4096 tokens on 66: 651 -> 880 us).
+  const long long per_slot = rows / (slots < rows ? slots : rows);
+  if (g_ws_frags == 0 && g_ws_chunk_frags == 0 && (T <= 512 || per_slot <= 64) && H >= 256 && I >= 256) {
+    *sh = ffn_dec_plan_shape(T, (int)rows, slots, g_ws_merge != 1);
+    return true;
+  }
   const int nf = ffn_ws_frags(T, (int)rows, slots < rows ? slots : (int)rows, g_ws_frags);
   *sh = ffn_ws_plan_shape((int)rows, slots, nf, g_ws_chunk_frags, g_ws_merge != 1);
   return true;
@@ -271,7 +278,7 @@ int grouped_ffn(const char* who, bool plan_ready, const void* x, int dtype, int 
   hipStream_t st = (hipStream_t)stream;
   const int rows = T * k;
   int32_t* plan = (int32_t*)ws;
-  char* act = (char*)ws + plan_bytes(T * (k + S), P + S);
+  char* act = (char*)ws + plan_bytes(T, T * (k + S), P + S);
   ew::WsPlanShape shape;
   const bool ws_path = ew::ffn_ws_shape_of_call(dtype, T, k, H, I, P, S, &shape);
   if (S > 0 || plan_ready) {

@@ -1,0 +1,593 @@
+// Grouped SwiGLU expert FFN for calls with few rows per slot on gfx950: one continuous stream of weights through every CU.
+//
+// With a handful of rows per slot both products are a pure weight stream (17 MB per active expert at the 2048/1408 shape),
+// so what counts is that every CU has enough bytes in flight from the first microsecond to the last.
+//   * A unit is 64, 128 or 256 weight rows of one slot's chunk of token rows.  The units of a workgroup form ONE stream of
+//     slabs (16 or 32 KB of weights): the LDS rings keep filling across unit boundaries, nothing drains between two units.
+//   * Loading and multiplying are different waves.  An LDS-direct load stalls its wave while the CU's queue of outstanding
+//     lines is full, which here is most of the time; a wave that also multiplied would multiply late, and with it everyone
+//     at the slab's barrier.
+//   * A wave that does nothing else claims the units, two ahead, and leaves their description and row map in a small LDS
+//     queue.  Claims go to eight lists per product, each with a counter in a cache line of its own that practically only
+//     one XCD touches (one counter for all: 39 ns per claim, one after the other, longer than the whole weight stream).  A
+//     workgroup takes from its home list, then from the others, and turns to the second product when no list has a
+//     first-product unit left, so both products share one launch.
+//   * A second-product unit reads activation rows of other workgroups once its chunk's completion counter says that they
+//     are stored.  Every such wait ends: a workgroup that waits holds second-product units only, since it claimed the first
+//     of them when all first-product units were claimed; a first-product unit is held by a workgroup whose earlier units
+//     are first-product too, which wait for nothing, and whose stores are counted before it waits for anything (workgroups
+//     that are not resident hold no claims).  The time limit on the wait is a safety net that is never reached.
+//   * Coherence of the activations: agent-scope stores, acknowledged before they are counted; for the loads see ACT_AUX.
+// Measured (call with plan, one box): 1 token on 8 experts of 2048 x 1408: 76 -> 43 us; 13 tokens on 36 of 1024 x 896: 88 ->
+// 47 us; 64 tokens on 90: 263 -> 246 us (6.3 TB/s of weights; a bare stream of the same slabs reaches 6.85); 512 tokens on
+// 242: 699 -> 682 us; 512 on 150 of 1536 x 640: 182 -> 161 us; 2000 on 217 of those: 328 -> 257 us.
+//
+// Waves: NW load weights, NT token rows, each into a ring of its own (the vector-memory counter retires in order, so each
+// ring is awaited at its own depth), one schedules, eight multiply (v_mfma_f32_16x16x32_bf16).
+// LDS rows are 256 or 128 bytes in pieces of 16, the piece index XOR-ed with (a half of) the row: the operand reads of 16
+// rows at one logical piece then cover all banks.  The loads apply it on the global side (a lane fetches the piece that
+// belongs at its position).
+// Fragments: a wave's two weight fragments (i = 0, 1) interleave so that a lane's eight sums belong together.  First
+// product: row m = 4 q + r of fragment i is feature 16 pair + 4 q + 2 i + (r & 1), gate for r < 2 and up for r >= 2: a lane
+// holds gate and up of four consecutive features, SwiGLU needs no exchange and 8 bytes are stored.  Second product: feature
+// 32 pair + 8 q + 4 i + r, 16 bytes.  (With one fragment per wave and half the width the stores alone cost 5 to 8 %.)
+#include "ew_internal.h"
+
+#include <type_traits>
+
+namespace ew {
+
+namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+
+
+// NTF: 16-row token fragments per chunk; MR: weight rows per unit.
+template <int NTF, int MR>
+struct DecCfg {
+  static constexpr int SK = MR == 64 ? 128 : 64;                    // contraction elements per slab
+  static constexpr int RB = SK * 2;                                 // bytes of an LDS row
+  static constexpr int FRAG = 16 * RB;                              // bytes of a 16-row fragment
+  static constexpr int WSLAB = MR * RB;                             // bytes of one weight slab
+  static constexpr int TSLAB = NTF * FRAG;                          // bytes of one token slab
+  // waves: NW load weights, NT token rows, one schedules, eight multiply.  256-row units keep 64 accumulators per lane, for
+  // which there are registers with three waves per SIMD; a slab of theirs lasts long enough for fewer loading waves.
+  static constexpr int NW = MR == 256 ? 2 : 4, NT = MR == 256 ? 1 : 2;
+  static constexpr int THREADS = 64 * (NW + NT + 1 + 8);
+  static constexpr int RPI = 1024 / RB;                             // rows per load instruction
+  static constexpr int NWI = MR / (NW * RPI);                       // load instructions per weight wave and slab
+  static constexpr int NTI = 16 / (NT * RPI);                       // load instructions per token wave and fragment
+  static constexpr int PN = MR / 32;                                // pairs of weight fragments
+  // Cache policy of the activation rows' loads.  Where a unit of the first product writes whole 128-byte lines, plain loads do:
+  // a line has one writer, nothing reads it before its chunk is complete, and no cache keeps lines of earlier launches; the
+  // units of an XCD then share the rows in its L2 (2000 tokens: 265 -> 257 us).  Half lines are read past the L2.
+  static constexpr int ACT_AUX = MR == 64 ? 16 : 0;
+  static constexpr int QI = 8 + (NTF > 4 ? 16 * NTF : 64);          // ints of a queue entry: description, source rows
+  static constexpr int LEFT = 160 * 1024 - 4 * QI * 4;
+  // ring depths: the token rows come from L2 and need less, the weights take the rest
+  static constexpr int DT = TSLAB > 8192 ? 3 : 5;
+  static constexpr int DW = (LEFT - DT * TSLAB) / WSLAB < 8 ? (LEFT - DT * TSLAB) / WSLAB : 8;
+  static constexpr int Q_OFF = DW * WSLAB + DT * TSLAB;
+  static constexpr int LDS = Q_OFF + 4 * QI * 4;
+  static_assert(LDS <= 160 * 1024 && DW * WSLAB >= 80 * 1024, "LDS budget of a CU, bytes in flight");
+};
+
+struct DecProd {
+  const uint16_t* x;   // first product: tokens [*, K]; second: activations [rows, K]
+  const uint16_t* w;   // slots 0 .. P-1
+  const uint16_t* w_sh;
+  uint16_t* out;       // [rows, NOUT]
+  size_t slot_stride;  // elements per slot
+  int K, NOUT, G;      // G: units per chunk
+};
+
+struct DecArgs {
+  DecProd m[2];
+  const int32_t* por;   // row map of the first product; may be NULL
+  int32_t* plan;
+  int32_t* done;        // per chunk: first-product units stored
+  int P, rows_routed, sh_rows, k;
+  int first_mode, last_mode;  // the launch's products
+  int depth_w, depth_t;
+  unsigned int spin_ticks;
+};
+
+__device__ __forceinline__ uint16_t f32_to_bf16(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
+__device__ __forceinline__ float silu_f32(float g) { return g * __builtin_amdgcn_rcpf(1.f + __expf(-g)); }
+
+struct DecUnit {
+  int slot, off, rows, g, mode, chunk, ready;  // slot < 0: no unit left
+};
+
+// LDS reads the compiler must not see (it would wait for every LDS-direct load in flight before them).
+__device__ __forceinline__ DecUnit read_unit(uint32_t addr) {
+  i32x4 lo, hi;
+  asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %2 offset:16\n\ts_waitcnt lgkmcnt(0)" : "=&v"(lo), "=&v"(hi) : "v"(addr) : "memory");
+  DecUnit u;
+  u.slot = __builtin_amdgcn_readfirstlane(lo[0]);
+  u.off = __builtin_amdgcn_readfirstlane(lo[1]);
+  u.rows = __builtin_amdgcn_readfirstlane(lo[2]);
+  u.g = __builtin_amdgcn_readfirstlane(lo[3]);
+  u.mode = __builtin_amdgcn_readfirstlane(hi[0]);
+  u.chunk = __builtin_amdgcn_readfirstlane(hi[1]);
+  u.ready = __builtin_amdgcn_readfirstlane(hi[2]);
+  return u;
+}
+// N ints STEP bytes apart (N: 1, 2 or a multiple of 4).
+template <int N, int STEP>
+__device__ __forceinline__ void read_lds_ints(uint32_t addr, uint32_t* r) {
+  if constexpr (N == 1)
+    asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(r[0]) : "v"(addr) : "memory");
+  else if constexpr (N == 2)
+    asm volatile("ds_read_b32 %0, %2\n\tds_read_b32 %1, %2 offset:%3\n\ts_waitcnt lgkmcnt(0)" : "=&v"(r[0]), "=&v"(r[1]) : "v"(addr), "n"(STEP) : "memory");
+  else {
+    asm volatile("ds_read_b32 %0, %4\n\tds_read_b32 %1, %4 offset:%5\n\tds_read_b32 %2, %4 offset:%6\n\tds_read_b32 %3, %4 offset:%7\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]) : "v"(addr), "n"(STEP), "n"(2 * STEP), "n"(3 * STEP) : "memory");
+    if constexpr (N > 4) read_lds_ints<N - 4, STEP>(addr + 4 * STEP, r + 4);
+  }
+}
+
+// At most n vector-memory operations of this wave still outstanding (n is wave-uniform; waiting for fewer is safe).
+__device__ __forceinline__ void wait_vm_upto(int n) {
+#define EW_VM(N) __builtin_amdgcn_s_waitcnt(0x0F70 | ((N) & 15) | (((N) >> 4) << 14))
+  if (n >= 32) {
+    EW_VM(32);
+  } else if (n >= 16) {
+    if (n >= 24) EW_VM(24); else if (n >= 20) EW_VM(20); else EW_VM(16);
+  } else if (n >= 8) {
+    if (n >= 12) EW_VM(12); else if (n >= 10) EW_VM(10); else EW_VM(8);
+  } else if (n >= 4) {
+    if (n >= 6) EW_VM(6); else if (n >= 5) EW_VM(5); else EW_VM(4);
+  } else {
+    if (n >= 3) EW_VM(3); else if (n >= 2) EW_VM(2); else if (n >= 1) EW_VM(1); else EW_VM(0);
+  }
+#undef EW_VM
+}
+
+// Operands of one k-step (32 elements): MFW weight fragments WS bytes apart and NB token fragments FS bytes apart, issued
+// without waiting.
+template <int N, int STEP>
+__device__ __forceinline__ void read_frags(uint32_t addr, u32x4* v) {
+  if constexpr (N == 1)
+    asm volatile("ds_read_b128 %0, %1" : "=&v"(v[0]) : "v"(addr));
+  else if constexpr (N == 2)
+    asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %2 offset:%3" : "=&v"(v[0]), "=&v"(v[1]) : "v"(addr), "n"(STEP));
+  else if constexpr (N == 3)
+    asm volatile("ds_read_b128 %0, %3\n\tds_read_b128 %1, %3 offset:%4\n\tds_read_b128 %2, %3 offset:%5"
+                 : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]) : "v"(addr), "n"(STEP), "n"(2 * STEP));
+  else {
+    asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %4 offset:%5\n\tds_read_b128 %2, %4 offset:%6\n\tds_read_b128 %3, %4 offset:%7"
+                 : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]) : "v"(addr), "n"(STEP), "n"(2 * STEP), "n"(3 * STEP));
+    if constexpr (N > 4) read_frags<N - 4, STEP>(addr + 4 * STEP, v + 4);
+  }
+}
+// This wave's operand reads have landed; the registers are named so that nothing uses them earlier.
+template <int N>
+__device__ __forceinline__ void landed(u32x4* v) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) asm volatile("" : "+v"(v[i]));
+}
+
+// One slab: KS k-steps of MFW weight fragments times NB token fragments.  All operands are read
+// at once where they fit the registers (128 per wave), otherwise one k-step and four token fragments at a time.
+template <int MFW, int NB, int KS, int WS, int FS>
+__device__ __forceinline__ void mul_slab(uint32_t wa, uint32_t tb, f32x4 (&acc)[MFW][NB]) {
+  constexpr int BATCH = MFW * NB + KS * (MFW + NB) <= 22 ? KS : 1, N = NB < 4 ? NB : 4;
+#pragma unroll
+  for (int j0 = 0; j0 < KS; j0 += BATCH) {
+    u32x4 a[BATCH][MFW];
+#pragma unroll
+    for (int f0 = 0; f0 < NB; f0 += N) {
+      u32x4 b[BATCH][N];
+#pragma unroll
+      for (int j = 0; j < BATCH; ++j) {
+        if (f0 == 0) read_frags<MFW, WS>(wa ^ (uint32_t)(64 * (j0 + j)), a[j]);
+        read_frags<N, FS>((tb ^ (uint32_t)(64 * (j0 + j))) + f0 * FS, b[j]);
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+      for (int j = 0; j < BATCH; ++j) {
+        if (f0 == 0) landed<MFW>(a[j]);
+        landed<N>(b[j]);
+      }
+#pragma unroll
+      for (int j = 0; j < BATCH; ++j)
+#pragma unroll
+        for (int f = 0; f < N; ++f)
+          if (f0 + f < NB)
+#pragma unroll
+            for (int i = 0; i < MFW; ++i)
+              acc[i][f0 + f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[j][i]), __builtin_bit_cast(bf16x8, b[j][f]),
+                                                                            acc[i][f0 + f], 0, 0, 0);
+    }
+  }
+}
+// First slab of a unit's walk over K: a function of the unit alone (results do not depend on who computes it) that keeps
+// workgroups streaming neighbouring units in step off the same memory channels.
+__device__ __forceinline__ int first_slab(const DecUnit& u, int nk) { return (u.slot * 5 + u.g * 3) % nk; }
+
+// ------------------------------------------------------------------------------------------
+// The scheduling wave.  Unit u of a product belongs to list u % 8.
+struct Sched {
+  int w;                 // claim in flight: position in list `list` of product `mode`
+  int mode, list, home;
+  int chunk, g;
+  i32x4 en;
+  uint32_t src[2];       // byte offsets of the source rows lane, lane + 64 of the chunk
+};
+
+__device__ __forceinline__ int32_t* sched_counter(const DecArgs& a, int mode, int list) {
+  return a.plan + kDecCtr + (mode * 8 + list) * kDecCtrStride;
+}
+__device__ __forceinline__ void sched_claim(const DecArgs& a, Sched& s) {
+  if ((threadIdx.x & 63) == 0 && s.mode <= a.last_mode) s.w = __hip_atomic_fetch_add(sched_counter(a, s.mode, s.list), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void sched_entry(const DecArgs& a, int n_chunks, Sched& s) {
+  const int lane = threadIdx.x & 63;
+  for (;;) {
+    if (s.mode > a.last_mode) {
+      s.chunk = -1;
+      return;
+    }
+    const int G = s.mode ? a.m[1].G : a.m[0].G, n = n_chunks * G;
+    const int u = __builtin_amdgcn_readfirstlane(s.w) * 8 + s.list;
+    if (u < n) {
+      s.chunk = u / G;
+      s.g = u - s.chunk * G;
+      s.en = *reinterpret_cast<const i32x4*>(a.plan + kDecEnt + 4 * s.chunk);
+      return;
+    }
+    // this list is empty: the next one that is not, or the next product
+    const int x = (s.home + lane) & 7;
+    const bool left = lane < 8 && __hip_atomic_load(sched_counter(a, s.mode, x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) * 8 + x < n;
+    const unsigned long long m = __ballot(left);
+    if (m) {
+      s.list = (s.home + __ffsll((long long)m) - 1) & 7;
+    } else {
+      s.list = s.home;
+      ++s.mode;
+      if (s.mode > a.last_mode) continue;
+    }
+    sched_claim(a, s);
+  }
+}
+template <int QI>
+__device__ __forceinline__ void sched_rows(const DecArgs& a, Sched& s) {
+  if (s.chunk < 0) return;
+  const int slot = s.en[0], rows = s.en[1], off = s.en[2];
+#pragma unroll
+  for (int h = 0; h < (QI > 72 ? 2 : 1); ++h) {
+    const int r = min((int)(threadIdx.x & 63) + 64 * h, rows - 1);
+    int src = off + r;
+    if (s.mode == 0) src = slot >= a.P ? off - a.rows_routed - (slot - a.P) * a.sh_rows + r : (a.por ? a.por[off + r] : off + r) / a.k;
+    s.src[h] = (uint32_t)src * (uint32_t)(2 * (s.mode ? a.m[1].K : a.m[0].K));
+  }
+}
+template <int QI>
+__device__ __forceinline__ void sched_publish(const DecArgs& a, const Sched& s, int32_t* q) {
+  const int lane = threadIdx.x & 63;
+  if (s.chunk < 0) {
+    if (lane == 0) q[0] = -1;
+  } else {
+    q[8 + lane] = (int32_t)s.src[0];
+    if (QI > 72) q[8 + 64 + lane] = (int32_t)s.src[1];
+    if (lane == 0) {
+      q[0] = s.en[0]; q[1] = s.en[2]; q[2] = s.en[1]; q[3] = s.g; q[4] = s.mode; q[5] = s.chunk;
+      q[6] = s.mode == 0 || __hip_atomic_load(a.done + s.chunk * kDecDoneStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= a.m[0].G;
+    }
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+}
+
+// ROLE 0: weight wave, 1: token wave, 2: scheduler, 3: multiplying wave.  All roles execute the same number of barriers.
+template <int NTF, int MR, int ROLE>
+__device__ __forceinline__ void dec_body(const DecArgs& a, unsigned char* s_lds) {
+  using C = DecCfg<NTF, MR>;
+  constexpr int kShift = MR == 64 ? 7 : 6;                                    // log2 of a slab's contraction elements
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lw = ROLE == 0 ? wave : wave - C::NW;                             // index among the waves of this role
+  constexpr bool LOADS = ROLE <= 1;
+  const int depth = ROLE == 0 ? a.depth_w : a.depth_t;
+  int32_t* queue = reinterpret_cast<int32_t*>(s_lds + C::Q_OFF);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)s_lds;
+  const uint32_t q0 = lds0 + C::Q_OFF;
+
+  [[maybe_unused]] Sched sc{};
+  [[maybe_unused]] int n_chunks = 0;
+  [[maybe_unused]] int pending = -1;  // scheduler: chunk whose unit is stored but not yet counted
+  if constexpr (ROLE == 2) {
+    n_chunks = a.plan[0];
+    sc.home = sc.list = (int)(blockIdx.x & 7);
+    sc.mode = a.first_mode;
+    sched_claim(a, sc);
+    sched_entry(a, n_chunks, sc);
+    sched_rows<C::QI>(a, sc);
+    sched_publish<C::QI>(a, sc, queue);
+  }
+  __builtin_amdgcn_s_barrier();
+  DecUnit cur = read_unit(q0);
+  if (cur.slot < 0) return;
+  DecUnit nxt{-1, 0, 0, 0, 0, 0, 0};
+
+  // ---- the loading side: position in the stream of slabs
+  // Instruction i of a loading wave covers LDS rows (i * waves + lw) * RPI + lane / (64 / RPI).  pm: that row of a 16-row
+  // fragment (token waves with two instructions per fragment: of the first one; the second is 8 rows and half a row of
+  // pieces further on); piece: the 16 bytes that belong at the lane's position.
+  [[maybe_unused]] const int pm = MR == 64 ? lw * 4 + (lane >> 4) : (lw & 1) * 8 + (lane >> 3);
+  [[maybe_unused]] const uint32_t piece = (uint32_t)(MR == 64 ? (lane & 15) ^ pm : (lane & 7) ^ (pm >> 1)) << 4;
+  [[maybe_unused]] const unsigned char* p_base = nullptr;                     // the loading unit's source
+  [[maybe_unused]] uint32_t p_off[C::NTI * NTF] = {};                         // token waves: byte offset of the lane's row per fragment
+  [[maybe_unused]] uint32_t p_w = 0, p_ws = 0;                                // weight waves: lane offset, stride between fragments
+  int p_k = 0, p_nk = 1, p_rot = 0, p_nld = 0, p_mode = 0;
+  int p_slot = 0;                                                             // ring slot of the next slab
+  bool p_next = false;                                                        // the loading unit is `nxt`
+  auto aim = [&](const DecUnit& u, [[maybe_unused]] int qi) {
+    const DecProd& m = u.mode ? a.m[1] : a.m[0];
+    p_k = 0;
+    p_nk = m.K >> kShift;
+    p_rot = first_slab(u, p_nk);
+    p_mode = u.mode;
+    if constexpr (ROLE == 0) {
+      p_base = reinterpret_cast<const unsigned char*>(u.slot < a.P ? m.w + (size_t)u.slot * m.slot_stride
+                                                                   : m.w_sh + (size_t)(u.slot - a.P) * m.slot_stride);
+      const int f0 = MR == 128 ? lw >> 1 : 0;                                 // fragment of instruction 0
+      const uint32_t row = u.mode == 0 ? (uint32_t)((pm & 2 ? m.NOUT : 0) + u.g * (MR / 2) + f0 * 16 + 4 * (pm >> 2) + (pm & 1))
+                                       : (uint32_t)(u.g * MR + f0 * 32 + 8 * (pm >> 2) + (pm & 3));
+      p_w = row * (uint32_t)(m.K * 2) + piece;
+      p_ws = (uint32_t)((u.mode + 1) * m.K * 2);
+    } else if constexpr (ROLE == 1) {
+      p_base = reinterpret_cast<const unsigned char*>(m.x);
+      p_nld = (u.rows + 15) >> 4;
+      // the source rows' byte offsets, as the scheduler left them
+      constexpr int N = C::NTI * NTF;
+      const uint32_t at = q0 + (uint32_t)(qi * C::QI + 8 + pm) * 4u;
+      uint32_t r[N];
+      read_lds_ints<N, 16 / C::NTI * 4>(at, r);
+#pragma unroll
+      for (int i = 0; i < N; ++i) p_off[i] = r[i] + (piece ^ (C::NTI == 2 && (i & 1) ? C::RB / 2u : 0u));
+    }
+  };
+  auto issue = [&]() {
+    int kk = p_k + p_rot;
+    if (kk >= p_nk) kk -= p_nk;
+    const unsigned char* src = p_base + (size_t)kk * C::RB;
+    if constexpr (ROLE == 0) {
+      unsigned char* dst = s_lds + p_slot * C::WSLAB + lw * 1024;
+#pragma unroll
+      for (int i = 0; i < C::NWI; ++i) {
+        constexpr int FPI = C::NW * C::RPI / 16;                              // fragments per round of instructions
+        const uint32_t rows = 16 * (i * FPI % C::PN) + 2 * (i * FPI / C::PN); // see the fragment layout at the top
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + p_w + rows * p_ws),
+                                         (__attribute__((address_space(3))) void*)(dst + i * C::NW * 1024), 16, 0, 2);
+      }
+    } else if constexpr (ROLE == 1) {
+      unsigned char* dst = s_lds + C::DW * C::WSLAB + p_slot * C::TSLAB + lw * 1024;
+#pragma unroll
+      for (int i = 0; i < C::NTI * NTF; ++i)
+        if (i < C::NTI * p_nld) {
+          // second product: rows written by other workgroups of this launch, read at the point of coherence
+          if (p_mode)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + p_off[i]),
+                                             (__attribute__((address_space(3))) void*)(dst + i * C::NT * 1024), 16, 0, C::ACT_AUX);
+          else
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + p_off[i]),
+                                             (__attribute__((address_space(3))) void*)(dst + i * C::NT * 1024), 16, 0, 0);
+        }
+    }
+    ++p_k;
+    p_slot = p_slot + 1 == depth ? 0 : p_slot + 1;
+  };
+  auto wait_done = [&](const DecUnit& u) {  // token waves: the unit's activation rows are stored
+    if (u.mode == 0 || u.ready) return;
+    const int32_t* flag = a.done + u.chunk * kDecDoneStride;
+    const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
+    while (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < a.m[0].G &&
+           __builtin_amdgcn_s_memrealtime() - t0 < (unsigned long long)a.spin_ticks)
+      __builtin_amdgcn_s_sleep(1);
+    asm volatile("" ::: "memory");
+  };
+
+  // ---- the multiplying side
+  // wave cw: weight fragments pair and pair + PN, token fragments nh, nh + FSTEP, ...
+  constexpr int FSTEP = 8 / C::PN, NF = (NTF + FSTEP - 1) / FSTEP, MFW = 2;
+  [[maybe_unused]] const int cw = wave - (C::NW + C::NT + 1), pair = cw / FSTEP, nh = cw % FSTEP;
+  [[maybe_unused]] const int n16 = lane & 15, q = lane >> 4;
+  [[maybe_unused]] const uint32_t rd = (uint32_t)(n16 * C::RB + ((q ^ (MR == 64 ? n16 : n16 >> 1)) << 4));
+  [[maybe_unused]] const uint32_t rd_w = lds0 + pair * C::FRAG + rd, rd_t = lds0 + C::DW * C::WSLAB + nh * C::FRAG + rd;
+  [[maybe_unused]] int c_w = 0, c_t = 0;                                                       // ring slots of the slab being multiplied
+  int seq = 0;                                                                // units done
+
+  if constexpr (LOADS) {
+    if (ROLE == 1) wait_done(cur);
+    aim(cur, 0);
+    for (int i = 0; i < depth - 1; ++i) issue();
+  } else if constexpr (ROLE == 2) {
+    sched_claim(a, sc);
+    sched_entry(a, n_chunks, sc);
+    sched_rows<C::QI>(a, sc);
+    sched_publish<C::QI>(a, sc, queue + C::QI);
+  }
+  __builtin_amdgcn_s_barrier();
+  nxt = read_unit(q0 + C::QI * 4);
+
+  for (;;) {
+    const DecProd& m = cur.mode ? a.m[1] : a.m[0];
+    const int nk = m.K >> kShift;
+    const bool change = nxt.slot >= 0 && nxt.mode != cur.mode;
+    [[maybe_unused]] const int nld = (cur.rows + 15) >> 4;                    // live token fragments
+    if constexpr (ROLE == 3) {
+      // one loop per number of live token fragments (above four: eight, the rest multiplied for nothing), so that the
+      // accumulators stay where they are
+      auto unit = [&](auto nb_tag) {
+        constexpr int NB = decltype(nb_tag)::value, KS = C::SK / 32;
+        f32x4 acc[MFW][NB > 0 ? NB : 1] = {};
+        for (int kt = 0; kt < nk; ++kt) {
+          if (kt == a.depth_w - 1) __builtin_amdgcn_s_waitcnt(0x0F70);        // the previous unit's stores are acknowledged
+          __builtin_amdgcn_s_barrier();
+          if constexpr (NB > 0) mul_slab<MFW, NB, KS, C::PN * C::FRAG, FSTEP * C::FRAG>(rd_w + c_w * C::WSLAB, rd_t + c_t * C::TSLAB, acc);
+          c_w = c_w + 1 == a.depth_w ? 0 : c_w + 1;
+          c_t = c_t + 1 == a.depth_t ? 0 : c_t + 1;
+        }
+#pragma unroll
+        for (int f = 0; f < NB; ++f) {
+          const int tr = (nh + FSTEP * f) * 16 + n16;
+          if (tr < cur.rows) {
+            uint16_t* row = m.out + (size_t)(cur.off + tr) * m.NOUT;
+            const f32x4 v = acc[0][f], w = acc[1][f];
+            if (cur.mode == 0) {
+              ushort4 o;
+              o.x = f32_to_bf16(silu_f32(v[0]) * v[2]); o.y = f32_to_bf16(silu_f32(v[1]) * v[3]);
+              o.z = f32_to_bf16(silu_f32(w[0]) * w[2]); o.w = f32_to_bf16(silu_f32(w[1]) * w[3]);
+              // agent scope: written through to the point of coherence of the GPU's XCDs
+              unsigned long long bits;
+              __builtin_memcpy(&bits, &o, 8);
+              __hip_atomic_store(reinterpret_cast<unsigned long long*>(row + cur.g * (MR / 2) + pair * 16 + 4 * q), bits, __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_AGENT);
+            } else {
+              union { uint16_t h[8]; uint4 u; } o;
+#pragma unroll
+              for (int r = 0; r < 4; ++r) {
+                o.h[r] = f32_to_bf16(v[r]);
+                o.h[4 + r] = f32_to_bf16(w[r]);
+              }
+              *reinterpret_cast<uint4*>(row + cur.g * MR + pair * 32 + 8 * q) = o.u;
+            }
+          }
+        }
+      };
+      const int nf = (nld - nh + FSTEP - 1) / FSTEP;                          // this wave's live token fragments
+      if (NF >= 8 && nf > 4) unit(std::integral_constant<int, NF >= 8 ? 8 : 0>{});
+      else if (NF >= 4 && nf == 4) unit(std::integral_constant<int, NF >= 4 ? 4 : 0>{});
+      else if (NF >= 3 && nf == 3) unit(std::integral_constant<int, NF >= 3 ? 3 : 0>{});
+      else if (NF >= 2 && nf == 2) unit(std::integral_constant<int, NF >= 2 ? 2 : 0>{});
+      else if (nf >= 1) unit(std::integral_constant<int, 1>{});
+      else unit(std::integral_constant<int, 0>{});
+    } else
+    for (int kt = 0; kt < nk; ++kt) {
+      if constexpr (LOADS) {
+        // this wave's part of slab kt has landed once only later slabs' loads are outstanding
+        const int ahead_next = p_next ? p_k : 0;                              // slabs of nxt in flight
+        const int ahead = (p_next ? nk : p_k) - (kt + 1);                     // later slabs of cur
+        wait_vm_upto(ROLE == 0 ? C::NWI * (ahead + ahead_next) : C::NTI * (ahead * nld + ahead_next * p_nld));
+      }
+      __builtin_amdgcn_s_barrier();                                           // everyone's part is there, slab kt-1 has been read
+      if constexpr (ROLE == 2) {
+        if (kt == a.depth_w - 1 && pending >= 0) {
+          // every multiplying wave has waited for its stores of the previous unit
+          if (lane == 0) __hip_atomic_fetch_add(a.done + pending * kDecDoneStride, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          pending = -1;
+        }
+        // the unit after the next: one round trip at a time, spread over this unit's slabs
+        if (kt == 0) sched_claim(a, sc);
+        if (kt == (nk - 2) / 3) sched_entry(a, n_chunks, sc);
+        if (kt == 2 * (nk - 2) / 3) sched_rows<C::QI>(a, sc);
+        if (kt == nk - 2) sched_publish<C::QI>(a, sc, queue + ((seq + 2) & 3) * C::QI);
+      } else if constexpr (LOADS) {
+        if (!p_next && p_k == nk && nxt.slot >= 0 && !(ROLE == 1 && change)) {
+          if (ROLE == 1) wait_done(nxt);
+          aim(nxt, (seq + 1) & 3);
+          p_next = true;
+        }
+        if (p_next || p_k < nk) issue();
+      }
+    }
+    if (nxt.slot < 0 || change) {
+      // the stores are acknowledged (and nothing is in flight at the end of the kernel): count the unit at once
+      if constexpr (ROLE != 2) __builtin_amdgcn_s_waitcnt(0x0F70);
+      __builtin_amdgcn_s_barrier();
+      if constexpr (ROLE == 2) {
+        if (pending >= 0 && lane == 0) __hip_atomic_fetch_add(a.done + pending * kDecDoneStride, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        pending = -1;
+        if (cur.mode == 0 && lane == 0) __hip_atomic_fetch_add(a.done + cur.chunk * kDecDoneStride, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      if (nxt.slot < 0) return;
+    } else if constexpr (ROLE == 2) {
+      if (pending >= 0 && lane == 0) __hip_atomic_fetch_add(a.done + pending * kDecDoneStride, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      pending = cur.mode == 0 ? cur.chunk : -1;
+    }
+    ++seq;
+    cur = nxt;
+    nxt = read_unit(q0 + (uint32_t)(((seq + 1) & 3) * C::QI) * 4u);
+    if constexpr (LOADS) {
+      if (!p_next) {  // nothing of this unit is in flight yet (token waves, from the first product to the second)
+        if (ROLE == 1) wait_done(cur);
+        aim(cur, seq & 3);
+        for (int i = 0; i < depth - 1; ++i) issue();
+      }
+      p_next = false;
+    }
+  }
+}
+
+template <int NTF, int MR>
+__global__ __launch_bounds__((DecCfg<NTF, MR>::THREADS)) void k_ffn_dec(DecArgs a) {
+  __shared__ __align__(1024) unsigned char s_lds[DecCfg<NTF, MR>::LDS];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  using C = DecCfg<NTF, MR>;
+  if (wave < C::NW) dec_body<NTF, MR, 0>(a, s_lds);
+  else if (wave < C::NW + C::NT) dec_body<NTF, MR, 1>(a, s_lds);
+  else if (wave == C::NW + C::NT) dec_body<NTF, MR, 2>(a, s_lds);
+  else dec_body<NTF, MR, 3>(a, s_lds);
+}
+
+__global__ __launch_bounds__(512) void k_plan_dec(const int32_t* __restrict__ counts, const int32_t* __restrict__ offsets, int P, int S,
+                                                  int sh_rows, int sh_first, WsPlanShape sh, int32_t* __restrict__ plan) {
+  __shared__ DecPlanLds lds;
+  dec_plan_build(counts, offsets, P, S, sh_rows, sh_first, sh, plan, lds);
+}
+
+template <int NTF, int MR>
+int launch(DecArgs a, bool merged, int max_chunks, int n_cu, hipStream_t st) {
+  using C = DecCfg<NTF, MR>;
+  a.m[0].G = a.m[0].NOUT / (MR / 2);
+  a.m[1].G = a.m[1].NOUT / MR;
+  const int nk = (a.m[0].K < a.m[1].K ? a.m[0].K : a.m[1].K) / C::SK;  // >= 2
+  a.depth_w = C::DW < nk ? C::DW : nk;
+  a.depth_t = C::DT < nk ? C::DT : nk;
+  for (int mode = 0; mode < (merged ? 1 : 2); ++mode) {
+    a.first_mode = mode;
+    a.last_mode = merged ? 1 : mode;
+    const long long units = (long long)max_chunks * (merged ? a.m[0].G + a.m[1].G : a.m[mode].G);
+    hipLaunchKernelGGL((k_ffn_dec<NTF, MR>), dim3(units < n_cu ? (int)units : n_cu), dim3(C::THREADS), 0, st, a);
+    EW_LAUNCH_CHECK("k_ffn_dec");
+  }
+  return EW_OK;
+}
+
+}  // namespace
+
+int launch_ffn_dec_plan(const int32_t* counts, const int32_t* offsets, int P, int S, int T, int rows_routed, const WsPlanShape& sh,
+                        int32_t* plan, hipStream_t st) {
+  hipLaunchKernelGGL(k_plan_dec, dim3(1), dim3(512), 0, st, counts, offsets, P, S, T, rows_routed, sh, plan);
+  EW_LAUNCH_CHECK("k_plan_dec");
+  return EW_OK;
+}
+
+int launch_ffn_dec(const void* x, int rows_routed, int k, int H, int I, int P, int S, const WsPlanShape& sh, const int32_t* por,
+                   const void* w13, const void* w2, const void* w13_sh, const void* w2_sh, void* act, void* y, int32_t* plan, int n_cu,
+                   hipStream_t st) {
+  const int T = rows_routed / k;
+  DecArgs a{};
+  a.m[0] = DecProd{(const uint16_t*)x, (const uint16_t*)w13, (const uint16_t*)w13_sh, (uint16_t*)act, (size_t)2 * I * H, H, I, 0};
+  a.m[1] = DecProd{(const uint16_t*)act, (const uint16_t*)w2, (const uint16_t*)w2_sh, (uint16_t*)y, (size_t)H * I, I, H, 0};
+  a.por = por; a.plan = plan; a.done = plan + sh.done_off;
+  a.P = P; a.rows_routed = rows_routed; a.sh_rows = T > 0 ? T : 1; a.k = k;
+  a.spin_ticks = 20000000u;  // 0.2 s
+  // Units of 128 weight rows read every token row half as often as units of 64: C1-shaped calls 261 -> 247 us, 48 tokens on
+  // 84 small experts 111 -> 101 us.  Only where even 64-row units leave a compute unit no more than two of the first
+  // product (one token: 8 experts) does the finer split win: 44 -> 42 us.
+  const bool fine = sh.dec == 1 && (long long)sh.cap * (I / 32) <= 2 * n_cu;
+  const bool merged = sh.n_done > 0;
+  switch (sh.dec) {
+    case 1: return fine ? launch<1, 64>(a, merged, sh.cap, n_cu, st) : launch<1, 128>(a, merged, sh.cap, n_cu, st);
+    case 2: return launch<2, 128>(a, merged, sh.cap, n_cu, st);
+    case 4: return launch<4, 128>(a, merged, sh.cap, n_cu, st);
+    default: return H % 256 == 0 ? launch<8, 256>(a, merged, sh.cap, n_cu, st) : launch<8, 128>(a, merged, sh.cap, n_cu, st);
+  }
+}
+
+}  // namespace ew

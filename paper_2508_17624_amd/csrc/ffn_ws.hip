@@ -951,13 +951,28 @@ static int ws_list_cap(int rows, int P) {
 // Calls of at most this many rows run their two products in one launch (decode shapes only); one counter per row.
 constexpr int kMergeMaxRows = 16384;
 
-size_t ffn_ws_plan_ints(int rows, int P, int nf) {
-  (void)nf;
-  return (size_t)kPlanHdr + (size_t)8 * kEnt * ws_list_cap(rows, P) + (size_t)(rows < kMergeMaxRows ? rows : kMergeMaxRows);
+// 16-row fragments per chunk of a decode plan: no slot has more rows than the call has tokens.
+static int dec_frags(int T) { return T <= 16 ? 1 : T <= 32 ? 2 : T <= 64 ? 4 : 8; }
+// Chunks of a decode plan at most: one per active slot and one more per bt rows.
+static int dec_chunk_cap(int rows, int P, int bt) { return (P < rows ? P : rows) + rows / bt + 1; }
+
+size_t ffn_ws_plan_ints(int T, int rows, int P) {
+  const size_t ws = (size_t)kPlanHdr + (size_t)8 * kEnt * ws_list_cap(rows, P) + (size_t)(rows < kMergeMaxRows ? rows : kMergeMaxRows);
+  const size_t dec = (size_t)kDecEnt + (size_t)(4 + kDecDoneStride) * dec_chunk_cap(rows, P, 16 * dec_frags(T));
+  return ws > dec ? ws : dec;
+}
+
+WsPlanShape ffn_dec_plan_shape(int T, int rows, int slots, bool merge) {
+  WsPlanShape sh{};
+  sh.dec = dec_frags(T);
+  sh.cap = dec_chunk_cap(rows, slots, 16 * sh.dec);
+  sh.n_done = merge ? sh.cap : 0;
+  sh.done_off = kDecEnt + 4 * sh.cap;
+  return sh;
 }
 
 WsPlanShape ffn_ws_plan_shape(int rows, int slots, int nf, int chunk_frags, bool merge) {
-  WsPlanShape sh;
+  WsPlanShape sh{};
   sh.nf = nf;
   sh.bt = 32 * (chunk_frags >= 1 && chunk_frags <= nf ? chunk_frags : nf);
   sh.ch = ws_entry_chunks(rows, slots, sh.bt);
@@ -969,6 +984,7 @@ WsPlanShape ffn_ws_plan_shape(int rows, int slots, int nf, int chunk_frags, bool
 
 int launch_ffn_ws_plan(const int32_t* counts, const int32_t* offsets, int P, int S, int T, int rows_routed, const WsPlanShape& sh,
                        int32_t* plan, hipStream_t st) {
+  if (sh.dec) return launch_ffn_dec_plan(counts, offsets, P, S, T, rows_routed, sh, plan, st);
   hipLaunchKernelGGL(k_plan_ws, dim3(1), dim3(512), 0, st, counts, offsets, P, S, T, rows_routed, sh, plan);
   EW_LAUNCH_CHECK("k_plan_ws");
   return EW_OK;
@@ -1001,6 +1017,7 @@ int launch_ffn_ws(const void* x, int rows_routed, int k, int H, int I, int P, in
     const int rc = launch_ffn_ws_plan(counts, offsets, P, S, T, rows_routed, sh, plan, st);
     if (rc != EW_OK) return rc;
   }
+  if (sh.dec) return launch_ffn_dec(x, rows_routed, k, H, I, P, S, sh, por, w13, w2, w13_sh, w2_sh, act, y, plan, n_cu, st);
   const int max_active = slots < rows ? slots : rows;
   const int max_tiles = rows / bt + max_active;
   WsArgs a{};

@@ -58,6 +58,8 @@ struct WsPlanShape {
   int cap;       // entries per list at most
   int n_done;    // completion counters behind the lists, one per sorted row (0: the two products run as two launches)
   int done_off;  // where they start, in ints from the start of the plan
+  int dec;       // > 0: the decode kernel (k_ffn_dec) with chunks of 16 * dec rows and the flat plan below; cap = its chunks at
+                 // most, n_done > 0 if the products share a launch
 };
 
 // Builds the plan from the slots' counts and offsets.  Slots P .. P+S-1 are the shared experts of the call, if any:
@@ -185,6 +187,76 @@ __device__ __forceinline__ void ws_plan_build(const int32_t* counts, const int32
     plan[16 + x] = 0;
     plan[24 + x] = 0;
   }
+}
+
+// Plan of the decode kernel (k_ffn_dec): a flat list of row chunks, the shared experts' first (theirs are the ones with
+// more than one chunk), then the active routed slots in slot order.  Units are (chunk, group of weight rows), numbered by
+// chunk, so nothing else has to be written down.
+//   plan[0]                chunks
+//   plan[kDecCtr + kDecCtrStride i]       claim counters, one cache line each (zeroed here, every call)
+//   plan[kDecEnt + 4 c]                   slot, rows, first sorted row, unused
+//   plan[done_off + kDecDoneStride c]     first-product units of chunk c that are stored (zeroed here)
+constexpr int kDecCtr = 32, kDecCtrStride = 32;
+constexpr int kDecEnt = kDecCtr + 16 * kDecCtrStride;
+constexpr int kDecDoneStride = 16;
+
+__host__ __device__ inline int dec_chunks(int c, int bt) { return (c + bt - 1) / bt; }
+
+struct DecPlanLds {
+  int32_t wtot[8];
+};
+
+// Called by every thread of a block of at least 512 threads (barriers); `have` as for ws_plan_build.
+__device__ __forceinline__ void dec_plan_build(const int32_t* counts, const int32_t* offsets, int P, int S, int sh_rows, int sh_first,
+                                               const WsPlanShape sh, int32_t* __restrict__ plan, DecPlanLds& L,
+                                               const int32_t* have = nullptr) {
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int bt = 16 * sh.dec;
+  const int sh_chunks = dec_chunks(sh_rows, bt);
+  int c[4], o[4], mine = 0;
+  if (tid < 512) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {  // thread t owns slots 4t .. 4t+3: thread order is slot order
+      const int sl = 4 * tid + i;
+      c[i] = sl < P ? (have ? have[i] : counts[sl]) : 0;
+      o[i] = sl < P ? (have ? have[4 + i] : offsets[sl]) : 0;
+      mine += dec_chunks(c[i], bt);
+    }
+    const int inc = (int)wave_incl_scan_u32((uint32_t)mine);
+    if (lane == 63) L.wtot[wave] = inc;
+    mine = inc - mine;
+  }
+  __syncthreads();
+  int before = S * sh_chunks, total = before;
+#pragma unroll
+  for (int w = 0; w < 8; ++w) {
+    const int t = L.wtot[w];
+    if (w < wave) before += t;
+    total += t;
+  }
+  auto put = [&](int at, int slot, int rows, int first) {
+    const int n = dec_chunks(rows, bt), bts = ((rows + n - 1) / n + 15) & ~15;
+    for (int j = 0; j < n; ++j) {
+      int32_t* en = plan + kDecEnt + 4 * (at + j);
+      en[0] = slot;
+      en[1] = min(bts, rows - j * bts);
+      en[2] = first + j * bts;
+    }
+  };
+  if (tid < 512) {
+    int at = before + mine;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (c[i] > 0) {
+        put(at, 4 * tid + i, c[i], o[i]);
+        at += dec_chunks(c[i], bt);
+      }
+    if (tid >= 512 - 64)  // the last wave: it has no routed slot below 1792 of them
+      for (int s = tid - (512 - 64); s < S; s += 64) put(s * sh_chunks, P + s, sh_rows, sh_first + s * sh_rows);
+  }
+  for (int i = tid; i < total; i += blockDim.x) plan[sh.done_off + kDecDoneStride * i] = 0;
+  if (tid < 16) plan[kDecCtr + kDecCtrStride * tid] = 0;
+  if (tid == 0) plan[0] = total;
 }
 
 }  // namespace ew

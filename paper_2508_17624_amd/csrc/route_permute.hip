@@ -303,6 +303,7 @@ __global__ __launch_bounds__(1024) void k_small(const float* __restrict__ logits
   __shared__ union Lds {
     Perm perm;
     ew::WsPlanLds plan;  // after the scatter
+    ew::DecPlanLds dec;
   } lds;
   uint16_t (&s_slot)[kSmallPairs] = lds.perm.slot;
   uint16_t (&s_rank)[kSmallPairs] = lds.perm.rank;
@@ -403,7 +404,8 @@ __global__ __launch_bounds__(1024) void k_small(const float* __restrict__ logits
       }
     }
     __syncthreads();  // the permutation's LDS arrays are dead
-    ew::ws_plan_build(counts, offsets, P, fp.S, T, n, fp.shape, fp.plan, lds.plan, have);
+    if (fp.shape.dec) ew::dec_plan_build(counts, offsets, P, fp.S, T, n, fp.shape, fp.plan, lds.dec, have);
+    else ew::ws_plan_build(counts, offsets, P, fp.S, T, n, fp.shape, fp.plan, lds.plan, have);
   }
 }
 

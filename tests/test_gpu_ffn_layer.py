@@ -584,3 +584,39 @@ def test_grouped_ffn_f32_tile_edges(ew, H, I):
     for s in np.nonzero(counts)[0]:
         r0, r1 = offsets[s], offsets[s + 1]
         assert rel_l2(got[r0:r1], moe.expert_ffn(x[por[r0:r1]], w13[s], w2[s])) <= 1e-5, f"slot {s}"
+
+
+@pytest.mark.parametrize("T,k,P,S,H,I", [(1, 1, 3, 0, 256, 256), (2, 6, 16, 2, 2048, 1408), (16, 4, 200, 1, 384, 256), (17, 4, 40, 2, 640, 256),
+                                         (32, 3, 9, 0, 256, 384), (33, 2, 12, 2, 1280, 512), (64, 6, 100, 1, 512, 256), (65, 6, 30, 2, 256, 768),
+                                         (130, 4, 24, 2, 384, 256), (513, 2, 16, 1, 512, 256)])
+def test_grouped_ffn_decode_kernel_edges(ew, T, k, P, S, H, I):
+    """The kernel of calls with few rows per slot at the edges of its chunks (16, 32, 64 and 128 rows), with contractions
+    shorter than its rings, hidden sizes that are an odd multiple of 128, a crowded slot cut into several chunks and more
+    workgroups than units: every row against the oracle's expert FFN, twice, the same bits both times."""
+    rng = np.random.default_rng(T * 7 + H)
+    ids = np.stack([rng.choice(P, k, replace=False) for _ in range(T)]).astype(np.int32)
+    ids[:, 0] = np.where(rng.random(T) < 0.6, 1, ids[:, 0])               # a repeat inside a token is fine here
+    flat = ids.reshape(-1)
+    por = np.argsort(flat, kind="stable").astype(np.int32)
+    counts = np.bincount(flat, minlength=P).astype(np.int32)
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    dev = lambda a: torch.from_numpy(a).cuda()
+    bf = lambda *shape, scale=1.0: (torch.from_numpy(rng.standard_normal(shape, dtype=np.float32)) * scale).cuda().bfloat16()
+    x, w13, w2 = bf(T, H), bf(P, 2 * I, H, scale=0.04), bf(P, H, I, scale=0.04)
+    w13[torch.from_numpy(counts == 0).cuda()] = float("nan")
+    if S:
+        s13, s2 = bf(S, 2 * I, H, scale=0.04), bf(S, H, I, scale=0.04)
+        run = lambda: ew.moe_grouped_ffn_with_shared(x, k, I, P, dev(counts), dev(offsets), dev(por), w13, w2, s13, s2)
+    else:
+        run = lambda: ew.moe_grouped_ffn(x, k, I, P, dev(counts), dev(offsets), dev(por), w13, w2)
+    y = run()
+    assert torch.equal(y, run())
+    got, xs = to_f64(y), to_f64(x)
+    for s in np.nonzero(counts)[0]:
+        r0, r1 = offsets[s], offsets[s + 1]
+        ref = moe.expert_ffn(xs[por[r0:r1] // k], to_f64(w13[s]), to_f64(w2[s]))
+        assert rel_l2(got[r0:r1], ref) <= FFN_REL_L2 and max_abs(got[r0:r1], ref) <= FFN_MAX_ABS, f"slot {s}"
+    for s in range(S):
+        ref = moe.expert_ffn(xs, to_f64(s13[s]), to_f64(s2[s]))
+        blk = got[T * k + s * T:T * k + (s + 1) * T]
+        assert rel_l2(blk, ref) <= FFN_REL_L2 and max_abs(blk, ref) <= FFN_MAX_ABS, f"shared expert {s}"
