@@ -82,6 +82,10 @@ int launch_ffn_dec_plan(const int32_t* counts, const int32_t* offsets, int P, in
 int launch_ffn_dec(const void* x, int rows_routed, int k, int H, int I, int P, int S, const WsPlanShape& sh, const int32_t* por,
                    const void* w13, const void* w2, const void* w13_sh, const void* w2_sh, void* act, void* y, int32_t* plan, int n_cu,
                    hipStream_t st);
+// ffn_big.hip: the calls with many rows per slot; max_chunks: row chunks of the plan at most.
+int launch_ffn_big(const void* x, int rows_routed, int k, int H, int I, int P, int S, const WsPlanShape& sh, int max_chunks, const int32_t* por,
+                   const void* w13, const void* w2, const void* w13_sh, const void* w2_sh, void* act, void* y, int32_t* plan, int n_cu,
+                   hipStream_t st);
 WsPlanShape ffn_dec_plan_shape(int T, int rows, int slots, bool merge);
 
 // Whether moe_grouped_ffn / moe_grouped_ffn_with_shared with these dimensions runs the weight-stationary kernel, and

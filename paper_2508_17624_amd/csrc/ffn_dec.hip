@@ -31,19 +31,11 @@
 // product: row m = 4 q + r of fragment i is feature 16 pair + 4 q + 2 i + (r & 1), gate for r < 2 and up for r >= 2: a lane
 // holds gate and up of four consecutive features, SwiGLU needs no exchange and 8 bytes are stored.  Second product: feature
 // 32 pair + 8 q + 4 i + r, 16 bytes.  (With one fragment per wave and half the width the stores alone cost 5 to 8 %.)
-#include "ew_internal.h"
-
-#include <type_traits>
+#include "ffn_roles.h"
 
 namespace ew {
 
 namespace {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
-
 
 // NTF: 16-row token fragments per chunk; MR: weight rows per unit.
 template <int NTF, int MR>
@@ -74,78 +66,6 @@ struct DecCfg {
   static constexpr int LDS = Q_OFF + 4 * QI * 4;
   static_assert(LDS <= 160 * 1024 && DW * WSLAB >= 80 * 1024, "LDS budget of a CU, bytes in flight");
 };
-
-struct DecProd {
-  const uint16_t* x;   // first product: tokens [*, K]; second: activations [rows, K]
-  const uint16_t* w;   // slots 0 .. P-1
-  const uint16_t* w_sh;
-  uint16_t* out;       // [rows, NOUT]
-  size_t slot_stride;  // elements per slot
-  int K, NOUT, G;      // G: units per chunk
-};
-
-struct DecArgs {
-  DecProd m[2];
-  const int32_t* por;   // row map of the first product; may be NULL
-  int32_t* plan;
-  int32_t* done;        // per chunk: first-product units stored
-  int P, rows_routed, sh_rows, k;
-  int first_mode, last_mode;  // the launch's products
-  int depth_w, depth_t;
-  unsigned int spin_ticks;
-};
-
-__device__ __forceinline__ uint16_t f32_to_bf16(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
-__device__ __forceinline__ float silu_f32(float g) { return g * __builtin_amdgcn_rcpf(1.f + __expf(-g)); }
-
-struct DecUnit {
-  int slot, off, rows, g, mode, chunk, ready;  // slot < 0: no unit left
-};
-
-// LDS reads the compiler must not see (it would wait for every LDS-direct load in flight before them).
-__device__ __forceinline__ DecUnit read_unit(uint32_t addr) {
-  i32x4 lo, hi;
-  asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %2 offset:16\n\ts_waitcnt lgkmcnt(0)" : "=&v"(lo), "=&v"(hi) : "v"(addr) : "memory");
-  DecUnit u;
-  u.slot = __builtin_amdgcn_readfirstlane(lo[0]);
-  u.off = __builtin_amdgcn_readfirstlane(lo[1]);
-  u.rows = __builtin_amdgcn_readfirstlane(lo[2]);
-  u.g = __builtin_amdgcn_readfirstlane(lo[3]);
-  u.mode = __builtin_amdgcn_readfirstlane(hi[0]);
-  u.chunk = __builtin_amdgcn_readfirstlane(hi[1]);
-  u.ready = __builtin_amdgcn_readfirstlane(hi[2]);
-  return u;
-}
-// N ints STEP bytes apart (N: 1, 2 or a multiple of 4).
-template <int N, int STEP>
-__device__ __forceinline__ void read_lds_ints(uint32_t addr, uint32_t* r) {
-  if constexpr (N == 1)
-    asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(r[0]) : "v"(addr) : "memory");
-  else if constexpr (N == 2)
-    asm volatile("ds_read_b32 %0, %2\n\tds_read_b32 %1, %2 offset:%3\n\ts_waitcnt lgkmcnt(0)" : "=&v"(r[0]), "=&v"(r[1]) : "v"(addr), "n"(STEP) : "memory");
-  else {
-    asm volatile("ds_read_b32 %0, %4\n\tds_read_b32 %1, %4 offset:%5\n\tds_read_b32 %2, %4 offset:%6\n\tds_read_b32 %3, %4 offset:%7\n\ts_waitcnt lgkmcnt(0)"
-                 : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]) : "v"(addr), "n"(STEP), "n"(2 * STEP), "n"(3 * STEP) : "memory");
-    if constexpr (N > 4) read_lds_ints<N - 4, STEP>(addr + 4 * STEP, r + 4);
-  }
-}
-
-// At most n vector-memory operations of this wave still outstanding (n is wave-uniform; waiting for fewer is safe).
-__device__ __forceinline__ void wait_vm_upto(int n) {
-#define EW_VM(N) __builtin_amdgcn_s_waitcnt(0x0F70 | ((N) & 15) | (((N) >> 4) << 14))
-  if (n >= 32) {
-    EW_VM(32);
-  } else if (n >= 16) {
-    if (n >= 24) EW_VM(24); else if (n >= 20) EW_VM(20); else EW_VM(16);
-  } else if (n >= 8) {
-    if (n >= 12) EW_VM(12); else if (n >= 10) EW_VM(10); else EW_VM(8);
-  } else if (n >= 4) {
-    if (n >= 6) EW_VM(6); else if (n >= 5) EW_VM(5); else EW_VM(4);
-  } else {
-    if (n >= 3) EW_VM(3); else if (n >= 2) EW_VM(2); else if (n >= 1) EW_VM(1); else EW_VM(0);
-  }
-#undef EW_VM
-}
 
 // Operands of one k-step (32 elements): MFW weight fragments WS bytes apart and NB token fragments FS bytes apart, issued
 // without waiting.
@@ -207,7 +127,7 @@ __device__ __forceinline__ void mul_slab(uint32_t wa, uint32_t tb, f32x4 (&acc)[
 }
 // First slab of a unit's walk over K: a function of the unit alone (results do not depend on who computes it) that keeps
 // workgroups streaming neighbouring units in step off the same memory channels.
-__device__ __forceinline__ int first_slab(const DecUnit& u, int nk) { return (u.slot * 5 + u.g * 3) % nk; }
+__device__ __forceinline__ int first_slab(const FfnUnit& u, int nk) { return (u.slot * 5 + u.g * 3) % nk; }
 
 // ------------------------------------------------------------------------------------------
 // The scheduling wave.  Unit u of a product belongs to list u % 8.
@@ -219,13 +139,13 @@ struct Sched {
   uint32_t src[2];       // byte offsets of the source rows lane, lane + 64 of the chunk
 };
 
-__device__ __forceinline__ int32_t* sched_counter(const DecArgs& a, int mode, int list) {
+__device__ __forceinline__ int32_t* sched_counter(const FfnArgs& a, int mode, int list) {
   return a.plan + kDecCtr + (mode * 8 + list) * kDecCtrStride;
 }
-__device__ __forceinline__ void sched_claim(const DecArgs& a, Sched& s) {
+__device__ __forceinline__ void sched_claim(const FfnArgs& a, Sched& s) {
   if ((threadIdx.x & 63) == 0 && s.mode <= a.last_mode) s.w = __hip_atomic_fetch_add(sched_counter(a, s.mode, s.list), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ void sched_entry(const DecArgs& a, int n_chunks, Sched& s) {
+__device__ __forceinline__ void sched_entry(const FfnArgs& a, int n_chunks, Sched& s) {
   const int lane = threadIdx.x & 63;
   for (;;) {
     if (s.mode > a.last_mode) {
@@ -255,7 +175,7 @@ __device__ __forceinline__ void sched_entry(const DecArgs& a, int n_chunks, Sche
   }
 }
 template <int QI>
-__device__ __forceinline__ void sched_rows(const DecArgs& a, Sched& s) {
+__device__ __forceinline__ void sched_rows(const FfnArgs& a, Sched& s) {
   if (s.chunk < 0) return;
   const int slot = s.en[0], rows = s.en[1], off = s.en[2];
 #pragma unroll
@@ -267,7 +187,7 @@ __device__ __forceinline__ void sched_rows(const DecArgs& a, Sched& s) {
   }
 }
 template <int QI>
-__device__ __forceinline__ void sched_publish(const DecArgs& a, const Sched& s, int32_t* q) {
+__device__ __forceinline__ void sched_publish(const FfnArgs& a, const Sched& s, int32_t* q) {
   const int lane = threadIdx.x & 63;
   if (s.chunk < 0) {
     if (lane == 0) q[0] = -1;
@@ -284,7 +204,7 @@ __device__ __forceinline__ void sched_publish(const DecArgs& a, const Sched& s, 
 
 // ROLE 0: weight wave, 1: token wave, 2: scheduler, 3: multiplying wave.  All roles execute the same number of barriers.
 template <int NTF, int MR, int ROLE>
-__device__ __forceinline__ void dec_body(const DecArgs& a, unsigned char* s_lds) {
+__device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds) {
   using C = DecCfg<NTF, MR>;
   constexpr int kShift = MR == 64 ? 7 : 6;                                    // log2 of a slab's contraction elements
   const int lane = threadIdx.x & 63;
@@ -309,9 +229,9 @@ __device__ __forceinline__ void dec_body(const DecArgs& a, unsigned char* s_lds)
     sched_publish<C::QI>(a, sc, queue);
   }
   __builtin_amdgcn_s_barrier();
-  DecUnit cur = read_unit(q0);
+  FfnUnit cur = read_unit(q0);
   if (cur.slot < 0) return;
-  DecUnit nxt{-1, 0, 0, 0, 0, 0, 0};
+  FfnUnit nxt{-1, 0, 0, 0, 0, 0, 0, 0};
 
   // ---- the loading side: position in the stream of slabs
   // Instruction i of a loading wave covers LDS rows (i * waves + lw) * RPI + lane / (64 / RPI).  pm: that row of a 16-row
@@ -325,8 +245,8 @@ __device__ __forceinline__ void dec_body(const DecArgs& a, unsigned char* s_lds)
   int p_k = 0, p_nk = 1, p_rot = 0, p_nld = 0, p_mode = 0;
   int p_slot = 0;                                                             // ring slot of the next slab
   bool p_next = false;                                                        // the loading unit is `nxt`
-  auto aim = [&](const DecUnit& u, [[maybe_unused]] int qi) {
-    const DecProd& m = u.mode ? a.m[1] : a.m[0];
+  auto aim = [&](const FfnUnit& u, [[maybe_unused]] int qi) {
+    const FfnProd& m = u.mode ? a.m[1] : a.m[0];
     p_k = 0;
     p_nk = m.K >> kShift;
     p_rot = first_slab(u, p_nk);
@@ -381,7 +301,7 @@ __device__ __forceinline__ void dec_body(const DecArgs& a, unsigned char* s_lds)
     ++p_k;
     p_slot = p_slot + 1 == depth ? 0 : p_slot + 1;
   };
-  auto wait_done = [&](const DecUnit& u) {  // token waves: the unit's activation rows are stored
+  auto wait_done = [&](const FfnUnit& u) {  // token waves: the unit's activation rows are stored
     if (u.mode == 0 || u.ready) return;
     const int32_t* flag = a.done + u.chunk * kDecDoneStride;
     const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
@@ -415,7 +335,7 @@ __device__ __forceinline__ void dec_body(const DecArgs& a, unsigned char* s_lds)
   nxt = read_unit(q0 + C::QI * 4);
 
   for (;;) {
-    const DecProd& m = cur.mode ? a.m[1] : a.m[0];
+    const FfnProd& m = cur.mode ? a.m[1] : a.m[0];
     const int nk = m.K >> kShift;
     const bool change = nxt.slot >= 0 && nxt.mode != cur.mode;
     [[maybe_unused]] const int nld = (cur.rows + 15) >> 4;                    // live token fragments
@@ -524,7 +444,7 @@ __device__ __forceinline__ void dec_body(const DecArgs& a, unsigned char* s_lds)
 }
 
 template <int NTF, int MR>
-__global__ __launch_bounds__((DecCfg<NTF, MR>::THREADS)) void k_ffn_dec(DecArgs a) {
+__global__ __launch_bounds__((DecCfg<NTF, MR>::THREADS)) void k_ffn_dec(FfnArgs a) {
   __shared__ __align__(1024) unsigned char s_lds[DecCfg<NTF, MR>::LDS];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   using C = DecCfg<NTF, MR>;
@@ -541,7 +461,7 @@ __global__ __launch_bounds__(512) void k_plan_dec(const int32_t* __restrict__ co
 }
 
 template <int NTF, int MR>
-int launch(DecArgs a, bool merged, int max_chunks, int n_cu, hipStream_t st) {
+int launch(FfnArgs a, bool merged, int max_chunks, int n_cu, hipStream_t st) {
   using C = DecCfg<NTF, MR>;
   a.m[0].G = a.m[0].NOUT / (MR / 2);
   a.m[1].G = a.m[1].NOUT / MR;
@@ -571,9 +491,9 @@ int launch_ffn_dec(const void* x, int rows_routed, int k, int H, int I, int P, i
                    const void* w13, const void* w2, const void* w13_sh, const void* w2_sh, void* act, void* y, int32_t* plan, int n_cu,
                    hipStream_t st) {
   const int T = rows_routed / k;
-  DecArgs a{};
-  a.m[0] = DecProd{(const uint16_t*)x, (const uint16_t*)w13, (const uint16_t*)w13_sh, (uint16_t*)act, (size_t)2 * I * H, H, I, 0};
-  a.m[1] = DecProd{(const uint16_t*)act, (const uint16_t*)w2, (const uint16_t*)w2_sh, (uint16_t*)y, (size_t)H * I, I, H, 0};
+  FfnArgs a{};
+  a.m[0] = FfnProd{(const uint16_t*)x, (const uint16_t*)w13, (const uint16_t*)w13_sh, (uint16_t*)act, (size_t)2 * I * H, H, I, 0};
+  a.m[1] = FfnProd{(const uint16_t*)act, (const uint16_t*)w2, (const uint16_t*)w2_sh, (uint16_t*)y, (size_t)H * I, I, H, 0};
   a.por = por; a.plan = plan; a.done = plan + sh.done_off;
   a.P = P; a.rows_routed = rows_routed; a.sh_rows = T > 0 ? T : 1; a.k = k;
   a.spin_ticks = 20000000u;  // 0.2 s
@@ -581,7 +501,7 @@ int launch_ffn_dec(const void* x, int rows_routed, int k, int H, int I, int P, i
   // 84 small experts 111 -> 101 us.  Only where even 64-row units leave a compute unit no more than two of the first
   // product (one token: 8 experts) does the finer split win: 44 -> 42 us.
   const bool fine = sh.dec == 1 && (long long)sh.cap * (I / 32) <= 2 * n_cu;
-  const bool merged = sh.n_done > 0;
+  const bool merged = sh.merged != 0;
   switch (sh.dec) {
     case 1: return fine ? launch<1, 64>(a, merged, sh.cap, n_cu, st) : launch<1, 128>(a, merged, sh.cap, n_cu, st);
     case 2: return launch<2, 128>(a, merged, sh.cap, n_cu, st);

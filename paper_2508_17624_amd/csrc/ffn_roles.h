@@ -1,0 +1,95 @@
+// Pieces shared by the grouped-FFN kernels whose loading, scheduling and multiplying are different waves (ffn_dec.hip,
+// ffn_big.hip): argument structs, LDS accesses and waits placed by hand.
+#pragma once
+#include "ew_internal.h"
+
+#include <type_traits>
+
+namespace ew {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+
+struct FfnProd {
+  const uint16_t* x;   // first product: tokens [*, K]; second: activations [rows, K]
+  const uint16_t* w;   // slots 0 .. P-1
+  const uint16_t* w_sh;
+  uint16_t* out;       // [rows, NOUT]
+  size_t slot_stride;  // elements per slot
+  int K, NOUT, G;      // G: units per chunk
+};
+
+struct FfnArgs {
+  FfnProd m[2];
+  const int32_t* por;   // row map of the first product; may be NULL
+  int32_t* plan;
+  int32_t* done;        // per chunk: first-product units stored
+  int P, rows_routed, sh_rows, k;
+  int first_mode, last_mode;  // the launch's products
+  int depth_w, depth_t;       // k_ffn_dec: slabs in its rings
+  int cap, list_chunks;       // k_ffn_big: entries and chunks per list of the plan at most
+  unsigned int spin_ticks;
+};
+
+__device__ __forceinline__ uint16_t f32_to_bf16(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
+__device__ __forceinline__ float silu_f32(float g) { return g * __builtin_amdgcn_rcpf(1.f + __expf(-g)); }
+
+struct FfnUnit {
+  int slot, off, rows, g, mode, chunk, ready, alone;  // slot < 0: no unit left
+};
+
+// 16 bytes written through to the point of coherence of the GPU's XCDs (an agent-scope store; the language's go to 8 bytes).
+__device__ __forceinline__ void store_agent_16(void* p, u32x4 v) {
+  asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");  // (nop: the data registers may be written next)
+}
+
+// LDS reads the compiler must not see (it would wait for every LDS-direct load in flight before them).
+__device__ __forceinline__ FfnUnit read_unit(uint32_t addr) {
+  i32x4 lo, hi;
+  asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %2 offset:16\n\ts_waitcnt lgkmcnt(0)" : "=&v"(lo), "=&v"(hi) : "v"(addr) : "memory");
+  FfnUnit u;
+  u.slot = __builtin_amdgcn_readfirstlane(lo[0]);
+  u.off = __builtin_amdgcn_readfirstlane(lo[1]);
+  u.rows = __builtin_amdgcn_readfirstlane(lo[2]);
+  u.g = __builtin_amdgcn_readfirstlane(lo[3]);
+  u.mode = __builtin_amdgcn_readfirstlane(hi[0]);
+  u.chunk = __builtin_amdgcn_readfirstlane(hi[1]);
+  u.ready = __builtin_amdgcn_readfirstlane(hi[2]);
+  u.alone = __builtin_amdgcn_readfirstlane(hi[3]);
+  return u;
+}
+// N ints STEP bytes apart (N: 1, 2 or a multiple of 4).
+template <int N, int STEP>
+__device__ __forceinline__ void read_lds_ints(uint32_t addr, uint32_t* r) {
+  if constexpr (N == 1)
+    asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(r[0]) : "v"(addr) : "memory");
+  else if constexpr (N == 2)
+    asm volatile("ds_read_b32 %0, %2\n\tds_read_b32 %1, %2 offset:%3\n\ts_waitcnt lgkmcnt(0)" : "=&v"(r[0]), "=&v"(r[1]) : "v"(addr), "n"(STEP) : "memory");
+  else {
+    asm volatile("ds_read_b32 %0, %4\n\tds_read_b32 %1, %4 offset:%5\n\tds_read_b32 %2, %4 offset:%6\n\tds_read_b32 %3, %4 offset:%7\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]) : "v"(addr), "n"(STEP), "n"(2 * STEP), "n"(3 * STEP) : "memory");
+    if constexpr (N > 4) read_lds_ints<N - 4, STEP>(addr + 4 * STEP, r + 4);
+  }
+}
+
+// At most n vector-memory operations of this wave still outstanding (n is wave-uniform; waiting for fewer is safe).
+__device__ __forceinline__ void wait_vm_upto(int n) {
+#define EW_VM(N) __builtin_amdgcn_s_waitcnt(0x0F70 | ((N) & 15) | (((N) >> 4) << 14))
+  if (n >= 32) {
+    EW_VM(32);
+  } else if (n >= 16) {
+    if (n >= 24) EW_VM(24); else if (n >= 20) EW_VM(20); else EW_VM(16);
+  } else if (n >= 8) {
+    if (n >= 12) EW_VM(12); else if (n >= 10) EW_VM(10); else EW_VM(8);
+  } else if (n >= 4) {
+    if (n >= 6) EW_VM(6); else if (n >= 5) EW_VM(5); else EW_VM(4);
+  } else {
+    if (n >= 3) EW_VM(3); else if (n >= 2) EW_VM(2); else if (n >= 1) EW_VM(1); else EW_VM(0);
+  }
+#undef EW_VM
+}
+
+}  // namespace ew

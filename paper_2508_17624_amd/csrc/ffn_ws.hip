@@ -957,7 +957,9 @@ static int dec_frags(int T) { return T <= 16 ? 1 : T <= 32 ? 2 : T <= 64 ? 4 : 8
 static int dec_chunk_cap(int rows, int P, int bt) { return (P < rows ? P : rows) + rows / bt + 1; }
 
 size_t ffn_ws_plan_ints(int T, int rows, int P) {
-  const size_t ws = (size_t)kPlanHdr + (size_t)8 * kEnt * ws_list_cap(rows, P) + (size_t)(rows < kMergeMaxRows ? rows : kMergeMaxRows);
+  const int cap = ws_list_cap(rows, P);
+  const size_t big_done = (size_t)8 * ws_entry_chunks(rows, P, 32) * cap, ws_done = (size_t)(rows < kMergeMaxRows ? rows : kMergeMaxRows);
+  const size_t ws = (size_t)kPlanHdr + (size_t)8 * kEnt * cap + (big_done > ws_done ? big_done : ws_done);
   const size_t dec = (size_t)kDecEnt + (size_t)(4 + kDecDoneStride) * dec_chunk_cap(rows, P, 16 * dec_frags(T));
   return ws > dec ? ws : dec;
 }
@@ -966,7 +968,7 @@ WsPlanShape ffn_dec_plan_shape(int T, int rows, int slots, bool merge) {
   WsPlanShape sh{};
   sh.dec = dec_frags(T);
   sh.cap = dec_chunk_cap(rows, slots, 16 * sh.dec);
-  sh.n_done = merge ? sh.cap : 0;
+  sh.merged = merge;
   sh.done_off = kDecEnt + 4 * sh.cap;
   return sh;
 }
@@ -977,7 +979,13 @@ WsPlanShape ffn_ws_plan_shape(int rows, int slots, int nf, int chunk_frags, bool
   sh.bt = 32 * (chunk_frags >= 1 && chunk_frags <= nf ? chunk_frags : nf);
   sh.ch = ws_entry_chunks(rows, slots, sh.bt);
   sh.cap = ws_list_cap(rows, slots);
-  sh.n_done = merge && nf < 8 && rows <= kMergeMaxRows ? rows : 0;
+  sh.big = nf == 8;
+  if (sh.big) {
+    sh.merged = merge;
+    sh.n_done = 8 * sh.ch * sh.cap;
+  } else {
+    sh.n_done = merge && rows <= kMergeMaxRows ? rows : 0;
+  }
   sh.done_off = kPlanHdr + 8 * kEnt * sh.cap;
   return sh;
 }
@@ -1018,6 +1026,9 @@ int launch_ffn_ws(const void* x, int rows_routed, int k, int H, int I, int P, in
     if (rc != EW_OK) return rc;
   }
   if (sh.dec) return launch_ffn_dec(x, rows_routed, k, H, I, P, S, sh, por, w13, w2, w13_sh, w2_sh, act, y, plan, n_cu, st);
+  if (sh.big)
+    return launch_ffn_big(x, rows_routed, k, H, I, P, S, sh, rows / bt + (slots < rows ? slots : rows), por, w13, w2, w13_sh, w2_sh, act, y, plan,
+                          n_cu, st);
   const int max_active = slots < rows ? slots : rows;
   const int max_tiles = rows / bt + max_active;
   WsArgs a{};

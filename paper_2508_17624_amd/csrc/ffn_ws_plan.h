@@ -25,11 +25,12 @@ namespace ew {
 //   plan[x]        x < 8   entries of list x
 //   plan[8 + x]            row chunks of list x
 //   plan[16 + x], plan[24 + x]   work counters of the two products (zeroed here, every call)
-//   plan[32 + 6 (x cap + e)] ...  entry e of list x: slot, chunks, chunks of the list before it,
+//   plan[kPlanHdr + 6 (x cap + e)] ...  entry e of list x: slot, chunks, chunks of the list before it,
 //                                 rows per chunk, rows of the entry, first row of the entry
 //   plan[done_off + r]     calls whose two products share a launch: waves that have stored their part of the
 //                          activation rows of the chunk that starts at sorted row r (zeroed here, every call)
-constexpr int kPlanHdr = 32;
+constexpr int kPlanCtr = 32, kPlanCtrStride = 32;  // claim counters of k_ffn_big, one cache line each: product 0's lists, then product 1's
+constexpr int kPlanHdr = kPlanCtr + 16 * kPlanCtrStride;
 constexpr int kEnt = 6;
 constexpr int kPlanMaxP = 2048;    // slots a plan can sort
 constexpr int kPlanMaxEnt = 4096;  // entries a plan can hold (the host picks ch accordingly)
@@ -58,8 +59,9 @@ struct WsPlanShape {
   int cap;       // entries per list at most
   int n_done;    // completion counters behind the lists, one per sorted row (0: the two products run as two launches)
   int done_off;  // where they start, in ints from the start of the plan
-  int dec;       // > 0: the decode kernel (k_ffn_dec) with chunks of 16 * dec rows and the flat plan below; cap = its chunks at
-                 // most, n_done > 0 if the products share a launch
+  int big;       // the 256-row kernel (k_ffn_big)
+  int merged;    // the two products share a launch
+  int dec;       // > 0: the decode kernel (k_ffn_dec) with chunks of 16 * dec rows and the flat plan below; cap = its chunks at most
 };
 
 // Builds the plan from the slots' counts and offsets.  Slots P .. P+S-1 are the shared experts of the call, if any:
@@ -186,6 +188,8 @@ __device__ __forceinline__ void ws_plan_build(const int32_t* counts, const int32
     plan[8 + x] = n_chunks;
     plan[16 + x] = 0;
     plan[24 + x] = 0;
+    plan[kPlanCtr + x * kPlanCtrStride] = 0;
+    plan[kPlanCtr + (8 + x) * kPlanCtrStride] = 0;
   }
 }
 
