@@ -1,9 +1,6 @@
 // Grouped SwiGLU expert FFN for calls with many rows per slot on gfx950: 256 weight rows x up to 256 token rows per unit.
 #include "ffn_roles.h"
 
-#ifndef EW_WAUX
-#define EW_WAUX 16
-#endif
 namespace ew {
 
 namespace {
@@ -290,28 +287,26 @@ __device__ __forceinline__ void big_body(const FfnArgs& a, unsigned char* s_lds)
     if constexpr (ROLE == 0) {
       const int half = p_h & 1;
       const unsigned char* src = p_base + (size_t)(p_h >> 1) * 128 + (half && !p_part ? 2 * p_wr : 0u);
-      unsigned char* dst = s_lds + p_slot * kHalf + lw * 1024;
+      const uint32_t dst = lds0 + p_slot * kHalf + lw * 1024;
       auto load = [&](auto aux) {
 #pragma unroll
         for (int n = 0; n < 8; ++n)
-          __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + ((n & 1) * p_up + ((n >> 1) & 1) * p_i + (n >> 2) * p_wr) + p_w),
-                                           (__attribute__((address_space(3))) void*)(dst + n * 2048), 16, 0, decltype(aux)::value);
+          load_to_lds<decltype(aux)::value>(src + ((n & 1) * p_up + ((n >> 1) & 1) * p_i + (n >> 2) * p_wr), p_w, dst + n * 2048);
       };
       // Cache policy: weights that one chunk alone reads stream past the caches (nt), others are kept for the chunks beside
       // it (sc1).
       if (p_alone) load(std::integral_constant<int, 2>{});
-      else load(std::integral_constant<int, EW_WAUX>{});
+      else load(std::integral_constant<int, 16>{});
       p_slot = p_slot + 1 == kWRing ? 0 : p_slot + 1;
     } else if constexpr (ROLE == 1) {
       const unsigned char* src = p_base + (size_t)p_h * 128;
-      unsigned char* dst = s_lds + kTOff + p_slot * kTSlab;
+      const uint32_t dst = lds0 + kTOff + p_slot * kTSlab;
 #pragma unroll
       for (int f = 0; f < 8; ++f)
         if (f < p_nfl) {
 #pragma unroll
           for (int n = 4 * f; n < 4 * f + 4; ++n)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + p_off[n]),
-                                             (__attribute__((address_space(3))) void*)(dst + n * 1024), 16, 0, 0);
+            load_to_lds<0>(src, p_off[n], dst + n * 1024);
         }
       p_slot ^= 1;
     }

@@ -276,26 +276,21 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds)
     if (kk >= p_nk) kk -= p_nk;
     const unsigned char* src = p_base + (size_t)kk * C::RB;
     if constexpr (ROLE == 0) {
-      unsigned char* dst = s_lds + p_slot * C::WSLAB + lw * 1024;
+      const uint32_t dst = lds0 + p_slot * C::WSLAB + lw * 1024;
 #pragma unroll
       for (int i = 0; i < C::NWI; ++i) {
         constexpr int FPI = C::NW * C::RPI / 16;                              // fragments per round of instructions
         const uint32_t rows = 16 * (i * FPI % C::PN) + 2 * (i * FPI / C::PN); // see the fragment layout at the top
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + p_w + rows * p_ws),
-                                         (__attribute__((address_space(3))) void*)(dst + i * C::NW * 1024), 16, 0, 2);
+        load_to_lds<2>(src + rows * p_ws, p_w, dst + i * C::NW * 1024);
       }
     } else if constexpr (ROLE == 1) {
-      unsigned char* dst = s_lds + C::DW * C::WSLAB + p_slot * C::TSLAB + lw * 1024;
+      const uint32_t dst = lds0 + C::DW * C::WSLAB + p_slot * C::TSLAB + lw * 1024;
 #pragma unroll
       for (int i = 0; i < C::NTI * NTF; ++i)
         if (i < C::NTI * p_nld) {
           // second product: rows written by other workgroups of this launch, read at the point of coherence
-          if (p_mode)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + p_off[i]),
-                                             (__attribute__((address_space(3))) void*)(dst + i * C::NT * 1024), 16, 0, C::ACT_AUX);
-          else
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + p_off[i]),
-                                             (__attribute__((address_space(3))) void*)(dst + i * C::NT * 1024), 16, 0, 0);
+          if (C::ACT_AUX && p_mode) load_to_lds<C::ACT_AUX>(src, p_off[i], dst + i * C::NT * 1024);
+          else load_to_lds<0>(src, p_off[i], dst + i * C::NT * 1024);
         }
     }
     ++p_k;

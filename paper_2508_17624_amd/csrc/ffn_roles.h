@@ -41,6 +41,19 @@ struct FfnUnit {
   int slot, off, rows, g, mode, chunk, ready, alone;  // slot < 0: no unit left
 };
 
+// LDS-direct load: 16 bytes per lane from base + off (base: wave-uniform) to lds + 16 * lane.  AUX: 0 plain, 2 nt, 16 sc1.
+// Written out for its scalar base: given 64-bit lane addresses (which the compiler likes to compute ahead of a loop) the
+// same loads cost the 256-row kernel 5 %.  The loads are not seen by the compiler's own counting of outstanding ones.
+template <int AUX>
+__device__ __forceinline__ void load_to_lds(const unsigned char* base, uint32_t off, uint32_t lds) {
+  if constexpr (AUX == 2)
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(off), "s"(base), "s"(lds) : "memory");
+  else if constexpr (AUX == 16)
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 sc1" ::"v"(off), "s"(base), "s"(lds) : "memory");
+  else
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds) : "memory");
+}
+
 // 16 bytes written through to the point of coherence of the GPU's XCDs (an agent-scope store; the language's go to 8 bytes).
 __device__ __forceinline__ void store_agent_16(void* p, u32x4 v) {
   asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");  // (nop: the data registers may be written next)

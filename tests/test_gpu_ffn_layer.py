@@ -602,10 +602,10 @@ def test_grouped_ffn_decode_kernel_edges(ew, T, k, P, S, H, I):
     offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
     dev = lambda a: torch.from_numpy(a).cuda()
     bf = lambda *shape, scale=1.0: (torch.from_numpy(rng.standard_normal(shape, dtype=np.float32)) * scale).cuda().bfloat16()
-    x, w13, w2 = bf(T, H), bf(P, 2 * I, H, scale=0.04), bf(P, H, I, scale=0.04)
+    x, w13, w2 = bf(T, H), bf(P, 2 * I, H, scale=0.02), bf(P, H, I, scale=0.02)
     w13[torch.from_numpy(counts == 0).cuda()] = float("nan")
     if S:
-        s13, s2 = bf(S, 2 * I, H, scale=0.04), bf(S, H, I, scale=0.04)
+        s13, s2 = bf(S, 2 * I, H, scale=0.02), bf(S, H, I, scale=0.02)
         run = lambda: ew.moe_grouped_ffn_with_shared(x, k, I, P, dev(counts), dev(offsets), dev(por), w13, w2, s13, s2)
     else:
         run = lambda: ew.moe_grouped_ffn(x, k, I, P, dev(counts), dev(offsets), dev(por), w13, w2)
