@@ -425,15 +425,14 @@ int ew_probe_mfma_bf16(int workgroups, int iters, int random_operands, unsigned 
 
 /* Kernel selection of moe_grouped_ffn(bf16).  Every argument: 0 = automatic.
  *   path                1 = register-streaming kernel, 2 = LDS-tiled GEMM kernel,
- *                       3 = LDS-direct streaming kernel (the automatic choice wherever it applies)
+ *                       3 = the kernels with LDS-direct loads (the automatic choice wherever they apply)
  *   stream_token_tiles  path 1: 16-token tiles per slot chunk (1 or 2)
  *   stream_threads      path 1: threads per block (a multiple of 64, at most 512)
- *   ws_frags            path 3: kernel shape, 32-token fragments per row chunk (1, 2, 4 or 8)
+ *   ws_frags            path 3: kernel shape, 32-token fragments per row chunk (1, 2, 4: the kernel for
+ *                       few rows per slot; 8: the one for many)
  *   ws_chunk_frags      path 3: cap on the fragments per row chunk (1..ws_frags)
- *   ws_wait_ticks       path 3: longest rendezvous wait of a workgroup for the other workgroups of
- *                       its slot, in 10 ns ticks; 0 = never wait, negative = automatic
- *   ws_two_launches     path 3, decode shapes (ws_frags < 8): non-zero = the two products as two
- *                       launches, as the 256-row shape always runs them; 0 = one launch for both */
+ *   ws_wait_ticks       without effect (no kernel waits for other workgroups of its slot)
+ *   ws_two_launches     path 3: non-zero = the two products as two launches; 0 = one launch for both */
 void ew_tune_ffn(int path, int stream_token_tiles, int stream_threads, int ws_frags,
                  int ws_chunk_frags, int ws_wait_ticks, int ws_two_launches);
 

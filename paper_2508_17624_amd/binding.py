@@ -360,9 +360,8 @@ def tune_ffn(path: int = 0, stream_token_tiles: int = 0, stream_threads: int = 0
              ws_chunk_frags: int = 0, ws_wait_ticks: int = -1, ws_two_launches: bool = False):
     """Kernel-selection override of moe_grouped_ffn(bf16), process-global; no arguments = automatic.
     path 1 = register-streaming kernel (stream_token_tiles 1|2, stream_threads), 2 = LDS-tiled GEMM kernel,
-    3 = LDS-direct streaming kernel (ws_frags 1|2|4|8 = kernel shape, ws_chunk_frags = cap on 32-row fragments
-    per row chunk, ws_wait_ticks = rendezvous wait in 10 ns ticks, 0 = never, negative = automatic,
-    ws_two_launches = decode shapes run their two products as two launches instead of one)."""
+    3 = LDS-direct kernels (ws_frags 1|2|4|8 = kernel shape, ws_chunk_frags = cap on 32-row fragments
+    per row chunk, ws_two_launches = the two products as two launches; ws_wait_ticks has no effect)."""
     lib().ew_tune_ffn(path, stream_token_tiles, stream_threads, ws_frags, ws_chunk_frags, ws_wait_ticks, int(ws_two_launches))
 
 

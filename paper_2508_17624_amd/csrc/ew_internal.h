@@ -9,7 +9,7 @@
 
 #include "expertweave.h"
 
-#include "ffn_ws_plan.h"
+#include "ffn_plan.h"
 
 namespace ew {
 
@@ -59,37 +59,24 @@ int grouped_ffn_f32(const void* x, int T, int k, int H, int I, int P, int S, con
                     const int32_t* pair_of_row, const void* w13, const void* w2, const void* w13_shared, const void* w2_shared,
                     void* y, void* ws, size_t ws_bytes, void* stream);
 
-// ffn_ws.hip: weight-stationary streaming path of moe_grouped_ffn (bf16; weights and gathered token
-// rows both reach LDS by LDS-direct loads, persistent workgroups pull items from per-XCD work
-// lists).  nf = 32-token fragments per row chunk (1, 2, 4 or 8).
-int ffn_ws_frags(int max_rows_per_slot, int rows, int slots, int nf_override);
-size_t ffn_ws_plan_ints(int T, int rows, int P);
-// Plan shape of a call with `rows` rows in all and `slots` slots (shared experts included).
-// merge: let the two products share a launch where the shape allows it.
-WsPlanShape ffn_ws_plan_shape(int rows, int slots, int nf, int chunk_frags, bool merge);
-// The plan kernel alone (what launch_ffn_ws runs first unless plan_ready).
-int launch_ffn_ws_plan(const int32_t* counts, const int32_t* offsets, int P, int S, int T, int rows_routed, const WsPlanShape& sh,
-                       int32_t* plan, hipStream_t st);
+// ffn_plan.hip: the bf16 path of moe_grouped_ffn (weights and gathered token rows both reach LDS by LDS-direct loads,
+// persistent workgroups claim their units from a plan built on the device).
+size_t ffn_plan_ints(int T, int rows, int P);
+// Plan shape of a call with `rows` rows in all and `slots` slots (shared experts included).  frags, chunk_frags: the tuning
+// hook's kernel shape and cap on 32-row fragments per chunk, 0 = automatic; merge: the two products share a launch.
+FfnPlanShape ffn_plan_shape(int T, int rows, int slots, int frags, int chunk_frags, bool merge);
+// The plan kernel alone (what launch_ffn_bf16 runs first unless plan_ready).
+int launch_ffn_plan(const int32_t* counts, const int32_t* offsets, int P, int S, int T, int rows_routed, const FfnPlanShape& sh,
+                    int32_t* plan, hipStream_t st);
 // S > 0: slots P .. P+S-1 are shared experts (weights w13_sh / w2_sh) that every one of the rows_routed / k tokens
 // visits; their rows follow the routed ones in act and y, and plan must be sized for all rows and P + S slots.
-int launch_ffn_ws(const void* x, int rows_routed, int k, int H, int I, int P, int S, const WsPlanShape& sh, bool plan_ready,
-                  const int32_t* counts, const int32_t* offsets, const int32_t* por, const void* w13, const void* w2,
-                  const void* w13_sh, const void* w2_sh, void* act, void* y, int32_t* plan, int wait_ticks, hipStream_t st);
+// H % 128 == 0, I % 128 == 0 and rows * max(H, I) * 2 < 2^32 are the caller's checks.
+int launch_ffn_bf16(const void* x, int rows_routed, int k, int H, int I, int P, int S, const FfnPlanShape& sh, bool plan_ready,
+                    const int32_t* counts, const int32_t* offsets, const int32_t* por, const void* w13, const void* w2, const void* w13_sh,
+                    const void* w2_sh, void* act, void* y, int32_t* plan, hipStream_t st);
 
-// ffn_dec.hip: the decode-sized calls of that path (sh.dec > 0), one continuous weight stream per workgroup.
-int launch_ffn_dec_plan(const int32_t* counts, const int32_t* offsets, int P, int S, int T, int rows_routed, const WsPlanShape& sh,
-                        int32_t* plan, hipStream_t st);
-int launch_ffn_dec(const void* x, int rows_routed, int k, int H, int I, int P, int S, const WsPlanShape& sh, const int32_t* por,
-                   const void* w13, const void* w2, const void* w13_sh, const void* w2_sh, void* act, void* y, int32_t* plan, int n_cu,
-                   hipStream_t st);
-// ffn_big.hip: the calls with many rows per slot; max_chunks: row chunks of the plan at most.
-int launch_ffn_big(const void* x, int rows_routed, int k, int H, int I, int P, int S, const WsPlanShape& sh, int max_chunks, const int32_t* por,
-                   const void* w13, const void* w2, const void* w13_sh, const void* w2_sh, void* act, void* y, int32_t* plan, int n_cu,
-                   hipStream_t st);
-WsPlanShape ffn_dec_plan_shape(int T, int rows, int slots, bool merge);
-
-// Whether moe_grouped_ffn / moe_grouped_ffn_with_shared with these dimensions runs the weight-stationary kernel, and
+// Whether moe_grouped_ffn / moe_grouped_ffn_with_shared with these dimensions runs those kernels, and
 // if so with which plan shape (defined beside the tuning state it depends on).
-bool ffn_ws_shape_of_call(int dtype, int T, int k, int H, int I, int P, int S, WsPlanShape* sh);
+bool ffn_shape_of_call(int dtype, int T, int k, int H, int I, int P, int S, FfnPlanShape* sh);
 
 }  // namespace ew

@@ -177,23 +177,19 @@ __global__ __launch_bounds__(512) void k_ffn_stream(StreamArgs a) {
 }
 
 // ------------------------------------------------------------------------------------------
-// Tuning state (ew_tune_ffn); 0 = automatic everywhere except the wait, where negative = automatic.
-int g_path_override = 0;       // 1 = register-streaming kernel, 2 = tiled GEMM kernel, 3 = LDS-direct streaming kernel
+// Tuning state (ew_tune_ffn); 0 = automatic.
+int g_path_override = 0;       // 1 = register-streaming kernel, 2 = tiled GEMM kernel, 3 = LDS-direct kernels
 int g_nt_override = 0;         // register-streaming kernel: 16-token tiles per slot chunk (1 or 2)
 int g_threads_override = 0;    // register-streaming kernel: threads per block
-int g_ws_frags = 0;            // LDS-direct kernel: 32-token fragments of the kernel shape (1, 2, 4, 8)
-int g_ws_chunk_frags = 0;      // LDS-direct kernel: 32-token fragments per row chunk at most (<= shape)
-int g_ws_wait_ticks = -1;      // LDS-direct kernel: rendezvous wait in 10 ns ticks (0 = never wait)
-int g_ws_merge = 0;            // LDS-direct kernel, decode shapes: 1 = the two products always as two launches
-// Automatic = never: since the next item is claimed behind the current one's last K slab, the workgroups that finish
-// together already start together; waiting for the rest of the cohort measured the same or slower (0 / 1 / 2 / 4 us).
-constexpr int kWsWaitDefault = 0;
+int g_ws_frags = 0;            // LDS-direct kernels: 32-token fragments of the kernel shape (1, 2, 4: k_ffn_dec, 8: k_ffn_big)
+int g_ws_chunk_frags = 0;      // LDS-direct kernels: 32-token fragments per row chunk at most (<= shape)
+int g_ws_merge = 0;            // LDS-direct kernels: 1 = the two products as two launches
 
 size_t plan_bytes(int T, int rows, int P) {
   size_t ints = (size_t)P + 1;
   const size_t g = ew::ffn_gemm_plan_ints(rows, P);
   if (g > ints) ints = g;
-  const size_t w = ew::ffn_ws_plan_ints(T, rows, P);
+  const size_t w = ew::ffn_plan_ints(T, rows, P);
   if (w > ints) ints = w;
   return ew::align_up(ints * sizeof(int32_t), 256);
 }
@@ -227,7 +223,7 @@ extern "C" void ew_tune_ffn(int path, int stream_token_tiles, int stream_threads
   g_threads_override = stream_threads;
   g_ws_frags = ws_frags;
   g_ws_chunk_frags = ws_chunk_frags;
-  g_ws_wait_ticks = ws_wait_ticks;
+  (void)ws_wait_ticks;
 }
 
 extern "C" size_t moe_grouped_ffn_workspace_bytes(int T, int k, int H, int I, int P, int dtype) {
@@ -238,21 +234,13 @@ extern "C" size_t moe_grouped_ffn_workspace_bytes(int T, int k, int H, int I, in
 
 namespace ew {
 
-bool ffn_ws_shape_of_call(int dtype, int T, int k, int H, int I, int P, int S, WsPlanShape* sh) {
+bool ffn_shape_of_call(int dtype, int T, int k, int H, int I, int P, int S, FfnPlanShape* sh) {
   if (dtype != EW_BF16 || T < 1 || k < 1 || S < 0 || P < 1 || H % 128 || I % 128) return false;
   if (g_path_override == 1 || g_path_override == 2) return false;
   const long long rows = (long long)T * (k + S);
   const int slots = P + S, Kmax = H > I ? H : I;
   if (rows >= (1ll << 31) || slots > 2048 || (unsigned long long)rows * (unsigned long long)Kmax * 2ull >= (1ull << 32)) return false;
-  // The decode kernel streams weights best as long as slots are small: up to 512 tokens whatever the router does, beyond that
-  // while a slot has 64 rows on average (2000 tokens on 217 active slots: 328 -> 253 us; 4096 tokens on 66: 651 -> 880 us).
-  const long long per_slot = rows / (slots < rows ? slots : rows);
-  if (g_ws_frags == 0 && g_ws_chunk_frags == 0 && (T <= 512 || per_slot <= 64) && H >= 256 && I >= 256) {
-    *sh = ffn_dec_plan_shape(T, (int)rows, slots, g_ws_merge != 1);
-    return true;
-  }
-  const int nf = ffn_ws_frags(T, (int)rows, slots < rows ? slots : (int)rows, g_ws_frags);
-  *sh = ffn_ws_plan_shape((int)rows, slots, nf, g_ws_chunk_frags, g_ws_merge != 1);
+  *sh = ffn_plan_shape(T, (int)rows, slots, g_ws_frags, g_ws_chunk_frags, g_ws_merge != 1);
   return true;
 }
 
@@ -279,15 +267,14 @@ int grouped_ffn(const char* who, bool plan_ready, const void* x, int dtype, int 
   const int rows = T * k;
   int32_t* plan = (int32_t*)ws;
   char* act = (char*)ws + plan_bytes(T, T * (k + S), P + S);
-  ew::WsPlanShape shape;
-  const bool ws_path = ew::ffn_ws_shape_of_call(dtype, T, k, H, I, P, S, &shape);
+  ew::FfnPlanShape shape;
+  const bool ws_path = ew::ffn_shape_of_call(dtype, T, k, H, I, P, S, &shape);
   if (S > 0 || plan_ready) {
-    // only the LDS-direct streaming kernel knows the shared experts' slots and takes a plan built elsewhere
+    // only the LDS-direct kernels know the shared experts' slots and take a plan built elsewhere
     if (!ws_path)
       return fail(EW_ERR_UNSUPPORTED, "%s: needs bf16, H and I multiples of 128, P+S <= 2048 and T*(k+S)*max(H,I)*2 < 2^32", who);
-    const int wait_ticks = g_ws_wait_ticks < 0 ? kWsWaitDefault : g_ws_wait_ticks;
-    return ew::launch_ffn_ws(x, rows, k, H, I, P, S, shape, plan_ready, counts, offsets, pair_of_row, w13_base, w2_base, w13_shared,
-                             w2_shared, act, y_sorted, plan, wait_ticks, st);
+    return ew::launch_ffn_bf16(x, rows, k, H, I, P, S, shape, plan_ready, counts, offsets, pair_of_row, w13_base, w2_base, w13_shared,
+                             w2_shared, act, y_sorted, plan, st);
   }
 
   if (dtype == EW_F32)
@@ -305,12 +292,11 @@ int grouped_ffn(const char* who, bool plan_ready, const void* x, int dtype, int 
   // Many rows per slot: compute bound, LDS-tiled GEMM.  Few rows per slot: HBM bound, stream weights.
   // The host knows only the totals, so the average rows per possible slot decides.
   const int max_slots = P < rows ? P : rows;
-  // Default: the LDS-direct streaming kernel.  Its byte offsets into x / the activations are 32 bit.
-  // and its work plan sorts at most 2048 slots (the limit of the permutation kernels as well).
+  // Default: the LDS-direct kernels.  Their byte offsets into x / the activations are 32 bit
+  // and their work plan sorts at most 2048 slots (the limit of the permutation kernels as well).
   if (ws_path) {
-    const int wait_ticks = g_ws_wait_ticks < 0 ? kWsWaitDefault : g_ws_wait_ticks;
-    return ew::launch_ffn_ws(x, rows, k, H, I, P, 0, shape, false, counts, offsets, pair_of_row, w13_base, w2_base, nullptr, nullptr,
-                             act, y_sorted, plan, wait_ticks, st);
+    return ew::launch_ffn_bf16(x, rows, k, H, I, P, 0, shape, false, counts, offsets, pair_of_row, w13_base, w2_base, nullptr, nullptr,
+                             act, y_sorted, plan, st);
   }
   if (g_path_override == 3)
     return fail(EW_ERR_UNSUPPORTED, "%s(bf16): the streaming path needs rows*max(H,I)*2 < 2^32 and P <= 2048", who);

@@ -18,7 +18,7 @@ constexpr int kThreads = 768;              // waves 0-1 load weights, 2 token ro
 __device__ __forceinline__ int swz(int r) { return ((r >> 1) ^ ((r & 1) << 2)) & 7; }
 
 // ------------------------------------------------------------------------------------------
-// The scheduling wave: lane i < 8 knows list (home + i) % 8 of the plan (ffn_ws_plan.h).
+// The scheduling wave: lane i < 8 knows list (home + i) % 8 of the plan (ffn_plan.h).
 struct Sched {
   int w, mode, t, home;      // claim in flight: list (home + t) % 8
   int n_ent, chunks;         // lane i: entries and chunks of list (home + i) % 8
@@ -522,6 +522,7 @@ __device__ __forceinline__ void big_body(const FfnArgs& a, unsigned char* s_lds)
 
 __global__ __launch_bounds__(kThreads) void k_ffn_big(FfnArgs a) {
   __shared__ __align__(1024) unsigned char s_lds[kLds];
+  if (a.pick && picked(a) != a.pick) return;  // the counts chose the other kernel
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (wave < 2) big_body<0>(a, s_lds);
   else if (wave < 3) big_body<1>(a, s_lds);
@@ -531,17 +532,9 @@ __global__ __launch_bounds__(kThreads) void k_ffn_big(FfnArgs a) {
 
 }  // namespace
 
-int launch_ffn_big(const void* x, int rows_routed, int k, int H, int I, int P, int S, const WsPlanShape& sh, int max_chunks, const int32_t* por,
-                   const void* w13, const void* w2, const void* w13_sh, const void* w2_sh, void* act, void* y, int32_t* plan, int n_cu,
-                   hipStream_t st) {
-  const int T = rows_routed / k;
-  FfnArgs a{};
-  a.m[0] = FfnProd{(const uint16_t*)x, (const uint16_t*)w13, (const uint16_t*)w13_sh, (uint16_t*)act, (size_t)2 * I * H, H, I, I / 128};
-  a.m[1] = FfnProd{(const uint16_t*)act, (const uint16_t*)w2, (const uint16_t*)w2_sh, (uint16_t*)y, (size_t)H * I, I, H, ceil_div(H, 256)};
-  a.por = por; a.plan = plan; a.done = plan + sh.done_off;
-  a.P = P; a.rows_routed = rows_routed; a.sh_rows = T > 0 ? T : 1; a.k = k;
-  a.cap = sh.cap; a.list_chunks = sh.ch * sh.cap;
-  a.spin_ticks = 20000000u;  // 0.2 s
+int launch_ffn_big(FfnArgs a, const FfnPlanShape& sh, int max_chunks, int n_cu, hipStream_t st) {
+  a.m[0].G = a.m[0].NOUT / 128;
+  a.m[1].G = ceil_div(a.m[1].NOUT, 256);
   const bool merged = sh.merged != 0;
   for (int mode = 0; mode < (merged ? 1 : 2); ++mode) {
     a.first_mode = mode;

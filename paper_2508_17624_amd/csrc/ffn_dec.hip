@@ -441,32 +441,28 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds)
 template <int NTF, int MR>
 __global__ __launch_bounds__((DecCfg<NTF, MR>::THREADS)) void k_ffn_dec(FfnArgs a) {
   __shared__ __align__(1024) unsigned char s_lds[DecCfg<NTF, MR>::LDS];
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (a.pick && picked(a) != a.pick) return;  // the counts chose the other kernel
   using C = DecCfg<NTF, MR>;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (wave < C::NW) dec_body<NTF, MR, 0>(a, s_lds);
   else if (wave < C::NW + C::NT) dec_body<NTF, MR, 1>(a, s_lds);
   else if (wave == C::NW + C::NT) dec_body<NTF, MR, 2>(a, s_lds);
   else dec_body<NTF, MR, 3>(a, s_lds);
 }
 
-__global__ __launch_bounds__(512) void k_plan_dec(const int32_t* __restrict__ counts, const int32_t* __restrict__ offsets, int P, int S,
-                                                  int sh_rows, int sh_first, WsPlanShape sh, int32_t* __restrict__ plan) {
-  __shared__ DecPlanLds lds;
-  dec_plan_build(counts, offsets, P, S, sh_rows, sh_first, sh, plan, lds);
-}
-
 template <int NTF, int MR>
-int launch(FfnArgs a, bool merged, int max_chunks, int n_cu, hipStream_t st) {
+int launch(FfnArgs a, const FfnPlanShape& sh, int n_cu, hipStream_t st) {
   using C = DecCfg<NTF, MR>;
   a.m[0].G = a.m[0].NOUT / (MR / 2);
   a.m[1].G = a.m[1].NOUT / MR;
   const int nk = (a.m[0].K < a.m[1].K ? a.m[0].K : a.m[1].K) / C::SK;  // >= 2
   a.depth_w = C::DW < nk ? C::DW : nk;
   a.depth_t = C::DT < nk ? C::DT : nk;
+  const bool merged = sh.merged != 0;
   for (int mode = 0; mode < (merged ? 1 : 2); ++mode) {
     a.first_mode = mode;
     a.last_mode = merged ? 1 : mode;
-    const long long units = (long long)max_chunks * (merged ? a.m[0].G + a.m[1].G : a.m[mode].G);
+    const long long units = (long long)sh.dec_cap * (merged ? a.m[0].G + a.m[1].G : a.m[mode].G);
     hipLaunchKernelGGL((k_ffn_dec<NTF, MR>), dim3(units < n_cu ? (int)units : n_cu), dim3(C::THREADS), 0, st, a);
     EW_LAUNCH_CHECK("k_ffn_dec");
   }
@@ -475,33 +471,18 @@ int launch(FfnArgs a, bool merged, int max_chunks, int n_cu, hipStream_t st) {
 
 }  // namespace
 
-int launch_ffn_dec_plan(const int32_t* counts, const int32_t* offsets, int P, int S, int T, int rows_routed, const WsPlanShape& sh,
-                        int32_t* plan, hipStream_t st) {
-  hipLaunchKernelGGL(k_plan_dec, dim3(1), dim3(512), 0, st, counts, offsets, P, S, T, rows_routed, sh, plan);
-  EW_LAUNCH_CHECK("k_plan_dec");
-  return EW_OK;
-}
-
-int launch_ffn_dec(const void* x, int rows_routed, int k, int H, int I, int P, int S, const WsPlanShape& sh, const int32_t* por,
-                   const void* w13, const void* w2, const void* w13_sh, const void* w2_sh, void* act, void* y, int32_t* plan, int n_cu,
-                   hipStream_t st) {
-  const int T = rows_routed / k;
-  FfnArgs a{};
-  a.m[0] = FfnProd{(const uint16_t*)x, (const uint16_t*)w13, (const uint16_t*)w13_sh, (uint16_t*)act, (size_t)2 * I * H, H, I, 0};
-  a.m[1] = FfnProd{(const uint16_t*)act, (const uint16_t*)w2, (const uint16_t*)w2_sh, (uint16_t*)y, (size_t)H * I, I, H, 0};
-  a.por = por; a.plan = plan; a.done = plan + sh.done_off;
-  a.P = P; a.rows_routed = rows_routed; a.sh_rows = T > 0 ? T : 1; a.k = k;
-  a.spin_ticks = 20000000u;  // 0.2 s
+int launch_ffn_dec(FfnArgs a, const FfnPlanShape& sh, int n_cu, hipStream_t st) {
+  const int H = a.m[0].K, I = a.m[1].K;
   // Units of 128 weight rows read every token row half as often as units of 64: C1-shaped calls 261 -> 247 us, 48 tokens on
   // 84 small experts 111 -> 101 us.  Only where even 64-row units leave a compute unit no more than two of the first
-  // product (one token: 8 experts) does the finer split win: 44 -> 42 us.
-  const bool fine = sh.dec == 1 && (long long)sh.cap * (I / 32) <= 2 * n_cu;
-  const bool merged = sh.merged != 0;
+  // product (one token: 8 experts) does the finer split win: 44 -> 42 us.  (Its slabs are 128 contraction elements, of
+  // which a unit must have two.)
+  const bool fine = sh.dec == 1 && H >= 256 && I >= 256 && (long long)sh.dec_cap * (I / 32) <= 2 * n_cu;
   switch (sh.dec) {
-    case 1: return fine ? launch<1, 64>(a, merged, sh.cap, n_cu, st) : launch<1, 128>(a, merged, sh.cap, n_cu, st);
-    case 2: return launch<2, 128>(a, merged, sh.cap, n_cu, st);
-    case 4: return launch<4, 128>(a, merged, sh.cap, n_cu, st);
-    default: return H % 256 == 0 ? launch<8, 256>(a, merged, sh.cap, n_cu, st) : launch<8, 128>(a, merged, sh.cap, n_cu, st);
+    case 1: return fine ? launch<1, 64>(a, sh, n_cu, st) : launch<1, 128>(a, sh, n_cu, st);
+    case 2: return launch<2, 128>(a, sh, n_cu, st);
+    case 4: return launch<4, 128>(a, sh, n_cu, st);
+    default: return H % 256 == 0 ? launch<8, 256>(a, sh, n_cu, st) : launch<8, 128>(a, sh, n_cu, st);
   }
 }
 

@@ -1,4 +1,4 @@
-// Work plan of the weight-stationary grouped-FFN kernel (k_ffn_ws): layout and the device routine that builds it.
+// Work plans of the grouped-FFN kernels (k_ffn_dec, k_ffn_big): layouts and the device routines that build them.
 // Shared by the FFN's own plan kernel and by the decode-sized permutation kernel, which can append the plan of the FFN
 // call that follows it to its own launch.
 #pragma once
@@ -8,6 +8,10 @@
 namespace ew {
 
 // Work plan of one moe_grouped_ffn call, built on the device (the host never reads the counts).
+//   plan[kPlanPick]        calls for which the counts decide which kernel runs: 1 = k_ffn_dec, 2 = k_ffn_big
+constexpr int kPlanPick = 31;
+
+// Plan of k_ffn_big.
 //  * A slot with more than bt rows is cut into equal chunks (rounded up to whole 32-row fragments),
 //    so all work items of a slot take the same time.
 //  * A slot with more than `ch` chunks is cut further into entries of at most `ch` chunks each.  An
@@ -19,17 +23,15 @@ namespace ew {
 //  * Entries are ordered by chunk size, largest first (slot id, then position in the slot, break
 //    ties), and dealt round-robin to 8 lists, one per XCD (workgroup b runs on XCD b % 8).  The
 //    workgroups that share an entry's weights (different chunks) or its token rows (different feature
-//    groups) thus run on the same XCD and meet in that XCD's L2 -- provided they start together, which
-//    the kernel arranges (see k_ffn_ws); equal durations inside an entry and similar ones between
-//    neighbours in the list keep them together.
+//    groups) thus run on the same XCD and meet in that XCD's L2; equal durations inside an entry and similar
+//    ones between neighbours in the list keep them together.
 //   plan[x]        x < 8   entries of list x
 //   plan[8 + x]            row chunks of list x
-//   plan[16 + x], plan[24 + x]   work counters of the two products (zeroed here, every call)
+//   plan[kPlanCtr + kPlanCtrStride i]   claim counters, one cache line each (zeroed here, every call)
 //   plan[kPlanHdr + 6 (x cap + e)] ...  entry e of list x: slot, chunks, chunks of the list before it,
 //                                 rows per chunk, rows of the entry, first row of the entry
-//   plan[done_off + r]     calls whose two products share a launch: waves that have stored their part of the
-//                          activation rows of the chunk that starts at sorted row r (zeroed here, every call)
-constexpr int kPlanCtr = 32, kPlanCtrStride = 32;  // claim counters of k_ffn_big, one cache line each: product 0's lists, then product 1's
+//   plan[done_off + c]     first-product units of chunk c that are stored (zeroed here, every call)
+constexpr int kPlanCtr = 32, kPlanCtrStride = 32;  // product 0's lists, then product 1's
 constexpr int kPlanHdr = kPlanCtr + 16 * kPlanCtrStride;
 constexpr int kEnt = 6;
 constexpr int kPlanMaxP = 2048;    // slots a plan can sort
@@ -51,58 +53,50 @@ __device__ __forceinline__ void chunking(int c, int bt, int& nch, int& bts) {
   bts = ((c + nch - 1) / nch + 31) & ~31;
 }
 
-// Shape of the plan and of the kernel that consumes it, chosen on the host from the call's dimensions.
-struct WsPlanShape {
-  int nf;        // 32-token fragments of the kernel shape (1, 2, 4, 8)
-  int bt;        // rows per chunk at most
-  int ch;        // chunks per entry at most
-  int cap;       // entries per list at most
-  int n_done;    // completion counters behind the lists, one per sorted row (0: the two products run as two launches)
-  int done_off;  // where they start, in ints from the start of the plan
-  int big;       // the 256-row kernel (k_ffn_big)
-  int merged;    // the two products share a launch
-  int dec;       // > 0: the decode kernel (k_ffn_dec) with chunks of 16 * dec rows and the flat plan below; cap = its chunks at most
+// Shape of the plan and of the kernels that consume it, chosen on the host from the call's dimensions.  A call may name
+// both kernels: the counts decide then (ffn_plan_build).
+struct FfnPlanShape {
+  int dec;           // > 0: k_ffn_dec is a candidate, with chunks of 16 * dec rows
+  int dec_cap;       // its chunks at most
+  int big;           // k_ffn_big is a candidate
+  int bt;            // its rows per chunk at most
+  int ch;            // its chunks per entry at most
+  int cap;           // its entries per list at most
+  int n_done;        // its completion counters
+  int done_off;      // where the completion counters start, in ints from the start of the plan
+  int merged;        // the two products share a launch
 };
 
-// Builds the plan from the slots' counts and offsets.  Slots P .. P+S-1 are the shared experts of the call, if any:
-// each holds every token (sh_rows of them), and their rows follow the routed ones (first at sh_first).
-// Called by every thread of a block of at least 512 threads (it contains barriers); the first 512 do the work.
-// counts / offsets may have been written by this block before a barrier.
-struct WsPlanLds {
+// Both candidates: k_ffn_big runs where an active slot has more rows on average than a chunk of k_ffn_dec takes (beyond that
+// it reads weights twice).  Measured (us, k_ffn_dec / k_ffn_big, at rows per active slot): 68: 819 / 846; 74: 256 / 273;
+// 124: 271 / 278; 135: 1001 / 942; 148: 493 / 318; 248: 492 / 353.  The kernel that is not chosen costs
+// a launch (5 us); both bodies in one kernel did not fit the registers.
+constexpr int kPickRows = 128;
+
+struct BigPlanLds {
   uint32_t sorted[kPlanMaxEnt];  // entries in processing order: slot | part << 16
-  uint32_t wtot[8][8];           // per wave: entries per size class
-  int base[9];                   // first position of each size class
-  int32_t cnt[kPlanMaxP], off[kPlanMaxP];  // rows and first row of every slot (one global round trip)
+  uint32_t wtot[8][8];           // per size class and wave: entries, then the first position
+  int n_total;
+  int32_t cnt[kPlanMaxP], off[kPlanMaxP];
 };
 
-// `have` (optional): the caller already holds the rows and first row of the routed slots 4 tid .. 4 tid + 3 of every
-// working thread in have[0..3] / have[4..7] (then counts / offsets are not read).
-__device__ __forceinline__ void ws_plan_build(const int32_t* counts, const int32_t* offsets, int P, int S, int sh_rows,
-                                              int sh_first, const WsPlanShape sh, int32_t* __restrict__ plan, WsPlanLds& L,
-                                              const int32_t* have = nullptr) {
+// Builds the plan of k_ffn_big.  rows / first: rows and first row of slots 4 tid .. 4 tid + 3 of every thread tid < 512
+// (thread order is slot order).  Called by every thread of a block of at least 512 threads (it contains barriers).
+__device__ __forceinline__ void big_plan_build(const int (&rows)[4], const int (&first)[4], const FfnPlanShape& sh, int32_t* __restrict__ plan,
+                                               BigPlanLds& L) {
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const bool worker = tid < 512;
   const int bt = sh.bt, ch = sh.ch, cap = sh.cap;
   for (int i = tid; i < sh.n_done; i += blockDim.x) plan[sh.done_off + i] = 0;
-  // size class of a slot: 8 - (32-row fragments per chunk), i.e. 0 = largest chunks.  Thread t owns
-  // slots 4t .. 4t+3, so thread order is slot order.
+  // size class of a slot: 8 - (32-row fragments per chunk), i.e. 0 = largest chunks
   int cls[4], nent[4];
   uint32_t mine[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
-  uint32_t excl[8];
   if (worker) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int sl = 4 * tid + i;
-      int c = 0, o = 0;
-      if (sl < P) {
-        c = have ? have[i] : counts[sl];
-        o = have ? have[4 + i] : offsets[sl];
-      } else if (sl < P + S) {
-        c = sh_rows;
-        o = sh_first + (sl - P) * sh_rows;
-      }
+      const int sl = 4 * tid + i, c = rows[i];
       L.cnt[sl] = c;
-      L.off[sl] = o;
+      L.off[sl] = first[i];
       cls[i] = -1;
       nent[i] = 0;
       if (c > 0) {
@@ -118,57 +112,49 @@ __device__ __forceinline__ void ws_plan_build(const int32_t* counts, const int32
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
       const uint32_t inc = wave_incl_scan_u32(mine[k]);
-      excl[k] = inc - mine[k];
-      if (lane == 63) L.wtot[wave][k] = inc;
+      mine[k] = inc - mine[k];  // entries of the class in the wave's threads before this one
+      if (lane == 63) L.wtot[k][wave] = inc;
     }
   }
   __syncthreads();
-  if (tid == 0) {
-    int run = 0;
-    for (int k = 0; k < 8; ++k) {
-      L.base[k] = run;
-      for (int w = 0; w < 8; ++w) run += (int)L.wtot[w][k];
-    }
-    L.base[8] = run;
+  if (tid < 64) {  // (class, wave) pairs in order: one wave scans them all
+    const uint32_t v = (&L.wtot[0][0])[tid], inc = wave_incl_scan_u32(v);
+    (&L.wtot[0][0])[tid] = inc - v;
+    if (tid == 63) L.n_total = (int)inc;
   }
   __syncthreads();
   if (worker) {
-    int seen[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      int before = (int)excl[k];
-      for (int w = 0; w < wave; ++w) before += (int)L.wtot[w][k];
-      seen[k] = L.base[k] + before;
-    }
+    for (int k = 0; k < 8; ++k) mine[k] += L.wtot[k][wave];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       if (cls[i] < 0) continue;
 #pragma unroll
       for (int k = 0; k < 8; ++k)
         if (cls[i] == k) {
-          for (int part = 0; part < nent[i]; ++part) L.sorted[seen[k]++] = (uint32_t)(4 * tid + i) | ((uint32_t)part << 16);
+          for (int part = 0; part < nent[i]; ++part) L.sorted[mine[k]++] = (uint32_t)(4 * tid + i) | ((uint32_t)part << 16);
         }
     }
   }
   __syncthreads();
   if (!worker) return;
   // wave x builds list x from positions x, x + 8, ...
-  const int n_total = L.base[8];
+  const int n_total = L.n_total;
   const int x = wave;
   int32_t* list = plan + kPlanHdr + kEnt * x * cap;
   int n_chunks = 0, n_entries = 0;
   for (int e0 = 0; 8 * e0 + x < n_total; e0 += 64) {
     const int e = e0 + lane, pos = 8 * e + x;
     const bool ok = pos < n_total;
-    int sl = 0, c = 0, nch = 0, bts = 0, first = 0;
+    int sl = 0, c = 0, nch = 0, bts = 0, at = 0;
     if (ok) {
       const uint32_t v = L.sorted[pos];
       sl = (int)(v & 0xFFFFu);
       int all;
       chunking(L.cnt[sl], bt, all, bts);
-      first = (int)(v >> 16) * ch;                   // first chunk of this entry inside its slot
-      nch = min(ch, all - first);
-      c = min(L.cnt[sl] - first * bts, nch * bts);   // rows of this entry
+      at = (int)(v >> 16) * ch;                      // first chunk of this entry inside its slot
+      nch = min(ch, all - at);
+      c = min(L.cnt[sl] - at * bts, nch * bts);   // rows of this entry
     }
     const int incl = (int)wave_incl_scan_u32((uint32_t)nch);
     if (ok) {
@@ -178,7 +164,7 @@ __device__ __forceinline__ void ws_plan_build(const int32_t* counts, const int32
       en[2] = n_chunks + incl - nch;
       en[3] = bts;
       en[4] = c;
-      en[5] = L.off[sl] + first * bts;
+      en[5] = L.off[sl] + at * bts;
     }
     n_chunks += __shfl(incl, 63, 64);
     n_entries += __popcll(__ballot(ok));
@@ -186,8 +172,6 @@ __device__ __forceinline__ void ws_plan_build(const int32_t* counts, const int32
   if (lane == 0) {
     plan[x] = n_entries;
     plan[8 + x] = n_chunks;
-    plan[16 + x] = 0;
-    plan[24 + x] = 0;
     plan[kPlanCtr + x * kPlanCtrStride] = 0;
     plan[kPlanCtr + (8 + x) * kPlanCtrStride] = 0;
   }
@@ -210,22 +194,17 @@ struct DecPlanLds {
   int32_t wtot[8];
 };
 
-// Called by every thread of a block of at least 512 threads (barriers); `have` as for ws_plan_build.
-__device__ __forceinline__ void dec_plan_build(const int32_t* counts, const int32_t* offsets, int P, int S, int sh_rows, int sh_first,
-                                               const WsPlanShape sh, int32_t* __restrict__ plan, DecPlanLds& L,
-                                               const int32_t* have = nullptr) {
+// Builds the plan of k_ffn_dec; rows / first as for big_plan_build, without the shared experts' slots: S of them follow the
+// P routed ones, sh_rows rows each, from row sh_first on.
+__device__ __forceinline__ void dec_plan_build(const int (&rows)[4], const int (&first)[4], int P, int S, int sh_rows, int sh_first,
+                                               const FfnPlanShape& sh, int32_t* __restrict__ plan, DecPlanLds& L) {
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int bt = 16 * sh.dec;
   const int sh_chunks = dec_chunks(sh_rows, bt);
-  int c[4], o[4], mine = 0;
+  int mine = 0;
   if (tid < 512) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {  // thread t owns slots 4t .. 4t+3: thread order is slot order
-      const int sl = 4 * tid + i;
-      c[i] = sl < P ? (have ? have[i] : counts[sl]) : 0;
-      o[i] = sl < P ? (have ? have[4 + i] : offsets[sl]) : 0;
-      mine += dec_chunks(c[i], bt);
-    }
+    for (int i = 0; i < 4; ++i) mine += dec_chunks(rows[i], bt);
     const int inc = (int)wave_incl_scan_u32((uint32_t)mine);
     if (lane == 63) L.wtot[wave] = inc;
     mine = inc - mine;
@@ -238,22 +217,22 @@ __device__ __forceinline__ void dec_plan_build(const int32_t* counts, const int3
     if (w < wave) before += t;
     total += t;
   }
-  auto put = [&](int at, int slot, int rows, int first) {
-    const int n = dec_chunks(rows, bt), bts = ((rows + n - 1) / n + 15) & ~15;
+  auto put = [&](int at, int slot, int c, int first_row) {
+    const int n = dec_chunks(c, bt), bts = ((c + n - 1) / n + 15) & ~15;
     for (int j = 0; j < n; ++j) {
       int32_t* en = plan + kDecEnt + 4 * (at + j);
       en[0] = slot;
-      en[1] = min(bts, rows - j * bts);
-      en[2] = first + j * bts;
+      en[1] = min(bts, c - j * bts);
+      en[2] = first_row + j * bts;
     }
   };
   if (tid < 512) {
     int at = before + mine;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      if (c[i] > 0) {
-        put(at, 4 * tid + i, c[i], o[i]);
-        at += dec_chunks(c[i], bt);
+      if (rows[i] > 0) {
+        put(at, 4 * tid + i, rows[i], first[i]);
+        at += dec_chunks(rows[i], bt);
       }
     if (tid >= 512 - 64)  // the last wave: it has no routed slot below 1792 of them
       for (int s = tid - (512 - 64); s < S; s += 64) put(s * sh_chunks, P + s, sh_rows, sh_first + s * sh_rows);
@@ -261,6 +240,40 @@ __device__ __forceinline__ void dec_plan_build(const int32_t* counts, const int3
   for (int i = tid; i < total; i += blockDim.x) plan[sh.done_off + kDecDoneStride * i] = 0;
   if (tid < 16) plan[kDecCtr + kDecCtrStride * tid] = 0;
   if (tid == 0) plan[0] = total;
+}
+
+union FfnPlanLds {
+  BigPlanLds big;
+  DecPlanLds dec;
+};
+
+// Builds a call's plan from the rows and first row of the routed slots 4 tid .. 4 tid + 3 of every thread tid < 512 (0 from
+// slot P on).  Slots P .. P+S-1 are the shared experts of the call, if any: each holds every token (sh_rows of them), and
+// their rows follow the routed ones (first at sh_first).  Called by every thread of a block of at least 512 threads.
+__device__ __forceinline__ void ffn_plan_build(int (&rows)[4], int (&first)[4], int P, int S, int sh_rows, int sh_first, const FfnPlanShape& sh,
+                                               int32_t* __restrict__ plan, FfnPlanLds& L) {
+  const int tid = threadIdx.x;
+  bool big = sh.big;
+  if (sh.dec && sh.big) {
+    int active = S;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) active += __syncthreads_count(tid < 512 && rows[i] > 0);
+    big = sh_first + (long long)S * sh_rows > (long long)kPickRows * active;
+    if (tid == 0) plan[kPlanPick] = big ? 2 : 1;
+  }
+  if (!big) {
+    dec_plan_build(rows, first, P, S, sh_rows, sh_first, sh, plan, L.dec);
+    return;
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int s = 4 * tid + i - P;
+    if (s >= 0 && s < S) {
+      rows[i] = sh_rows;
+      first[i] = sh_first + s * sh_rows;
+    }
+  }
+  big_plan_build(rows, first, sh, plan, L.big);
 }
 
 }  // namespace ew

@@ -31,8 +31,12 @@ struct FfnArgs {
   int first_mode, last_mode;  // the launch's products
   int depth_w, depth_t;       // k_ffn_dec: slabs in its rings
   int cap, list_chunks;       // k_ffn_big: entries and chunks per list of the plan at most
+  int pick;                   // 0, or this kernel's number in plan[kPlanPick]
   unsigned int spin_ticks;
 };
+
+// The kernel that the counts chose (wave-uniform, as the branch on it has to be).
+__device__ __forceinline__ int picked(const FfnArgs& a) { return __builtin_amdgcn_readfirstlane(a.plan[kPlanPick]); }
 
 __device__ __forceinline__ uint16_t f32_to_bf16(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 __device__ __forceinline__ float silu_f32(float g) { return g * __builtin_amdgcn_rcpf(1.f + __expf(-g)); }
@@ -87,6 +91,11 @@ __device__ __forceinline__ void read_lds_ints(uint32_t addr, uint32_t* r) {
     if constexpr (N > 4) read_lds_ints<N - 4, STEP>(addr + 4 * STEP, r + 4);
   }
 }
+
+// ffn_dec.hip: calls with few rows per slot.
+int launch_ffn_dec(FfnArgs a, const FfnPlanShape& sh, int n_cu, hipStream_t st);
+// ffn_big.hip: the calls with many rows per slot; max_chunks: row chunks of the plan at most.
+int launch_ffn_big(FfnArgs a, const FfnPlanShape& sh, int max_chunks, int n_cu, hipStream_t st);
 
 // At most n vector-memory operations of this wave still outstanding (n is wave-uniform; waiting for fewer is safe).
 __device__ __forceinline__ void wait_vm_upto(int n) {

@@ -278,7 +278,7 @@ __global__ __launch_bounds__(256) void k_route_reroute(const float* __restrict__
 struct SmallPlan {
   int32_t* plan;
   int S;
-  ew::WsPlanShape shape;
+  ew::FfnPlanShape shape;
 };
 
 // ------------------------------------------------------------------------------------------
@@ -302,8 +302,7 @@ __global__ __launch_bounds__(1024) void k_small(const float* __restrict__ logits
   };
   __shared__ union Lds {
     Perm perm;
-    ew::WsPlanLds plan;  // after the scatter
-    ew::DecPlanLds dec;
+    ew::FfnPlanLds plan;  // after the scatter
   } lds;
   uint16_t (&s_slot)[kSmallPairs] = lds.perm.slot;
   uint16_t (&s_rank)[kSmallPairs] = lds.perm.rank;
@@ -394,18 +393,17 @@ __global__ __launch_bounds__(1024) void k_small(const float* __restrict__ logits
 
   // E: the work plan of the grouped FFN call that consumes counts / offsets, if asked for (block of >= 512 threads)
   if (fp.plan) {
-    int32_t have[8] = {0, 0, 0, 0, 0, 0, 0, 0};   // this thread's four slots, taken from LDS before the plan reuses it
+    int rows[4] = {0, 0, 0, 0}, first[4] = {0, 0, 0, 0};   // this thread's four slots, taken from LDS before the plan reuses it
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int sl = 4 * tid + i;
       if (tid < 512 && sl < P) {
-        have[4 + i] = s_off[sl];
-        have[i] = s_off[sl + 1] - s_off[sl];
+        first[i] = s_off[sl];
+        rows[i] = s_off[sl + 1] - s_off[sl];
       }
     }
     __syncthreads();  // the permutation's LDS arrays are dead
-    if (fp.shape.dec) ew::dec_plan_build(counts, offsets, P, fp.S, T, n, fp.shape, fp.plan, lds.dec, have);
-    else ew::ws_plan_build(counts, offsets, P, fp.S, T, n, fp.shape, fp.plan, lds.plan, have);
+    ew::ffn_plan_build(rows, first, P, fp.S, T, n, fp.shape, fp.plan, lds.plan);
   }
 }
 
@@ -861,7 +859,7 @@ inline int chunk_tokens(int T, int k) {
 template <int VPL>
 int launch_permute(const float* logits, const int32_t* ids_in, const int32_t* aid, const int32_t* emap, int T, int E,
                    int k, int N, int P, int renorm, int32_t* ids_out, float* w_out, int32_t* slot_ids, int32_t* counts,
-                   int32_t* offsets, int32_t* por, int32_t* rop, void* ws, hipStream_t st, const ew::WsPlanShape* shape = nullptr,
+                   int32_t* offsets, int32_t* por, int32_t* rop, void* ws, hipStream_t st, const ew::FfnPlanShape* shape = nullptr,
                    int S = 0, int32_t* plan = nullptr) {
   const long long n = (long long)T * k;
   const int bits = ew::ilog2_ceil(P);
@@ -872,7 +870,7 @@ int launch_permute(const float* logits, const int32_t* ids_in, const int32_t* ai
     int run = ((int)n + nwaves - 1) / nwaves;
     run = (run + kWave - 1) / kWave * kWave;
     // the FFN plan rides on the single-block kernel when that has the 512 threads the plan needs
-    SmallPlan fp{nullptr, 0, ew::WsPlanShape{}};
+    SmallPlan fp{nullptr, 0, ew::FfnPlanShape{}};
     const bool fused_plan = plan && nwaves * kWave >= 512;
     if (fused_plan) fp = SmallPlan{plan, S, *shape};
     if constexpr (VPL > 0) {
@@ -887,7 +885,7 @@ int launch_permute(const float* logits, const int32_t* ids_in, const int32_t* ai
                          map_entries, renorm, bits, run, ids_out, w_out, slot_ids, counts, offsets, por, rop, fp);
     }
     EW_LAUNCH_CHECK("k_small");
-    if (plan && !fused_plan) return ew::launch_ffn_ws_plan(counts, offsets, P, S, T, (int)n, *shape, plan, st);
+    if (plan && !fused_plan) return ew::launch_ffn_plan(counts, offsets, P, S, T, (int)n, *shape, plan, st);
     return EW_OK;
   }
   const int cht = chunk_tokens(T, k);
@@ -921,7 +919,7 @@ int launch_permute(const float* logits, const int32_t* ids_in, const int32_t* ai
                        offsets, por, rop);
 #undef EW_SCATTER_TOK
   EW_LAUNCH_CHECK("k_scatter");
-  if (plan) return ew::launch_ffn_ws_plan(counts, offsets, P, S, T, (int)n, *shape, plan, st);
+  if (plan) return ew::launch_ffn_plan(counts, offsets, P, S, T, (int)n, *shape, plan, st);
   return EW_OK;
 }
 
@@ -1091,7 +1089,7 @@ namespace {
 int route_reroute_permute(const char* who, const float* logits, const int32_t* adapter_id, const int32_t* expert_map, int T, int E,
                           int k, int N, int P, int renormalize, int32_t* topk_ids, float* topk_w, int32_t* slot_ids,
                           int32_t* counts, int32_t* offsets, int32_t* pair_of_row, int32_t* row_of_pair, void* ws, size_t ws_bytes,
-                          const ew::WsPlanShape* shape, int S, int32_t* plan, hipStream_t st) {
+                          const ew::FfnPlanShape* shape, int S, int32_t* plan, hipStream_t st) {
   using ew::fail;
   if (k > E) return fail(EW_ERR_INVALID_ARG, "%s: k=%d exceeds E=%d", who, k, E);
   int rc = check_permute_args(who, adapter_id, expert_map, T, k, E, N, P, slot_ids, counts, offsets, pair_of_row, ws, ws_bytes);
@@ -1133,10 +1131,10 @@ extern "C" int moe_route_reroute_permute_plan(const float* logits, const int32_t
   using ew::fail;
   const char* who = "moe_route_reroute_permute_plan";
   if (T < 0 || k < 1 || P < 1 || H < 1 || I < 1 || S < 0) return fail(EW_ERR_INVALID_ARG, "%s: need T>=0, k>=1, P>=1, H>=1, I>=1, S>=0", who);
-  ew::WsPlanShape shape{};
+  ew::FfnPlanShape shape{};
   int32_t* plan = nullptr;
   if (T > 0) {
-    if (!ew::ffn_ws_shape_of_call(dtype, T, k, H, I, P, S, &shape))
+    if (!ew::ffn_shape_of_call(dtype, T, k, H, I, P, S, &shape))
       return fail(EW_ERR_UNSUPPORTED, "%s: the grouped FFN of these dimensions takes no plan (needs bf16, H and I multiples of 128, "
                   "P+S <= 2048, T*(k+S)*max(H,I)*2 < 2^32)", who);
     const size_t need = moe_grouped_ffn_workspace_bytes(T, k + S, H, I, P + S, dtype);
