@@ -620,3 +620,45 @@ def test_grouped_ffn_decode_kernel_edges(ew, T, k, P, S, H, I):
         ref = moe.expert_ffn(xs, to_f64(s13[s]), to_f64(s2[s]))
         blk = got[T * k + s * T:T * k + (s + 1) * T]
         assert rel_l2(blk, ref) <= FFN_REL_L2 and max_abs(blk, ref) <= FFN_MAX_ABS, f"shared expert {s}"
+
+
+@pytest.mark.parametrize("T,k,P,S,H,I,used", [(768, 2, 64, 1, 384, 256, 64), (768, 2, 64, 1, 384, 256, 6), (1100, 4, 96, 0, 256, 128, 96),
+                                              (1100, 4, 96, 0, 256, 128, 4), (520, 2, 2046, 2, 128, 128, 5)],
+                         ids=["spread", "few-used", "spread-no-shared", "four-used", "largest-pool"])
+def test_grouped_ffn_counts_choose_the_kernel(ew, T, k, P, S, H, I, used):
+    """More than 512 tokens on more slots than they need: the counts decide on the device which kernel runs, by the average
+    rows of the slots in use.  Traffic over all slots and over a few of them, both against the oracle and against each
+    kernel asked for by name, bit for bit with the one the rule names."""
+    rng = np.random.default_rng(T + used)
+    slots = np.sort(rng.choice(P, used, replace=False))
+    ids = slots[np.stack([rng.choice(used, k, replace=False) for _ in range(T)])].astype(np.int32)
+    flat = ids.reshape(-1)
+    por = np.argsort(flat, kind="stable").astype(np.int32)
+    counts = np.bincount(flat, minlength=P).astype(np.int32)
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    dev = lambda a: torch.from_numpy(a).cuda()
+    bf = lambda *shape, scale=1.0: (torch.from_numpy(rng.standard_normal(shape, dtype=np.float32)) * scale).cuda().bfloat16()
+    x, w13, w2 = bf(T, H), bf(P, 2 * I, H, scale=0.02), bf(P, H, I, scale=0.02)
+    s13, s2 = (bf(S, 2 * I, H, scale=0.02), bf(S, H, I, scale=0.02)) if S else (None, None)
+    args = (dev(counts), dev(offsets), dev(por), w13, w2)
+
+    def run(frags=0):
+        ew.binding.tune_ffn(path=3 if frags else 0, ws_frags=frags)
+        try:
+            return ew.moe_grouped_ffn_with_shared(x, k, I, P, *args, s13, s2) if S else ew.moe_grouped_ffn(x, k, I, P, *args)
+        finally:
+            ew.binding.tune_ffn()
+
+    y = run()
+    few, many = run(4), run(8)
+    active = int((counts > 0).sum()) + S
+    assert torch.equal(y, many if T * (k + S) > 128 * active else few)
+    xs = to_f64(x)
+    for got in (to_f64(few), to_f64(many)):
+        for s in np.nonzero(counts)[0][:12]:
+            r0, r1 = offsets[s], offsets[s + 1]
+            ref = moe.expert_ffn(xs[por[r0:r1] // k], to_f64(w13[s]), to_f64(w2[s]))
+            assert rel_l2(got[r0:r1], ref) <= FFN_REL_L2 and max_abs(got[r0:r1], ref) <= FFN_MAX_ABS, f"slot {s}"
+        for s in range(S):
+            blk = got[T * k + s * T:T * k + (s + 1) * T]
+            assert rel_l2(blk, moe.expert_ffn(xs, to_f64(s13[s]), to_f64(s2[s]))) <= FFN_REL_L2, f"shared expert {s}"
