@@ -18,9 +18,8 @@ import torch
 
 from . import binding as B
 
-# attributes of a layer that its description for the library is made of
-_DESCRIBED = frozenset(("Wg", "bias", "renormalize", "shared_w13", "shared_w2", "w13_base", "w2_base", "emap", "buf", "dt", "H", "I", "M", "k",
-                        "N", "P", "S", "T_max"))
+# attributes of a layer that its description for the library is made of, apart from its weight tensors (_current)
+_DESCRIBED = frozenset(("renormalize", "w13_base", "w2_base", "emap", "buf", "dt", "H", "I", "M", "k", "N", "P", "S", "T_max"))
 
 
 def load_layer(pool: B.ExpertPool, layer: int, base, adapters, tuned):
@@ -33,6 +32,12 @@ def load_layer(pool: B.ExpertPool, layer: int, base, adapters, tuned):
 
 class LayerBuffers:
     """Every intermediate of one layer pass, allocated once; layers of a stack share one set."""
+
+    version = 0
+
+    def __setattr__(self, name, value):
+        super().__setattr__(name, value)
+        super().__setattr__("version", self.version + 1)   # layers that use the buffers describe themselves again
 
     def __init__(self, T_max: int, M: int, k: int, H: int, I: int, P: int, S: int, dtype: torch.dtype, device):
         self.T_max, self.M, self.k, self.H, self.I, self.P, self.S, self.dtype = T_max, M, k, H, I, P, S, dtype
@@ -86,14 +91,25 @@ class MoELayer:
         """The layer as moe_layer_forward reads it; kept until one of the attributes it is made of is set again."""
         b, ptr = self.buf, B._ptr
         d = B.LayerDesc(dtype=self.dt, H=self.H, I=self.I, M=self.M, k=self.k, N=self.N, P=self.P, S=self.S,
-                        renormalize=int(self.renormalize), T_max=self.T_max, Wg=ptr(self.Wg), bias=ptr(self.bias), expert_map=self.emap,
-                        w13=self.w13_base, w2=self.w2_base, w13_shared=ptr(self.shared_w13), w2_shared=ptr(self.shared_w2),
+                        renormalize=int(self.renormalize), T_max=self.T_max, expert_map=self.emap, w13=self.w13_base, w2=self.w2_base,
                         logits=ptr(b.logits), ids=ptr(b.ids), w=ptr(b.w), slot=ptr(b.slot), counts=ptr(b.counts), offsets=ptr(b.offsets),
                         pair_of_row=ptr(b.por), row_of_pair=ptr(b.rop), y=ptr(b.y), ws_perm=ptr(b.ws_perm),
                         ws_perm_bytes=b.ws_perm.numel() if b.ws_perm is not None else 0, ws_ffn=ptr(b.ws_ffn), ws_ffn_bytes=b.ws_ffn.numel())
-        self._desc_struct = d
-        self._desc = ctypes.addressof(d)
-        return self._desc
+        self._desc, self._desc_version = d, b.version
+        return d
+
+    def _current(self):
+        """Address of the description, with the addresses that the weight tensors have now: their storage may change
+        under the same tensor object (set_, .data)."""
+        d = self._desc
+        if d is None or self._desc_version != self.buf.version:
+            d = self._describe()
+        bias, w13, w2 = self.bias, self.shared_w13, self.shared_w2
+        d.Wg = self.Wg.data_ptr()
+        d.bias = None if bias is None else bias.data_ptr()
+        d.w13_shared = None if w13 is None else w13.data_ptr()
+        d.w2_shared = None if w2 is None else w2.data_ptr()
+        return ctypes.addressof(d)
 
     # intermediates of the last forward (views of the shared buffers)
     logits = property(lambda self: self.buf.logits)
@@ -137,7 +153,7 @@ class MoELayer:
         assert T <= self.T_max and x.dtype == self.dtype and x.is_contiguous()
         self._T = T
         dst = self.buf.out if out is None else out
-        rc = B.lib().moe_layer_forward(self._desc or self._describe(), x.data_ptr(), aid.data_ptr(), T,
+        rc = B.lib().moe_layer_forward(self._current(), x.data_ptr(), aid.data_ptr(), T,
                                        logits.data_ptr() if logits is not None else None,
                                        residual.data_ptr() if residual is not None else None, dst.data_ptr(),
                                        normed_out.data_ptr() if normed_out is not None else None, eps, B._stream())

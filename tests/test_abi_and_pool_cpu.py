@@ -391,3 +391,30 @@ def test_lru_eviction_order_keeps_a_fixed_number_of_adapters_resident():
     with pytest.raises(ew.EWError):
         p.touch([N + 1])
     p.close()
+
+
+def test_layer_description_follows_its_tensors():
+    """A layer's description for moe_layer_forward names the storage that its weights and buffers have at the call, also
+    when the storage changed under the same tensor object or a buffer was replaced."""
+    from paper_2508_17624_amd.layer import MoELayer
+    M, H, I, k, S, T = 4, 64, 32, 2, 1, 8
+    p = ew.ExpertPool(1, M, 1, 2, 2 * I * H * 4, H * I * 4, flags=FAKE)
+    sw13, sw2 = torch.zeros(S, 2 * I, H), torch.zeros(S, H, I)
+    layer = MoELayer(p, 0, torch.zeros(M, H), sw13, sw2, k, I, T, torch.float32, bias=torch.zeros(2, M))
+
+    def described():
+        d = ew.binding.LayerDesc.from_address(layer._current())
+        return d.Wg, d.bias, d.w13_shared, d.w2_shared, d.y, d.logits
+
+    def actual():
+        return tuple(t.data_ptr() for t in (layer.Wg, layer.bias, layer.shared_w13, layer.shared_w2, layer.buf.y, layer.buf.logits))
+
+    assert described() == actual()
+    layer.Wg.data, layer.bias.data = torch.ones(M, H), torch.ones(2, M)
+    sw13.set_(torch.ones(S, 2 * I, H))
+    sw2.data = torch.ones(S, H, I)
+    assert described() == actual()
+    layer.buf.y, layer.buf.logits = torch.zeros_like(layer.buf.y), torch.zeros_like(layer.buf.logits)
+    layer.shared_w2 = torch.zeros(S, H, I)
+    assert described() == actual()
+    p.close()
