@@ -31,7 +31,7 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X dense bf16, published
 # HBM bytes (read + written) of one launch sequence cannot be read live: they come from rocprofv3 FETCH_SIZE / WRITE_SIZE
 # runs scaled by a plain copy of known size.  The figure is taken from the committed summary of those runs (the line
 # "traffic_bytes_per_call = ..." of the profile that covers the workload), so it changes only when the profile is regenerated.
-PROFILE_OF = {"c2_dsv2lite_prefill": "ffn_ws_c2_prefill_20adapters.md", "c1_dsv2lite_decode": "ffn_ws_c1_decode.md",
+PROFILE_OF = {"c2_dsv2lite_prefill": "grouped_ffn_c2_prefill_20adapters.md", "c1_dsv2lite_decode": "grouped_ffn_c1_decode.md",
               "c3_reroute_permute_int": "reroute_permute_c3.md"}
 
 
@@ -652,7 +652,7 @@ def main():
         "config": {"workload": cfg.name, "tokens": cfg.T, "hidden": cfg.H, "experts": cfg.M, "intermediate": cfg.I,
                    "shared_experts": cfg.S, "top_k": cfg.k, "adapters": cfg.N, "E_max": cfg.E_max, "slots": cfg.P,
                    "active_slots": active, "pool": "vmm"},
-        "roofline": {"bound": "mfma", "kernel": "moe_grouped_ffn_with_shared: routed + shared experts (k_plan_ws, k_ffn_ws<0,8> gate/up+SwiGLU, k_ffn_ws<1,8> down)",
+        "roofline": {"bound": "mfma", "kernel": "moe_grouped_ffn_with_shared: routed + shared experts (k_ffn_plan, k_ffn_big: both products in one launch)",
                      "achieved": flops_ffn / t_ffn_avg / 1e12, "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": flops_ffn / t_ffn_avg / 1e12 / MFMA_BF16_PEAK_TFLOPS, "traffic": traffic_bytes(cfg.name),
                      "measured_peak": mfma_meas, "frac_of_measured": flops_ffn / t_ffn_avg / 1e12 / mfma_meas,
@@ -693,7 +693,7 @@ def main():
         result["extras"] = {"decode_c1": {
             "workload": c1.name, "tokens_per_s": c1.T / t1, "ms_per_step": t1 * 1e3, "median_ms_per_step": t1_med * 1e3,
             "active_slots": a1, "stage_us": stage1,
-            "roofline": {"bound": "hbm", "kernel": "moe_grouped_ffn_with_shared: routed + shared experts (k_plan_ws, k_ffn_ws2<2>: both products in one launch)",
+            "roofline": {"bound": "hbm", "kernel": "moe_grouped_ffn_with_shared: routed + shared experts (k_ffn_plan, k_ffn_dec<4, ...>: both products in one launch)",
                          "achieved": wbytes / f_avg / 1e9,
                          "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": wbytes / f_avg / 1e9 / HBM_PEAK_GBS,
                          "measured_peak": peaks["hbm_read_GBs"], "frac_of_measured": wbytes / f_avg / 1e9 / peaks["hbm_read_GBs"],
