@@ -5,6 +5,8 @@
 // Both kernels are bandwidth bound: 16-byte accesses, fp32 accumulation, one pass.
 #include "ew_internal.h"
 
+#include <type_traits>
+
 namespace {
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
@@ -119,6 +121,107 @@ __global__ __launch_bounds__(256) void k_unpermute_f32(const float* __restrict__
       float4 v = *reinterpret_cast<const float4*>(out + (size_t)t * H + h);  // this thread's own stores
       v.x *= scale; v.y *= scale; v.z *= scale; v.w *= scale;
       *reinterpret_cast<float4*>(normed + (size_t)t * H + h) = v;
+    }
+  }
+}
+
+// 16 bytes of a row, kept as the words that a load brings: taken apart where they are used, so that no load is waited
+// for at the end of the branch that issues it.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+template <bool BF16>
+struct Elem;
+template <>
+struct Elem<true> {
+  using T = uint16_t;
+  static constexpr int N = 8;
+  u32x4 r;
+  __device__ __forceinline__ float get(int i) const { return __uint_as_float(i & 1 ? r[i / 2] & 0xFFFF0000u : r[i / 2] << 16); }
+  __device__ __forceinline__ void set(const float (&f)[N]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r[i] = (uint32_t)f32_to_bf16(f[2 * i]) | ((uint32_t)f32_to_bf16(f[2 * i + 1]) << 16);
+  }
+};
+template <>
+struct Elem<false> {
+  using T = float;
+  static constexpr int N = 4;
+  u32x4 r;
+  __device__ __forceinline__ float get(int i) const { return __uint_as_float(r[i]); }
+  __device__ __forceinline__ void set(const float (&f)[N]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r[i] = __float_as_uint(f[i]);
+  }
+};
+
+// The same for few tokens and k = K <= 8, where the time is memory latency (a block or less per CU): a token's row numbers and
+// weights come in scalar loads (they are the same for the whole block) and its K rows, the first shared rows and the
+// residual are all in flight before the first is added.  Same sums in the same order.
+template <bool BF16, int K>
+__global__ __launch_bounds__(256) void k_unpermute_few(const typename Elem<BF16>::T* __restrict__ y, const int32_t* __restrict__ rop,
+                                                   const float* __restrict__ w, const typename Elem<BF16>::T* __restrict__ shared,
+                                                   const typename Elem<BF16>::T* __restrict__ residual, int S, int T, int H,
+                                                   typename Elem<BF16>::T* __restrict__ out, float eps,
+                                                   typename Elem<BF16>::T* __restrict__ normed) {
+  using E = Elem<BF16>;
+  constexpr int N = E::N, kStep = 256 * N, kAhead = 2;
+  const int t = blockIdx.x;
+  __shared__ float s_part[4];
+  float ss = 0.f;
+  const int32_t* __restrict__ rows = rop + (size_t)t * K;
+  const float* __restrict__ ws = w + (size_t)t * K;
+  E o;
+  auto row16 = [](const typename E::T* p) {
+    E v;
+    v.r = *reinterpret_cast<const u32x4*>(p);
+    return v;
+  };
+  for (int h = threadIdx.x * N; h < H; h += kStep) {
+    float acc[N] = {};
+    E sh_v[kAhead], res;
+    E v[K];
+#pragma unroll
+    for (int j = 0; j < K; ++j) v[j] = row16(y + (size_t)rows[j] * H + h);
+#pragma unroll
+    for (int s = 0; s < kAhead; ++s)
+      if (s < S) sh_v[s] = row16(shared + ((size_t)s * T + t) * H + h);
+    if (residual) res = row16(residual + (size_t)t * H + h);
+#pragma unroll
+    for (int j = 0; j < K; ++j)
+#pragma unroll
+      for (int i = 0; i < N; ++i) acc[i] += ws[j] * v[j].get(i);
+#pragma unroll
+    for (int s = 0; s < kAhead; ++s)
+      if (s < S) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) acc[i] += sh_v[s].get(i);
+      }
+    for (int s = kAhead; s < S; ++s) {
+      const E v = row16(shared + ((size_t)s * T + t) * H + h);
+#pragma unroll
+      for (int i = 0; i < N; ++i) acc[i] += v.get(i);
+    }
+    if (residual) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) acc[i] += res.get(i);
+    }
+    o.set(acc);
+    if constexpr (BF16) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) ss = fmaf(o.get(i), o.get(i), ss);
+    } else {
+      ss = fmaf(acc[0], acc[0], fmaf(acc[1], acc[1], fmaf(acc[2], acc[2], fmaf(acc[3], acc[3], ss))));
+    }
+    *reinterpret_cast<u32x4*>(out + (size_t)t * H + h) = o.r;
+  }
+  if (normed) {
+    const float scale = 1.f / sqrtf(block_sum_256(ss, s_part) / (float)H + eps);
+    for (int h = threadIdx.x * N; h < H; h += kStep) {
+      if (H > kStep) o = row16(out + (size_t)t * H + h);  // this thread's own stores; a single step is still in registers
+      float f[N];
+#pragma unroll
+      for (int i = 0; i < N; ++i) f[i] = o.get(i) * scale;
+      o.set(f);
+      *reinterpret_cast<u32x4*>(normed + (size_t)t * H + h) = o.r;
     }
   }
 }
@@ -314,12 +417,33 @@ int unpermute(const char* who, const void* y_sorted, const int32_t* row_of_pair,
   if (T == 0) return EW_OK;
   if (!y_sorted || !row_of_pair || !topk_w || !out) return fail(EW_ERR_INVALID_ARG, "%s: NULL device pointer", who);
   hipStream_t st = (hipStream_t)stream;
-  if (dtype == EW_BF16)
-    hipLaunchKernelGGL(k_unpermute_bf16, dim3(T), dim3(256), 0, st, (const uint16_t*)y_sorted, row_of_pair, topk_w,
-                       (const uint16_t*)shared_out, (const uint16_t*)residual, S, T, k, H, (uint16_t*)out, eps, (uint16_t*)normed);
-  else
-    hipLaunchKernelGGL(k_unpermute_f32, dim3(T), dim3(256), 0, st, (const float*)y_sorted, row_of_pair, topk_w,
-                       (const float*)shared_out, (const float*)residual, S, T, k, H, (float*)out, eps, (float*)normed);
+  auto few = [&](auto K) {
+    if (dtype == EW_BF16)
+      hipLaunchKernelGGL((k_unpermute_few<true, decltype(K)::value>), dim3(T), dim3(256), 0, st, (const uint16_t*)y_sorted, row_of_pair,
+                         topk_w, (const uint16_t*)shared_out, (const uint16_t*)residual, S, T, H, (uint16_t*)out, eps, (uint16_t*)normed);
+    else
+      hipLaunchKernelGGL((k_unpermute_few<false, decltype(K)::value>), dim3(T), dim3(256), 0, st, (const float*)y_sorted, row_of_pair,
+                         topk_w, (const float*)shared_out, (const float*)residual, S, T, H, (float*)out, eps, (float*)normed);
+  };
+  // k_unpermute_few up to a token per CU.  Whole passes, us, without / with it: 1 token 58.0 / 56.7, 13 tokens 62.8 / 62.5, 64
+  // tokens 239.8 / 238.6, 256 tokens (4 layers) 2113 / 2113; 1999 tokens 319 / 321, where its registers cost occupancy.
+  switch (T <= 256 ? k : 0) {
+    case 1: few(std::integral_constant<int, 1>{}); break;
+    case 2: few(std::integral_constant<int, 2>{}); break;
+    case 3: few(std::integral_constant<int, 3>{}); break;
+    case 4: few(std::integral_constant<int, 4>{}); break;
+    case 5: few(std::integral_constant<int, 5>{}); break;
+    case 6: few(std::integral_constant<int, 6>{}); break;
+    case 7: few(std::integral_constant<int, 7>{}); break;
+    case 8: few(std::integral_constant<int, 8>{}); break;
+    default:
+      if (dtype == EW_BF16)
+        hipLaunchKernelGGL(k_unpermute_bf16, dim3(T), dim3(256), 0, st, (const uint16_t*)y_sorted, row_of_pair, topk_w,
+                           (const uint16_t*)shared_out, (const uint16_t*)residual, S, T, k, H, (uint16_t*)out, eps, (uint16_t*)normed);
+      else
+        hipLaunchKernelGGL(k_unpermute_f32, dim3(T), dim3(256), 0, st, (const float*)y_sorted, row_of_pair, topk_w,
+                           (const float*)shared_out, (const float*)residual, S, T, k, H, (float*)out, eps, (float*)normed);
+  }
   EW_LAUNCH_CHECK("k_unpermute");
   return EW_OK;
 }

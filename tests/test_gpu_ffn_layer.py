@@ -360,6 +360,28 @@ def test_unpermute_rmsnorm_equals_the_two_calls(ew, dtype, T, k, H, S):
         ew.binding.moe_unpermute_rmsnorm(y, rop, w, eps, shared_out=sh, out=out1, normed_out=out1)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("T,k,H,S,res", [(11, 1, 8, 0, False), (1, 2, 2048, 1, True), (11, 3, 2056, 2, False), (256, 4, 1016, 3, True),
+                                         (257, 4, 1016, 3, True), (11, 5, 64, 0, True), (11, 6, 2048, 2, True), (11, 7, 4096, 5, False),
+                                         (11, 8, 1544, 1, False), (11, 9, 2048, 2, True), (11, 64, 72, 3, False)])
+def test_unpermute_every_width(ew, dtype, T, k, H, S, res):
+    """Every number of experts per token that has a kernel of its own and two that do not, both sides of the token count up to
+    which those kernels run, fewer and more shared rows than are loaded ahead, rows shorter and longer than a workgroup's step.
+    Small integers and powers of two: exact in fp32, one rounding in bf16."""
+    rng = np.random.default_rng(k * 100 + S)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    dev = lambda a: torch.from_numpy(a).cuda()
+    y = rng.integers(-8, 9, size=(T * k, H)).astype(np.float32)
+    w = rng.choice([0.25, 0.5, 1.0, 2.0], size=(T, k)).astype(np.float32)
+    sh = rng.integers(-4, 5, size=(S, T, H)).astype(np.float32)
+    r = rng.integers(-4, 5, size=(T, H)).astype(np.float32)
+    rop = rng.permutation(T * k).astype(np.int32)
+    ref = moe.unpermute(y, rop, w, sh.sum(0) if S else None) + (r if res else 0)
+    got = ew.moe_unpermute(dev(y).to(td), dev(rop), dev(w), dev(sh).to(td) if S else None, residual=dev(r).to(td) if res else None)
+    want = torch.from_numpy(np.ascontiguousarray(ref)).to(torch.float32).to(td)
+    assert torch.equal(got.cpu(), want)
+
+
 @pytest.mark.parametrize("cfg_index", [0, 1])
 def test_gate_logits(ew, cfg_index):
     cfg = wl.get_config(cfg_index).with_(gate_bias=2.0)
