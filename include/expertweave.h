@@ -431,7 +431,8 @@ int ew_probe_mfma_bf16(int workgroups, int iters, int random_operands, unsigned 
  *   ws_frags            path 3: kernel shape, 32-token fragments per row chunk (1, 2, 4: the kernel for
  *                       few rows per slot; 8: the one for many)
  *   ws_chunk_frags      path 3: cap on the fragments per row chunk (1..ws_frags)
- *   ws_wait_ticks       without effect (no kernel waits for other workgroups of its slot)
+ *   ws_wait_ticks       path 3: > 0: looks at the activation rows' completion counter before a unit of the
+ *                       second product gives up waiting and writes NaN; 0 or less = automatic (seconds)
  *   ws_two_launches     path 3: non-zero = the two products as two launches; 0 = one launch for both */
 void ew_tune_ffn(int path, int stream_token_tiles, int stream_threads, int ws_frags,
                  int ws_chunk_frags, int ws_wait_ticks, int ws_two_launches);

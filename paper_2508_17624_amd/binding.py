@@ -361,7 +361,8 @@ def tune_ffn(path: int = 0, stream_token_tiles: int = 0, stream_threads: int = 0
     """Kernel-selection override of moe_grouped_ffn(bf16), process-global; no arguments = automatic.
     path 1 = register-streaming kernel (stream_token_tiles 1|2, stream_threads), 2 = LDS-tiled GEMM kernel,
     3 = LDS-direct kernels (ws_frags 1|2|4|8 = kernel shape, ws_chunk_frags = cap on 32-row fragments
-    per row chunk, ws_two_launches = the two products as two launches; ws_wait_ticks has no effect)."""
+    per row chunk, ws_two_launches = the two products as two launches, ws_wait_ticks > 0 = looks before a unit of the second
+    product gives up waiting for its activation rows and writes NaN)."""
     lib().ew_tune_ffn(path, stream_token_tiles, stream_threads, ws_frags, ws_chunk_frags, ws_wait_ticks, int(ws_two_launches))
 
 

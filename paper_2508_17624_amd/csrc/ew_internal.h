@@ -63,8 +63,9 @@ int grouped_ffn_f32(const void* x, int T, int k, int H, int I, int P, int S, con
 // persistent workgroups claim their units from a plan built on the device).
 size_t ffn_plan_ints(int T, int rows, int P);
 // Plan shape of a call with `rows` rows in all and `slots` slots (shared experts included).  frags, chunk_frags: the tuning
-// hook's kernel shape and cap on 32-row fragments per chunk, 0 = automatic; merge: the two products share a launch.
-FfnPlanShape ffn_plan_shape(int T, int rows, int slots, int frags, int chunk_frags, bool merge);
+// hook's kernel shape and cap on 32-row fragments per chunk, 0 = automatic; merge: the two products share a launch;
+// wait_polls: the tuning hook's limit on a unit's wait, 0 = automatic.
+FfnPlanShape ffn_plan_shape(int T, int rows, int slots, int frags, int chunk_frags, bool merge, int wait_polls);
 // The plan kernel alone (what launch_ffn_bf16 runs first unless plan_ready).
 int launch_ffn_plan(const int32_t* counts, const int32_t* offsets, int P, int S, int T, int rows_routed, const FfnPlanShape& sh,
                     int32_t* plan, hipStream_t st);

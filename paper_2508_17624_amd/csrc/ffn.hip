@@ -183,6 +183,7 @@ int g_nt_override = 0;         // register-streaming kernel: 16-token tiles per 
 int g_threads_override = 0;    // register-streaming kernel: threads per block
 int g_ws_frags = 0;            // LDS-direct kernels: 32-token fragments of the kernel shape (1, 2, 4: k_ffn_dec, 8: k_ffn_big)
 int g_ws_chunk_frags = 0;      // LDS-direct kernels: 32-token fragments per row chunk at most (<= shape)
+int g_ws_wait = 0;             // LDS-direct kernels: looks at a completion counter before a wait is given up
 int g_ws_merge = 0;            // LDS-direct kernels: 1 = the two products as two launches
 
 size_t plan_bytes(int T, int rows, int P) {
@@ -223,7 +224,7 @@ extern "C" void ew_tune_ffn(int path, int stream_token_tiles, int stream_threads
   g_threads_override = stream_threads;
   g_ws_frags = ws_frags;
   g_ws_chunk_frags = ws_chunk_frags;
-  (void)ws_wait_ticks;
+  g_ws_wait = ws_wait_ticks > 0 ? ws_wait_ticks : 0;
 }
 
 extern "C" size_t moe_grouped_ffn_workspace_bytes(int T, int k, int H, int I, int P, int dtype) {
@@ -240,7 +241,7 @@ bool ffn_shape_of_call(int dtype, int T, int k, int H, int I, int P, int S, FfnP
   const long long rows = (long long)T * (k + S);
   const int slots = P + S, Kmax = H > I ? H : I;
   if (rows >= (1ll << 31) || slots > 2048 || (unsigned long long)rows * (unsigned long long)Kmax * 2ull >= (1ull << 32)) return false;
-  *sh = ffn_plan_shape(T, (int)rows, slots, g_ws_frags, g_ws_chunk_frags, g_ws_merge != 1);
+  *sh = ffn_plan_shape(T, (int)rows, slots, g_ws_frags, g_ws_chunk_frags, g_ws_merge != 1, g_ws_wait);
   return true;
 }
 

@@ -312,14 +312,10 @@ __device__ __forceinline__ void big_body(const FfnArgs& a, unsigned char* s_lds)
     }
     ++p_h;
   };
-  auto wait_done = [&](const FfnUnit& u) {
+  [[maybe_unused]] int polls = a.wait_polls;
+  auto wait_done = [&](const FfnUnit& u, int qi) {
     if (u.mode == 0 || u.ready) return;
-    const int32_t* flag = a.done + u.chunk;
-    const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
-    while (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < a.m[0].G &&
-           __builtin_amdgcn_s_memrealtime() - t0 < (unsigned long long)a.spin_ticks)
-      __builtin_amdgcn_s_sleep(1);
-    asm volatile("" ::: "memory");
+    wait_stored(a.done + u.chunk, a.m[0].G, polls, queue + qi * kQI);
   };
 
   // ---- the multiplying side: wave (wr, p) owns 64 weight rows and token fragments p, p + 2, ...
@@ -333,7 +329,7 @@ __device__ __forceinline__ void big_body(const FfnArgs& a, unsigned char* s_lds)
     aim(cur, 0);
     for (int i = 0; i < 3; ++i) issue();
   } else if constexpr (ROLE == 1) {
-    wait_done(cur);
+    wait_done(cur, 0);
     aim(cur, 0);
     issue();
   } else if constexpr (ROLE == 2) {
@@ -372,6 +368,10 @@ __device__ __forceinline__ void big_body(const FfnArgs& a, unsigned char* s_lds)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][f][e] = 0.f;
         multiply<NB>(nk, wa, tb, acc, step);
+        if (NB > 0 && wait_expired(cur, q0 + (uint32_t)((seq & 3) * kQI) * 4u)) {
+#pragma unroll
+          for (int f = 0; f < NB; ++f) acc[0][f] = acc[1][f] = __builtin_nanf("");
+        }
         // Every wave is done with the unit's last slab, whose ring slots (two weight halves, one token slab: 64 KB) are not
         // loaded into before the next unit's first barrier.  Each wave turns its output there, 8 KB at a time, so that whole
         // rows of it leave in one piece: accumulator element e = 4 b + j of fragment i is weight row 8 b + 4 h + j of the
@@ -482,7 +482,7 @@ __device__ __forceinline__ void big_body(const FfnArgs& a, unsigned char* s_lds)
 #pragma unroll
           for (int i = 0; i < (ROLE == 0 ? 2 : 1); ++i) {
             if (!p_next && p_h == p_n && nxt.slot >= 0 && !(ROLE == 1 && change)) {
-              if (ROLE == 1) wait_done(nxt);
+              if (ROLE == 1) wait_done(nxt, (seq + 1) & 3);
               aim(nxt, (seq + 1) & 3);
               p_next = true;
             }
@@ -511,7 +511,7 @@ __device__ __forceinline__ void big_body(const FfnArgs& a, unsigned char* s_lds)
     nxt = read_unit(q0 + (uint32_t)(((seq + 1) & 3) * kQI) * 4u);
     if constexpr (ROLE <= 1) {
       if (!p_next) {  // the token wave, from the first product to the second: nothing of this unit is in flight yet
-        if (ROLE == 1) wait_done(cur);
+        if (ROLE == 1) wait_done(cur, seq & 3);
         aim(cur, seq & 3);
         for (int i = 0; i < (ROLE == 0 ? 3 : 1); ++i) issue();
       }

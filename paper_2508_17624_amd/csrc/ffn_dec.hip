@@ -16,7 +16,7 @@
 //     are stored.  Every such wait ends: a workgroup that waits holds second-product units only, since it claimed the first
 //     of them when all first-product units were claimed; a first-product unit is held by a workgroup whose earlier units
 //     are first-product too, which wait for nothing, and whose stores are counted before it waits for anything (workgroups
-//     that are not resident hold no claims).  The time limit on the wait is a safety net that is never reached.
+//     that are not resident hold no claims).  A limit on the number of looks makes sure of it, see wait_stored.
 //   * Coherence of the activations: agent-scope stores, acknowledged before they are counted; for the loads see ACT_AUX.
 // Measured (call with plan, one box): 1 token on 8 experts of 2048 x 1408: 76 -> 43 us; 13 tokens on 36 of 1024 x 896: 88 ->
 // 47 us; 64 tokens on 90: 263 -> 246 us (6.3 TB/s of weights; a bare stream of the same slabs reaches 6.85); 512 tokens on
@@ -296,14 +296,10 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds)
     ++p_k;
     p_slot = p_slot + 1 == depth ? 0 : p_slot + 1;
   };
-  auto wait_done = [&](const FfnUnit& u) {  // token waves: the unit's activation rows are stored
+  [[maybe_unused]] int polls = a.wait_polls;
+  auto wait_done = [&](const FfnUnit& u, int qi) {  // token waves: the unit's activation rows are stored
     if (u.mode == 0 || u.ready) return;
-    const int32_t* flag = a.done + u.chunk * kDecDoneStride;
-    const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
-    while (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < a.m[0].G &&
-           __builtin_amdgcn_s_memrealtime() - t0 < (unsigned long long)a.spin_ticks)
-      __builtin_amdgcn_s_sleep(1);
-    asm volatile("" ::: "memory");
+    wait_stored(a.done + u.chunk * kDecDoneStride, a.m[0].G, polls, queue + qi * C::QI);
   };
 
   // ---- the multiplying side
@@ -317,7 +313,7 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds)
   int seq = 0;                                                                // units done
 
   if constexpr (LOADS) {
-    if (ROLE == 1) wait_done(cur);
+    if (ROLE == 1) wait_done(cur, 0);
     aim(cur, 0);
     for (int i = 0; i < depth - 1; ++i) issue();
   } else if constexpr (ROLE == 2) {
@@ -346,6 +342,10 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds)
           if constexpr (NB > 0) mul_slab<MFW, NB, KS, C::PN * C::FRAG, FSTEP * C::FRAG>(rd_w + c_w * C::WSLAB, rd_t + c_t * C::TSLAB, acc);
           c_w = c_w + 1 == a.depth_w ? 0 : c_w + 1;
           c_t = c_t + 1 == a.depth_t ? 0 : c_t + 1;
+        }
+        if (NB > 0 && wait_expired(cur, q0 + (uint32_t)((seq & 3) * C::QI) * 4u)) {
+#pragma unroll
+          for (int f = 0; f < NB; ++f) acc[0][f] = acc[1][f] = __builtin_nanf("");
         }
 #pragma unroll
         for (int f = 0; f < NB; ++f) {
@@ -403,7 +403,7 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds)
         if (kt == nk - 2) sched_publish<C::QI>(a, sc, queue + ((seq + 2) & 3) * C::QI);
       } else if constexpr (LOADS) {
         if (!p_next && p_k == nk && nxt.slot >= 0 && !(ROLE == 1 && change)) {
-          if (ROLE == 1) wait_done(nxt);
+          if (ROLE == 1) wait_done(nxt, (seq + 1) & 3);
           aim(nxt, (seq + 1) & 3);
           p_next = true;
         }
@@ -429,7 +429,7 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds)
     nxt = read_unit(q0 + (uint32_t)(((seq + 1) & 3) * C::QI) * 4u);
     if constexpr (LOADS) {
       if (!p_next) {  // nothing of this unit is in flight yet (token waves, from the first product to the second)
-        if (ROLE == 1) wait_done(cur);
+        if (ROLE == 1) wait_done(cur, seq & 3);
         aim(cur, seq & 3);
         for (int i = 0; i < depth - 1; ++i) issue();
       }

@@ -65,6 +65,7 @@ struct FfnPlanShape {
   int n_done;        // its completion counters
   int done_off;      // where the completion counters start, in ints from the start of the plan
   int merged;        // the two products share a launch
+  int wait_polls;    // looks at a completion counter before a wait is given up
 };
 
 // Both candidates: k_ffn_big runs where an active slot has more rows on average than a chunk of k_ffn_dec takes (beyond that

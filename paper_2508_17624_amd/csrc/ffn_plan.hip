@@ -43,6 +43,9 @@ int list_cap(int rows, int P) {
   return ceil_div((int)(worst < kPlanMaxEnt ? worst : kPlanMaxEnt), 8) + 1;
 }
 
+// A look takes well over half a microsecond: seconds, where a wait lasts as long as two units at most.
+constexpr int kWaitPolls = 1 << 22;
+
 // k_ffn_dec: chunks of a plan at most: one per active slot and one more per bt rows.
 int dec_chunk_cap(int rows, int P, int bt) { return (P < rows ? P : rows) + rows / bt + 1; }
 
@@ -58,9 +61,10 @@ size_t ffn_plan_ints(int T, int rows, int P) {
 // The host knows totals only: no slot has more rows than the call has tokens, and rows / slots is the least that an active
 // slot has on average.  Up to 512 tokens k_ffn_dec runs whatever the router does (512 tokens on 64 of 128 slots: 203 us,
 // against 290 with 256-row units), above that where the average says so; if it does not, the counts decide.
-FfnPlanShape ffn_plan_shape(int T, int rows, int slots, int frags, int chunk_frags, bool merge) {
+FfnPlanShape ffn_plan_shape(int T, int rows, int slots, int frags, int chunk_frags, bool merge, int wait_polls) {
   FfnPlanShape sh{};
   sh.merged = merge;
+  sh.wait_polls = wait_polls > 0 ? wait_polls : kWaitPolls;
   const int per_slot = rows / (slots < rows ? slots : rows);
   const bool forced = frags > 0 || chunk_frags > 0;
   if (forced ? frags == 8 || frags == 0 : T > 512 || per_slot > kPickRows) {
@@ -119,7 +123,7 @@ int launch_ffn_bf16(const void* x, int rows_routed, int k, int H, int I, int P, 
   a.por = por; a.plan = plan; a.done = plan + sh.done_off;
   a.P = P; a.rows_routed = rows_routed; a.sh_rows = T > 0 ? T : 1; a.k = k;
   a.cap = sh.cap; a.list_chunks = sh.ch * sh.cap;
-  a.spin_ticks = 20000000u;  // 0.2 s
+  a.wait_polls = sh.wait_polls;
   const bool both = sh.dec && sh.big;
   if (sh.dec) {
     a.pick = both ? 1 : 0;

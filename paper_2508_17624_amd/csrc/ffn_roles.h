@@ -32,7 +32,7 @@ struct FfnArgs {
   int depth_w, depth_t;       // k_ffn_dec: slabs in its rings
   int cap, list_chunks;       // k_ffn_big: entries and chunks per list of the plan at most
   int pick;                   // 0, or this kernel's number in plan[kPlanPick]
-  unsigned int spin_ticks;
+  int wait_polls;             // looks at a completion counter before a wait for it is given up
 };
 
 // The kernel that the counts chose (wave-uniform, as the branch on it has to be).
@@ -42,7 +42,7 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f) { return __builtin_bit_
 __device__ __forceinline__ float silu_f32(float g) { return g * __builtin_amdgcn_rcpf(1.f + __expf(-g)); }
 
 struct FfnUnit {
-  int slot, off, rows, g, mode, chunk, ready, alone;  // slot < 0: no unit left
+  int slot, off, rows, g, mode, chunk, ready, alone;  // slot < 0: no unit left; ready: 1 nothing to wait for, kExpired the wait was given up
 };
 
 // LDS-direct load: 16 bytes per lane from base + off (base: wave-uniform) to lds + 16 * lane.  AUX: 0 plain, 2 nt, 16 sc1.
@@ -90,6 +90,31 @@ __device__ __forceinline__ void read_lds_ints(uint32_t addr, uint32_t* r) {
                  : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]) : "v"(addr), "n"(STEP), "n"(2 * STEP), "n"(3 * STEP) : "memory");
     if constexpr (N > 4) read_lds_ints<N - 4, STEP>(addr + 4 * STEP, r + 4);
   }
+}
+
+// A token wave's wait for the first-product units of its unit's chunk, `target` of them.  It always ends by itself (the
+// argument is in ffn_dec.hip); should that ever fail it is given up after a number of looks, which only count while the wave
+// runs, and the unit's entry in the LDS queue says so: its output is then written as NaN, never made from rows that may not be
+// stored.  The waits after one that was given up look once.
+constexpr int kExpired = -1, kReadyWord = 6;  // the word of a queue entry
+__device__ __forceinline__ void wait_stored(const int32_t* flag, int target, int& polls, int32_t* entry) {
+  for (int looks = 1; __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target; ++looks) {
+    if (looks >= polls) {
+      polls = 1;
+      if ((threadIdx.x & 63) == 0) entry[kReadyWord] = kExpired;
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      break;
+    }
+    __builtin_amdgcn_s_sleep(1);
+  }
+  asm volatile("" ::: "memory");
+}
+// Multiplying waves, behind a unit's last slab: whether its token waves gave up.  entry: LDS address of the unit's queue entry.
+__device__ __forceinline__ bool wait_expired(const FfnUnit& u, uint32_t entry) {
+  if (u.mode == 0 || u.ready == 1) return false;
+  uint32_t r;
+  read_lds_ints<1, 4>(entry + 4 * kReadyWord, &r);
+  return (int)__builtin_amdgcn_readfirstlane(r) == kExpired;
 }
 
 // ffn_dec.hip: calls with few rows per slot.

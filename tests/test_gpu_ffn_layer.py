@@ -273,6 +273,32 @@ def test_one_launch_for_both_products_equals_two(ew, T, k, P, S, nf):
         assert rel_l2(got[r0:r1], want) <= FFN_REL_L2 and max_abs(got[r0:r1], want) <= FFN_MAX_ABS, f"slot {s}"
 
 
+@pytest.mark.parametrize("T", [16, 256], ids=["few-rows", "many-rows"])
+def test_a_wait_given_up_writes_nan(ew, T):
+    """One slot with fewer first-product units than workgroups: those left over start with units of the second product, whose
+    activation rows cannot be there at their first look.  Allowed one look only, they give up: what they write is NaN, everything
+    else has the bits of the undisturbed call, and so has the whole next call."""
+    k, P, H, I = 1, 1, 2048, 1408
+    rng = np.random.default_rng(T)
+    i32 = lambda *v: torch.tensor(v, dtype=torch.int32, device="cuda")
+    bf = lambda *shape, scale=1.0: (torch.from_numpy(rng.standard_normal(shape, dtype=np.float32)) * scale).cuda().bfloat16()
+    x, w13, w2 = bf(T, H), bf(P, 2 * I, H, scale=0.02), bf(P, H, I, scale=0.02)
+
+    def run(looks):
+        ew.binding.tune_ffn(ws_wait_ticks=looks)
+        try:
+            return ew.moe_grouped_ffn(x, k, I, P, i32(T), i32(0, T), None, w13, w2)
+        finally:
+            ew.binding.tune_ffn()
+
+    ref = run(-1)
+    assert torch.isfinite(ref.float()).all()
+    got = run(1)
+    given_up = torch.isnan(got)
+    assert given_up.any() and torch.equal(got[~given_up], ref[~given_up])
+    assert torch.equal(run(-1), ref)
+
+
 def test_one_launch_equals_two_on_random_decode_shapes(ew):
     """Twenty random decode-sized calls (token count, top-k, slots, shared experts, skew all drawn): the one-launch
     result equals the two-launch result bit for bit every time, with and without a row map."""
