@@ -51,10 +51,13 @@ int dec_chunk_cap(int rows, int P, int bt) { return (P < rows ? P : rows) + rows
 
 }  // namespace
 
+// Never less for more tokens (a workspace made for a largest batch serves the smaller ones): k_ffn_dec's chunks are 16 rows up
+// to 16 tokens and more above, so the first 16 tokens alone can take more chunks than the whole batch.
 size_t ffn_plan_ints(int T, int rows, int P) {
   const int cap = list_cap(rows, P);
   const size_t big = (size_t)kPlanHdr + (size_t)8 * kEnt * cap, big_done = (size_t)8 * entry_chunks(rows, P, 32) * cap;
-  const size_t chunks = dec_chunk_cap(rows, P, T <= 16 ? 16 : 32), dec = kDecEnt + 4 * chunks, dec_done = kDecDoneStride * chunks;
+  const int first = dec_chunk_cap(rows / T * (T < 16 ? T : 16), P, 16), all = T > 16 ? dec_chunk_cap(rows, P, 32) : 0;
+  const size_t chunks = first > all ? first : all, dec = kDecEnt + 4 * chunks, dec_done = kDecDoneStride * chunks;
   return (big > dec ? big : dec) + (big_done > dec_done ? big_done : dec_done);
 }
 

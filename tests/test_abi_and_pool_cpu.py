@@ -51,6 +51,17 @@ def test_host_side_argument_checks_need_no_gpu():
     assert need >= 64 * 6 * 1408 * 2 and need % 256 == 0
 
 
+@pytest.mark.parametrize("dtype", [ew.EW_F32, ew.EW_BF16])
+@pytest.mark.parametrize("I", [1, 4, 128])
+def test_ffn_workspace_never_shrinks_with_more_tokens(dtype, I):
+    """A workspace made for the largest batch serves every smaller one, also where the work plan's chunk size changes."""
+    size = ew.lib().moe_grouped_ffn_workspace_bytes
+    for k in (1, 2, 6, 9, 16):
+        for P in (1, 3, 7, 40, 386, 2048):
+            need = [size(T, k, 128, I, P, dtype) for T in (*range(1, 140), 511, 512, 513, 4096, 65536)]
+            assert all(a <= b for a, b in zip(need, need[1:])), (k, P)
+
+
 def test_pool_create_rejects_bad_arguments():
     for kw in (dict(num_layers=0), dict(M=0), dict(N=-1), dict(w13_bytes=0), dict(page_bytes=1000), dict(flags=64 | FAKE)):
         args = dict(num_layers=1, M=4, N=2, E_max=2, w13_bytes=4096, w2_bytes=4096, page_bytes=4096, flags=FAKE)
