@@ -369,7 +369,7 @@ int moe_unpermute_rmsnorm(const void* y_sorted, const int32_t* row_of_pair, cons
  *                   the routed rows of the T tokens, then the shared experts' [S, T, H] outputs
  *   ws_perm         moe_reroute_permute_workspace_bytes(T_max, k, P)
  *   ws_ffn          moe_grouped_ffn_workspace_bytes(T_max, k + S, H, I, P + S, dtype)
- * Errors: those of the calls; INVALID_ARG if T > T_max. */
+ * Errors: those of the calls; INVALID_ARG if T > T_max; UNSUPPORTED if T*(k+S) >= 2^31. */
 typedef struct ew_layer {
   int dtype, H, I, M, k, N, P, S, renormalize, T_max;
   const float* Wg;

@@ -11,6 +11,9 @@ extern "C" int moe_layer_forward(const ew_layer* L, const void* x, const int32_t
   if (!L) return fail(EW_ERR_INVALID_ARG, "moe_layer_forward: layer is NULL");
   if (T < 0 || T > L->T_max) return fail(EW_ERR_INVALID_ARG, "moe_layer_forward: T=%d outside 0..T_max=%d", T, L->T_max);
   if (L->S < 0 || L->k < 1 || L->H < 1 || L->I < 1 || L->P < 1) return fail(EW_ERR_INVALID_ARG, "moe_layer_forward: bad dimensions");
+  // (with logits given, the steps before the combine would take any other type for fp32, and count rows in 32 bits)
+  if (L->dtype != EW_F32 && L->dtype != EW_BF16) return fail(EW_ERR_INVALID_ARG, "moe_layer_forward: unknown dtype %d", L->dtype);
+  if ((long long)T * ((long long)L->k + L->S) >= (1ll << 31)) return fail(EW_ERR_UNSUPPORTED, "moe_layer_forward: the row count must be below 2^31");
   int rc;
   if (!logits) {
     rc = moe_gate_logits(x, L->dtype, L->Wg, T, L->H, L->M, L->bias ? adapter_id : nullptr, L->bias, L->logits, stream);

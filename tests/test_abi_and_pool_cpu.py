@@ -62,6 +62,31 @@ def test_ffn_workspace_never_shrinks_with_more_tokens(dtype, I):
             assert all(a <= b for a, b in zip(need, need[1:])), (k, P)
 
 
+def test_layer_forward_checks_its_arguments_before_any_launch():
+    """Errors that need no GPU: what is refused here has enqueued nothing (a launch would fail differently, and with logits
+    given no earlier step looks at the type)."""
+    lib = ew.lib()
+    one = C.c_void_p(256)                                       # never dereferenced
+
+    def call(T=4, logits=one, **kw):
+        d = dict(dtype=ew.EW_F32, H=64, I=32, M=8, k=2, N=1, P=16, S=1, T_max=1 << 30)
+        d.update({n: 256 for n, t in ew.binding.LayerDesc._fields_ if t is C.c_void_p})
+        d.update(ws_perm_bytes=1 << 40, ws_ffn_bytes=1 << 40, **kw)
+        return lib.moe_layer_forward(C.byref(ew.binding.LayerDesc(**d)), one, one, T, logits, None, one, None, 0.0, None)
+
+    assert lib.moe_layer_forward(None, one, one, 4, one, None, one, None, 0.0, None) == -1
+    for dtype in (2, 7, -1):
+        assert call(dtype=dtype) == -1 and b"dtype" in lib.ew_last_error()
+        assert call(dtype=dtype, logits=None) == -1
+    assert call(T=-1) == -1 and call(T=9, T_max=8) == -1
+    for field in ("k", "H", "I", "P"):
+        assert call(**{field: 0}) == -1
+    assert call(S=-1) == -1
+    # each row count of its own below 2^31, the sum not
+    assert call(T=1 << 29, k=2, S=2) == -6 and b"2^31" in lib.ew_last_error()
+    assert call(T=1 << 29, k=2, S=2, dtype=ew.EW_BF16, H=128, I=128) == -6
+
+
 def test_pool_create_rejects_bad_arguments():
     for kw in (dict(num_layers=0), dict(M=0), dict(N=-1), dict(w13_bytes=0), dict(page_bytes=1000), dict(flags=64 | FAKE)):
         args = dict(num_layers=1, M=4, N=2, E_max=2, w13_bytes=4096, w2_bytes=4096, page_bytes=4096, flags=FAKE)
