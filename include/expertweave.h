@@ -254,8 +254,8 @@ int moe_reroute_singleop(const int32_t* topk_ids, const int32_t* adapter_id, con
  *   y_sorted   [dev] dtype [T*k, H]
  * bf16: inputs bf16, fp32 accumulation on MFMA, the activation silu(g)*u is rounded to bf16
  * between the two products, y rounded to bf16.  f32: plain fp32 throughout.
- * Limits (bf16): H % 128 == 0 and I % 128 == 0.  Calls with T*k*max(H,I)*2 >= 2^32 bytes or
- * P > 2048 take an older, slower kernel, which also needs max(H, I) <= 5000.  T = 0 is a no-op.
+ * Limits (bf16): H % 128 == 0 and I % 128 == 0.  Calls with T*k*max(H,I)*2 >= 2^32 bytes, P > 2048
+ * or H*I >= 2^30 take an older, slower kernel, which also needs max(H, I) <= 5000.  T = 0 is a no-op.
  * Workspace: moe_grouped_ffn_workspace_bytes(T, k, H, I, P, dtype) with the same T and k.
  * Errors: INVALID_ARG, UNSUPPORTED, WORKSPACE, HIP. */
 size_t moe_grouped_ffn_workspace_bytes(int T, int k, int H, int I, int P, int dtype);
@@ -276,8 +276,8 @@ int moe_grouped_ffn(const void* x, int dtype, int T, int k, int H, int I, int P,
  *   counts, offsets, pair_of_row [dev]: those of the P routed slots, exactly as for moe_grouped_ffn
  *   w13_shared [dev] bf16 [S, 2I, H]   w2_shared [dev] bf16 [S, H, I]
  *   y_sorted   [dev] bf16 [T*(k+S), H]
- * Limits: bf16 only, H % 128 == 0, I % 128 == 0, P + S <= 2048, T*(k+S)*max(H,I)*2 < 2^32 bytes;
- * anything else is UNSUPPORTED (make two moe_grouped_ffn calls instead).  T = 0 is a no-op.
+ * Limits: bf16 only, H % 128 == 0, I % 128 == 0, P + S <= 2048, T*(k+S)*max(H,I)*2 < 2^32 bytes,
+ * H*I < 2^30; anything else is UNSUPPORTED (make two moe_grouped_ffn calls instead).  T = 0 is a no-op.
  * Workspace: moe_grouped_ffn_workspace_bytes(T, k + S, H, I, P + S, dtype).
  * Errors: INVALID_ARG, UNSUPPORTED, WORKSPACE, HIP. */
 int moe_grouped_ffn_with_shared(const void* x, int dtype, int T, int k, int H, int I, int P, int S,

@@ -71,7 +71,7 @@ int launch_ffn_plan(const int32_t* counts, const int32_t* offsets, int P, int S,
                     int32_t* plan, hipStream_t st);
 // S > 0: slots P .. P+S-1 are shared experts (weights w13_sh / w2_sh) that every one of the rows_routed / k tokens
 // visits; their rows follow the routed ones in act and y, and plan must be sized for all rows and P + S slots.
-// H % 128 == 0, I % 128 == 0 and rows * max(H, I) * 2 < 2^32 are the caller's checks.
+// H % 128 == 0, I % 128 == 0, rows * max(H, I) * 2 < 2^32 and H * I * 4 < 2^32 are the caller's checks.
 int launch_ffn_bf16(const void* x, int rows_routed, int k, int H, int I, int P, int S, const FfnPlanShape& sh, bool plan_ready,
                     const int32_t* counts, const int32_t* offsets, const int32_t* por, const void* w13, const void* w2, const void* w13_sh,
                     const void* w2_sh, void* act, void* y, int32_t* plan, hipStream_t st);

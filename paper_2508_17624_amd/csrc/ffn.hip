@@ -241,6 +241,8 @@ bool ffn_shape_of_call(int dtype, int T, int k, int H, int I, int P, int S, FfnP
   const long long rows = (long long)T * (k + S);
   const int slots = P + S, Kmax = H > I ? H : I;
   if (rows >= (1ll << 31) || slots > 2048 || (unsigned long long)rows * (unsigned long long)Kmax * 2ull >= (1ull << 32)) return false;
+  // lane offsets of 32 bits into a slot's gate and up rows
+  if ((unsigned long long)H * (unsigned long long)I * 4ull >= (1ull << 32)) return false;
   *sh = ffn_plan_shape(T, (int)rows, slots, g_ws_frags, g_ws_chunk_frags, g_ws_merge != 1, g_ws_wait);
   return true;
 }
@@ -273,7 +275,7 @@ int grouped_ffn(const char* who, bool plan_ready, const void* x, int dtype, int 
   if (S > 0 || plan_ready) {
     // only the LDS-direct kernels know the shared experts' slots and take a plan built elsewhere
     if (!ws_path)
-      return fail(EW_ERR_UNSUPPORTED, "%s: needs bf16, H and I multiples of 128, P+S <= 2048 and T*(k+S)*max(H,I)*2 < 2^32", who);
+      return fail(EW_ERR_UNSUPPORTED, "%s: needs bf16, H and I multiples of 128, P+S <= 2048, T*(k+S)*max(H,I)*2 < 2^32 and H*I < 2^30", who);
     return ew::launch_ffn_bf16(x, rows, k, H, I, P, S, shape, plan_ready, counts, offsets, pair_of_row, w13_base, w2_base, w13_shared,
                              w2_shared, act, y_sorted, plan, st);
   }
@@ -293,14 +295,14 @@ int grouped_ffn(const char* who, bool plan_ready, const void* x, int dtype, int 
   // Many rows per slot: compute bound, LDS-tiled GEMM.  Few rows per slot: HBM bound, stream weights.
   // The host knows only the totals, so the average rows per possible slot decides.
   const int max_slots = P < rows ? P : rows;
-  // Default: the LDS-direct kernels.  Their byte offsets into x / the activations are 32 bit
+  // Default: the LDS-direct kernels.  Their byte offsets into x, the activations and a slot's weights are 32 bit
   // and their work plan sorts at most 2048 slots (the limit of the permutation kernels as well).
   if (ws_path) {
     return ew::launch_ffn_bf16(x, rows, k, H, I, P, 0, shape, false, counts, offsets, pair_of_row, w13_base, w2_base, nullptr, nullptr,
                              act, y_sorted, plan, st);
   }
   if (g_path_override == 3)
-    return fail(EW_ERR_UNSUPPORTED, "%s(bf16): the streaming path needs rows*max(H,I)*2 < 2^32 and P <= 2048", who);
+    return fail(EW_ERR_UNSUPPORTED, "%s(bf16): the streaming path needs rows*max(H,I)*2 < 2^32, H*I < 2^30 and P <= 2048", who);
   const bool gemm = g_path_override ? g_path_override == 2 : (rows / max_slots >= 32 && I % 64 == 0);
   if (gemm)
     return ew::launch_ffn_gemm(x, rows, k, H, I, P, counts, offsets, pair_of_row, w13_base, w2_base, act, y_sorted, plan, st);

@@ -1136,7 +1136,7 @@ extern "C" int moe_route_reroute_permute_plan(const float* logits, const int32_t
   if (T > 0) {
     if (!ew::ffn_shape_of_call(dtype, T, k, H, I, P, S, &shape))
       return fail(EW_ERR_UNSUPPORTED, "%s: the grouped FFN of these dimensions takes no plan (needs bf16, H and I multiples of 128, "
-                  "P+S <= 2048, T*(k+S)*max(H,I)*2 < 2^32)", who);
+                  "P+S <= 2048, T*(k+S)*max(H,I)*2 < 2^32, H*I < 2^30)", who);
     const size_t need = moe_grouped_ffn_workspace_bytes(T, k + S, H, I, P + S, dtype);
     if (!ffn_ws || ((uintptr_t)ffn_ws & 255) || ffn_ws_bytes < need)
       return fail(EW_ERR_WORKSPACE, "%s: the FFN workspace needs %zu bytes aligned to 256 (got %zu at %p)", who, need, ffn_ws_bytes, ffn_ws);

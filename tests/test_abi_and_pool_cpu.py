@@ -87,6 +87,20 @@ def test_layer_forward_checks_its_arguments_before_any_launch():
     assert call(T=1 << 29, k=2, S=2, dtype=ew.EW_BF16, H=128, I=128) == -6
 
 
+@pytest.mark.parametrize("H,I", [(32768, 32768), (1 << 20, 1024), (128, 1 << 23)])
+def test_ffn_refuses_experts_beyond_its_weight_offsets(H, I):
+    """The kernels keep a lane's offset into a slot's gate and up rows in 32 bits: 4*H*I bytes must stay below 2^32."""
+    lib, one, T, k, P, S = ew.lib(), C.c_void_p(256), 1, 1, 2, 1
+    big = 1 << 50
+    for s in (0, S):
+        args = (one, ew.EW_BF16, T, k, H, I, P, s, one, one, one, one, one, one, one, one, one, big, None)
+        assert lib.moe_grouped_ffn_planned(*args) == -6 and b"2^30" in lib.ew_last_error()
+        assert lib.moe_route_reroute_permute_plan(one, one, one, T, 8, k, 1, P, 0, one, one, one, one, one, one, one, one, big, H, I, s,
+                                                  ew.EW_BF16, one, big, None) == -6
+    assert lib.moe_grouped_ffn_with_shared(*args) == -6
+    assert lib.moe_grouped_ffn(one, ew.EW_BF16, T, k, H, I, P, one, one, one, one, one, one, one, big, None) == -6
+
+
 def test_pool_create_rejects_bad_arguments():
     for kw in (dict(num_layers=0), dict(M=0), dict(N=-1), dict(w13_bytes=0), dict(page_bytes=1000), dict(flags=64 | FAKE)):
         args = dict(num_layers=1, M=4, N=2, E_max=2, w13_bytes=4096, w2_bytes=4096, page_bytes=4096, flags=FAKE)
