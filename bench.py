@@ -90,7 +90,7 @@ class LayerSetup:
         hand-over from the permutation call: the call builds its own plan here."""
         L, cfg = self.layer, self.cfg
         lib, st, b = B.lib(), B._stream(), self.layer.buf
-        if cfg.S and b.fused_shared:
+        if cfg.S:
             return lambda: B._check(lib.moe_grouped_ffn_with_shared(
                 self.x.data_ptr(), L.dt, cfg.T, cfg.k, cfg.H, cfg.I, cfg.P, cfg.S, b.counts.data_ptr(), b.offsets.data_ptr(),
                 b.por.data_ptr(), L.w13_base, L.w2_base, L.shared_w13.data_ptr(), L.shared_w2.data_ptr(), b.y.data_ptr(),
@@ -145,8 +145,8 @@ class LayerSetup:
         bias_ptr = L.bias.data_ptr() if L.bias is not None else None
         gate = lambda: B._check(lib.moe_gate_logits(self.x.data_ptr(), L.dt, L.Wg.data_ptr(), T, H, cfg.M,
                                                     self.aid.data_ptr() if bias_ptr else None, bias_ptr, b.logits.data_ptr(), st))
-        route = lambda: L.route(self.x, self.aid, logits=b.logits, plan=b.planned)
-        S = cfg.S if b.fused_shared else 0
+        route = lambda: L.route(self.x, self.aid, logits=b.logits, plan=True)
+        S = cfg.S
         sh_ptr = b.y.data_ptr() + T * k * H * 2 if S else None
         comb = lambda: B._check(lib.moe_unpermute(b.y.data_ptr(), b.rop.data_ptr(), b.w.data_ptr(), sh_ptr, S, None, T, k, H, L.dt,
                                                   b.out.data_ptr(), st))

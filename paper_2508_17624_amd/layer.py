@@ -54,10 +54,7 @@ class LayerBuffers:
         lib = B.lib()
         self.dt = B.EW_BF16 if dtype == torch.bfloat16 else B.EW_F32
         self.ws_perm = B._workspace(lib.moe_reroute_permute_workspace_bytes(T_max, k, P), device)
-        # the permutation call of a bf16 layer also writes the grouped FFN's work plan
-        self.planned = dtype == torch.bfloat16
         # routed and shared experts run in one launch
-        self.fused_shared = bool(S)
         self.y = torch.empty((T_max * (k + S), H), dtype=dtype, device=device)
         self.ws_ffn = B._workspace(lib.moe_grouped_ffn_workspace_bytes(T_max, k + S, H, I, P + S, self.dt), device)
 
@@ -140,7 +137,7 @@ class MoELayer:
                 b.w.data_ptr(), b.slot.data_ptr(), b.counts.data_ptr(), b.offsets.data_ptr(), b.por.data_ptr(), b.rop.data_ptr(),
                 B._ptr(b.ws_perm), b.ws_perm.numel() if b.ws_perm is not None else 0)
         if plan:
-            B._check(lib.moe_route_reroute_permute_plan(*args, H, self.I, self.S if b.fused_shared else 0, self.dt,
+            B._check(lib.moe_route_reroute_permute_plan(*args, H, self.I, self.S, self.dt,
                                                         b.ws_ffn.data_ptr(), b.ws_ffn.numel(), st))
         else:
             B._check(lib.moe_route_reroute_permute(*args, st))
