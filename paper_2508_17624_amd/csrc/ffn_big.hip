@@ -227,7 +227,7 @@ __device__ __forceinline__ void big_body(const FfnArgs& a, unsigned char* s_lds)
   const uint32_t q0 = lds0 + kQOff;
 
   [[maybe_unused]] Sched sc{};
-  [[maybe_unused]] int pending = -1;
+  [[maybe_unused]] int pending = -1;  // scheduler: chunk of the previous unit, counted in the last slab of the present one
   if constexpr (ROLE == 2) {
     sc.home = (int)(blockIdx.x & 7);
     sc.mode = a.first_mode;
@@ -497,13 +497,10 @@ __device__ __forceinline__ void big_body(const FfnArgs& a, unsigned char* s_lds)
       if constexpr (ROLE != 2) __builtin_amdgcn_s_waitcnt(0x0F70);
       __builtin_amdgcn_s_barrier();
       if constexpr (ROLE == 2) {
-        if (pending >= 0 && lane == 0) __hip_atomic_fetch_add(a.done + pending, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        pending = -1;
         if (cur.mode == 0 && lane == 0) __hip_atomic_fetch_add(a.done + cur.chunk, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
       if (nxt.slot < 0) return;
     } else if constexpr (ROLE == 2) {
-      if (pending >= 0 && lane == 0) __hip_atomic_fetch_add(a.done + pending, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       pending = cur.mode == 0 ? cur.chunk : -1;
     }
     ++seq;

@@ -218,7 +218,7 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds)
 
   [[maybe_unused]] Sched sc{};
   [[maybe_unused]] int n_chunks = 0;
-  [[maybe_unused]] int pending = -1;  // scheduler: chunk whose unit is stored but not yet counted
+  [[maybe_unused]] int pending = -1;  // scheduler: chunk of the previous unit, counted inside the slab loop of the present one
   if constexpr (ROLE == 2) {
     n_chunks = a.plan[0];
     sc.home = sc.list = (int)(blockIdx.x & 7);
@@ -415,13 +415,10 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds)
       if constexpr (ROLE != 2) __builtin_amdgcn_s_waitcnt(0x0F70);
       __builtin_amdgcn_s_barrier();
       if constexpr (ROLE == 2) {
-        if (pending >= 0 && lane == 0) __hip_atomic_fetch_add(a.done + pending * kDecDoneStride, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        pending = -1;
         if (cur.mode == 0 && lane == 0) __hip_atomic_fetch_add(a.done + cur.chunk * kDecDoneStride, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
       if (nxt.slot < 0) return;
     } else if constexpr (ROLE == 2) {
-      if (pending >= 0 && lane == 0) __hip_atomic_fetch_add(a.done + pending * kDecDoneStride, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       pending = cur.mode == 0 ? cur.chunk : -1;
     }
     ++seq;
