@@ -273,6 +273,42 @@ def test_one_launch_for_both_products_equals_two(ew, T, k, P, S, nf):
         assert rel_l2(got[r0:r1], want) <= FFN_REL_L2 and max_abs(got[r0:r1], want) <= FFN_MAX_ABS, f"slot {s}"
 
 
+@pytest.mark.parametrize("T,k,P,S,H,I", [(1500, 2, 6, 2, 640, 128), (1100, 2, 8, 2, 2176, 1408), (700, 3, 40, 0, 896, 256), (900, 4, 5, 1, 384, 1408)],
+                         ids=["two-slabs", "more-units-than-cus", "thin-slots", "odd-hidden"])
+def test_one_launch_of_the_many_rows_kernel_equals_two(ew, T, k, P, S, H, I):
+    """k_ffn_big asked for by name: crowded slots cut into several chunks beside thin ones, hidden sizes that are an odd multiple
+    of 128, two-slab contractions, fewer and more units than CUs.  One launch, whose second product reads rows that other
+    workgroups have just stored, gives the bits of two launches on every one of several calls; some rows against the oracle."""
+    rng = np.random.default_rng(T * 5 + H)
+    ids = np.stack([rng.choice(P, k, replace=False) for _ in range(T)]).astype(np.int32)
+    ids[:, 0] = np.where(rng.random(T) < 0.6, 1, ids[:, 0])               # a repeat inside a token is fine here
+    flat = ids.reshape(-1)
+    por = np.argsort(flat, kind="stable").astype(np.int32)
+    counts = np.bincount(flat, minlength=P).astype(np.int32)
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    dev = lambda a: torch.from_numpy(a).cuda()
+    bf = lambda *shape, scale=1.0: (torch.from_numpy(rng.standard_normal(shape, dtype=np.float32)) * scale).cuda().bfloat16()
+    x, w13, w2 = bf(T, H), bf(P, 2 * I, H, scale=0.02), bf(P, H, I, scale=0.02)
+    s13, s2 = (bf(S, 2 * I, H, scale=0.02), bf(S, H, I, scale=0.02)) if S else (None, None)
+    args = (dev(counts), dev(offsets), dev(por), w13, w2)
+
+    def run(two_launches):
+        ew.binding.tune_ffn(path=3, ws_frags=8, ws_two_launches=two_launches)
+        try:
+            return ew.moe_grouped_ffn_with_shared(x, k, I, P, *args, s13, s2) if S else ew.moe_grouped_ffn(x, k, I, P, *args)
+        finally:
+            ew.binding.tune_ffn()
+
+    ref = run(True)
+    for _ in range(4):
+        assert torch.equal(run(False), ref)
+    got, xs = to_f64(ref), to_f64(x)
+    for s in (1, int(np.argmin(np.where(counts > 0, counts, T * k + 1)))):
+        r0, r1 = offsets[s], offsets[s + 1]
+        want = moe.expert_ffn(xs[por[r0:r1] // k], to_f64(w13[s]), to_f64(w2[s]))
+        assert rel_l2(got[r0:r1], want) <= FFN_REL_L2 and max_abs(got[r0:r1], want) <= FFN_MAX_ABS, f"slot {s}"
+
+
 @pytest.mark.parametrize("T", [16, 256], ids=["few-rows", "many-rows"])
 def test_a_wait_given_up_writes_nan(ew, T):
     """One slot with fewer first-product units than workgroups: those left over start with units of the second product, whose
@@ -640,7 +676,10 @@ def test_grouped_ffn_f32_tile_edges(ew, H, I):
 def test_grouped_ffn_decode_kernel_edges(ew, T, k, P, S, H, I):
     """The kernel of calls with few rows per slot at the edges of its chunks (16, 32, 64 and 128 rows), with contractions
     shorter than its rings, hidden sizes that are an odd multiple of 128, a crowded slot cut into several chunks and more
-    workgroups than units: every row against the oracle's expert FFN, twice, the same bits both times."""
+    workgroups than units: every row against the oracle's expert FFN, twice, the same bits both times.
+    Weights of deviation 0.02 keep outputs within the range that FFN_MAX_ABS is meant for: a gate or up value has deviation
+    0.02 sqrt(2048) = 0.9 at most, an activation about 0.4, an output 0.02 sqrt(1408) 0.4 = 0.3, so below 4 with certainty, where
+    bf16 rounds by 2^-7 at most.  At twice the weights outputs are eight times larger and bf16 alone rounds by 2^-5 = 0.03."""
     rng = np.random.default_rng(T * 7 + H)
     ids = np.stack([rng.choice(P, k, replace=False) for _ in range(T)]).astype(np.int32)
     ids[:, 0] = np.where(rng.random(T) < 0.6, 1, ids[:, 0])               # a repeat inside a token is fine here
@@ -700,6 +739,7 @@ def test_grouped_ffn_counts_choose_the_kernel(ew, T, k, P, S, H, I, used):
     y = run()
     few, many = run(4), run(8)
     active = int((counts > 0).sum()) + S
+    assert not torch.equal(few, many)                                      # their sums differ in order: the next line tells them apart
     assert torch.equal(y, many if T * (k + S) > 128 * active else few)
     xs = to_f64(x)
     for got in (to_f64(few), to_f64(many)):
