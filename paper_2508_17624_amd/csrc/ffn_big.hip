@@ -368,10 +368,6 @@ __device__ __forceinline__ void big_body(const FfnArgs& a, unsigned char* s_lds)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][f][e] = 0.f;
         multiply<NB>(nk, wa, tb, acc, step);
-        if (NB > 0 && wait_expired(cur, q0 + (uint32_t)((seq & 3) * kQI) * 4u)) {
-#pragma unroll
-          for (int f = 0; f < NB; ++f) acc[0][f] = acc[1][f] = __builtin_nanf("");
-        }
         // Every wave is done with the unit's last slab, whose ring slots (two weight halves, one token slab: 64 KB) are not
         // loaded into before the next unit's first barrier.  Each wave turns its output there, 8 KB at a time, so that whole
         // rows of it leave in one piece: accumulator element e = 4 b + j of fragment i is weight row 8 b + 4 h + j of the
@@ -457,6 +453,13 @@ __device__ __forceinline__ void big_body(const FfnArgs& a, unsigned char* s_lds)
         case 2: unit(std::integral_constant<int, 2>{}); break;
         case 1: unit(std::integral_constant<int, 1>{}); break;
         default: unit(std::integral_constant<int, 0>{}); break;
+      }
+      if (wait_expired(cur, q0 + (uint32_t)((seq & 3) * kQI) * 4u)) {         // over what this wave has just stored
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+        if (cur.g * 256 + wr * 64 < m.NOUT)
+#pragma unroll 1
+          for (int tr = p * 32 + (lane >> 3); tr < cur.rows; tr += (tr & 31) < 24 ? 8 : 40)
+            store_nan(m.out + (size_t)(cur.off + tr) * m.NOUT + cur.g * 256 + wr * 64 + (lane & 7) * 8);
       }
     } else {
       for (int kt = 0; kt < nk; ++kt) {

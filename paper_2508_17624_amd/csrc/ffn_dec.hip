@@ -343,10 +343,6 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds)
           c_w = c_w + 1 == a.depth_w ? 0 : c_w + 1;
           c_t = c_t + 1 == a.depth_t ? 0 : c_t + 1;
         }
-        if (NB > 0 && wait_expired(cur, q0 + (uint32_t)((seq & 3) * C::QI) * 4u)) {
-#pragma unroll
-          for (int f = 0; f < NB; ++f) acc[0][f] = acc[1][f] = __builtin_nanf("");
-        }
 #pragma unroll
         for (int f = 0; f < NB; ++f) {
           const int tr = (nh + FSTEP * f) * 16 + n16;
@@ -381,6 +377,12 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds)
       else if (NF >= 2 && nf == 2) unit(std::integral_constant<int, NF >= 2 ? 2 : 0>{});
       else if (nf >= 1) unit(std::integral_constant<int, 1>{});
       else unit(std::integral_constant<int, 0>{});
+      if (wait_expired(cur, q0 + (uint32_t)((seq & 3) * C::QI) * 4u)) {       // over what this wave has just stored
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+#pragma unroll 1
+        for (int tr = nh * 16 + n16; tr < cur.rows; tr += FSTEP * 16)
+          store_nan(m.out + (size_t)(cur.off + tr) * m.NOUT + cur.g * MR + pair * 32 + 8 * q);
+      }
     } else
     for (int kt = 0; kt < nk; ++kt) {
       if constexpr (LOADS) {

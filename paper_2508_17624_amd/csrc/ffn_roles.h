@@ -109,9 +109,10 @@ __device__ __forceinline__ void wait_stored(const int32_t* flag, int target, int
   }
   asm volatile("" ::: "memory");
 }
-// Multiplying waves, behind a unit's last slab: whether its token waves gave up.  entry: LDS address of the unit's queue entry.
+__device__ __forceinline__ void store_nan(uint16_t* p) { *reinterpret_cast<u32x4*>(p) = (u32x4)0x7FC07FC0u; }
+// Multiplying waves, behind a unit: whether its token waves gave up.  entry: LDS address of the unit's queue entry.
 __device__ __forceinline__ bool wait_expired(const FfnUnit& u, uint32_t entry) {
-  if (u.mode == 0 || u.ready == 1) return false;
+  if (u.mode == 0) return false;
   uint32_t r;
   read_lds_ints<1, 4>(entry + 4 * kReadyWord, &r);
   return (int)__builtin_amdgcn_readfirstlane(r) == kExpired;
