@@ -1,4 +1,9 @@
 // Grouped SwiGLU expert FFN for calls with many rows per slot on gfx950: 256 weight rows x up to 256 token rows per unit.
+//
+// What bounds it: the operand loads into LDS.  Whole passes of 8192 tokens, us (64 + 2 experts in use / 254 + 2): 1066 / 1330; the
+// loads alone, nothing multiplied or stored, 909 / 1213; everything but the loads (operands that stay the same, so at a higher
+// clock as well) 721 / 772; the other kernels of a pass are about 130 of these.  One token slab and up to three weight halves
+// are in flight while a slab is multiplied.
 #include "ffn_roles.h"
 
 namespace ew {

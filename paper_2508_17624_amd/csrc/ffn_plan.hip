@@ -11,7 +11,7 @@ namespace ew {
 
 namespace {
 
-// Thread t reads the four slots 4 t .. 4 t + 3 in two loads where all of them exist.
+// Thread t reads the slots 4 t .. 4 t + 3.
 __global__ __launch_bounds__(512) void k_ffn_plan(const int32_t* __restrict__ counts, const int32_t* __restrict__ offsets, int P, int S,
                                                   int sh_rows, int sh_first, FfnPlanShape sh, int32_t* __restrict__ plan) {
   __shared__ FfnPlanLds lds;
@@ -62,8 +62,12 @@ size_t ffn_plan_ints(int T, int rows, int P) {
 }
 
 // The host knows totals only: no slot has more rows than the call has tokens, and rows / slots is the least that an active
-// slot has on average.  Up to 512 tokens k_ffn_dec runs whatever the router does (512 tokens on 64 of 128 slots: 203 us,
-// against 290 with 256-row units), above that where the average says so; if it does not, the counts decide.
+// slot has on average.  Above kPickRows rows per slot k_ffn_big runs; at or below it k_ffn_dec does up to 512 tokens, and above
+// 512 the counts decide.  Measured at 192 to 512 tokens (call with plan, us, k_ffn_dec / k_ffn_big; 2048 x 1408 experts, rows per
+// active slot x slots): 48 x 64: 203 / 290; 64 x 32: 117 / 151; 128 x 4: 66 / 94; 128 x 16: 105 / 110; 192 x 8: 92 / 89; 256 x 4:
+// 74 / 98; 256 x 8: 101 / 100; 256 x 16: 133 / 114; 384 x 4: 75 / 89; 384 x 8: 112 / 90.  So k_ffn_big wins in a corner only, eight
+// or more slots of 256 rows and more while the pool's other slots keep the average low; to let the counts find it would cost
+// every call up to 512 tokens a second launch (5 us).
 FfnPlanShape ffn_plan_shape(int T, int rows, int slots, int frags, int chunk_frags, bool merge, int wait_polls) {
   FfnPlanShape sh{};
   sh.merged = merge;

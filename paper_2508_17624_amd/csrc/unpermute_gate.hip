@@ -425,8 +425,10 @@ int unpermute(const char* who, const void* y_sorted, const int32_t* row_of_pair,
       hipLaunchKernelGGL((k_unpermute_few<false, decltype(K)::value>), dim3(T), dim3(256), 0, st, (const float*)y_sorted, row_of_pair,
                          topk_w, (const float*)shared_out, (const float*)residual, S, T, H, (float*)out, eps, (float*)normed);
   };
-  // k_unpermute_few up to a token per CU.  Whole passes, us, without / with it: 1 token 58.0 / 56.7, 13 tokens 62.8 / 62.5, 64
-  // tokens 239.8 / 238.6, 256 tokens (4 layers) 2113 / 2113; 1999 tokens 319 / 321, where its registers cost occupancy.
+  // k_unpermute_few up to a token per CU.  The kernel alone (replayed in a graph), us, without / with it, bf16: 1 token, k = 6, H =
+  // 2048, two shared rows 2.8 / 2.2, 64 tokens 3.1 / 2.5, 256 tokens 3.2 / 2.7; k = 1, H = 256 2.3 / 2.2.  fp32: 3.4 / 2.5, 3.6 / 2.7,
+  // 3.9 / 3.1, 2.2 / 2.2.  Whole passes: 1 token 58.0 / 56.7, 64 tokens 239.8 / 238.6; 1999 tokens 319 / 321, where its registers
+  // cost occupancy.
   switch (T <= 256 ? k : 0) {
     case 1: few(std::integral_constant<int, 1>{}); break;
     case 2: few(std::integral_constant<int, 2>{}); break;
