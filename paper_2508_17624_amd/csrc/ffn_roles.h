@@ -42,7 +42,9 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f) { return __builtin_bit_
 __device__ __forceinline__ float silu_f32(float g) { return g * __builtin_amdgcn_rcpf(1.f + __expf(-g)); }
 
 struct FfnUnit {
-  int slot, off, rows, g, mode, chunk, ready, alone;  // slot < 0: no unit left; ready: 1 nothing to wait for, kExpired the wait was given up
+  int slot, off, rows, g, mode, chunk;  // slot < 0: no unit left
+  int ready;                            // 1: nothing to wait for; kExpired: the wait was given up
+  int alone;                            // k_ffn_big: no other chunk reads these weights
 };
 
 // LDS-direct load: 16 bytes per lane from base + off (base: wave-uniform) to lds + 16 * lane.  AUX: 0 plain, 2 nt, 16 sc1.
