@@ -213,6 +213,9 @@ __device__ __forceinline__ void multiply(int nk, uint32_t& wa, uint32_t& tb, f32
     read_op<kWFrag>(wa, a[1]);
     const std::false_type fwd{};
     const std::true_type rev{};
+    // The loop's place in the instruction stream is pinned: left to chance, a change anywhere before it moves passes of 8192
+    // tokens by up to 1 % (4 bytes behind a 128-byte line 1129 us, on one 1134, other distances 1131 .. 1137; unpinned 1127 or 1140).
+    asm volatile(".p2align 7\n\ts_nop 0");
     for (int kt = 0; kt < nk; ++kt) {
       kstep(fwd, true, [] { return 16u; });
       kstep(rev, true, [] { return 32u; });
