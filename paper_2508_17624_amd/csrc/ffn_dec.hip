@@ -18,7 +18,7 @@
 //     are first-product too, which wait for nothing, and whose stores are counted before it waits for anything (workgroups
 //     that are not resident hold no claims).  A limit on the number of looks makes sure of it, see wait_stored.
 //   * Coherence of the activations: agent-scope stores, acknowledged before they are counted; for the loads see ACT_AUX.
-// Measured (call with plan, one box): 1 token on 8 experts of 2048 x 1408: 76 -> 43 us; 13 tokens on 36 of 1024 x 896: 88 ->
+// Measured (call with plan, one card): 1 token on 8 experts of 2048 x 1408: 76 -> 43 us; 13 tokens on 36 of 1024 x 896: 88 ->
 // 47 us; 64 tokens on 90: 263 -> 246 us (6.3 TB/s of weights; a bare stream of the same slabs reaches 6.85); 512 tokens on
 // 242: 699 -> 682 us; 512 on 150 of 1536 x 640: 182 -> 161 us; 2000 on 217 of those: 328 -> 257 us.
 //
