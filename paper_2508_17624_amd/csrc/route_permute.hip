@@ -4,9 +4,9 @@
 // (TopK'(x) = {Pi[A(x), j] : j in TopK(x)}) and Sec. 4.3 (rerouting fused into one kernel).
 //
 // Design for CDNA4:
-//  * top-k: one wavefront per token, experts strided over the 64 lanes.  Each logit becomes an
-//    order-preserving 32-bit key; a radix select over its bits, driven by wave ballots, finds
-//    the k winners with scalar-unit mask arithmetic only (ties go to the lower index).
+//  * top-k: sixteen lanes per token, so four tokens per wave (up to 256 experts and k = 16); beyond
+//    that one wave per token.  Each logit becomes an order-preserving 32-bit key (ties go to the
+//    lower index).
 //  * rerouting is a lookup in the expert map (staged in LDS), fused into whichever kernel first
 //    touches the ids: it never costs a launch or a pass over memory of its own.
 //  * permutation is a stable counting sort by slot.  Order inside a slot must be ascending
@@ -20,6 +20,7 @@
 #include "ew_internal.h"
 
 #include <atomic>
+#include <type_traits>
 
 namespace {
 
@@ -190,6 +191,88 @@ __device__ __forceinline__ void wave_topk(const float* __restrict__ row, int E, 
     if ((sel[v] >> lane) & 1ull) emit(rank[v], lane + v * kWave, ex[v] / denom * scale);
 }
 
+// All 16 lanes of a row: the row's maximum / minimum / sum (the sum in one fixed order, the same in every lane).
+template <typename F>
+__device__ __forceinline__ uint32_t row_reduce(uint32_t v, F f) {
+#define EW_ROR(x, n) (uint32_t) __builtin_amdgcn_update_dpp(0, (int)(x), 0x120 + (n), 0xf, 0xf, false)
+  v = f(v, EW_ROR(v, 8));
+  v = f(v, EW_ROR(v, 4));
+  v = f(v, EW_ROR(v, 2));
+  return f(v, EW_ROR(v, 1));
+#undef EW_ROR
+}
+__device__ __forceinline__ uint32_t row_max(uint32_t v) { return row_reduce(v, [](uint32_t a, uint32_t b) { return a > b ? a : b; }); }
+__device__ __forceinline__ uint32_t row_min(uint32_t v) { return row_reduce(v, [](uint32_t a, uint32_t b) { return a < b ? a : b; }); }
+__device__ __forceinline__ float row_sum_f32(float v) {
+  return __uint_as_float(row_reduce(__float_as_uint(v), [](uint32_t a, uint32_t b) { return __float_as_uint(__uint_as_float(a) + __uint_as_float(b)); }));
+}
+
+// The value a key stands for (+0.0 for either zero).
+__device__ __forceinline__ float key_value(uint32_t key) { return __uint_as_float(key & 0x80000000u ? key & 0x7FFFFFFFu : ~key); }
+
+// Sixteen lanes select the top-k of one token, so a wave does four: lane l of them holds experts l, l + 16, ... (V per lane,
+// E <= 16 V, k <= 16).  k rounds of "largest key, lowest index that has it, take it out"; the winner of round j stays in lane j,
+// so ids and weights leave in one coalesced store.  What bounds the selection is the chain of dependent instructions, and the
+// wave-wide radix select above spends it on one token at a time, through the scalar unit that all waves of a SIMD share: k_hist
+// at 8192 tokens of 64 experts, k = 6: 15.8 -> 5.0 us, at 512 tokens 8.0 -> 4.7; k_route at 64 tokens 4.5 -> 4.2.
+template <int V, typename Emit>
+__device__ __forceinline__ void group_topk(const float* __restrict__ row, int E, int k, int renorm, Emit emit) {
+  const int l = threadIdx.x & 15;
+  float val[V];
+  uint32_t key[V];
+#pragma unroll
+  for (int v = 0; v < V; ++v) val[v] = row[min(l + 16 * v, E - 1)];
+#pragma unroll
+  for (int v = 0; v < V; ++v) {
+    const uint32_t o = order_key(val[v]);
+    key[v] = l + 16 * v < E ? (o ? o : 1u) : 0u;  // 0: not there, or taken out
+  }
+  uint32_t my_key = 0u, top = 0u;
+  int my_e = 0;
+  for (int j = 0; j < k; ++j) {
+    uint32_t m = key[0];
+#pragma unroll
+    for (int v = 1; v < V; ++v) m = m > key[v] ? m : key[v];
+    m = row_max(m);
+    uint32_t e = 0xFFFFu;
+#pragma unroll
+    for (int v = V - 1; v >= 0; --v) e = key[v] == m ? (uint32_t)(l + 16 * v) : e;
+    e = row_min(e);
+#pragma unroll
+    for (int v = 0; v < V; ++v) key[v] = e == (uint32_t)(l + 16 * v) ? 0u : key[v];
+    if (j == 0) top = m;
+    if (j == l) {
+      my_key = m;
+      my_e = (int)e;
+    }
+  }
+  // softmax over all E logits: max = the first winner
+  const float vmax = key_value(top);
+  float part = 0.f;
+#pragma unroll
+  for (int v = 0; v < V; ++v) part += l + 16 * v < E ? expf(val[v] - vmax) : 0.f;
+  const float denom = row_sum_f32(part);
+  const float p = l < k ? expf(key_value(my_key) - vmax) / denom : 0.f;
+  const float scale = renorm ? 1.f / row_sum_f32(p) : 1.f;
+  if (l < k) emit(l, my_e, p * scale);
+}
+
+// Top-k of tokens first, first + 1, ... below end, as many as a wave takes at once: V > 0: sixteen lanes per token with V logits
+// each, V < 0: all 64 lanes on one token with -V logits each.  emit(token, rank, expert, weight).
+template <int V>
+constexpr int kTokensPerWave = V > 0 ? 4 : 1;
+template <int V, typename Emit>
+__device__ __forceinline__ void wave_select(const float* __restrict__ logits, int first, int end, int E, int k, int renorm, Emit emit) {
+  if constexpr (V < 0) {
+    wave_topk<-V>(logits + (size_t)first * E, E, k, renorm, [&](int rank, int e, float wt) { emit(first, rank, e, wt); });
+  } else {
+    const int t = first + (int)((threadIdx.x & (kWave - 1)) >> 4);
+    group_topk<V>(logits + (size_t)min(t, end - 1) * E, E, k, renorm, [&](int rank, int e, float wt) {
+      if (t < end) emit(t, rank, e, wt);
+    });
+  }
+}
+
 // Stages the expert map in LDS when it fits; returns the pointer lookups should use.
 __device__ __forceinline__ const int32_t* stage_map(const int32_t* __restrict__ emap, int32_t* s_map, int entries) {
   if (entries > kMapLds) return emap;
@@ -240,37 +323,20 @@ __device__ __forceinline__ void wave0_exscan(int32_t* v, int P) {
 }
 
 // ------------------------------------------------------------------------------------------
-// stand-alone router top-k: one wave per token, 4 waves per block
-template <int VPL>
-__global__ __launch_bounds__(256) void k_route_topk(const float* __restrict__ logits, int T, int E, int k, int renorm,
-                                                    int32_t* __restrict__ ids, float* __restrict__ w) {
-  const int wave = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
-  const int waves_total = gridDim.x * (blockDim.x / kWave);
-  for (int t = blockIdx.x * (blockDim.x / kWave) + wave; t < T; t += waves_total) {
-    wave_topk<VPL>(logits + (size_t)t * E, E, k, renorm, [&](int rank, int e, float wt) {
-      ids[(size_t)t * k + rank] = e;
-      w[(size_t)t * k + rank] = wt;
-    });
-  }
-}
-
-// Router top-k with the rerouting fused in (Sec. 4.3: the lookup rides on the kernel that produces
-// the ids), one wave per token over as many blocks as the batch needs: the first half of the
-// decode-sized path, whose second half (k_small with slots given) is a single block.
-template <int VPL>
-__global__ __launch_bounds__(256) void k_route_reroute(const float* __restrict__ logits, const int32_t* __restrict__ aid,
-                                                       const int32_t* __restrict__ emap, int T, int E, int k, int renorm,
-                                                       int32_t* __restrict__ ids, float* __restrict__ w,
-                                                       int32_t* __restrict__ slot_ids) {
-  const int wave = threadIdx.x / kWave;
-  const int t = blockIdx.x * (blockDim.x / kWave) + wave;
-  if (t >= T) return;
-  const int32_t* maprow = emap + (size_t)aid[t] * E;
-  wave_topk<VPL>(logits + (size_t)t * E, E, k, renorm, [&](int rank, int e, float wt) {
+// Router top-k, four waves per block.  REROUTE: with the rerouting fused in (Sec. 4.3: the lookup rides on the kernel that
+// produces the ids), over as many blocks as the batch needs: the first half of the decode-sized path, whose second half (k_small
+// with slots given) is a single block.
+template <int V, bool REROUTE>
+__global__ __launch_bounds__(256) void k_route(const float* __restrict__ logits, const int32_t* __restrict__ aid,
+                                               const int32_t* __restrict__ emap, int T, int E, int k, int renorm,
+                                               int32_t* __restrict__ ids, float* __restrict__ w, int32_t* __restrict__ slot_ids) {
+  const int first = (blockIdx.x * 4 + threadIdx.x / kWave) * kTokensPerWave<V>;
+  if (first >= T) return;
+  wave_select<V>(logits, first, T, E, k, renorm, [&](int t, int rank, int e, float wt) {
     const size_t p = (size_t)t * k + rank;
     ids[p] = e;
     w[p] = wt;
-    slot_ids[p] = maprow[e];
+    if constexpr (REROUTE) slot_ids[p] = emap[(size_t)aid[t] * E + e];
   });
 }
 
@@ -283,14 +349,11 @@ struct SmallPlan {
 
 // ------------------------------------------------------------------------------------------
 // Single-block path (decode-sized batches).  With given ids everything happens in this one launch;
-// with the router fused, k_route_reroute runs first (a single block would walk the tokens' top-k
-// selections 16 at a time) and this kernel receives slots (emap == nullptr).
-// run = pairs per wave, a multiple of 64.  VPL = 0: ids are given (no top-k).
-template <int VPL>
-__global__ __launch_bounds__(1024) void k_small(const float* __restrict__ logits, const int32_t* __restrict__ ids_in,
+// with the router fused, k_route runs first and this kernel receives slots (emap == nullptr).
+// run = pairs per wave, a multiple of 64.
+__global__ __launch_bounds__(1024) void k_small(const int32_t* __restrict__ ids_in,
                                                 const int32_t* __restrict__ aid, const int32_t* __restrict__ emap,
-                                                int T, int E, int k, int P, int map_entries, int renorm, int bits, int run,
-                                                int32_t* __restrict__ ids_out, float* __restrict__ w_out,
+                                                int T, int E, int k, int P, int bits, int run,
                                                 int32_t* __restrict__ slot_ids, int32_t* __restrict__ counts,
                                                 int32_t* __restrict__ offsets, int32_t* __restrict__ pair_of_row,
                                                 int32_t* __restrict__ row_of_pair, SmallPlan fp) {
@@ -314,30 +377,16 @@ __global__ __launch_bounds__(1024) void k_small(const float* __restrict__ logits
 
   for (int i = tid; i < nwaves * P; i += nthreads) s_cnt[i] = 0;
 
-  // A: ids (top-k or given) -> slot through the expert map
-  if constexpr (VPL > 0) {
-    for (int t = wave; t < T; t += nwaves) {
-      const int32_t* maprow = emap + (size_t)aid[t] * E;
-      wave_topk<VPL>(logits + (size_t)t * E, E, k, renorm, [&](int rank, int e, float wt) {
-        const int s = maprow[e];
-        const int p = t * k + rank;
-        ids_out[p] = e;
-        w_out[p] = wt;
-        slot_ids[p] = s;
-        s_slot[p] = (uint16_t)s;
-      });
+  // A: ids -> slot through the expert map
+  for (int p = tid; p < n; p += nthreads) {
+    int s;
+    if (emap) {
+      s = emap[(size_t)aid[p / k] * E + ids_in[p]];
+      slot_ids[p] = s;
+    } else {
+      s = ids_in[p];  // already slots (written by k_route)
     }
-  } else {
-    for (int p = tid; p < n; p += nthreads) {
-      int s;
-      if (emap) {
-        s = emap[(size_t)aid[p / k] * E + ids_in[p]];
-        slot_ids[p] = s;
-      } else {
-        s = ids_in[p];  // already slots (written by k_route_reroute)
-      }
-      s_slot[p] = (uint16_t)s;
-    }
+    s_slot[p] = (uint16_t)s;
   }
   __syncthreads();
 
@@ -410,25 +459,23 @@ __global__ __launch_bounds__(1024) void k_small(const float* __restrict__ logits
 // ------------------------------------------------------------------------------------------
 // Multi-block path, kernel 1: block b owns tokens [b*cht, (b+1)*cht).  ids (top-k or given) ->
 // slots (written out) -> LDS histogram -> hist[b][0..P).
-template <int VPL>
+template <int V>
 __global__ __launch_bounds__(kHistThreads) void k_hist(const float* __restrict__ logits, const int32_t* __restrict__ ids_in,
                                                       const int32_t* __restrict__ aid, const int32_t* __restrict__ emap,
                                                       int T, int E, int k, int P, int map_entries, int renorm, int cht,
                                                       int32_t* __restrict__ ids_out, float* __restrict__ w_out,
                                                       int32_t* __restrict__ slot_ids, int32_t* __restrict__ hist) {
   __shared__ int32_t s_hist[kMaxP];
-  __shared__ int32_t s_map[kMapLds];
   const int tid = threadIdx.x;
-  const int wave = tid / kWave;
   const int t0 = blockIdx.x * cht, t1 = min(T, t0 + cht);
-  for (int i = tid; i < P; i += kHistThreads) s_hist[i] = 0;
-  const int32_t* map = stage_map(emap, s_map, map_entries);
-  __syncthreads();
-  if constexpr (VPL > 0) {
-    for (int t = t0 + wave; t < t1; t += kHistThreads / kWave) {
-      const int32_t* maprow = map + aid[t] * E;
-      wave_topk<VPL>(logits + (size_t)t * E, E, k, renorm, [&](int rank, int e, float wt) {
-        const int s = maprow[e];
+  for (int i = tid; i < P; i += blockDim.x) s_hist[i] = 0;
+  if constexpr (V != 0) {
+    __syncthreads();
+    const int step = blockDim.x / kWave * kTokensPerWave<V>;
+    for (int first = t0 + tid / kWave * kTokensPerWave<V>; first < t1; first += step) {
+      // (a block has few tokens: its lookups go to the map itself)
+      wave_select<V>(logits, first, t1, E, k, renorm, [&](int t, int rank, int e, float wt) {
+        const int s = emap[(size_t)aid[t] * E + e];
         const size_t p = (size_t)t * k + rank;
         ids_out[p] = e;
         w_out[p] = wt;
@@ -437,6 +484,9 @@ __global__ __launch_bounds__(kHistThreads) void k_hist(const float* __restrict__
       });
     }
   } else {
+    __shared__ int32_t s_map[kMapLds];
+    const int32_t* map = stage_map(emap, s_map, map_entries);
+    __syncthreads();
     // four pairs per thread and pass, all loads of a pass issued before their first use; the
     // token of local pair q is floor((q + 0.5) / k), exact in fp32 for q < 2^14 and k <= 64
     const size_t p0 = (size_t)t0 * k;
@@ -464,7 +514,7 @@ __global__ __launch_bounds__(kHistThreads) void k_hist(const float* __restrict__
   }
   __syncthreads();
   int32_t* out = hist + (size_t)blockIdx.x * P;
-  for (int i = tid; i < P; i += kHistThreads) out[i] = s_hist[i];
+  for (int i = tid; i < P; i += blockDim.x) out[i] = s_hist[i];
 }
 
 // Kernel 2: exclusive scan down the columns of hist[nb][P] in place; counts[s] = column total.
@@ -856,7 +906,23 @@ inline int chunk_tokens(int T, int k) {
   return want < cap ? want : cap;
 }
 
-template <int VPL>
+// f(V) with the selection (wave_select) that E experts and k choices take.
+template <typename F>
+int with_selection(int E, int k, F f) {
+  if (k <= 16 && E <= 256) {
+    if (E <= 16) return f(std::integral_constant<int, 1>{});
+    if (E <= 64) return f(std::integral_constant<int, 4>{});
+    if (E <= 128) return f(std::integral_constant<int, 8>{});
+    return f(std::integral_constant<int, 16>{});
+  }
+  if (E <= 64) return f(std::integral_constant<int, -1>{});
+  if (E <= 128) return f(std::integral_constant<int, -2>{});
+  if (E <= 256) return f(std::integral_constant<int, -4>{});
+  if (E <= 512) return f(std::integral_constant<int, -8>{});
+  return f(std::integral_constant<int, -16>{});
+}
+
+template <int V>
 int launch_permute(const float* logits, const int32_t* ids_in, const int32_t* aid, const int32_t* emap, int T, int E,
                    int k, int N, int P, int renorm, int32_t* ids_out, float* w_out, int32_t* slot_ids, int32_t* counts,
                    int32_t* offsets, int32_t* por, int32_t* rop, void* ws, hipStream_t st, const ew::FfnPlanShape* shape = nullptr,
@@ -873,17 +939,13 @@ int launch_permute(const float* logits, const int32_t* ids_in, const int32_t* ai
     SmallPlan fp{nullptr, 0, ew::FfnPlanShape{}};
     const bool fused_plan = plan && nwaves * kWave >= 512;
     if (fused_plan) fp = SmallPlan{plan, S, *shape};
-    if constexpr (VPL > 0) {
-      hipLaunchKernelGGL((k_route_reroute<VPL>), dim3(ew::ceil_div(T, 4)), dim3(256), 0, st, logits, aid, emap, T, E, k, renorm,
-                         ids_out, w_out, slot_ids);
-      EW_LAUNCH_CHECK("k_route_reroute");
-      hipLaunchKernelGGL((k_small<0>), dim3(1), dim3(nwaves * kWave), 0, st, logits, (const int32_t*)slot_ids, aid,
-                         (const int32_t*)nullptr, T, E, k, P, map_entries, renorm, bits, run, ids_out, w_out, slot_ids, counts,
-                         offsets, por, rop, fp);
-    } else {
-      hipLaunchKernelGGL((k_small<0>), dim3(1), dim3(nwaves * kWave), 0, st, logits, ids_in, aid, emap, T, E, k, P,
-                         map_entries, renorm, bits, run, ids_out, w_out, slot_ids, counts, offsets, por, rop, fp);
+    if constexpr (V != 0) {
+      hipLaunchKernelGGL((k_route<V, true>), dim3(ew::ceil_div(T, 4 * kTokensPerWave<V>)), dim3(256), 0, st, logits, aid, emap, T, E, k,
+                         renorm, ids_out, w_out, slot_ids);
+      EW_LAUNCH_CHECK("k_route");
     }
+    hipLaunchKernelGGL(k_small, dim3(1), dim3(nwaves * kWave), 0, st, V != 0 ? (const int32_t*)slot_ids : ids_in, aid,
+                       V != 0 ? (const int32_t*)nullptr : emap, T, E, k, P, bits, run, slot_ids, counts, offsets, por, rop, fp);
     EW_LAUNCH_CHECK("k_small");
     if (plan && !fused_plan) return ew::launch_ffn_plan(counts, offsets, P, S, T, (int)n, *shape, plan, st);
     return EW_OK;
@@ -892,7 +954,9 @@ int launch_permute(const float* logits, const int32_t* ids_in, const int32_t* ai
   const int nb = ew::ceil_div(T, cht);
   const int run = (int)ew::align_up((size_t)ew::ceil_div(cht * k, kBigWaves), kWave);
   int32_t* hist = (int32_t*)ws;
-  hipLaunchKernelGGL((k_hist<VPL>), dim3(nb), dim3(kHistThreads), 0, st, logits, ids_in, aid, emap, T, E, k, P,
+  // with the router fused, a thread for every lane that a block's tokens keep busy
+  const int hist_threads = V == 0 ? kHistThreads : (int)ew::align_up((size_t)ew::ceil_div(cht, kTokensPerWave<V>) * kWave, 256);
+  hipLaunchKernelGGL((k_hist<V>), dim3(nb), dim3(hist_threads < kHistThreads ? hist_threads : kHistThreads), 0, st, logits, ids_in, aid, emap, T, E, k, P,
                      map_entries, renorm, cht, ids_out, w_out, slot_ids, hist);
   EW_LAUNCH_CHECK("k_hist");
   hipLaunchKernelGGL(k_colscan, dim3(ew::ceil_div(P, kScanCols)), dim3(kScanCols * kScanGroups), 0, st, hist, nb, P, counts);
@@ -1055,14 +1119,12 @@ extern "C" int moe_route_topk(const float* logits, int T, int E, int k, int reno
   if (T == 0) return EW_OK;
   if (!logits || !topk_ids || !topk_w) return fail(EW_ERR_INVALID_ARG, "moe_route_topk: NULL device pointer");
   hipStream_t st = (hipStream_t)stream;
-  const int blocks = ew::ceil_div(T, 4) < 65536 ? ew::ceil_div(T, 4) : 65536;
-#define EW_TOPK(V) hipLaunchKernelGGL((k_route_topk<V>), dim3(blocks), dim3(256), 0, st, logits, T, E, k, renormalize, topk_ids, topk_w)
-  if (E <= 64) EW_TOPK(1);
-  else if (E <= 128) EW_TOPK(2);
-  else if (E <= 256) EW_TOPK(4);
-  else if (E <= 512) EW_TOPK(8);
-  else EW_TOPK(16);
-#undef EW_TOPK
+  with_selection(E, k, [&](auto tag) {
+    constexpr int V = decltype(tag)::value;
+    hipLaunchKernelGGL((k_route<V, false>), dim3(ew::ceil_div(T, 4 * kTokensPerWave<V>)), dim3(256), 0, st, logits, (const int32_t*)nullptr,
+                       (const int32_t*)nullptr, T, E, k, renormalize, topk_ids, topk_w, (int32_t*)nullptr);
+    return EW_OK;
+  });
   EW_LAUNCH_CHECK("k_route_topk");
   return EW_OK;
 }
@@ -1101,15 +1163,10 @@ int route_reroute_permute(const char* who, const float* logits, const int32_t* a
     return EW_OK;
   }
   if (!logits || !topk_ids || !topk_w) return fail(EW_ERR_INVALID_ARG, "%s: NULL device pointer", who);
-#define EW_FUSED(V)                                                                                                      \
-  return launch_permute<V>(logits, nullptr, adapter_id, expert_map, T, E, k, N, P, renormalize, topk_ids, topk_w, slot_ids, \
-                           counts, offsets, pair_of_row, row_of_pair, ws, st, shape, S, plan)
-  if (E <= 64) EW_FUSED(1);
-  else if (E <= 128) EW_FUSED(2);
-  else if (E <= 256) EW_FUSED(4);
-  else if (E <= 512) EW_FUSED(8);
-  else EW_FUSED(16);
-#undef EW_FUSED
+  return with_selection(E, k, [&](auto tag) {
+    return launch_permute<decltype(tag)::value>(logits, nullptr, adapter_id, expert_map, T, E, k, N, P, renormalize, topk_ids, topk_w,
+                                                slot_ids, counts, offsets, pair_of_row, row_of_pair, ws, st, shape, S, plan);
+  });
 }
 
 }  // namespace

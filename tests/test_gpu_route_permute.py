@@ -56,6 +56,28 @@ def test_route_topk_ties_and_signed_zero(ew):
     np.testing.assert_allclose(w.cpu().numpy(), rw, rtol=2e-5)
 
 
+@pytest.mark.parametrize("E,k", [(1, 1), (16, 16), (17, 3), (64, 16), (64, 17), (65, 6), (128, 8), (129, 4), (256, 16), (257, 2)])
+@pytest.mark.parametrize("T", [1, 4, 6, 67])
+def test_route_topk_selection_edges(ew, T, E, k):
+    """Both sides of every rule that picks a selection (experts per lane, choices per token) and tokens that do not fill a wave:
+    ids exact with ties, both zeros, minus infinity and the largest values; the fused call gives the same bits."""
+    rng = np.random.default_rng(1000 * E + k + T)
+    logits = (rng.integers(-3, 4, size=(T, E)) * 0.5).astype(np.float32)
+    logits[rng.random((T, E)) < 0.2] = -0.0
+    logits[rng.random((T, E)) < 0.2] = -np.inf
+    logits[:, rng.integers(E)] = np.float32(3e38) if T == 4 else np.float32(2.0)
+    d = lambda a: torch.from_numpy(a).cuda()
+    for renorm in (False, True):
+        ids, w = ew.moe_route_topk(d(logits), k, renorm)
+        rids, rw = moe.route_topk(logits, k, renorm)
+        np.testing.assert_array_equal(ids.cpu().numpy(), rids)
+        np.testing.assert_allclose(w.cpu().numpy(), rw, rtol=2e-5, atol=1e-9)
+        emap = rng.permutation(E).astype(np.int32)[None]
+        fused = ew.moe_route_reroute_permute(d(logits), torch.zeros(T, dtype=torch.int32, device="cuda"), d(emap), k, 0, E, renorm)
+        assert torch.equal(fused[0], ids) and torch.equal(fused[1], w)
+        _check_permutation(fused[2:], emap[0][rids], E)
+
+
 @pytest.mark.parametrize("T", [1, 64, 256, 341, 342, 682, 683, 1366, 2048, 2049, 5000])
 def test_reroute_permute_configs(ew, T):
     """C2/C3-shaped: k=6, E=64, N=20, P=384.  T=341 is the last size of the single-block permutation
