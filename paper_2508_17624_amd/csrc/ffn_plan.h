@@ -37,13 +37,17 @@ constexpr int kEnt = 6;
 constexpr int kPlanMaxP = 2048;    // slots a plan can sort
 constexpr int kPlanMaxEnt = 4096;  // entries a plan can hold (the host picks ch accordingly)
 
+// Inclusive scan over the wave's 64 lanes (all active): inside rows of 16, then row totals to the rows behind.  DPP moves cost a
+// few cycles each, shuffles through LDS over a hundred.
 __device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t v) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t t = (uint32_t)__shfl_up((int)v, o, 64);
-    if (lane >= o) v += t;
-  }
+#define EW_DPP_ADD(ctrl, rows) v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, rows, 0xf, false)
+  EW_DPP_ADD(0x111, 0xf);  // row_shr:1
+  EW_DPP_ADD(0x112, 0xf);  // row_shr:2
+  EW_DPP_ADD(0x114, 0xf);  // row_shr:4
+  EW_DPP_ADD(0x118, 0xf);  // row_shr:8
+  EW_DPP_ADD(0x142, 0xa);  // row_bcast:15 into rows 1 and 3
+  EW_DPP_ADD(0x143, 0xc);  // row_bcast:31 into rows 2 and 3
+#undef EW_DPP_ADD
   return v;
 }
 

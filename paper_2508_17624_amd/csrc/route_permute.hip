@@ -29,6 +29,9 @@ constexpr int kMaxP = 2048;          // slots supported by the permutation kerne
 constexpr int kMaxE = 1024;          // experts supported by the top-k kernels
 constexpr int kSmallPairs = 4096;    // single-block path: capacity of its LDS arrays (T*k at most this)
 int g_small_pairs = 2048;            // single-block path is used up to this many pairs (tunable, <= kSmallPairs)
+// Single-block path: the selection joins it up to this many tokens, one round of its 16 waves.  A stack of layers at 256 tokens,
+// us, with the selection in a launch of its own / joined (four rounds): 2033 / 2058.
+constexpr int kSelectTokens = 64;
 constexpr int kSmallCnt = 12288;     // single-block path: waves * P at most this (uint16 counters)
 constexpr int kBigThreads = 512;     // multi-block path: threads per block
 constexpr int kBigWaves = kBigThreads / kWave;
@@ -55,15 +58,7 @@ __device__ __forceinline__ float wave_sum_f32(float v) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
-__device__ __forceinline__ int wave_incl_scan_i32(int v) {
-  const int lane = threadIdx.x & (kWave - 1);
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const int u = __shfl_up(v, o, kWave);
-    if (lane >= o) v += u;
-  }
-  return v;
-}
+__device__ __forceinline__ int wave_incl_scan_i32(int v) { return (int)ew::wave_incl_scan_u32((uint32_t)v); }
 
 // Monotone map float -> uint32 (larger float, larger key); -0.0 and +0.0 share one key.
 __device__ __forceinline__ uint32_t order_key(float f) {
@@ -212,38 +207,41 @@ __device__ __forceinline__ float key_value(uint32_t key) { return __uint_as_floa
 
 // Sixteen lanes select the top-k of one token, so a wave does four: lane l of them holds experts l, l + 16, ... (V per lane,
 // E <= 16 V, k <= 16).  k rounds of "largest key, lowest index that has it, take it out"; the winner of round j stays in lane j,
-// so ids and weights leave in one coalesced store.  What bounds the selection is the chain of dependent instructions, and the
+// so ids and weights leave in one coalesced store.  REROUTE: maprow is the token's row of the expert map; it is read while the
+// selection runs, and the slots ride in the low bits of the index that the rounds reduce, so no lookup follows.  emit(rank, expert,
+// slot, weight).  What bounds the selection is the chain of dependent instructions, and the
 // wave-wide radix select above spends it on one token at a time, through the scalar unit that all waves of a SIMD share: k_hist
 // at 8192 tokens of 64 experts, k = 6: 15.8 -> 5.0 us, at 512 tokens 8.0 -> 4.7; k_route at 64 tokens 4.5 -> 4.2.
-template <int V, typename Emit>
-__device__ __forceinline__ void group_topk(const float* __restrict__ row, int E, int k, int renorm, Emit emit) {
+template <int V, bool REROUTE, typename Emit>
+__device__ __forceinline__ void group_topk(const float* __restrict__ row, const int32_t* __restrict__ maprow, int E, int k, int renorm, Emit emit) {
   const int l = threadIdx.x & 15;
   float val[V];
-  uint32_t key[V];
+  uint32_t key[V], at[V];  // at: expert << 16 | slot
 #pragma unroll
   for (int v = 0; v < V; ++v) val[v] = row[min(l + 16 * v, E - 1)];
+#pragma unroll
+  for (int v = 0; v < V; ++v) at[v] = ((uint32_t)(l + 16 * v) << 16) | (REROUTE ? (uint32_t)maprow[min(l + 16 * v, E - 1)] & 0xFFFFu : 0u);
 #pragma unroll
   for (int v = 0; v < V; ++v) {
     const uint32_t o = order_key(val[v]);
     key[v] = l + 16 * v < E ? (o ? o : 1u) : 0u;  // 0: not there, or taken out
   }
-  uint32_t my_key = 0u, top = 0u;
-  int my_e = 0;
+  uint32_t my_key = 0u, my_at = 0u, top = 0u;
   for (int j = 0; j < k; ++j) {
     uint32_t m = key[0];
 #pragma unroll
     for (int v = 1; v < V; ++v) m = m > key[v] ? m : key[v];
     m = row_max(m);
-    uint32_t e = 0xFFFFu;
+    uint32_t first = ~0u;
 #pragma unroll
-    for (int v = V - 1; v >= 0; --v) e = key[v] == m ? (uint32_t)(l + 16 * v) : e;
-    e = row_min(e);
+    for (int v = V - 1; v >= 0; --v) first = key[v] == m ? at[v] : first;
+    first = row_min(first);
 #pragma unroll
-    for (int v = 0; v < V; ++v) key[v] = e == (uint32_t)(l + 16 * v) ? 0u : key[v];
+    for (int v = 0; v < V; ++v) key[v] = first == at[v] ? 0u : key[v];
     if (j == 0) top = m;
     if (j == l) {
       my_key = m;
-      my_e = (int)e;
+      my_at = first;
     }
   }
   // softmax over all E logits: max = the first winner
@@ -254,22 +252,26 @@ __device__ __forceinline__ void group_topk(const float* __restrict__ row, int E,
   const float denom = row_sum_f32(part);
   const float p = l < k ? expf(key_value(my_key) - vmax) / denom : 0.f;
   const float scale = renorm ? 1.f / row_sum_f32(p) : 1.f;
-  if (l < k) emit(l, my_e, p * scale);
+  if (l < k) emit(l, (int)(my_at >> 16), (int)(my_at & 0xFFFFu), p * scale);
 }
 
 // Top-k of tokens first, first + 1, ... below end, as many as a wave takes at once: V > 0: sixteen lanes per token with V logits
-// each, V < 0: all 64 lanes on one token with -V logits each.  emit(token, rank, expert, weight).
+// each, V < 0: all 64 lanes on one token with -V logits each.  emit(token, rank, expert, slot, weight); REROUTE: the slots come
+// from the expert map, otherwise they mean nothing.
 template <int V>
 constexpr int kTokensPerWave = V > 0 ? 4 : 1;
-template <int V, typename Emit>
-__device__ __forceinline__ void wave_select(const float* __restrict__ logits, int first, int end, int E, int k, int renorm, Emit emit) {
+template <int V, bool REROUTE, typename Emit>
+__device__ __forceinline__ void wave_select(const float* __restrict__ logits, const int32_t* __restrict__ aid, const int32_t* __restrict__ emap,
+                                            int first, int end, int E, int k, int renorm, Emit emit) {
   if constexpr (V < 0) {
-    wave_topk<-V>(logits + (size_t)first * E, E, k, renorm, [&](int rank, int e, float wt) { emit(first, rank, e, wt); });
+    const int32_t* maprow = REROUTE ? emap + (size_t)aid[first] * E : nullptr;
+    wave_topk<-V>(logits + (size_t)first * E, E, k, renorm, [&](int rank, int e, float wt) { emit(first, rank, e, REROUTE ? maprow[e] : 0, wt); });
   } else {
-    const int t = first + (int)((threadIdx.x & (kWave - 1)) >> 4);
-    group_topk<V>(logits + (size_t)min(t, end - 1) * E, E, k, renorm, [&](int rank, int e, float wt) {
-      if (t < end) emit(t, rank, e, wt);
-    });
+    const int t = first + (int)((threadIdx.x & (kWave - 1)) >> 4), row = min(t, end - 1);
+    group_topk<V, REROUTE>(logits + (size_t)row * E, REROUTE ? emap + (size_t)aid[row] * E : nullptr, E, k, renorm,
+                           [&](int rank, int e, int slot, float wt) {
+                             if (t < end) emit(t, rank, e, slot, wt);
+                           });
   }
 }
 
@@ -304,6 +306,17 @@ __device__ __forceinline__ void block_exscan2(int a, int b, int& ea, int& eb, in
   eb = pb + ib - b;
 }
 
+// Exclusive scan of one value per thread over the block (thread order).  s_w: an int per wave.  Contains one barrier.
+__device__ __forceinline__ int block_exscan(int a, int32_t* s_w) {
+  const int wave = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1), nwaves = blockDim.x / kWave;
+  const int ia = wave_incl_scan_i32(a);
+  if (lane == kWave - 1) s_w[wave] = ia;
+  __syncthreads();
+  int before = 0;
+  for (int w = 0; w < nwaves; ++w) before += w < wave ? s_w[w] : 0;
+  return before + ia - a;
+}
+
 // Exclusive scan of v[0..P) in place by wave 0 (P <= kMaxP); v[P] = total.  Needs barriers around.
 __device__ __forceinline__ void wave0_exscan(int32_t* v, int P) {
   if (threadIdx.x >= kWave) return;
@@ -332,11 +345,11 @@ __global__ __launch_bounds__(256) void k_route(const float* __restrict__ logits,
                                                int32_t* __restrict__ ids, float* __restrict__ w, int32_t* __restrict__ slot_ids) {
   const int first = (blockIdx.x * 4 + threadIdx.x / kWave) * kTokensPerWave<V>;
   if (first >= T) return;
-  wave_select<V>(logits, first, T, E, k, renorm, [&](int t, int rank, int e, float wt) {
+  wave_select<V, REROUTE>(logits, aid, emap, first, T, E, k, renorm, [&](int t, int rank, int e, int slot, float wt) {
     const size_t p = (size_t)t * k + rank;
     ids[p] = e;
     w[p] = wt;
-    if constexpr (REROUTE) slot_ids[p] = emap[(size_t)aid[t] * E + e];
+    if constexpr (REROUTE) slot_ids[p] = slot;
   });
 }
 
@@ -348,12 +361,17 @@ struct SmallPlan {
 };
 
 // ------------------------------------------------------------------------------------------
-// Single-block path (decode-sized batches).  With given ids everything happens in this one launch;
-// with the router fused, k_route runs first and this kernel receives slots (emap == nullptr).
-// run = pairs per wave, a multiple of 64.
-__global__ __launch_bounds__(1024) void k_small(const int32_t* __restrict__ ids_in,
+// Single-block path (decode-sized batches): ids -> slots, ranking, scan, scatter and, if asked for, the FFN's work plan in one
+// launch.  V = 0: ids are given (emap == nullptr: they are slots already, written by k_route), otherwise the selection
+// (wave_select) runs here too.  What bounds it is the chain of dependent steps, each a memory round trip or a barrier; so only the
+// waves that a batch gives 64 pairs rank, the scans run on DPP instead of through LDS, and one scan over all threads makes the
+// offsets.  Selection to plan, us, as two launches before / now: 1 token 8.9 / 5.9, 64 tokens 10.0 / 8.0.
+// run = pairs per ranking wave, a multiple of 64.
+template <int V>
+__global__ __launch_bounds__(1024) void k_small(const float* __restrict__ logits, const int32_t* __restrict__ ids_in,
                                                 const int32_t* __restrict__ aid, const int32_t* __restrict__ emap,
-                                                int T, int E, int k, int P, int bits, int run,
+                                                int T, int E, int k, int P, int renorm, int bits, int run,
+                                                int32_t* __restrict__ ids_out, float* __restrict__ w_out,
                                                 int32_t* __restrict__ slot_ids, int32_t* __restrict__ counts,
                                                 int32_t* __restrict__ offsets, int32_t* __restrict__ pair_of_row,
                                                 int32_t* __restrict__ row_of_pair, SmallPlan fp) {
@@ -362,6 +380,7 @@ __global__ __launch_bounds__(1024) void k_small(const int32_t* __restrict__ ids_
     uint16_t rank[kSmallPairs];
     uint16_t cnt[kSmallCnt];
     int32_t off[kMaxP + 1];
+    int32_t w[1024 / kWave];
   };
   __shared__ union Lds {
     Perm perm;
@@ -373,20 +392,31 @@ __global__ __launch_bounds__(1024) void k_small(const int32_t* __restrict__ ids_
   int32_t (&s_off)[kMaxP + 1] = lds.perm.off;
   const int tid = threadIdx.x, nthreads = blockDim.x;
   const int wave = tid / kWave, lane = tid & (kWave - 1), nwaves = nthreads / kWave;
-  const int n = T * k;
+  const int n = T * k, nrank = (n + run - 1) / run;  // nrank <= nwaves
 
-  for (int i = tid; i < nwaves * P; i += nthreads) s_cnt[i] = 0;
+  for (int i = tid; i < nrank * P; i += nthreads) s_cnt[i] = 0;
 
-  // A: ids -> slot through the expert map
-  for (int p = tid; p < n; p += nthreads) {
-    int s;
-    if (emap) {
-      s = emap[(size_t)aid[p / k] * E + ids_in[p]];
-      slot_ids[p] = s;
-    } else {
-      s = ids_in[p];  // already slots (written by k_route)
+  // A: ids (top-k or given) -> slots through the expert map
+  if constexpr (V != 0) {
+    for (int first = wave * kTokensPerWave<V>; first < T; first += nwaves * kTokensPerWave<V>)
+      wave_select<V, true>(logits, aid, emap, first, T, E, k, renorm, [&](int t, int rank, int e, int s, float wt) {
+        const int p = t * k + rank;
+        ids_out[p] = e;
+        w_out[p] = wt;
+        slot_ids[p] = s;
+        s_slot[p] = (uint16_t)s;
+      });
+  } else {
+    for (int p = tid; p < n; p += nthreads) {
+      int s;
+      if (emap) {
+        s = emap[(size_t)aid[p / k] * E + ids_in[p]];
+        slot_ids[p] = s;
+      } else {
+        s = ids_in[p];
+      }
+      s_slot[p] = (uint16_t)s;
     }
-    s_slot[p] = (uint16_t)s;
   }
   __syncthreads();
 
@@ -413,24 +443,32 @@ __global__ __launch_bounds__(1024) void k_small(const int32_t* __restrict__ ids_
   }
   __syncthreads();
 
-  // C: per slot, exclusive scan over waves (in place); slot totals -> s_off
-  for (int s = tid; s < P; s += nthreads) {
+  // C: per slot, exclusive scan over the ranking waves (in place); then over the slots, each thread taking `per` in a row
+  const int per = (P + nthreads - 1) / nthreads, s0 = tid * per;
+  int mine = 0;
+  for (int s = s0; s < min(P, s0 + per); ++s) {
     int tot = 0;
-    for (int w = 0; w < nwaves; ++w) {
+    for (int w = 0; w < nrank; ++w) {
       const int c = s_cnt[(size_t)w * P + s];
       s_cnt[(size_t)w * P + s] = (uint16_t)tot;
       tot += c;
     }
     s_off[s] = tot;
+    mine += tot;
+  }
+  int at = block_exscan(mine, lds.perm.w);
+  for (int s = s0; s < min(P, s0 + per); ++s) {
+    const int tot = s_off[s];
+    s_off[s] = at;
+    offsets[s] = at;
+    counts[s] = tot;
+    at += tot;
+  }
+  if (tid == 0) {
+    s_off[P] = n;
+    offsets[P] = n;
   }
   __syncthreads();
-  wave0_exscan(s_off, P);
-  __syncthreads();
-  for (int s = tid; s < P; s += nthreads) {
-    offsets[s] = s_off[s];
-    counts[s] = s_off[s + 1] - s_off[s];
-  }
-  if (tid == 0) offsets[P] = n;
 
   // D: scatter
   for (int p = tid; p < n; p += nthreads) {
@@ -473,9 +511,7 @@ __global__ __launch_bounds__(kHistThreads) void k_hist(const float* __restrict__
     __syncthreads();
     const int step = blockDim.x / kWave * kTokensPerWave<V>;
     for (int first = t0 + tid / kWave * kTokensPerWave<V>; first < t1; first += step) {
-      // (a block has few tokens: its lookups go to the map itself)
-      wave_select<V>(logits, first, t1, E, k, renorm, [&](int t, int rank, int e, float wt) {
-        const int s = emap[(size_t)aid[t] * E + e];
+      wave_select<V, true>(logits, aid, emap, first, t1, E, k, renorm, [&](int t, int rank, int e, int s, float wt) {
         const size_t p = (size_t)t * k + rank;
         ids_out[p] = e;
         w_out[p] = wt;
@@ -939,13 +975,19 @@ int launch_permute(const float* logits, const int32_t* ids_in, const int32_t* ai
     SmallPlan fp{nullptr, 0, ew::FfnPlanShape{}};
     const bool fused_plan = plan && nwaves * kWave >= 512;
     if (fused_plan) fp = SmallPlan{plan, S, *shape};
-    if constexpr (V != 0) {
-      hipLaunchKernelGGL((k_route<V, true>), dim3(ew::ceil_div(T, 4 * kTokensPerWave<V>)), dim3(256), 0, st, logits, aid, emap, T, E, k,
-                         renorm, ids_out, w_out, slot_ids);
-      EW_LAUNCH_CHECK("k_route");
+    if (V > 0 && T <= kSelectTokens) {
+      hipLaunchKernelGGL(k_small<(V > 0 ? V : 0)>, dim3(1), dim3(nwaves * kWave), 0, st, logits, ids_in, aid, emap, T, E, k, P, renorm, bits,
+                         run, ids_out, w_out, slot_ids, counts, offsets, por, rop, fp);
+    } else {
+      if constexpr (V != 0) {
+        hipLaunchKernelGGL((k_route<V, true>), dim3(ew::ceil_div(T, 4 * kTokensPerWave<V>)), dim3(256), 0, st, logits, aid, emap, T, E, k,
+                           renorm, ids_out, w_out, slot_ids);
+        EW_LAUNCH_CHECK("k_route");
+      }
+      hipLaunchKernelGGL(k_small<0>, dim3(1), dim3(nwaves * kWave), 0, st, logits, V != 0 ? (const int32_t*)slot_ids : ids_in, aid,
+                         V != 0 ? (const int32_t*)nullptr : emap, T, E, k, P, renorm, bits, run, ids_out, w_out, slot_ids, counts,
+                         offsets, por, rop, fp);
     }
-    hipLaunchKernelGGL(k_small, dim3(1), dim3(nwaves * kWave), 0, st, V != 0 ? (const int32_t*)slot_ids : ids_in, aid,
-                       V != 0 ? (const int32_t*)nullptr : emap, T, E, k, P, bits, run, slot_ids, counts, offsets, por, rop, fp);
     EW_LAUNCH_CHECK("k_small");
     if (plan && !fused_plan) return ew::launch_ffn_plan(counts, offsets, P, S, T, (int)n, *shape, plan, st);
     return EW_OK;
