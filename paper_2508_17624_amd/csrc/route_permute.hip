@@ -13,10 +13,12 @@
 //    pair index, so no atomic cursors: every wave ranks a contiguous run of pairs 64 at a time
 //    with a ballot-built peer mask (rank = popcount of lower peers) and a wave-private LDS
 //    counter; runs are stitched by exclusive scans over waves (LDS) and over blocks (global).
-//  * small batches (decode): with ids given, ONE single-block kernel does lookup, histogram, scan
-//    and scatter without leaving the CU; with the router fused, a multi-block top-k + lookup
-//    kernel (one wave per token) runs first and that block receives slots.  Large batches use
-//    three kernels: per-block histogram (fused with top-k and lookup), column scan, ranked scatter.
+//  * small batches (decode): ONE single-block kernel does top-k, lookup, histogram, scan and scatter
+//    without leaving the CU (above 64 tokens a multi-block top-k + lookup kernel runs first and that
+//    block receives slots).  Large batches use three kernels: per-block histogram (fused with top-k
+//    and lookup), column scan, ranked scatter.
+//  * the grouped FFN's work plan, if asked for, never is a launch of its own: the single block goes
+//    on to build it, and the scatter's launch has one more block for it.
 #include "ew_internal.h"
 
 #include <atomic>
@@ -354,11 +356,30 @@ __global__ __launch_bounds__(256) void k_route(const float* __restrict__ logits,
 }
 
 // Plan request of a permutation call: the grouped FFN's work plan is written too (plan == nullptr: not asked for).
-struct SmallPlan {
+struct PlanReq {
   int32_t* plan;
   int S;
   ew::FfnPlanShape shape;
 };
+
+// Block 0 of a scatter launch that was asked for a plan: builds it from the counts while the other blocks scatter.  Scatter and
+// plan, us, as two launches before / now: 512 tokens 5.7 + 3.7 / 5.1; 8192 tokens 7.7 + 10.3 / 9.2.  T tokens, n pairs; a block of 512 threads; lds: the scatter's sorted-pairs array.
+__device__ __forceinline__ void plan_block(const int32_t* __restrict__ counts, int T, int n, int P, const PlanReq& fp, int32_t* s_w, void* lds) {
+  int rows[4], first[4], sum = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int sl = 4 * (int)threadIdx.x + i;
+    rows[i] = sl < P ? counts[sl] : 0;
+    sum += rows[i];
+  }
+  int at = block_exscan(sum, s_w);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    first[i] = at;
+    at += rows[i];
+  }
+  ew::ffn_plan_build(rows, first, P, fp.S, T, n, fp.shape, fp.plan, *reinterpret_cast<ew::FfnPlanLds*>(lds));
+}
 
 // ------------------------------------------------------------------------------------------
 // Single-block path (decode-sized batches): ids -> slots, ranking, scan, scatter and, if asked for, the FFN's work plan in one
@@ -374,7 +395,7 @@ __global__ __launch_bounds__(1024) void k_small(const float* __restrict__ logits
                                                 int32_t* __restrict__ ids_out, float* __restrict__ w_out,
                                                 int32_t* __restrict__ slot_ids, int32_t* __restrict__ counts,
                                                 int32_t* __restrict__ offsets, int32_t* __restrict__ pair_of_row,
-                                                int32_t* __restrict__ row_of_pair, SmallPlan fp) {
+                                                int32_t* __restrict__ row_of_pair, PlanReq fp) {
   struct Perm {
     uint16_t slot[kSmallPairs];
     uint16_t rank[kSmallPairs];
@@ -665,21 +686,27 @@ template <int MAXP>
 __global__ __launch_bounds__(kBigThreads) void k_scatter(const int32_t* __restrict__ slot_ids, const int32_t* __restrict__ counts,
                                                          const int32_t* __restrict__ base, int T, int k, int P, int bits, int cht,
                                                          int run, int32_t* __restrict__ offsets, int32_t* __restrict__ pair_of_row,
-                                                         int32_t* __restrict__ row_of_pair) {
+                                                         int32_t* __restrict__ row_of_pair, PlanReq fp) {
   __shared__ uint16_t s_cnt[kBigWaves * MAXP];
   __shared__ int32_t s_off[MAXP + 1];    // first row of the block's pairs of slot s
   __shared__ int32_t s_loc[MAXP + 1];    // first position of slot s in the block's sorted order
-  __shared__ uint32_t s_sorted[kBigPairs];  // slot << 16 | pair index inside the block, sorted by slot
+  __shared__ __align__(16) uint32_t s_sorted[kBigPairs];  // slot << 16 | pair index inside the block, sorted by slot
+  static_assert(sizeof(ew::FfnPlanLds) <= sizeof(s_sorted), "a plan is built in the sorted-pairs array");
+  if (fp.plan && blockIdx.x == 0) {
+    plan_block(counts, T, T * k, P, fp, s_off, s_sorted);
+    return;
+  }
+  const int block = blockIdx.x - (fp.plan ? 1 : 0);
   const int tid = threadIdx.x;
   const int wave = tid / kWave, lane = tid & (kWave - 1);
-  const int t0 = blockIdx.x * cht, t1 = min(T, t0 + cht);
+  const int t0 = block * cht, t1 = min(T, t0 + cht);
   const size_t p0 = (size_t)t0 * k;
   const int n = (t1 - t0) * k;                                    // pairs of this block, <= kBigPairs
   const int lo = wave * run, hi = min(n, lo + run);               // run: pairs per wave, a multiple of 64
   const int steps = run / kWave;                                  // <= kBigSteps
   uint32_t packed[kBigSteps];                                     // slot | rank << 12 | valid << 31
   load_pairs(slot_ids, p0, lo, hi, steps, packed);
-  const int32_t* mybase = base + (size_t)blockIdx.x * P;
+  const int32_t* mybase = base + (size_t)block * P;
   int32_t base_v[MAXP / kBigThreads];                             // this block's row of the scanned histogram
 #pragma unroll
   for (int j = 0; j < MAXP / kBigThreads; ++j) {
@@ -702,7 +729,7 @@ __global__ __launch_bounds__(kBigThreads) void k_scatter(const int32_t* __restri
   __syncthreads();
   wave0_exscan(s_off, P);
   __syncthreads();
-  if (blockIdx.x == 0)
+  if (block == 0)
     for (int i = tid; i <= P; i += kBigThreads) offsets[i] = s_off[i];
 
   rank_pairs<kMasks>(lo, hi, steps, bits, s_cnt + (size_t)wave * P, s_mask + (size_t)wave * P, packed);
@@ -755,20 +782,27 @@ template <int K>
 __global__ __launch_bounds__(kBigThreads) void k_scatter_tok(const int32_t* __restrict__ slot_ids, const int32_t* __restrict__ counts,
                                                              const int32_t* __restrict__ base, int T, int P, int bits, int cht,
                                                              int tpw, int run, int32_t* __restrict__ offsets,
-                                                             int32_t* __restrict__ pair_of_row, int32_t* __restrict__ row_of_pair) {
+                                                             int32_t* __restrict__ pair_of_row, int32_t* __restrict__ row_of_pair,
+                                                             PlanReq fp) {
   constexpr int MAXP = 512;
   constexpr int STEPS = ((kBigPairs / K + kBigWaves - 1) / kBigWaves + kWave - 1) / kWave;  // 64-token steps per wave at most
   constexpr int NV = STEPS * K > kBigSteps ? STEPS * K : kBigSteps;                        // values per lane
   __shared__ uint16_t s_cnt[kBigWaves * MAXP];
   __shared__ int32_t s_off[MAXP + 1];    // first row of the block's pairs of slot s
   __shared__ int32_t s_loc[MAXP + 1];    // first position of slot s in the block's sorted order
-  __shared__ uint32_t s_sorted[kBigPairs];  // slot << 16 | pair index inside the block, sorted by slot
+  __shared__ __align__(16) uint32_t s_sorted[kBigPairs];  // slot << 16 | pair index inside the block, sorted by slot
   __shared__ int32_t s_w[2 * kBigWaves];
   __shared__ int s_dup;
   static_assert((size_t)kBigWaves * MAXP * 8 <= sizeof(s_sorted), "the lane masks borrow the sorted-pairs array");
+  static_assert(sizeof(ew::FfnPlanLds) <= sizeof(s_sorted), "a plan is built in the sorted-pairs array");
+  if (fp.plan && blockIdx.x == 0) {
+    plan_block(counts, T, T * K, P, fp, s_w, s_sorted);
+    return;
+  }
+  const int block = blockIdx.x - (fp.plan ? 1 : 0);
   const int tid = threadIdx.x;
   const int wave = tid / kWave, lane = tid & (kWave - 1);
-  const int t0 = blockIdx.x * cht, t1 = min(T, t0 + cht);
+  const int t0 = block * cht, t1 = min(T, t0 + cht);
   const size_t p0 = (size_t)t0 * K;
   const int ntok = t1 - t0, n = ntok * K;                          // pairs of this block, <= kBigPairs
   const int wt0 = wave * tpw, wt1 = min(ntok, wt0 + tpw);          // this wave's tokens
@@ -785,7 +819,7 @@ __global__ __launch_bounds__(kBigThreads) void k_scatter_tok(const int32_t* __re
   }
 #pragma unroll
   for (int i = STEPS * K; i < NV; ++i) packed[i] = 0u;
-  const int32_t* mybase = base + (size_t)blockIdx.x * P;
+  const int32_t* mybase = base + (size_t)block * P;
   const int32_t base_v = tid < P ? mybase[tid] : 0;                // this block's row of the scanned histogram
   const int32_t count_v = tid < P ? counts[tid] : 0;
   unsigned long long* s_mask = reinterpret_cast<unsigned long long*>(s_sorted);
@@ -868,11 +902,11 @@ __global__ __launch_bounds__(kBigThreads) void k_scatter_tok(const int32_t* __re
     if (tid < P) {
       s_off[tid] = first_row + base_v;
       s_loc[tid] = first_pos;
-      if (blockIdx.x == 0) offsets[tid] = first_row;
+      if (block == 0) offsets[tid] = first_row;
     }
     if (tid == 0) {
       s_loc[P] = pos_total;
-      if (blockIdx.x == 0) offsets[P] = rows_total;
+      if (block == 0) offsets[P] = rows_total;
     }
   }
   __syncthreads();
@@ -972,9 +1006,9 @@ int launch_permute(const float* logits, const int32_t* ids_in, const int32_t* ai
     int run = ((int)n + nwaves - 1) / nwaves;
     run = (run + kWave - 1) / kWave * kWave;
     // the FFN plan rides on the single-block kernel when that has the 512 threads the plan needs
-    SmallPlan fp{nullptr, 0, ew::FfnPlanShape{}};
+    PlanReq fp{nullptr, 0, ew::FfnPlanShape{}};
     const bool fused_plan = plan && nwaves * kWave >= 512;
-    if (fused_plan) fp = SmallPlan{plan, S, *shape};
+    if (fused_plan) fp = PlanReq{plan, S, *shape};
     if (V > 0 && T <= kSelectTokens) {
       hipLaunchKernelGGL(k_small<(V > 0 ? V : 0)>, dim3(1), dim3(nwaves * kWave), 0, st, logits, ids_in, aid, emap, T, E, k, P, renorm, bits,
                          run, ids_out, w_out, slot_ids, counts, offsets, por, rop, fp);
@@ -1004,9 +1038,11 @@ int launch_permute(const float* logits, const int32_t* ids_in, const int32_t* ai
   hipLaunchKernelGGL(k_colscan, dim3(ew::ceil_div(P, kScanCols)), dim3(kScanCols * kScanGroups), 0, st, hist, nb, P, counts);
   EW_LAUNCH_CHECK("k_colscan");
   const int tpw = (int)ew::align_up((size_t)ew::ceil_div(cht, kBigWaves), kWave);  // tokens per wave of the token-per-lane kernel
-#define EW_SCATTER_TOK(KK)                                                                                                  \
-  hipLaunchKernelGGL(k_scatter_tok<KK>, dim3(nb), dim3(kBigThreads), 0, st, slot_ids, counts, hist, T, P, bits, cht, tpw, run, \
-                     offsets, por, rop)
+  const PlanReq fp = plan ? PlanReq{plan, S, *shape} : PlanReq{nullptr, 0, ew::FfnPlanShape{}};
+  const int blocks = nb + (plan ? 1 : 0);
+#define EW_SCATTER_TOK(KK)                                                                                                      \
+  hipLaunchKernelGGL(k_scatter_tok<KK>, dim3(blocks), dim3(kBigThreads), 0, st, slot_ids, counts, hist, T, P, bits, cht, tpw, run, \
+                     offsets, por, rop, fp)
   if (P <= 512 && k >= 2 && k <= 8) {
     switch (k) {
       case 2: EW_SCATTER_TOK(2); break;
@@ -1018,14 +1054,13 @@ int launch_permute(const float* logits, const int32_t* ids_in, const int32_t* ai
       default: EW_SCATTER_TOK(8); break;
     }
   } else if (P <= 512)
-    hipLaunchKernelGGL(k_scatter<512>, dim3(nb), dim3(kBigThreads), 0, st, slot_ids, counts, hist, T, k, P, bits, cht, run,
-                       offsets, por, rop);
+    hipLaunchKernelGGL(k_scatter<512>, dim3(blocks), dim3(kBigThreads), 0, st, slot_ids, counts, hist, T, k, P, bits, cht, run,
+                       offsets, por, rop, fp);
   else
-    hipLaunchKernelGGL(k_scatter<kMaxP>, dim3(nb), dim3(kBigThreads), 0, st, slot_ids, counts, hist, T, k, P, bits, cht, run,
-                       offsets, por, rop);
+    hipLaunchKernelGGL(k_scatter<kMaxP>, dim3(blocks), dim3(kBigThreads), 0, st, slot_ids, counts, hist, T, k, P, bits, cht, run,
+                       offsets, por, rop, fp);
 #undef EW_SCATTER_TOK
   EW_LAUNCH_CHECK("k_scatter");
-  if (plan) return ew::launch_ffn_plan(counts, offsets, P, S, T, (int)n, *shape, plan, st);
   return EW_OK;
 }
 
