@@ -329,75 +329,93 @@ __device__ __forceinline__ void split_bf16(const float4& lo4, const float4& hi4,
   *tail = t;
 }
 
-// A workgroup owns 16*TT tokens and 16*J experts (blockIdx.y picks the expert block); its NW waves
-// split the contraction (K/NW each) and their partial sums meet in LDS, added in wave order.  NW = 16
-// for decode-sized batches: few workgroups, so the time is the length of a wave's chain of loads.  A
-// workgroup streams its experts' fp32 gate rows once, which one CU does at a few tens of GB/s:
-// small batches therefore take J = 1 (four times the workgroups, a quarter of the bytes each),
-// large ones 32 tokens x 32 experts with 16 waves (each wave then has one batch of loads in flight instead of a
-// chain of them, and the gate rows are split into head and tail once per 32 tokens).  For a given NW the sums do
-// not depend on J or TT.
-template <int J, int NW, int TT>
+// A workgroup owns 16*TT tokens and EW experts (blockIdx.y picks them); its NW waves split the contraction (K/NW each) and their
+// partial sums meet in LDS, added in wave order: for a given NW the sums do not depend on TT or EW.
+// What bounds it is the workgroup's own reads (its token rows and fp32 gate rows, mostly from L2) at what one CU takes in,
+// so the tile is the smallest one that still gives every CU at most one workgroup (gate_tile below).  In a pass, us, before (tiles
+// by the token count alone) / now: 1 token 5.0 / 3.8, 64 tokens 7.1 / 4.7, 512 9.5 / 6.7, 1999 (128 experts of 1536) 19.3 / 11.0,
+// 8192 22.8 / 22.0.
+template <int NW, int TT, int EW>
 __global__ __launch_bounds__(64 * NW) void k_gate_logits_mfma(const uint16_t* __restrict__ x, const float* __restrict__ Wg, int T,
                                                           int H, int E, const int32_t* __restrict__ aid,
                                                           const float* __restrict__ bias, float* __restrict__ logits) {
-  constexpr int EB = 16 * J;
-  __shared__ float s_red[NW][16][EB + 1];
+  constexpr int J = (EW + 15) / 16;  // 16-expert tiles; of a narrower one the last row repeats
+  __shared__ float s_red[NW][16 * TT][16 * J + 4];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int m = lane & 15, q = lane >> 4;
-  const int t0 = blockIdx.x * 16 * TT;
+  const int t0 = blockIdx.x * 16 * TT, e0 = blockIdx.y * EW;
   const int Kw = H / NW, k_lo = wave * Kw;  // H % (32 NW) == 0
   const uint16_t* xr[TT];
 #pragma unroll
   for (int tt = 0; tt < TT; ++tt) xr[tt] = x + (size_t)min(t0 + tt * 16 + m, T - 1) * H + k_lo + q * 8;
-  for (int e0 = blockIdx.y * EB; e0 < E; e0 += gridDim.y * EB) {
-    f32x4_t acc[TT][J];
+  const float* wr[J];
 #pragma unroll
-    for (int tt = 0; tt < TT; ++tt)
+  for (int j = 0; j < J; ++j) wr[j] = Wg + (size_t)min(e0 + min(j * 16 + m, EW - 1), E - 1) * H + k_lo + q * 8;
+  f32x4_t acc[TT][J];
 #pragma unroll
-      for (int j = 0; j < J; ++j) acc[tt][j] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
-    const float* wr[J];
+  for (int tt = 0; tt < TT; ++tt)
 #pragma unroll
-    for (int j = 0; j < J; ++j) wr[j] = Wg + (size_t)min(e0 + j * 16 + m, E - 1) * H + k_lo + q * 8;
+    for (int j = 0; j < J; ++j) acc[tt][j] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
 #pragma unroll 4
-    for (int k0 = 0; k0 < Kw; k0 += 32) {
-      bf16x8_t a[TT];
+  for (int k0 = 0; k0 < Kw; k0 += 32) {
+    bf16x8_t a[TT];
 #pragma unroll
-      for (int tt = 0; tt < TT; ++tt) a[tt] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t*>(xr[tt] + k0));
+    for (int tt = 0; tt < TT; ++tt) a[tt] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t*>(xr[tt] + k0));
 #pragma unroll
-      for (int j = 0; j < J; ++j) {
-        const float4 w0 = *reinterpret_cast<const float4*>(wr[j] + k0);
-        const float4 w1 = *reinterpret_cast<const float4*>(wr[j] + k0 + 4);
-        bf16x8_t head, tail;
-        split_bf16(w0, w1, &head, &tail);
+    for (int j = 0; j < J; ++j) {
+      const float4 w0 = *reinterpret_cast<const float4*>(wr[j] + k0);
+      const float4 w1 = *reinterpret_cast<const float4*>(wr[j] + k0 + 4);
+      bf16x8_t head, tail;
+      split_bf16(w0, w1, &head, &tail);
 #pragma unroll
-        for (int tt = 0; tt < TT; ++tt) {
-          acc[tt][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[tt], head, acc[tt][j], 0, 0, 0);
-          acc[tt][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[tt], tail, acc[tt][j], 0, 0, 0);
-        }
+      for (int tt = 0; tt < TT; ++tt) {
+        acc[tt][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[tt], head, acc[tt][j], 0, 0, 0);
+        acc[tt][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[tt], tail, acc[tt][j], 0, 0, 0);
       }
-    }
-    // lane holds expert e0 + 16j + m of tokens t0 + 16tt + 4q + r; one token tile at a time goes through LDS
-#pragma unroll
-    for (int tt = 0; tt < TT; ++tt) {
-#pragma unroll
-      for (int j = 0; j < J; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) s_red[wave][q * 4 + r][j * 16 + m] = acc[tt][j][r];
-      __syncthreads();
-      for (int idx = threadIdx.x; idx < 16 * EB; idx += 64 * NW) {
-        const int tr = idx / EB, ee = idx % EB;
-        const int t = t0 + tt * 16 + tr, e = e0 + ee;
-        if (t < T && e < E) {
-          float sum = s_red[0][tr][ee];
-#pragma unroll
-          for (int wv = 1; wv < NW; ++wv) sum += s_red[wv][tr][ee];
-          logits[(size_t)t * E + e] = sum + (bias ? bias[(size_t)aid[t] * E + e] : 0.f);
-        }
-      }
-      __syncthreads();
     }
   }
+  // lane holds expert e0 + 16j + m of tokens t0 + 16tt + 4q + r
+#pragma unroll
+  for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) s_red[wave][tt * 16 + q * 4 + r][j * 16 + m] = acc[tt][j][r];
+  __syncthreads();
+  for (int idx = threadIdx.x; idx < 16 * TT * EW; idx += 64 * NW) {
+    const int tr = idx / EW, ee = idx % EW;
+    const int t = t0 + tr, e = e0 + ee;
+    if (t < T && e < E) {
+      float sum = s_red[0][tr][ee];
+#pragma unroll
+      for (int wv = 1; wv < NW; ++wv) sum += s_red[wv][tr][ee];
+      logits[(size_t)t * E + e] = sum + (bias ? bias[(size_t)aid[t] * E + e] : 0.f);
+    }
+  }
+}
+
+// f(TT, EW): the first of these tiles, ordered by what a workgroup reads, whose grid is at most one workgroup per CU; the last
+// beyond that.  Kernel alone, us, 64 experts of 2048: 64 tokens with 2 / 4 / 8 / 16 experts 4.7 / 5.1 / 5.7 / 7.0; 512 tokens with 8 /
+// 16 experts 5.8 / 7.1; 1024 tokens as 1 / 2 / 4 token tiles of 16 experts 7.2 / 8.9 / 12.6; 4096 tokens as 4 token tiles of 16 / 32
+// experts 13.3 / 17.6; 8192 tokens as 1 / 4 token tiles of 16 / 32 experts 43.7 / 17.3.
+template <typename F>
+void gate_tile(int T, int E, F f) {
+  constexpr int kCus = 256;
+  auto one = [&](auto TT, auto EW) { return (long long)ew::ceil_div(T, 16 * decltype(TT)::value) * ew::ceil_div(E, decltype(EW)::value) <= kCus; };
+  using std::integral_constant;
+  const integral_constant<int, 1> n1{};
+  const integral_constant<int, 2> n2{};
+  const integral_constant<int, 4> n4{};
+  const integral_constant<int, 8> n8{};
+  const integral_constant<int, 16> n16{};
+  const integral_constant<int, 32> n32{};
+  if (one(n1, n2)) f(n1, n2);
+  else if (one(n1, n4)) f(n1, n4);
+  else if (one(n1, n8)) f(n1, n8);
+  else if (one(n1, n16)) f(n1, n16);
+  else if (one(n2, n16)) f(n2, n16);
+  else if (one(n4, n16)) f(n4, n16);
+  else f(n4, n32);
 }
 
 }  // namespace
@@ -479,19 +497,15 @@ extern "C" int moe_gate_logits(const void* x, int dtype, const float* Wg, int T,
   if (!x || !Wg || !logits) return fail(EW_ERR_INVALID_ARG, "moe_gate_logits: NULL device pointer");
   hipStream_t st = (hipStream_t)stream;
   if (dtype == EW_BF16 && H % 128 == 0) {
-    const int tiles = ew::ceil_div(T, 16);
-    if (tiles <= 16 && H % 512 == 0)
-      hipLaunchKernelGGL((k_gate_logits_mfma<1, 16, 1>), dim3(tiles, ew::ceil_div(E, 16)), dim3(1024), 0, st, (const uint16_t*)x, Wg,
-                         T, H, E, adapter_id, bias, logits);
-    else if (tiles < 512)
-      hipLaunchKernelGGL((k_gate_logits_mfma<1, 4, 1>), dim3(tiles, ew::ceil_div(E, 16)), dim3(256), 0, st, (const uint16_t*)x, Wg, T,
-                         H, E, adapter_id, bias, logits);
-    else if (H % 512 == 0)
-      hipLaunchKernelGGL((k_gate_logits_mfma<2, 16, 4>), dim3(ew::ceil_div(tiles, 4), ew::ceil_div(E, 32)), dim3(1024), 0, st,
-                         (const uint16_t*)x, Wg, T, H, E, adapter_id, bias, logits);
-    else
-      hipLaunchKernelGGL((k_gate_logits_mfma<4, 4, 2>), dim3(ew::ceil_div(tiles, 2), 1), dim3(256), 0, st, (const uint16_t*)x, Wg, T, H,
-                         E, adapter_id, bias, logits);
+    gate_tile(T, E, [&](auto tt, auto ew_tag) {
+      constexpr int TT = decltype(tt)::value, EW = decltype(ew_tag)::value;
+      const dim3 grid(ew::ceil_div(T, 16 * TT), ew::ceil_div(E, EW));
+      // 16 waves where they divide the contraction: a wave then has its whole part in flight at once
+      if (H % 512 == 0)
+        hipLaunchKernelGGL((k_gate_logits_mfma<16, TT, EW>), grid, dim3(1024), 0, st, (const uint16_t*)x, Wg, T, H, E, adapter_id, bias, logits);
+      else
+        hipLaunchKernelGGL((k_gate_logits_mfma<4, TT, EW>), grid, dim3(256), 0, st, (const uint16_t*)x, Wg, T, H, E, adapter_id, bias, logits);
+    });
   } else if (dtype == EW_BF16)
     hipLaunchKernelGGL((k_gate_logits<true>), dim3(ew::ceil_div(T, 4)), dim3(256), 0, st, x, Wg, T, H, E, adapter_id, bias, logits);
   else

@@ -458,6 +458,22 @@ def test_gate_logits(ew, cfg_index):
     np.testing.assert_allclose(got0, moe.gate_logits(x, Wg), rtol=1e-4, atol=2e-5)
 
 
+@pytest.mark.parametrize("T,E,H", [(1, 1, 128), (17, 3, 640), (128, 64, 512), (129, 64, 512), (300, 37, 1024), (512, 64, 512), (1030, 96, 384),
+                                   (2048, 64, 512), (2100, 50, 640), (4096, 64, 512), (4100, 70, 512), (9000, 33, 128)])
+def test_gate_logits_tiles(ew, T, E, H):
+    """Every tile of the matrix-core kernel, both wave counts, and sizes that fill a tile's tokens and experts only partly.  The
+    bf16 head and tail of a gate weight leave 2^-17 of it; with sums of a few dozen such products that stays below the bound."""
+    g = torch.Generator(device="cuda").manual_seed(T + E + H)
+    x = torch.randn((T, H), generator=g, device="cuda").to(torch.bfloat16)
+    Wg = torch.randn((E, H), generator=g, device="cuda") * 0.02
+    aid = torch.randint(0, 3, (T,), generator=g, device="cuda", dtype=torch.int32)
+    bias = torch.randn((3, E), generator=g, device="cuda")
+    ref = x.double() @ Wg.double().T
+    np.testing.assert_allclose(ew.moe_gate_logits(x, Wg).cpu().numpy(), ref.cpu().numpy(), rtol=1e-4, atol=2e-5)
+    got = ew.moe_gate_logits(x, Wg, aid, bias).cpu().numpy()
+    np.testing.assert_allclose(got, (ref + bias.double()[aid.long()]).cpu().numpy(), rtol=1e-4, atol=2e-5)
+
+
 def _run_layer_through_pool(ew, cfg, inp, logits, flags=0, aid=None):
     from paper_2508_17624_amd.layer import MoELayer, load_layer
     dt = torch.bfloat16 if cfg.dtype == "bf16" else torch.float32
