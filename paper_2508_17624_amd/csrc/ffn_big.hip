@@ -3,7 +3,9 @@
 // What bounds it: the operand loads into LDS.  Whole passes of 8192 tokens, us (64 + 2 experts in use / 254 + 2): 1066 / 1330; the
 // loads alone, nothing multiplied or stored, 909 / 1213; everything but the loads (operands that stay the same, so at a higher
 // clock as well) 721 / 772; the other kernels of a pass are about 130 of these.  One token slab and up to three weight halves
-// are in flight while a slab is multiplied.
+// are in flight while a slab is multiplied.  What bounds the whole pass is the chip's power limit: the complete kernel takes 1.64
+// M cycles at 1.70 GHz, its loads and LDS reads without the multiplications 1.62 M at 2.38 GHz, the multiplications on constant
+// operands beside the loads 1.76 M at 2.13 GHz.  So fewer stalls on loads turn into a lower clock for the most part.
 #include "ffn_roles.h"
 
 namespace ew {
@@ -18,6 +20,8 @@ constexpr int kTRing = 2;
 constexpr int kQI = 8 + 256;               // ints of a queue entry
 constexpr int kTOff = kWRing * kHalf, kQOff = kTOff + kTRing * kTSlab, kLds = kQOff + 4 * kQI * 4;
 static_assert(kLds <= 160 * 1024, "LDS budget of a CU");
+constexpr int kAlone = 1;                  // FfnUnit::how: no other chunk reads this unit's weights
+constexpr int kSwap = 2;                   // the unit walks over K by pairs of slabs, the second of a pair first
 constexpr int kThreads = 768;              // waves 0-1 load weights, 2 token rows, 3 schedules, 4-11 multiply
 
 __device__ __forceinline__ int swz(int r) { return ((r >> 1) ^ ((r & 1) << 2)) & 7; }
@@ -28,7 +32,7 @@ struct Sched {
   int w, mode, t, home;      // claim in flight: list (home + t) % 8
   int n_ent, chunks;         // lane i: entries and chunks of list (home + i) % 8
   int ent[6];                // lane e: entry e of the claimed list
-  int ok, slot, rows, off, g, chunk, alone;
+  int ok, slot, rows, off, g, chunk, how;
   uint32_t src[4];
 };
 
@@ -82,7 +86,13 @@ __device__ __forceinline__ void sched_rows(const FfnArgs& a, Sched& s) {
   const int i = s.w - base * G, j = i % nch;
   s.slot = __builtin_amdgcn_readfirstlane(__shfl(s.ent[0], e, 64));
   s.g = i / nch;
-  s.alone = nch == 1;
+  // Half of the units that share weights (chunks of one feature group) and half of those that share token rows (feature groups of
+  // one chunk) walk over each pair of slabs in the opposite order, so that what one half fetches is in the XCD's L2 when the other
+  // half asks for it: units in step all wait for the same line to come from memory.  (j: entries have an even number of chunks
+  // but for a slot's last one, so its parity is that of the chunk's place in the slot and nothing depends on the plan.)  The
+  // loads alone, us: 819 -> 726 base-only, 1121 -> 1037 with 20 adapters; whole passes 1089 -> 1082, 1390 -> 1381.  Four
+  // orders over four slabs: the loads alone 706 and 1040, whole passes no better.
+  s.how = (nch == 1 ? kAlone : 0) | ((j + s.g) & 1 ? kSwap : 0);
   s.rows = min(bts, c - j * bts);
   s.off = __shfl(s.ent[5], e, 64) + j * bts;
   s.chunk = ((s.home + s.t) & 7) * a.list_chunks + base + j;
@@ -102,7 +112,7 @@ __device__ __forceinline__ void sched_publish(const FfnArgs& a, const Sched& s, 
 #pragma unroll
     for (int h = 0; h < 4; ++h) q[8 + 64 * h + lane] = (int32_t)s.src[h];
     if (lane == 0) {
-      q[0] = s.slot; q[1] = s.off; q[2] = s.rows; q[3] = s.g; q[4] = s.mode; q[5] = s.chunk; q[7] = s.alone;
+      q[0] = s.slot; q[1] = s.off; q[2] = s.rows; q[3] = s.g; q[4] = s.mode; q[5] = s.chunk; q[7] = s.how;
       q[6] = s.mode == 0 || __hip_atomic_load(a.done + s.chunk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= a.m[0].G;
     }
   }
@@ -262,6 +272,7 @@ __device__ __forceinline__ void big_body(const FfnArgs& a, unsigned char* s_lds)
   [[maybe_unused]] const unsigned char* p_base = nullptr;
   [[maybe_unused]] uint32_t p_w = 0, p_up = 0, p_i = 0, p_wr = 0;
   [[maybe_unused]] bool p_alone = false;                                      // no other chunk reads this unit's weights
+  [[maybe_unused]] int p_swap = 0;                                            // 1: slab kt ^ 1 in place of kt
   [[maybe_unused]] bool p_part = false;                                       // the unit's second half of weight rows does not exist
   [[maybe_unused]] uint32_t p_off[ROLE == 1 ? 32 : 1] = {};
   int p_h = 0, p_n = 1, p_nfl = 0, p_slot = 0;                                // next piece of the loading unit, their number
@@ -269,6 +280,7 @@ __device__ __forceinline__ void big_body(const FfnArgs& a, unsigned char* s_lds)
   auto aim = [&](const FfnUnit& u, [[maybe_unused]] int qi) {
     const FfnProd& m = u.mode ? a.m[1] : a.m[0];
     p_h = 0;
+    p_swap = u.how & kSwap ? 1 : 0;                                           // (K has an even number of slabs)
     if constexpr (ROLE == 0) {
       p_n = m.K >> 5;
       const uint32_t k2 = (uint32_t)(m.K * 2);
@@ -280,7 +292,7 @@ __device__ __forceinline__ void big_body(const FfnArgs& a, unsigned char* s_lds)
       p_up = (u.mode == 0 ? (uint32_t)m.NOUT : 16u) * k2;
       p_i = 4u * k2;
       p_wr = (u.mode == 0 ? 32u : 64u) * k2;
-      p_alone = u.alone;
+      p_alone = u.how & kAlone;
       p_part = u.mode == 1 && u.g * 256 + 128 >= m.NOUT;
     } else if constexpr (ROLE == 1) {
       p_n = m.K >> 6;
@@ -294,7 +306,7 @@ __device__ __forceinline__ void big_body(const FfnArgs& a, unsigned char* s_lds)
   auto issue = [&]() {
     if constexpr (ROLE == 0) {
       const int half = p_h & 1;
-      const unsigned char* src = p_base + (size_t)(p_h >> 1) * 128 + (half && !p_part ? 2 * p_wr : 0u);
+      const unsigned char* src = p_base + (size_t)((p_h >> 1) ^ p_swap) * 128 + (half && !p_part ? 2 * p_wr : 0u);
       const uint32_t dst = lds0 + p_slot * kHalf + lw * 1024;
       auto load = [&](auto aux) {
 #pragma unroll
@@ -307,7 +319,7 @@ __device__ __forceinline__ void big_body(const FfnArgs& a, unsigned char* s_lds)
       else load(std::integral_constant<int, 16>{});
       p_slot = p_slot + 1 == kWRing ? 0 : p_slot + 1;
     } else if constexpr (ROLE == 1) {
-      const unsigned char* src = p_base + (size_t)p_h * 128;
+      const unsigned char* src = p_base + (size_t)(p_h ^ p_swap) * 128;
       const uint32_t dst = lds0 + kTOff + p_slot * kTSlab;
 #pragma unroll
       for (int f = 0; f < 8; ++f)

@@ -44,7 +44,7 @@ __device__ __forceinline__ float silu_f32(float g) { return g * __builtin_amdgcn
 struct FfnUnit {
   int slot, off, rows, g, mode, chunk;  // slot < 0: no unit left
   int ready;                            // 1: nothing to wait for; kExpired: the wait was given up
-  int alone;                            // k_ffn_big: no other chunk reads these weights
+  int how;                              // k_ffn_big: kAlone, kSwap
 };
 
 // LDS-direct load: 16 bytes per lane from base + off (base: wave-uniform) to lds + 16 * lane.  AUX: 0 plain, 2 nt, 16 sc1.
@@ -77,7 +77,7 @@ __device__ __forceinline__ FfnUnit read_unit(uint32_t addr) {
   u.mode = __builtin_amdgcn_readfirstlane(hi[0]);
   u.chunk = __builtin_amdgcn_readfirstlane(hi[1]);
   u.ready = __builtin_amdgcn_readfirstlane(hi[2]);
-  u.alone = __builtin_amdgcn_readfirstlane(hi[3]);
+  u.how = __builtin_amdgcn_readfirstlane(hi[3]);
   return u;
 }
 // N ints STEP bytes apart (N: 1, 2 or a multiple of 4).
