@@ -17,9 +17,9 @@
 //     of them when all first-product units were claimed; a first-product unit is held by a workgroup whose earlier units
 //     are first-product too, which wait for nothing, and whose stores are counted before it waits for anything (workgroups
 //     that are not resident hold no claims).  A limit on the number of looks makes sure of it, see wait_stored.
-//   * Coherence of the activations: agent-scope stores, acknowledged before they are counted; for the loads see ACT_AUX.
-// Measured (call with plan, one card): 1 token on 8 experts of 2048 x 1408: 76 -> 43 us; 13 tokens on 36 of 1024 x 896: 88 ->
-// 47 us; 64 tokens on 90: 263 -> 246 us (6.3 TB/s of weights; a bare stream of the same slabs reaches 6.85); 512 tokens on
+//   * Coherence of the activations: agent-scope stores, acknowledged before they are counted; for the loads see kHalfLines.
+// Measured (call with plan, one card): 1 token on 8 experts of 2048 x 1408: 76 -> 43 us (kernel alone now 37.4 -> 34.7); 13 tokens
+// on 36 of 1024 x 896: 88 -> 47 us (42.2 -> 40.2); 64 tokens on 90: 263 -> 246 us (6.3 TB/s of weights; a bare stream of the same slabs reaches 6.85); 512 tokens on
 // 242: 699 -> 682 us; 512 on 150 of 1536 x 640: 182 -> 161 us; 2000 on 217 of those: 328 -> 257 us.
 //
 // Waves: NW load weights, NT token rows, each into a ring of its own (the vector-memory counter retires in order, so each
@@ -53,18 +53,18 @@ struct DecCfg {
   static constexpr int NWI = MR / (NW * RPI);                       // load instructions per weight wave and slab
   static constexpr int NTI = 16 / (NT * RPI);                       // load instructions per token wave and fragment
   static constexpr int PN = MR / 32;                                // pairs of weight fragments
-  // Cache policy of the activation rows' loads.  Where a unit of the first product writes whole 128-byte lines, plain loads do:
-  // a line has one writer, nothing reads it before its chunk is complete, and no cache keeps lines of earlier launches; the
-  // units of an XCD then share the rows in its L2 (2000 tokens: 265 -> 257 us).  Half lines are read past the L2.
-  static constexpr int ACT_AUX = MR == 64 ? 16 : 0;
   static constexpr int QI = 8 + (NTF > 4 ? 16 * NTF : 64);          // ints of a queue entry: description, source rows
   static constexpr int LEFT = 160 * 1024 - 4 * QI * 4;
   // ring depths: the token rows come from L2 and need less, the weights take the rest
-  static constexpr int DT = TSLAB > 8192 ? 3 : 5;
-  static constexpr int DW = (LEFT - DT * TSLAB) / WSLAB < 8 ? (LEFT - DT * TSLAB) / WSLAB : 8;
+  static constexpr int DT = TSLAB > 8192 ? 3 : NTF == 1 ? 6 : 5;
+  static constexpr int MOST = NTF == 1 ? 6 : 8;                     // (1 and 13 tokens: 8 and 5 slabs 48.2, 54.9 us, 6 and 6 47.6, 54.4)
+  static constexpr int DW = (LEFT - DT * TSLAB) / WSLAB < MOST ? (LEFT - DT * TSLAB) / WSLAB : MOST;
   static constexpr int Q_OFF = DW * WSLAB + DT * TSLAB;
   static constexpr int LDS = Q_OFF + 4 * QI * 4;
   static_assert(LDS <= 160 * 1024 && DW * WSLAB >= 80 * 1024, "LDS budget of a CU, bytes in flight");
+  static constexpr int FPI = NW * RPI / 16;                         // fragments per round of the weight waves' instructions
+  static constexpr bool SPLIT = NTF == 1;                           // units of the first product may come in halves, see whole_units
+  static_assert(!SPLIT || (PN / 2 % FPI == 0 && NWI % 2 == 0), "half a unit: whole pairs of fragments, loads for every weight wave");
 };
 
 // Operands of one k-step (32 elements): MFW weight fragments WS bytes apart and NB token fragments FS bytes apart, issued
@@ -130,11 +130,27 @@ __device__ __forceinline__ void mul_slab(uint32_t wa, uint32_t tb, f32x4 (&acc)[
 __device__ __forceinline__ int first_slab(const FfnUnit& u, int nk) { return (u.slot * 5 + u.g * 3) % nk; }
 
 // ------------------------------------------------------------------------------------------
-// The scheduling wave.  Unit u of a product belongs to list u % 8.
+// A call of a few tokens has one to three units of the first product per workgroup, and the second product waits for the last
+// one: where the units beyond the last full round fit one round as halves (of their weight rows), they are split.  1 token: 96
+// units beyond 256, a pass 48.9 -> 47.9 us; 13 tokens: 62 beyond 512, 56.9 -> 54.6.  Halves keep their unit's walk over K, so no
+// result depends on the split.  Not for more rounds or more tokens, and not in the second product, where the workgroups end 7 to 26
+// us apart: a slab costs about half a microsecond of hand-overs between the waves however small it is, and the last units in
+// halves or quarters cost more than the even end gave (64 tokens 241 -> 247 us, 256 tokens 2028 -> 2046).
+template <typename C>
+__device__ __forceinline__ int whole_units(int mode, int n) {  // positions below are whole units, above there are two for each
+  if (!C::SPLIT || mode) return n;
+  const int grid = (int)gridDim.x, over = n % grid;
+  return n < 3 * grid && 2 * over <= grid ? n - over : n;
+}
+// What a stored unit of the first product adds to its chunk's completion counter, which ends at kDone G.
+constexpr int kDone = 2;
+__device__ __forceinline__ int done_by(const FfnUnit& u) { return u.how ? 1 : kDone; }
+
+// The scheduling wave.  Position v of a product's units belongs to list v % 8.
 struct Sched {
   int w;                 // claim in flight: position in list `list` of product `mode`
   int mode, list, home;
-  int chunk, g;
+  int chunk, g, how;
   i32x4 en;
   uint32_t src[2];       // byte offsets of the source rows lane, lane + 64 of the chunk
 };
@@ -145,6 +161,7 @@ __device__ __forceinline__ int32_t* sched_counter(const FfnArgs& a, int mode, in
 __device__ __forceinline__ void sched_claim(const FfnArgs& a, Sched& s) {
   if ((threadIdx.x & 63) == 0 && s.mode <= a.last_mode) s.w = __hip_atomic_fetch_add(sched_counter(a, s.mode, s.list), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+template <typename C>
 __device__ __forceinline__ void sched_entry(const FfnArgs& a, int n_chunks, Sched& s) {
   const int lane = threadIdx.x & 63;
   for (;;) {
@@ -152,9 +169,15 @@ __device__ __forceinline__ void sched_entry(const FfnArgs& a, int n_chunks, Sche
       s.chunk = -1;
       return;
     }
-    const int G = s.mode ? a.m[1].G : a.m[0].G, n = n_chunks * G;
-    const int u = __builtin_amdgcn_readfirstlane(s.w) * 8 + s.list;
-    if (u < n) {
+    const int G = s.mode ? a.m[1].G : a.m[0].G, units = n_chunks * G, whole = whole_units<C>(s.mode, units), n = units + (units - whole);
+    const int v = __builtin_amdgcn_readfirstlane(s.w) * 8 + s.list;
+    if (v < n) {
+      int u = v;
+      s.how = 0;
+      if (C::SPLIT && v >= whole) {
+        u = whole + ((v - whole) >> 1);
+        s.how = 1 + ((v - whole) & 1);
+      }
       s.chunk = u / G;
       s.g = u - s.chunk * G;
       s.en = *reinterpret_cast<const i32x4*>(a.plan + kDecEnt + 4 * s.chunk);
@@ -195,8 +218,8 @@ __device__ __forceinline__ void sched_publish(const FfnArgs& a, const Sched& s, 
     q[8 + lane] = (int32_t)s.src[0];
     if (QI > 72) q[8 + 64 + lane] = (int32_t)s.src[1];
     if (lane == 0) {
-      q[0] = s.en[0]; q[1] = s.en[2]; q[2] = s.en[1]; q[3] = s.g; q[4] = s.mode; q[5] = s.chunk;
-      q[6] = s.mode == 0 || __hip_atomic_load(a.done + s.chunk * kDecDoneStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= a.m[0].G;
+      q[0] = s.en[0]; q[1] = s.en[2]; q[2] = s.en[1]; q[3] = s.g; q[4] = s.mode; q[5] = s.chunk; q[7] = s.how;
+      q[6] = s.mode == 0 || __hip_atomic_load(a.done + s.chunk * kDecDoneStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= kDone * a.m[0].G;
     }
   }
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -218,15 +241,22 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds)
 
   [[maybe_unused]] Sched sc{};
   [[maybe_unused]] int n_chunks = 0;
-  [[maybe_unused]] int pending = -1;  // scheduler: chunk of the previous unit, counted inside the slab loop of the present one
+  [[maybe_unused]] int pending = -1, pending_by = 0;  // scheduler: chunk of the previous unit, counted inside the slab loop of the present one
   if constexpr (ROLE == 2) {
+    // The first two units, three round trips each, the second one's a step behind: its last one alone competes with the bulk
+    // loads that the first unit starts.  One after the other the second unit was known 5.8 us into the launch, and
+    // nothing can be multiplied before.
     n_chunks = a.plan[0];
-    sc.home = sc.list = (int)(blockIdx.x & 7);
-    sc.mode = a.first_mode;
+    Sched s0{};
+    s0.home = s0.list = (int)(blockIdx.x & 7);
+    s0.mode = a.first_mode;
+    sched_claim(a, s0);
+    sched_entry<C>(a, n_chunks, s0);
+    sc = s0;
     sched_claim(a, sc);
-    sched_entry(a, n_chunks, sc);
-    sched_rows<C::QI>(a, sc);
-    sched_publish<C::QI>(a, sc, queue);
+    sched_rows<C::QI>(a, s0);
+    sched_entry<C>(a, n_chunks, sc);
+    sched_publish<C::QI>(a, s0, queue);
   }
   __builtin_amdgcn_s_barrier();
   FfnUnit cur = read_unit(q0);
@@ -242,7 +272,13 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds)
   [[maybe_unused]] const unsigned char* p_base = nullptr;                     // the loading unit's source
   [[maybe_unused]] uint32_t p_off[C::NTI * NTF] = {};                         // token waves: byte offset of the lane's row per fragment
   [[maybe_unused]] uint32_t p_w = 0, p_ws = 0;                                // weight waves: lane offset, stride between fragments
+  // Cache policy of the activation rows' loads.  Where a unit of the first product writes whole 128-byte lines, plain loads do:
+  // a line has one writer, nothing reads it before its chunk is complete, and no cache keeps lines of earlier launches; the
+  // units of an XCD then share the rows in its L2 (2000 tokens: 265 -> 257 us).  Half lines (units of 64 rows, halves of units of
+  // 128) are read past the L2.
+  constexpr bool kHalfLines = MR == 64 || C::SPLIT;
   int p_k = 0, p_nk = 1, p_rot = 0, p_nld = 0, p_mode = 0;
+  [[maybe_unused]] bool p_half = false;
   int p_slot = 0;                                                             // ring slot of the next slab
   bool p_next = false;                                                        // the loading unit is `nxt`
   auto aim = [&](const FfnUnit& u, [[maybe_unused]] int qi) {
@@ -251,10 +287,11 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds)
     p_nk = m.K >> kShift;
     p_rot = first_slab(u, p_nk);
     p_mode = u.mode;
+    p_half = C::SPLIT && u.how;
     if constexpr (ROLE == 0) {
       p_base = reinterpret_cast<const unsigned char*>(u.slot < a.P ? m.w + (size_t)u.slot * m.slot_stride
                                                                    : m.w_sh + (size_t)(u.slot - a.P) * m.slot_stride);
-      const int f0 = MR == 128 ? lw >> 1 : 0;                                 // fragment of instruction 0
+      const int f0 = (MR == 128 ? lw >> 1 : 0) + (C::SPLIT && u.how == 2 ? C::PN / 2 : 0);  // pair of instruction 0
       const uint32_t row = u.mode == 0 ? (uint32_t)((pm & 2 ? m.NOUT : 0) + u.g * (MR / 2) + f0 * 16 + 4 * (pm >> 2) + (pm & 1))
                                        : (uint32_t)(u.g * MR + f0 * 32 + 8 * (pm >> 2) + (pm & 3));
       p_w = row * (uint32_t)(m.K * 2) + piece;
@@ -277,19 +314,23 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds)
     const unsigned char* src = p_base + (size_t)kk * C::RB;
     if constexpr (ROLE == 0) {
       const uint32_t dst = lds0 + p_slot * C::WSLAB + lw * 1024;
+      auto load = [&](auto half) {
 #pragma unroll
-      for (int i = 0; i < C::NWI; ++i) {
-        constexpr int FPI = C::NW * C::RPI / 16;                              // fragments per round of instructions
-        const uint32_t rows = 16 * (i * FPI % C::PN) + 2 * (i * FPI / C::PN); // see the fragment layout at the top
-        load_to_lds<2>(src + rows * p_ws, p_w, dst + i * C::NW * 1024);
-      }
+        for (int i = 0; i < C::NWI; ++i) {
+          const int pair = i * C::FPI % C::PN;
+          const uint32_t rows = 16 * pair + 2 * (i * C::FPI / C::PN);         // see the fragment layout at the top
+          if (!decltype(half)::value || pair < C::PN / 2) load_to_lds<2>(src + rows * p_ws, p_w, dst + i * C::NW * 1024);
+        }
+      };
+      if (C::SPLIT && p_half) load(std::true_type{});
+      else load(std::false_type{});
     } else if constexpr (ROLE == 1) {
       const uint32_t dst = lds0 + C::DW * C::WSLAB + p_slot * C::TSLAB + lw * 1024;
 #pragma unroll
       for (int i = 0; i < C::NTI * NTF; ++i)
         if (i < C::NTI * p_nld) {
           // second product: rows written by other workgroups of this launch, read at the point of coherence
-          if (C::ACT_AUX && p_mode) load_to_lds<C::ACT_AUX>(src, p_off[i], dst + i * C::NT * 1024);
+          if (kHalfLines && p_mode) load_to_lds<16>(src, p_off[i], dst + i * C::NT * 1024);
           else load_to_lds<0>(src, p_off[i], dst + i * C::NT * 1024);
         }
     }
@@ -299,7 +340,7 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds)
   [[maybe_unused]] int polls = a.wait_polls;
   auto wait_done = [&](const FfnUnit& u, int qi) {  // token waves: the unit's activation rows are stored
     if (u.mode == 0 || u.ready) return;
-    wait_stored(a.done + u.chunk * kDecDoneStride, a.m[0].G, polls, queue + qi * C::QI);
+    wait_stored(a.done + u.chunk * kDecDoneStride, kDone * a.m[0].G, polls, queue + qi * C::QI);
   };
 
   // ---- the multiplying side
@@ -317,8 +358,6 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds)
     aim(cur, 0);
     for (int i = 0; i < depth - 1; ++i) issue();
   } else if constexpr (ROLE == 2) {
-    sched_claim(a, sc);
-    sched_entry(a, n_chunks, sc);
     sched_rows<C::QI>(a, sc);
     sched_publish<C::QI>(a, sc, queue + C::QI);
   }
@@ -330,7 +369,10 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds)
     const int nk = m.K >> kShift;
     const bool change = nxt.slot >= 0 && nxt.mode != cur.mode;
     [[maybe_unused]] const int nld = (cur.rows + 15) >> 4;                    // live token fragments
+    [[maybe_unused]] const bool half = C::SPLIT && cur.how;
+    [[maybe_unused]] const int live = half ? C::PN / 2 : C::PN;               // pairs of weight fragments that the unit has
     if constexpr (ROLE == 3) {
+      const int at_pair = C::SPLIT && cur.how == 2 ? live + pair : pair;      // inside the whole unit
       // one loop per number of live token fragments (above four: eight, the rest multiplied for nothing), so that the
       // accumulators stay where they are
       auto unit = [&](auto nb_tag) {
@@ -356,7 +398,7 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds)
               // agent scope: written through to the point of coherence of the GPU's XCDs
               unsigned long long bits;
               __builtin_memcpy(&bits, &o, 8);
-              __hip_atomic_store(reinterpret_cast<unsigned long long*>(row + cur.g * (MR / 2) + pair * 16 + 4 * q), bits, __ATOMIC_RELAXED,
+              __hip_atomic_store(reinterpret_cast<unsigned long long*>(row + cur.g * (MR / 2) + at_pair * 16 + 4 * q), bits, __ATOMIC_RELAXED,
                                  __HIP_MEMORY_SCOPE_AGENT);
             } else {
               union { uint16_t h[8]; uint4 u; } o;
@@ -370,14 +412,14 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds)
           }
         }
       };
-      const int nf = (nld - nh + FSTEP - 1) / FSTEP;                          // this wave's live token fragments
+      const int nf = !C::SPLIT || pair < live ? (nld - nh + FSTEP - 1) / FSTEP : 0;  // this wave's live token fragments
       if (NF >= 8 && nf > 4) unit(std::integral_constant<int, NF >= 8 ? 8 : 0>{});
       else if (NF >= 4 && nf == 4) unit(std::integral_constant<int, NF >= 4 ? 4 : 0>{});
       else if (NF >= 3 && nf == 3) unit(std::integral_constant<int, NF >= 3 ? 3 : 0>{});
       else if (NF >= 2 && nf == 2) unit(std::integral_constant<int, NF >= 2 ? 2 : 0>{});
       else if (nf >= 1) unit(std::integral_constant<int, 1>{});
       else unit(std::integral_constant<int, 0>{});
-      if (wait_expired(cur, q0 + (uint32_t)((seq & 3) * C::QI) * 4u)) {       // over what this wave has just stored
+      if (wait_expired(cur, q0 + (uint32_t)((seq & 3) * C::QI) * 4u)) {       // over what this wave has just stored (second product: a whole unit)
         __builtin_amdgcn_s_waitcnt(0x0F70);
 #pragma unroll 1
         for (int tr = nh * 16 + n16; tr < cur.rows; tr += FSTEP * 16)
@@ -389,18 +431,18 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds)
         // this wave's part of slab kt has landed once only later slabs' loads are outstanding
         const int ahead_next = p_next ? p_k : 0;                              // slabs of nxt in flight
         const int ahead = (p_next ? nk : p_k) - (kt + 1);                     // later slabs of cur
-        wait_vm_upto(ROLE == 0 ? C::NWI * (ahead + ahead_next) : C::NTI * (ahead * nld + ahead_next * p_nld));
+        wait_vm_upto(ROLE == 0 ? (half ? C::NWI / 2 : C::NWI) * ahead + (C::SPLIT && p_half ? C::NWI / 2 : C::NWI) * ahead_next : C::NTI * (ahead * nld + ahead_next * p_nld));
       }
       __builtin_amdgcn_s_barrier();                                           // everyone's part is there, slab kt-1 has been read
       if constexpr (ROLE == 2) {
         if (kt == a.depth_w - 1 && pending >= 0) {
           // every multiplying wave has waited for its stores of the previous unit
-          if (lane == 0) __hip_atomic_fetch_add(a.done + pending * kDecDoneStride, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if (lane == 0) __hip_atomic_fetch_add(a.done + pending * kDecDoneStride, pending_by, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           pending = -1;
         }
         // the unit after the next: one round trip at a time, spread over this unit's slabs
         if (kt == 0) sched_claim(a, sc);
-        if (kt == (nk - 2) / 3) sched_entry(a, n_chunks, sc);
+        if (kt == (nk - 2) / 3) sched_entry<C>(a, n_chunks, sc);
         if (kt == 2 * (nk - 2) / 3) sched_rows<C::QI>(a, sc);
         if (kt == nk - 2) sched_publish<C::QI>(a, sc, queue + ((seq + 2) & 3) * C::QI);
       } else if constexpr (LOADS) {
@@ -417,11 +459,12 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds)
       if constexpr (ROLE != 2) __builtin_amdgcn_s_waitcnt(0x0F70);
       __builtin_amdgcn_s_barrier();
       if constexpr (ROLE == 2) {
-        if (cur.mode == 0 && lane == 0) __hip_atomic_fetch_add(a.done + cur.chunk * kDecDoneStride, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (cur.mode == 0 && lane == 0) __hip_atomic_fetch_add(a.done + cur.chunk * kDecDoneStride, done_by(cur), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
       if (nxt.slot < 0) return;
     } else if constexpr (ROLE == 2) {
       pending = cur.mode == 0 ? cur.chunk : -1;
+      pending_by = done_by(cur);
     }
     ++seq;
     cur = nxt;
