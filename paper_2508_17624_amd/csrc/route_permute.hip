@@ -15,8 +15,8 @@
 //    counter; runs are stitched by exclusive scans over waves (LDS) and over blocks (global).
 //  * small batches (decode): ONE single-block kernel does top-k, lookup, histogram, scan and scatter
 //    without leaving the CU (above 64 tokens a multi-block top-k + lookup kernel runs first and that
-//    block receives slots).  Large batches use three kernels: per-block histogram (fused with top-k
-//    and lookup), column scan, ranked scatter.
+//    block receives slots).  Larger ones use two kernels, per-block histogram (fused with top-k
+//    and lookup) and ranked scatter; the largest have a column scan between them.
 //  * the grouped FFN's work plan, if asked for, never is a launch of its own: the single block goes
 //    on to build it, and the scatter's launch has one more block for it.
 #include "ew_internal.h"
@@ -40,6 +40,8 @@ constexpr int kBigWaves = kBigThreads / kWave;
 constexpr int kHistThreads = 1024;   // the histogram kernel is a plain stream: more waves per block hide its latency
 constexpr int kBigPairs = 12288;     // multi-block path: pairs per block at most this
 constexpr int kBigSteps = kBigPairs / kBigWaves / kWave;  // 64-pair steps per wave = 24
+constexpr int kDirectPairs = 1 << 18;  // up to this many pairs the scatter sums the histogram's columns itself (chunk_tokens)
+constexpr int kDirectBlocks = 128;
 constexpr int kMapLds = 8192;        // expert-map entries staged in LDS at most
 
 // ------------------------------------------------------------------------------------------
@@ -364,7 +366,7 @@ struct PlanReq {
 
 // Block 0 of a scatter launch that was asked for a plan: builds it from the counts while the other blocks scatter.  Scatter and
 // plan, us, as two launches before / now: 512 tokens 5.7 + 3.7 / 5.1; 8192 tokens 7.7 + 10.3 / 9.2.  T tokens, n pairs; a block of 512 threads; lds: the scatter's sorted-pairs array.
-__device__ __forceinline__ void plan_block(const int32_t* __restrict__ counts, int T, int n, int P, const PlanReq& fp, int32_t* s_w, void* lds) {
+__device__ __forceinline__ void plan_block(const int32_t* counts, int T, int n, int P, const PlanReq& fp, int32_t* s_w, void* lds) {
   int rows[4], first[4], sum = 0;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
@@ -771,6 +773,42 @@ __global__ __launch_bounds__(kBigThreads) void k_scatter(const int32_t* __restri
   }
 }
 
+// Column s of the histogram matrix hist[nb][P], P <= 512 and a multiple of 4: its sum, and its sum over the rows before `row`, for
+// thread s < P of a block of 512 threads.  A thread loads four columns at once from its share of the rows, so that the whole matrix
+// is a few loads per thread, all in flight together; the shares meet in s_a (kColumnSumInts ints).  Contains a barrier; s_a may be
+// reused after another one.
+constexpr int kColumnSumInts = 2 * 4 * kBigThreads;
+__device__ __forceinline__ void column_sums(const int32_t* __restrict__ hist, int nb, int P, int row, int32_t* s_a, int& total, int& before) {
+  const int lg = P > 256 ? 7 : P > 128 ? 6 : 5, parts = kBigThreads >> lg;  // (groups of columns, threads per group)
+  const int tid = threadIdx.x, group = tid & ((1 << lg) - 1), part = tid >> lg;
+  const int per = (nb + parts - 1) / parts, r0 = part * per, r1 = min(nb, r0 + per);
+  int4 sum = make_int4(0, 0, 0, 0), pre = sum;
+  if (4 * group < P) {
+    constexpr int kAhead = 8;
+    for (int r = r0; r < r1; r += kAhead) {
+      int4 v[kAhead];
+#pragma unroll
+      for (int j = 0; j < kAhead; ++j) v[j] = r + j < r1 ? *reinterpret_cast<const int4*>(hist + (size_t)(r + j) * P + 4 * group) : make_int4(0, 0, 0, 0);
+#pragma unroll
+      for (int j = 0; j < kAhead; ++j) {
+        sum.x += v[j].x; sum.y += v[j].y; sum.z += v[j].z; sum.w += v[j].w;
+        if (r + j < row) { pre.x += v[j].x; pre.y += v[j].y; pre.z += v[j].z; pre.w += v[j].w; }
+      }
+    }
+  }
+  int32_t* s_b = s_a + 4 * kBigThreads;
+  reinterpret_cast<int4*>(s_a)[tid] = sum;
+  reinterpret_cast<int4*>(s_b)[tid] = pre;
+  __syncthreads();
+  total = 0;
+  before = 0;
+  if (tid < P)
+    for (int q = 0; q < parts; ++q) {
+      total += s_a[(q << (lg + 2)) + tid];
+      before += s_b[(q << (lg + 2)) + tid];
+    }
+}
+
 // Kernel 3 for 2 <= k <= 8 and P <= 512: the same stable scatter with the ranking done one TOKEN per lane.  A wave
 // step then covers 64 tokens = 64 k pairs; a token's k slots are distinct (the ids of a top-k are, and a row of the
 // expert map is injective), so a lane's k pairs never meet each other in a slot's lane mask and one mask round ranks
@@ -778,9 +816,12 @@ __global__ __launch_bounds__(kBigThreads) void k_scatter(const int32_t* __restri
 // (the ranking, not memory, bounded the pair-per-lane kernel).  A block that does find a token with a repeated slot
 // (ids that no top-k would produce) ranks pair per lane as k_scatter does, so the result is exact for any input.
 //   tpw = tokens per wave, a multiple of 64.
+// direct: `base` is the blocks' histograms as k_hist left them, and counts is written here; every block sums its columns over
+// them instead of a launch in between (us, scan and scatter with plan, before / now: 512 tokens 4.0 + 5.1 / 5.9; 8192 tokens
+// 3.8 + 9.2 / 12.9).
 template <int K>
-__global__ __launch_bounds__(kBigThreads) void k_scatter_tok(const int32_t* __restrict__ slot_ids, const int32_t* __restrict__ counts,
-                                                             const int32_t* __restrict__ base, int T, int P, int bits, int cht,
+__global__ __launch_bounds__(kBigThreads) void k_scatter_tok(const int32_t* __restrict__ slot_ids, int32_t* __restrict__ counts,
+                                                             const int32_t* __restrict__ base, int direct, int nb, int T, int P, int bits, int cht,
                                                              int tpw, int run, int32_t* __restrict__ offsets,
                                                              int32_t* __restrict__ pair_of_row, int32_t* __restrict__ row_of_pair,
                                                              PlanReq fp) {
@@ -795,12 +836,20 @@ __global__ __launch_bounds__(kBigThreads) void k_scatter_tok(const int32_t* __re
   __shared__ int s_dup;
   static_assert((size_t)kBigWaves * MAXP * 8 <= sizeof(s_sorted), "the lane masks borrow the sorted-pairs array");
   static_assert(sizeof(ew::FfnPlanLds) <= sizeof(s_sorted), "a plan is built in the sorted-pairs array");
+  static_assert(kColumnSumInts * 4 <= sizeof(s_sorted), "the column sums borrow it too");
+  int32_t* s_a = reinterpret_cast<int32_t*>(s_sorted);
+  const int tid = threadIdx.x;
   if (fp.plan && blockIdx.x == 0) {
-    plan_block(counts, T, T * K, P, fp, s_w, s_sorted);
+    if (direct) {
+      int total, before;
+      column_sums(base, nb, P, 0, s_a, total, before);
+      if (tid < P) s_off[tid] = total;
+      __syncthreads();
+    }
+    plan_block(direct ? s_off : counts, T, T * K, P, fp, s_w, s_sorted);
     return;
   }
   const int block = blockIdx.x - (fp.plan ? 1 : 0);
-  const int tid = threadIdx.x;
   const int wave = tid / kWave, lane = tid & (kWave - 1);
   const int t0 = block * cht, t1 = min(T, t0 + cht);
   const size_t p0 = (size_t)t0 * K;
@@ -819,9 +868,15 @@ __global__ __launch_bounds__(kBigThreads) void k_scatter_tok(const int32_t* __re
   }
 #pragma unroll
   for (int i = STEPS * K; i < NV; ++i) packed[i] = 0u;
-  const int32_t* mybase = base + (size_t)block * P;
-  const int32_t base_v = tid < P ? mybase[tid] : 0;                // this block's row of the scanned histogram
-  const int32_t count_v = tid < P ? counts[tid] : 0;
+  int base_v = 0, count_v = 0;                                     // slot tid: pairs in the blocks before this one, in all
+  if (direct) {
+    column_sums(base, nb, P, block, s_a, count_v, base_v);
+    if (block == 0 && tid < P) counts[tid] = count_v;
+    __syncthreads();                                               // s_a becomes the lane masks
+  } else if (tid < P) {
+    base_v = base[(size_t)block * P + tid];                        // the scanned histogram
+    count_v = counts[tid];
+  }
   unsigned long long* s_mask = reinterpret_cast<unsigned long long*>(s_sorted);
   for (int i = tid; i < kBigWaves * P; i += kBigThreads) {
     s_cnt[i] = 0;
@@ -969,9 +1024,15 @@ __global__ void k_zero_counts(int32_t* counts, int32_t* offsets, int P) {
 // batch spreads over about 512 blocks: two 512-thread blocks fit a CU (LDS of k_scatter), so up to
 // 2^20 tokens at k = 6 the whole grid is resident at once, and longer chunks mean longer runs per
 // slot in the scatter's coalesced writes.
-inline int chunk_tokens(int T, int k) {
+// Up to kDirectPairs pairs of a call that k_scatter_tok takes there are kDirectBlocks blocks at most, few enough for the scatter
+// to do without the column scan (direct_sums).  Hist, scan and scatter of 30011 tokens, k = 8, us: 3.4 + 4.0 + 7.2, without the scan
+// 3.1 + 7.8, and the call, which takes the host about as long, 20.5 -> 18.0.  More pairs want two blocks on every CU.
+inline bool direct_sums(int T, int k, int P) {
+  return P <= 512 && P % 4 == 0 && k >= 2 && k <= 8 && (long long)T * k <= kDirectPairs;
+}
+inline int chunk_tokens(int T, int k, int P) {
   const int cap = kBigPairs / k;  // >= 192 for k <= 64
-  int want = ew::ceil_div(T, 512);
+  int want = ew::ceil_div(T, direct_sums(T, k, P) ? kDirectBlocks : 512);
   if (want < 16) want = 16;
   return want < cap ? want : cap;
 }
@@ -1026,7 +1087,8 @@ int launch_permute(const float* logits, const int32_t* ids_in, const int32_t* ai
     if (plan && !fused_plan) return ew::launch_ffn_plan(counts, offsets, P, S, T, (int)n, *shape, plan, st);
     return EW_OK;
   }
-  const int cht = chunk_tokens(T, k);
+  const int cht = chunk_tokens(T, k, P);
+  const bool direct = direct_sums(T, k, P);
   const int nb = ew::ceil_div(T, cht);
   const int run = (int)ew::align_up((size_t)ew::ceil_div(cht * k, kBigWaves), kWave);
   int32_t* hist = (int32_t*)ws;
@@ -1035,13 +1097,15 @@ int launch_permute(const float* logits, const int32_t* ids_in, const int32_t* ai
   hipLaunchKernelGGL((k_hist<V>), dim3(nb), dim3(hist_threads < kHistThreads ? hist_threads : kHistThreads), 0, st, logits, ids_in, aid, emap, T, E, k, P,
                      map_entries, renorm, cht, ids_out, w_out, slot_ids, hist);
   EW_LAUNCH_CHECK("k_hist");
-  hipLaunchKernelGGL(k_colscan, dim3(ew::ceil_div(P, kScanCols)), dim3(kScanCols * kScanGroups), 0, st, hist, nb, P, counts);
-  EW_LAUNCH_CHECK("k_colscan");
+  if (!direct) {
+    hipLaunchKernelGGL(k_colscan, dim3(ew::ceil_div(P, kScanCols)), dim3(kScanCols * kScanGroups), 0, st, hist, nb, P, counts);
+    EW_LAUNCH_CHECK("k_colscan");
+  }
   const int tpw = (int)ew::align_up((size_t)ew::ceil_div(cht, kBigWaves), kWave);  // tokens per wave of the token-per-lane kernel
   const PlanReq fp = plan ? PlanReq{plan, S, *shape} : PlanReq{nullptr, 0, ew::FfnPlanShape{}};
   const int blocks = nb + (plan ? 1 : 0);
 #define EW_SCATTER_TOK(KK)                                                                                                      \
-  hipLaunchKernelGGL(k_scatter_tok<KK>, dim3(blocks), dim3(kBigThreads), 0, st, slot_ids, counts, hist, T, P, bits, cht, tpw, run, \
+  hipLaunchKernelGGL(k_scatter_tok<KK>, dim3(blocks), dim3(kBigThreads), 0, st, slot_ids, counts, hist, (int)direct, nb, T, P, bits, cht, tpw, run, \
                      offsets, por, rop, fp)
   if (P <= 512 && k >= 2 && k <= 8) {
     switch (k) {
@@ -1184,8 +1248,10 @@ extern "C" void ew_tune_route(int small_pairs) {
 extern "C" size_t moe_reroute_permute_workspace_bytes(int T, int k, int P) {
   if (T <= 0 || k < 1 || k > 64 || P < 1) return 0;
   // sized for the multi-block path even where the single-block one will run: the switch-over is a tuning knob
-  const int nb = ew::ceil_div(T, chunk_tokens(T, k));
-  return ew::align_up((size_t)nb * P * sizeof(int32_t), 256);
+  // and never less for more tokens (a workspace made for a largest batch serves the smaller ones): chunk_tokens gives at most 512
+  // blocks, of 16 tokens at least, until a block's pairs reach their limit
+  const int most = ew::ceil_div(T, 16) < 512 ? ew::ceil_div(T, 16) : 512, full = ew::ceil_div(T, kBigPairs / k);
+  return ew::align_up((size_t)(most > full ? most : full) * P * sizeof(int32_t), 256);
 }
 
 extern "C" int moe_route_topk(const float* logits, int T, int E, int k, int renormalize, int32_t* topk_ids,

@@ -107,6 +107,23 @@ def test_reroute_permute_shapes_with_duplicates(ew, T, k, E, N, P):
     _check_permutation(got, moe.reroute(ids, aid, emap), P)
 
 
+@pytest.mark.parametrize("T,k,E,P", [(600, 4, 32, 100), (2100, 2, 16, 128), (2100, 2, 16, 129), (5000, 3, 64, 256), (700, 7, 64, 257), (900, 5, 64, 512),
+                                     (900, 5, 64, 513), (32768, 8, 64, 200), (32769, 8, 64, 200), (131072, 2, 16, 40), (131073, 2, 16, 40)])
+def test_reroute_permute_two_or_three_launches(ew, T, k, E, P):
+    """Both sides of the rules that choose them (2^18 pairs, 512 slots) and every width of the column sums; ids distinct inside a
+    token as a top-k gives them, and a workspace sized for more tokens serves."""
+    rng = np.random.default_rng(T + k + P)
+    ids = np.argsort(rng.random((T, E)), axis=1)[:, :k].astype(np.int32)
+    aid = rng.integers(0, 3, size=T).astype(np.int32)
+    emap = np.stack([rng.choice(P, E, replace=P < E) for _ in range(3)]).astype(np.int32)
+    d = lambda a: torch.from_numpy(a).cuda()
+    need = [ew.lib().moe_reroute_permute_workspace_bytes(t, k, P) for t in (T, T + 1, T + 17, 2 * T)]
+    assert need == sorted(need)
+    ws = torch.empty(need[1], dtype=torch.uint8, device="cuda")
+    got = ew.moe_reroute_permute(d(ids), d(aid), d(emap), 2, P, ws=ws)
+    _check_permutation(got, moe.reroute(ids, aid, emap), P)
+
+
 def test_reroute_permute_all_to_one_slot_and_skip_inverse(ew):
     T, k, P = 3000, 4, 16
     ids = np.zeros((T, k), np.int32); aid = np.zeros(T, np.int32)
