@@ -277,10 +277,17 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds)
   // units of an XCD then share the rows in its L2 (2000 tokens: 265 -> 257 us).  Half lines (units of 64 rows, halves of units of
   // 128) are read past the L2.
   constexpr bool kHalfLines = MR == 64 || C::SPLIT;
-  int p_k = 0, p_nk = 1, p_rot = 0, p_nld = 0, p_mode = 0;
+  int p_k = 0, p_nk = 1, p_rot = 0, p_n = 0, p_mode = 0;
   [[maybe_unused]] bool p_half = false;
   int p_slot = 0;                                                             // ring slot of the next slab
   bool p_next = false;                                                        // the loading unit is `nxt`
+  // Token waves: instructions per slab.  Rows that the chunk does not have are not loaded, down to a whole instruction: their places
+  // hold what was there, which reaches only sums that are not stored.  (A chunk has five rows on average at 64 tokens, and a
+  // token wave waits for the weights in flight with every instruction.)
+  [[maybe_unused]] auto token_loads = [&](const FfnUnit& u) {
+    const int n = (u.rows - lw * C::RPI + C::NT * C::RPI - 1) / (C::NT * C::RPI);
+    return n > 0 ? n : 0;
+  };
   auto aim = [&](const FfnUnit& u, [[maybe_unused]] int qi) {
     const FfnProd& m = u.mode ? a.m[1] : a.m[0];
     p_k = 0;
@@ -298,7 +305,7 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds)
       p_ws = (uint32_t)((u.mode + 1) * m.K * 2);
     } else if constexpr (ROLE == 1) {
       p_base = reinterpret_cast<const unsigned char*>(m.x);
-      p_nld = (u.rows + 15) >> 4;
+      p_n = token_loads(u);
       // the source rows' byte offsets, as the scheduler left them
       constexpr int N = C::NTI * NTF;
       const uint32_t at = q0 + (uint32_t)(qi * C::QI + 8 + pm) * 4u;
@@ -328,7 +335,7 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds)
       const uint32_t dst = lds0 + C::DW * C::WSLAB + p_slot * C::TSLAB + lw * 1024;
 #pragma unroll
       for (int i = 0; i < C::NTI * NTF; ++i)
-        if (i < C::NTI * p_nld) {
+        if (i < p_n) {
           // second product: rows written by other workgroups of this launch, read at the point of coherence
           if (kHalfLines && p_mode) load_to_lds<16>(src, p_off[i], dst + i * C::NT * 1024);
           else load_to_lds<0>(src, p_off[i], dst + i * C::NT * 1024);
@@ -369,6 +376,7 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds)
     const int nk = m.K >> kShift;
     const bool change = nxt.slot >= 0 && nxt.mode != cur.mode;
     [[maybe_unused]] const int nld = (cur.rows + 15) >> 4;                    // live token fragments
+    [[maybe_unused]] const int t_n = ROLE == 1 ? token_loads(cur) : 0;
     [[maybe_unused]] const bool half = C::SPLIT && cur.how;
     [[maybe_unused]] const int live = half ? C::PN / 2 : C::PN;               // pairs of weight fragments that the unit has
     if constexpr (ROLE == 3) {
@@ -431,7 +439,7 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds)
         // this wave's part of slab kt has landed once only later slabs' loads are outstanding
         const int ahead_next = p_next ? p_k : 0;                              // slabs of nxt in flight
         const int ahead = (p_next ? nk : p_k) - (kt + 1);                     // later slabs of cur
-        wait_vm_upto(ROLE == 0 ? (half ? C::NWI / 2 : C::NWI) * ahead + (C::SPLIT && p_half ? C::NWI / 2 : C::NWI) * ahead_next : C::NTI * (ahead * nld + ahead_next * p_nld));
+        wait_vm_upto(ROLE == 0 ? (half ? C::NWI / 2 : C::NWI) * ahead + (C::SPLIT && p_half ? C::NWI / 2 : C::NWI) * ahead_next : t_n * ahead + p_n * ahead_next);
       }
       __builtin_amdgcn_s_barrier();                                           // everyone's part is there, slab kt-1 has been read
       if constexpr (ROLE == 2) {
