@@ -273,8 +273,10 @@ __global__ __launch_bounds__(256) void k_rmsnorm(const void* __restrict__ x_, in
   }
 }
 
-// Router scores: one wave per token; the token's hidden vector lives in registers (strided over
-// lanes), each expert's gate row is read coalesced and reduced across the wave.
+// Router scores without the matrix cores (fp32 tokens, odd widths): one wave per token and eight experts (blockIdx.y), whose gate
+// rows are read coalesced, so that eight reductions run side by side: in the first three steps a lane gives half of its sums away
+// and keeps the other half.  What bounds it is the chain of loads and shuffles of a wave; one expert after the other, each with
+// six dependent shuffles, 64 tokens of 8 experts of 256 in fp32 took 4.9 us, now 3.6.
 template <bool BF16>
 __global__ __launch_bounds__(256) void k_gate_logits(const void* __restrict__ x_, const float* __restrict__ Wg, int T, int H,
                                                      int E, const int32_t* __restrict__ aid, const float* __restrict__ bias,
@@ -282,28 +284,36 @@ __global__ __launch_bounds__(256) void k_gate_logits(const void* __restrict__ x_
   const int wave = threadIdx.x / 64, lane = threadIdx.x & 63;
   const int t = blockIdx.x * 4 + wave;
   if (t >= T) return;
-  const float* brow = bias ? bias + (size_t)aid[t] * E : nullptr;
-  for (int e = 0; e < E; ++e) {
-    float acc = 0.f;
-    const float* wrow = Wg + (size_t)e * H;
-    if constexpr (BF16) {
-      const uint16_t* x = reinterpret_cast<const uint16_t*>(x_) + (size_t)t * H;
-      for (int h = lane * 4; h < H; h += 256) {
-        const float4 wv = *reinterpret_cast<const float4*>(wrow + h);
-        const ushort4 xv = *reinterpret_cast<const ushort4*>(x + h);
-        acc += bf16_to_f32(xv.x) * wv.x + bf16_to_f32(xv.y) * wv.y + bf16_to_f32(xv.z) * wv.z + bf16_to_f32(xv.w) * wv.w;
+  for (int e0 = 8 * blockIdx.y; e0 < E; e0 += 8 * gridDim.y) {
+    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    for (int h = lane * 4; h < H; h += 256) {
+      float4 xv;
+      if constexpr (BF16) {
+        const ushort4 v = *reinterpret_cast<const ushort4*>(reinterpret_cast<const uint16_t*>(x_) + (size_t)t * H + h);
+        xv = make_float4(bf16_to_f32(v.x), bf16_to_f32(v.y), bf16_to_f32(v.z), bf16_to_f32(v.w));
+      } else {
+        xv = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(x_) + (size_t)t * H + h);
       }
-    } else {
-      const float* x = reinterpret_cast<const float*>(x_) + (size_t)t * H;
-      for (int h = lane * 4; h < H; h += 256) {
-        const float4 wv = *reinterpret_cast<const float4*>(wrow + h);
-        const float4 xv = *reinterpret_cast<const float4*>(x + h);
-        acc += xv.x * wv.x + xv.y * wv.y + xv.z * wv.z + xv.w * wv.w;
+      float4 wv[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) wv[j] = *reinterpret_cast<const float4*>(Wg + (size_t)min(e0 + j, E - 1) * H + h);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) acc[j] += xv.x * wv[j].x + xv.y * wv[j].y + xv.z * wv[j].z + xv.w * wv[j].w;
+    }
+    // lane l ends with expert e0 + (l >> 3): bits 5, 4, 3 of the lane are bits 2, 1, 0 of the expert
+#pragma unroll
+    for (int n = 4; n > 0; n >>= 1) {
+      const bool up = lane & (8 * n);
+#pragma unroll
+      for (int j = 0; j < n; ++j) {
+        const float keep = up ? acc[j + n] : acc[j], give = up ? acc[j] : acc[j + n];
+        acc[j] = keep + __shfl_xor(give, 8 * n, 64);
       }
     }
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
-    if (lane == 0) logits[(size_t)t * E + e] = acc + (brow ? brow[e] : 0.f);
+    for (int o = 4; o > 0; o >>= 1) acc[0] += __shfl_xor(acc[0], o, 64);
+    const int e = e0 + (lane >> 3);
+    if ((lane & 7) == 0 && e < E) logits[(size_t)t * E + e] = acc[0] + (bias ? bias[(size_t)aid[t] * E + e] : 0.f);
   }
 }
 
@@ -506,10 +516,14 @@ extern "C" int moe_gate_logits(const void* x, int dtype, const float* Wg, int T,
       else
         hipLaunchKernelGGL((k_gate_logits_mfma<4, TT, EW>), grid, dim3(256), 0, st, (const uint16_t*)x, Wg, T, H, E, adapter_id, bias, logits);
     });
-  } else if (dtype == EW_BF16)
-    hipLaunchKernelGGL((k_gate_logits<true>), dim3(ew::ceil_div(T, 4)), dim3(256), 0, st, x, Wg, T, H, E, adapter_id, bias, logits);
+    EW_LAUNCH_CHECK("k_gate_logits");
+    return EW_OK;
+  }
+  const dim3 grid(ew::ceil_div(T, 4), ew::ceil_div(E, 8) < 65535 ? ew::ceil_div(E, 8) : 65535);
+  if (dtype == EW_BF16)
+    hipLaunchKernelGGL((k_gate_logits<true>), grid, dim3(256), 0, st, x, Wg, T, H, E, adapter_id, bias, logits);
   else
-    hipLaunchKernelGGL((k_gate_logits<false>), dim3(ew::ceil_div(T, 4)), dim3(256), 0, st, x, Wg, T, H, E, adapter_id, bias, logits);
+    hipLaunchKernelGGL((k_gate_logits<false>), grid, dim3(256), 0, st, x, Wg, T, H, E, adapter_id, bias, logits);
   EW_LAUNCH_CHECK("k_gate_logits");
   return EW_OK;
 }

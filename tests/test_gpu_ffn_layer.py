@@ -474,6 +474,22 @@ def test_gate_logits_tiles(ew, T, E, H):
     np.testing.assert_allclose(got, (ref + bias.double()[aid.long()]).cpu().numpy(), rtol=1e-4, atol=2e-5)
 
 
+@pytest.mark.parametrize("dtype,T,E,H", [("f32", 1, 1, 4), ("f32", 5, 7, 252), ("f32", 64, 8, 256), ("f32", 6, 9, 260), ("f32", 3, 130, 1028),
+                                         ("bf16", 5, 8, 64), ("bf16", 9, 21, 324)])
+def test_gate_logits_without_matrix_cores(ew, dtype, T, E, H):
+    """Experts that do not fill a group of eight, widths that do not fill a wave's loads, with and without the bias.  Plain fp32 sums
+    of at most 1028 products of deviation 0.02: a few dozen roundings of 2^-24 of sums below 4."""
+    g = torch.Generator(device="cuda").manual_seed(T + E + H)
+    x = torch.randn((T, H), generator=g, device="cuda").to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    Wg = torch.randn((E, H), generator=g, device="cuda") * 0.02
+    aid = torch.randint(0, 3, (T,), generator=g, device="cuda", dtype=torch.int32)
+    bias = torch.randn((3, E), generator=g, device="cuda")
+    ref = x.double() @ Wg.double().T
+    np.testing.assert_allclose(ew.moe_gate_logits(x, Wg).cpu().numpy(), ref.cpu().numpy(), rtol=1e-5, atol=5e-6)
+    got = ew.moe_gate_logits(x, Wg, aid, bias).cpu().numpy()
+    np.testing.assert_allclose(got, (ref + bias.double()[aid.long()]).cpu().numpy(), rtol=1e-5, atol=5e-6)
+
+
 def _run_layer_through_pool(ew, cfg, inp, logits, flags=0, aid=None):
     from paper_2508_17624_amd.layer import MoELayer, load_layer
     dt = torch.bfloat16 if cfg.dtype == "bf16" else torch.float32
