@@ -21,7 +21,6 @@ constexpr int kQI = 8 + 256;               // ints of a queue entry
 constexpr int kTOff = kWRing * kHalf, kQOff = kTOff + kTRing * kTSlab, kLds = kQOff + 4 * kQI * 4;
 static_assert(kLds <= 160 * 1024, "LDS budget of a CU");
 constexpr int kAlone = 1;                  // FfnUnit::how: no other chunk reads this unit's weights
-constexpr int kSwap = 2;                   // the unit walks over K by pairs of slabs, the second of a pair first
 constexpr int kThreads = 768;              // waves 0-1 load weights, 2 token rows, 3 schedules, 4-11 multiply
 
 __device__ __forceinline__ int swz(int r) { return ((r >> 1) ^ ((r & 1) << 2)) & 7; }
@@ -86,13 +85,10 @@ __device__ __forceinline__ void sched_rows(const FfnArgs& a, Sched& s) {
   const int i = s.w - base * G, j = i % nch;
   s.slot = __builtin_amdgcn_readfirstlane(__shfl(s.ent[0], e, 64));
   s.g = i / nch;
-  // Half of the units that share weights (chunks of one feature group) and half of those that share token rows (feature groups of
-  // one chunk) walk over each pair of slabs in the opposite order, so that what one half fetches is in the XCD's L2 when the other
-  // half asks for it: units in step all wait for the same line to come from memory.  (j: entries have an even number of chunks
-  // but for a slot's last one, so its parity is that of the chunk's place in the slot and nothing depends on the plan.)  The
-  // loads alone, us: 819 -> 726 base-only, 1121 -> 1037 with 20 adapters; whole passes 1089 -> 1082, 1390 -> 1381.  Four
-  // orders over four slabs: the loads alone 706 and 1040, whole passes no better.
-  s.how = (nch == 1 ? kAlone : 0) | ((j + s.g) & 1 ? kSwap : 0);
+  // Every unit walks over K from slab 0 on, so that a row's result does not depend on the chunk it falls into, that is on what else
+  // is in the batch.  Half of the units walking over each pair of slabs in the opposite order, by the parity of chunk and feature
+  // group, would shorten the loads alone (us: 819 -> 726 base-only, 1121 -> 1037 with 20 adapters) and the whole pass by 0.6 %.
+  s.how = nch == 1 ? kAlone : 0;
   s.rows = min(bts, c - j * bts);
   s.off = __shfl(s.ent[5], e, 64) + j * bts;
   s.chunk = ((s.home + s.t) & 7) * a.list_chunks + base + j;
@@ -272,7 +268,6 @@ __device__ __forceinline__ void big_body(const FfnArgs& a, unsigned char* s_lds)
   [[maybe_unused]] const unsigned char* p_base = nullptr;
   [[maybe_unused]] uint32_t p_w = 0, p_up = 0, p_i = 0, p_wr = 0;
   [[maybe_unused]] bool p_alone = false;                                      // no other chunk reads this unit's weights
-  [[maybe_unused]] int p_swap = 0;                                            // 1: slab kt ^ 1 in place of kt
   [[maybe_unused]] bool p_part = false;                                       // the unit's second half of weight rows does not exist
   [[maybe_unused]] uint32_t p_off[ROLE == 1 ? 32 : 1] = {};
   int p_h = 0, p_n = 1, p_nfl = 0, p_slot = 0;                                // next piece of the loading unit, their number
@@ -280,7 +275,6 @@ __device__ __forceinline__ void big_body(const FfnArgs& a, unsigned char* s_lds)
   auto aim = [&](const FfnUnit& u, [[maybe_unused]] int qi) {
     const FfnProd& m = u.mode ? a.m[1] : a.m[0];
     p_h = 0;
-    p_swap = u.how & kSwap ? 1 : 0;                                           // (K has an even number of slabs)
     if constexpr (ROLE == 0) {
       p_n = m.K >> 5;
       const uint32_t k2 = (uint32_t)(m.K * 2);
@@ -306,7 +300,7 @@ __device__ __forceinline__ void big_body(const FfnArgs& a, unsigned char* s_lds)
   auto issue = [&]() {
     if constexpr (ROLE == 0) {
       const int half = p_h & 1;
-      const unsigned char* src = p_base + (size_t)((p_h >> 1) ^ p_swap) * 128 + (half && !p_part ? 2 * p_wr : 0u);
+      const unsigned char* src = p_base + (size_t)(p_h >> 1) * 128 + (half && !p_part ? 2 * p_wr : 0u);
       const uint32_t dst = lds0 + p_slot * kHalf + lw * 1024;
       auto load = [&](auto aux) {
 #pragma unroll
@@ -319,7 +313,7 @@ __device__ __forceinline__ void big_body(const FfnArgs& a, unsigned char* s_lds)
       else load(std::integral_constant<int, 16>{});
       p_slot = p_slot + 1 == kWRing ? 0 : p_slot + 1;
     } else if constexpr (ROLE == 1) {
-      const unsigned char* src = p_base + (size_t)(p_h ^ p_swap) * 128;
+      const unsigned char* src = p_base + (size_t)p_h * 128;
       const uint32_t dst = lds0 + kTOff + p_slot * kTSlab;
 #pragma unroll
       for (int f = 0; f < 8; ++f)

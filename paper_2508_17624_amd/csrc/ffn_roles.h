@@ -44,7 +44,7 @@ __device__ __forceinline__ float silu_f32(float g) { return g * __builtin_amdgcn
 struct FfnUnit {
   int slot, off, rows, g, mode, chunk;  // slot < 0: no unit left
   int ready;                            // 1: nothing to wait for; kExpired: the wait was given up
-  int how;                              // k_ffn_big: kAlone, kSwap; k_ffn_dec: 0 a whole unit, 1 / 2 the first / second half of one
+  int how;                              // k_ffn_big: kAlone; k_ffn_dec: 0 a whole unit, 1 / 2 the first / second half of one
 };
 
 // LDS-direct load: 16 bytes per lane from base + off (base: wave-uniform) to lds + 16 * lane.  AUX: 0 plain, 2 nt, 16 sc1.

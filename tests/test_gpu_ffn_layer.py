@@ -741,6 +741,39 @@ def test_grouped_ffn_decode_kernel_edges(ew, T, k, P, S, H, I):
         assert rel_l2(blk, ref) <= FFN_REL_L2 and max_abs(blk, ref) <= FFN_MAX_ABS, f"shared expert {s}"
 
 
+@pytest.mark.parametrize("frags", [4, 8], ids=["few-rows", "many-rows"])
+def test_grouped_ffn_rows_do_not_depend_on_their_place(ew, frags):
+    """A token's rows have the same bits wherever it stands in the batch: slots of one to three chunks, crowded and thin ones, and a
+    shared expert, whose rows are copies of five tokens in random order.  The same token alone on its slots gives these bits too."""
+    T, P, S, H, I = 1100, 8, 1, 640, 384
+    rng = np.random.default_rng(frags)
+    flat = np.repeat(np.arange(P), [600, 257, 130, 70, 33, 9, 1, 0]).astype(np.int32)[rng.permutation(T)]
+    who = rng.integers(0, 5, size=T)
+    dev = lambda a: torch.from_numpy(a).cuda()
+    bf = lambda *shape, scale=1.0: (torch.from_numpy(rng.standard_normal(shape, dtype=np.float32)) * scale).cuda().bfloat16()
+    x5, w13, w2, s13, s2 = bf(5, H), bf(P, 2 * I, H, scale=0.02), bf(P, H, I, scale=0.02), bf(S, 2 * I, H, scale=0.02), bf(S, H, I, scale=0.02)
+
+    def run(who, flat):
+        por = np.argsort(flat, kind="stable").astype(np.int32)
+        counts = np.bincount(flat, minlength=P).astype(np.int32)
+        offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+        ew.binding.tune_ffn(path=3, ws_frags=frags)
+        try:
+            y = ew.moe_grouped_ffn_with_shared(x5[dev(who)].contiguous(), 1, I, P, dev(counts), dev(offsets), dev(por), w13, w2, s13, s2)
+        finally:
+            ew.binding.tune_ffn()
+        n = len(flat)
+        return y[:n].view(torch.int16).cpu().numpy(), y[n:].view(torch.int16).cpu().numpy(), flat[por], who[por]
+
+    y, sh, slot, tok = run(who, flat)
+    y1, sh1, slot1, tok1 = run(np.arange(5 * P) % 5, (np.arange(5 * P) // 5).astype(np.int32))    # every token once on every slot
+    for r in range(5 * P):
+        rows = y[(slot == slot1[r]) & (tok == tok1[r])]
+        assert (rows == y1[r]).all(), f"slot {slot1[r]}, token {tok1[r]}: {int((rows != y1[r]).any(axis=1).sum())} of {len(rows)} rows differ"
+    for t in range(5):
+        assert (sh[who == t] == sh1[t]).all(), f"shared expert, token {t}"
+
+
 @pytest.mark.parametrize("T,k,P,S,H,I,used", [(768, 2, 64, 1, 384, 256, 64), (768, 2, 64, 1, 384, 256, 6), (1100, 4, 96, 0, 256, 128, 96),
                                               (1100, 4, 96, 0, 256, 128, 4), (520, 2, 2046, 2, 128, 128, 5)],
                          ids=["spread", "few-used", "spread-no-shared", "four-used", "largest-pool"])
