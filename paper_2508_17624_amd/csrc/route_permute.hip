@@ -190,7 +190,7 @@ __device__ __forceinline__ void wave_topk(const float* __restrict__ row, int E, 
     if ((sel[v] >> lane) & 1ull) emit(rank[v], lane + v * kWave, ex[v] / denom * scale);
 }
 
-// All 16 lanes of a row: the row's maximum / minimum / sum (the sum in one fixed order, the same in every lane).
+// All 16 lanes of a row: the row's maximum / minimum.
 template <typename F>
 __device__ __forceinline__ uint32_t row_reduce(uint32_t v, F f) {
 #define EW_ROR(x, n) (uint32_t) __builtin_amdgcn_update_dpp(0, (int)(x), 0x120 + (n), 0xf, 0xf, false)
@@ -202,8 +202,23 @@ __device__ __forceinline__ uint32_t row_reduce(uint32_t v, F f) {
 }
 __device__ __forceinline__ uint32_t row_max(uint32_t v) { return row_reduce(v, [](uint32_t a, uint32_t b) { return a > b ? a : b; }); }
 __device__ __forceinline__ uint32_t row_min(uint32_t v) { return row_reduce(v, [](uint32_t a, uint32_t b) { return a < b ? a : b; }); }
-__device__ __forceinline__ float row_sum_f32(float v) {
-  return __uint_as_float(row_reduce(__float_as_uint(v), [](uint32_t a, uint32_t b) { return __float_as_uint(__uint_as_float(a) + __uint_as_float(b)); }));
+// All 16 lanes of a row: wave_sum_f32 of 64 values that the row holds R per lane (value r of lane l for wave lane l + 16 r, zero from
+// R on), bit for bit: that sum pairs neighbours, then pairs of pairs, inside each row, and the row totals as (3 + 2) + (1 + 0).
+template <int R>
+__device__ __forceinline__ float row_sum_f32(const float (&part)[R]) {
+#define EW_DPP_ADD(ctrl) v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, false))
+  float row[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    float v = part[r];
+    EW_DPP_ADD(0xB1);   // quad_perm 1,0,3,2
+    EW_DPP_ADD(0x4E);   // quad_perm 2,3,0,1
+    EW_DPP_ADD(0x141);  // row_half_mirror
+    EW_DPP_ADD(0x140);  // row_mirror
+    row[r] = v;
+  }
+#undef EW_DPP_ADD
+  return (row[3] + row[2]) + (row[1] + row[0]);
 }
 
 // The value a key stands for (+0.0 for either zero).
@@ -248,14 +263,25 @@ __device__ __forceinline__ void group_topk(const float* __restrict__ row, const 
       my_at = first;
     }
   }
-  // softmax over all E logits: max = the first winner
+  // softmax over all E logits: max = the first winner.  Both sums run in the order of wave_topk, so that a weight does not depend
+  // on which of the two selected it (one ulp of it flips a bf16 rounding of the layer's output, and the layers behind carry that on).
   const float vmax = key_value(top);
-  float part = 0.f;
+  constexpr int R = V < 4 ? V : 4;
+  float part[R] = {}, chosen[R] = {};
 #pragma unroll
-  for (int v = 0; v < V; ++v) part += l + 16 * v < E ? expf(val[v] - vmax) : 0.f;
+  for (int v = 0; v < V; ++v) {
+    const float ex = l + 16 * v < E ? expf(val[v] - vmax) : 0.f;
+    part[v % R] += ex;
+    chosen[v % R] += key[v] == 0u ? ex : 0.f;
+  }
   const float denom = row_sum_f32(part);
   const float p = l < k ? expf(key_value(my_key) - vmax) / denom : 0.f;
-  const float scale = renorm ? 1.f / row_sum_f32(p) : 1.f;
+  float scale = 1.f;
+  if (renorm) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) chosen[r] /= denom;
+    scale = 1.f / row_sum_f32(chosen);
+  }
   if (l < k) emit(l, (int)(my_at >> 16), (int)(my_at & 0xFFFFu), p * scale);
 }
 

@@ -78,6 +78,21 @@ def test_route_topk_selection_edges(ew, T, E, k):
         _check_permutation(fused[2:], emap[0][rids], E)
 
 
+@pytest.mark.parametrize("E,k", [(1, 1), (8, 2), (16, 16), (17, 3), (48, 8), (64, 6), (65, 16), (96, 4), (128, 8), (200, 5), (256, 16)])
+def test_route_topk_weights_do_not_depend_on_the_selection(ew, E, k):
+    """Sixteen lanes per token and one wave per token give a weight the same bits: behind the E experts others that weigh exactly
+    zero, up to the first number of experts that takes the wave."""
+    rng = np.random.default_rng(E + k)
+    logits = torch.from_numpy((rng.standard_normal((501, E)) * 1.5).astype(np.float32)).cuda()
+    padded = torch.full((501, 257), -1e30, device="cuda")
+    padded[:, :E] = logits
+    for renorm in (False, True):
+        ids, w = ew.moe_route_topk(logits, k, renorm)
+        ids_w, w_w = ew.moe_route_topk(padded, k, renorm)
+        assert torch.equal(ids, ids_w)
+        assert torch.equal(w, w_w), f"{int((w != w_w).sum())} of {w.numel()} weights differ, renorm {renorm}"
+
+
 @pytest.mark.parametrize("T", [1, 64, 256, 341, 342, 682, 683, 1366, 2048, 2049, 5000])
 def test_reroute_permute_configs(ew, T):
     """C2/C3-shaped: k=6, E=64, N=20, P=384.  T=341 is the last size of the single-block permutation
