@@ -297,10 +297,11 @@ __device__ __forceinline__ void wave_select(const float* __restrict__ logits, co
     const int32_t* maprow = REROUTE ? emap + (size_t)aid[first] * E : nullptr;
     wave_topk<-V>(logits + (size_t)first * E, E, k, renorm, [&](int rank, int e, float wt) { emit(first, rank, e, REROUTE ? maprow[e] : 0, wt); });
   } else {
-    const int t = first + (int)((threadIdx.x & (kWave - 1)) >> 4), row = min(t, end - 1);
+    const unsigned mine = (unsigned)first + ((threadIdx.x & (kWave - 1)) >> 4);  // (may lie past 2^31)
+    const int t = (int)mine, row = (int)min(mine, (unsigned)end - 1);
     group_topk<V, REROUTE>(logits + (size_t)row * E, REROUTE ? emap + (size_t)aid[row] * E : nullptr, E, k, renorm,
                            [&](int rank, int e, int slot, float wt) {
-                             if (t < end) emit(t, rank, e, slot, wt);
+                             if (mine < (unsigned)end) emit(t, rank, e, slot, wt);
                            });
   }
 }
@@ -368,19 +369,20 @@ __device__ __forceinline__ void wave0_exscan(int32_t* v, int P) {
 // ------------------------------------------------------------------------------------------
 // Router top-k, four waves per block.  REROUTE: with the rerouting fused in (Sec. 4.3: the lookup rides on the kernel that
 // produces the ids), over as many blocks as the batch needs: the first half of the decode-sized path, whose second half (k_small
-// with slots given) is a single block.
+// with slots given) is a single block.  The grid strides over the tokens: a launch takes less than 2^32 threads in a dimension,
+// which one wave per token would pass at 2^26 tokens.
+constexpr int kRouteBlocks = 1 << 20;
 template <int V, bool REROUTE>
 __global__ __launch_bounds__(256) void k_route(const float* __restrict__ logits, const int32_t* __restrict__ aid,
                                                const int32_t* __restrict__ emap, int T, int E, int k, int renorm,
                                                int32_t* __restrict__ ids, float* __restrict__ w, int32_t* __restrict__ slot_ids) {
-  const int first = (blockIdx.x * 4 + threadIdx.x / kWave) * kTokensPerWave<V>;
-  if (first >= T) return;
-  wave_select<V, REROUTE>(logits, aid, emap, first, T, E, k, renorm, [&](int t, int rank, int e, int slot, float wt) {
-    const size_t p = (size_t)t * k + rank;
-    ids[p] = e;
-    w[p] = wt;
-    if constexpr (REROUTE) slot_ids[p] = slot;
-  });
+  for (unsigned first = (blockIdx.x * 4 + threadIdx.x / kWave) * kTokensPerWave<V>; first < (unsigned)T; first += gridDim.x * 4 * kTokensPerWave<V>)
+    wave_select<V, REROUTE>(logits, aid, emap, (int)first, T, E, k, renorm, [&](int t, int rank, int e, int slot, float wt) {
+      const size_t p = (size_t)t * k + rank;
+      ids[p] = e;
+      w[p] = wt;
+      if constexpr (REROUTE) slot_ids[p] = slot;
+    });
 }
 
 // Plan request of a permutation call: the grouped FFN's work plan is written too (plan == nullptr: not asked for).
@@ -1293,7 +1295,8 @@ extern "C" int moe_route_topk(const float* logits, int T, int E, int k, int reno
   hipStream_t st = (hipStream_t)stream;
   with_selection(E, k, [&](auto tag) {
     constexpr int V = decltype(tag)::value;
-    hipLaunchKernelGGL((k_route<V, false>), dim3(ew::ceil_div(T, 4 * kTokensPerWave<V>)), dim3(256), 0, st, logits, (const int32_t*)nullptr,
+    const int full = (T - 1) / (4 * kTokensPerWave<V>);  // (T up to 2^31 - 1: no rounding up before the division)
+    hipLaunchKernelGGL((k_route<V, false>), dim3(full < kRouteBlocks ? full + 1 : kRouteBlocks), dim3(256), 0, st, logits, (const int32_t*)nullptr,
                        (const int32_t*)nullptr, T, E, k, renormalize, topk_ids, topk_w, (int32_t*)nullptr);
     return EW_OK;
   });

@@ -93,6 +93,26 @@ def test_route_topk_weights_do_not_depend_on_the_selection(ew, E, k):
         assert torch.equal(w, w_w), f"{int((w != w_w).sum())} of {w.numel()} weights differ, renorm {renorm}"
 
 
+@pytest.mark.parametrize("T,E,k", [((1 << 24) + 5, 2, 2), ((1 << 28) + 37, 1, 1), ((1 << 26) + 3, 17, 17)], ids=["second-stride", "sixteen-lanes", "wave"])
+def test_route_topk_more_tokens_than_one_launch_has_threads_for(ew, T, E, k):
+    """A few tokens more than fit a launch of less than 2^32 threads at sixteen lanes and at a wave per token, and more than the grid
+    holds at once.  Logits 0 .. E-1 in an order that turns with the token: every choice of every token is known."""
+    if torch.cuda.mem_get_info()[0] < 24 << 30:
+        pytest.skip("needs 24 GB")
+    B, step = ew.binding, 1 << 22
+    e = torch.arange(E, device="cuda", dtype=torch.int32)
+    turn = lambda t0: torch.arange(t0, min(T, t0 + step), device="cuda", dtype=torch.int32)[:, None] % E
+    logits = torch.empty((T, E), device="cuda")
+    for t0 in range(0, T, step):
+        logits[t0:t0 + step] = ((e + turn(t0)) % E).float()
+    ids, w = torch.full((T, k), -1, dtype=torch.int32, device="cuda"), torch.full((T, k), -1.0, device="cuda")
+    B._check(B.lib().moe_route_topk(logits.data_ptr(), T, E, k, 0, ids.data_ptr(), w.data_ptr(), B._stream()))
+    want_w = torch.softmax(torch.arange(E, dtype=torch.float64), 0).flip(0)[:k].float().cuda()
+    for t0 in range(0, T, step):
+        assert torch.equal(ids[t0:t0 + step], (E - 1 - e[:k] - turn(t0)) % E), f"ids from token {t0}"
+        torch.testing.assert_close(w[t0:t0 + step], want_w.expand(min(step, T - t0), k), rtol=2e-5, atol=1e-9)
+
+
 @pytest.mark.parametrize("T", [1, 64, 256, 341, 342, 682, 683, 1366, 2048, 2049, 5000])
 def test_reroute_permute_configs(ew, T):
     """C2/C3-shaped: k=6, E=64, N=20, P=384.  T=341 is the last size of the single-block permutation
