@@ -337,14 +337,15 @@ __device__ __forceinline__ void block_exscan2(int a, int b, int& ea, int& eb, in
   eb = pb + ib - b;
 }
 
-// Exclusive scan of one value per thread over the block (thread order).  s_w: an int per wave.  Contains one barrier.
+// Exclusive scan of one value per thread over the block (thread order).  s_w: an int per wave.  Contains one barrier.  The wave totals
+// are read by the lanes at once and scanned there: a loop over them is a chain of LDS round trips, 0.4 to 0.6 us with 16 waves.
 __device__ __forceinline__ int block_exscan(int a, int32_t* s_w) {
   const int wave = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1), nwaves = blockDim.x / kWave;
   const int ia = wave_incl_scan_i32(a);
   if (lane == kWave - 1) s_w[wave] = ia;
   __syncthreads();
-  int before = 0;
-  for (int w = 0; w < nwaves; ++w) before += w < wave ? s_w[w] : 0;
+  const int totals = wave_incl_scan_i32(lane < nwaves ? s_w[lane] : 0);
+  const int before = wave ? __builtin_amdgcn_readlane(totals, __builtin_amdgcn_readfirstlane(wave) - 1) : 0;
   return before + ia - a;
 }
 
@@ -417,11 +418,13 @@ __device__ __forceinline__ void plan_block(const int32_t* counts, int T, int n, 
 // (wave_select) runs here too.  What bounds it is the chain of dependent steps, each a memory round trip or a barrier; so only the
 // waves that a batch gives 64 pairs rank, the scans run on DPP instead of through LDS, and one scan over all threads makes the
 // offsets.  Selection to plan, us, as two launches before / now: 1 token 8.9 / 5.9, 64 tokens 10.0 / 8.0.
-// run = pairs per ranking wave, a multiple of 64.
+// run = pairs per ranking wave, a multiple of 64; nrank = ranking waves, ceil(T k / run); per = slots per thread of the scan (both
+// from the host: an integer division is a few dozen dependent instructions).  Ids given, us, with the waves' totals summed in a loop
+// and both divisions here / now: 256 tokens of k = 2 on 128 slots 4.4 / 3.6, 1024 6.6 / 5.7; 341 of k = 6 on 384 7.1 / 6.3.
 template <int V>
 __global__ __launch_bounds__(1024) void k_small(const float* __restrict__ logits, const int32_t* __restrict__ ids_in,
                                                 const int32_t* __restrict__ aid, const int32_t* __restrict__ emap,
-                                                int T, int E, int k, int P, int renorm, int bits, int run,
+                                                int T, int E, int k, int P, int renorm, int bits, int run, int nrank, int per,
                                                 int32_t* __restrict__ ids_out, float* __restrict__ w_out,
                                                 int32_t* __restrict__ slot_ids, int32_t* __restrict__ counts,
                                                 int32_t* __restrict__ offsets, int32_t* __restrict__ pair_of_row,
@@ -443,7 +446,7 @@ __global__ __launch_bounds__(1024) void k_small(const float* __restrict__ logits
   int32_t (&s_off)[kMaxP + 1] = lds.perm.off;
   const int tid = threadIdx.x, nthreads = blockDim.x;
   const int wave = tid / kWave, lane = tid & (kWave - 1), nwaves = nthreads / kWave;
-  const int n = T * k, nrank = (n + run - 1) / run;  // nrank <= nwaves
+  const int n = T * k;
 
   for (int i = tid; i < nrank * P; i += nthreads) s_cnt[i] = 0;
 
@@ -494,8 +497,8 @@ __global__ __launch_bounds__(1024) void k_small(const float* __restrict__ logits
   }
   __syncthreads();
 
-  // C: per slot, exclusive scan over the ranking waves (in place); then over the slots, each thread taking `per` in a row
-  const int per = (P + nthreads - 1) / nthreads, s0 = tid * per;
+  // C: per slot, exclusive scan over the ranking waves (in place); then over the slots, each thread taking `per` of them in a row
+  const int s0 = tid * per;
   int mine = 0;
   for (int s = s0; s < min(P, s0 + per); ++s) {
     int tot = 0;
@@ -1097,13 +1100,14 @@ int launch_permute(const float* logits, const int32_t* ids_in, const int32_t* ai
     if (nwaves > most) nwaves = most;
     int run = ((int)n + nwaves - 1) / nwaves;
     run = (run + kWave - 1) / kWave * kWave;
+    const int nrank = ew::ceil_div((int)n, run), per = ew::ceil_div(P, nwaves * kWave);  // nrank <= nwaves
     // the FFN plan rides on the single-block kernel when that has the 512 threads the plan needs
     PlanReq fp{nullptr, 0, ew::FfnPlanShape{}};
     const bool fused_plan = plan && nwaves * kWave >= 512;
     if (fused_plan) fp = PlanReq{plan, S, *shape};
     if (V > 0 && T <= kSelectTokens) {
       hipLaunchKernelGGL(k_small<(V > 0 ? V : 0)>, dim3(1), dim3(nwaves * kWave), 0, st, logits, ids_in, aid, emap, T, E, k, P, renorm, bits,
-                         run, ids_out, w_out, slot_ids, counts, offsets, por, rop, fp);
+                         run, nrank, per, ids_out, w_out, slot_ids, counts, offsets, por, rop, fp);
     } else {
       if constexpr (V != 0) {
         hipLaunchKernelGGL((k_route<V, true>), dim3(ew::ceil_div(T, 4 * kTokensPerWave<V>)), dim3(256), 0, st, logits, aid, emap, T, E, k,
@@ -1111,7 +1115,7 @@ int launch_permute(const float* logits, const int32_t* ids_in, const int32_t* ai
         EW_LAUNCH_CHECK("k_route");
       }
       hipLaunchKernelGGL(k_small<0>, dim3(1), dim3(nwaves * kWave), 0, st, logits, V != 0 ? (const int32_t*)slot_ids : ids_in, aid,
-                         V != 0 ? (const int32_t*)nullptr : emap, T, E, k, P, renorm, bits, run, ids_out, w_out, slot_ids, counts,
+                         V != 0 ? (const int32_t*)nullptr : emap, T, E, k, P, renorm, bits, run, nrank, per, ids_out, w_out, slot_ids, counts,
                          offsets, por, rop, fp);
     }
     EW_LAUNCH_CHECK("k_small");

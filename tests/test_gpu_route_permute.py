@@ -159,6 +159,20 @@ def test_reroute_permute_two_or_three_launches(ew, T, k, E, P):
     _check_permutation(got, moe.reroute(ids, aid, emap), P)
 
 
+@pytest.mark.parametrize("T,k,P", [(1, 1, 1), (1, 1, 2048), (9, 7, 63), (32, 2, 1025), (33, 31, 769), (64, 1, 64), (65, 16, 1024), (128, 16, 512),
+                                   (341, 6, 384), (683, 3, 2048), (2048, 1, 2047)])
+def test_reroute_permute_single_block_scan(ew, T, k, P):
+    """One block: 6 to 16 waves whose totals the scan adds up, one to six slots per thread, one ranking wave up to all of them."""
+    rng = np.random.default_rng(T + k + P)
+    E = max(k, 8)
+    ids = np.argsort(rng.random((T, E)), axis=1)[:, :k].astype(np.int32)
+    aid = rng.integers(0, 3, size=T).astype(np.int32)
+    emap = rng.integers(0, P, size=(3, E)).astype(np.int32)
+    emap[2, 0] = P - 1
+    d = lambda a: torch.from_numpy(a).cuda()
+    _check_permutation(ew.moe_reroute_permute(d(ids), d(aid), d(emap), 2, P), moe.reroute(ids, aid, emap), P)
+
+
 def test_reroute_permute_all_to_one_slot_and_skip_inverse(ew):
     T, k, P = 3000, 4, 16
     ids = np.zeros((T, k), np.int32); aid = np.zeros(T, np.int32)
