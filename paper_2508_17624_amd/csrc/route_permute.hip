@@ -14,7 +14,7 @@
 //    with a ballot-built peer mask (rank = popcount of lower peers) and a wave-private LDS
 //    counter; runs are stitched by exclusive scans over waves (LDS) and over blocks (global).
 //  * small batches (decode): ONE single-block kernel does top-k, lookup, histogram, scan and scatter
-//    without leaving the CU (above 64 tokens a multi-block top-k + lookup kernel runs first and that
+//    without leaving the CU (above 64 tokens, and below for many experts, a multi-block top-k + lookup kernel runs first and that
 //    block receives slots).  Larger ones use two kernels, per-block histogram (fused with top-k
 //    and lookup) and ranked scatter; the largest have a column scan between them.
 //  * the grouped FFN's work plan, if asked for, never is a launch of its own: the single block goes
@@ -31,9 +31,7 @@ constexpr int kMaxP = 2048;          // slots supported by the permutation kerne
 constexpr int kMaxE = 1024;          // experts supported by the top-k kernels
 constexpr int kSmallPairs = 4096;    // single-block path: capacity of its LDS arrays (T*k at most this)
 int g_small_pairs = 2048;            // single-block path is used up to this many pairs (tunable, <= kSmallPairs)
-// Single-block path: the selection joins it up to this many tokens, one round of its 16 waves.  A stack of layers at 256 tokens,
-// us, with the selection in a launch of its own / joined (four rounds): 2033 / 2058.
-constexpr int kSelectTokens = 64;
+constexpr int kSelectTokens = 64;    // single-block path: the selection can join it up to this many tokens (joins_selection)
 constexpr int kSmallCnt = 12288;     // single-block path: waves * P at most this (uint16 counters)
 constexpr int kBigThreads = 512;     // multi-block path: threads per block
 constexpr int kBigWaves = kBigThreads / kWave;
@@ -1084,6 +1082,20 @@ int with_selection(int E, int k, F f) {
   return f(std::integral_constant<int, -16>{});
 }
 
+// Whether the single block of nwaves waves makes the selection too, sixteen lanes of V logits each per token, or a launch before it
+// does on many CUs.  Joined it saves that launch, about 1.4 us, but four waves share a SIMD whose time V k bounds; beyond two waves on
+// a SIMD or one round of the waves it has to be cheap.  Selection to plan, us, joined / own launch: 32 tokens, V k = 256 9.5 / 10.4;
+// 48 tokens, V k = 96 (128 experts) 9.8 / 10.0, 128 11.0 / 10.7, of 256 experts 64 9.5 / 9.1; 64 tokens, V k = 32 8.1 / 8.1, 48 8.9 /
+// 8.6, 128 (256 experts) 13.0 / 10.9; two rounds, V k = 24 12.5 / 12.5, 64 12.5 / 12.0; three rounds, V k = 2 9.5 / 10.0, 24 13.6 / 13.0.
+// (256 tokens, four rounds of V k = 24: a stack of layers 2058 / 2033.)
+inline bool joins_selection(int V, int T, int k, int nwaves) {
+  if (V <= 0 || T > kSelectTokens) return false;
+  const int rounds = ew::ceil_div(T, 4 * nwaves), cost = V * k;
+  if (cost <= 8) return true;
+  if (rounds > 1) return rounds == 2 && V < 16 && cost <= 32;
+  return T <= 32 || (V < 16 && cost <= (T <= 48 ? 96 : 32));
+}
+
 template <int V>
 int launch_permute(const float* logits, const int32_t* ids_in, const int32_t* aid, const int32_t* emap, int T, int E,
                    int k, int N, int P, int renorm, int32_t* ids_out, float* w_out, int32_t* slot_ids, int32_t* counts,
@@ -1105,7 +1117,7 @@ int launch_permute(const float* logits, const int32_t* ids_in, const int32_t* ai
     PlanReq fp{nullptr, 0, ew::FfnPlanShape{}};
     const bool fused_plan = plan && nwaves * kWave >= 512;
     if (fused_plan) fp = PlanReq{plan, S, *shape};
-    if (V > 0 && T <= kSelectTokens) {
+    if (joins_selection(V, T, k, nwaves)) {
       hipLaunchKernelGGL(k_small<(V > 0 ? V : 0)>, dim3(1), dim3(nwaves * kWave), 0, st, logits, ids_in, aid, emap, T, E, k, P, renorm, bits,
                          run, nrank, per, ids_out, w_out, slot_ids, counts, offsets, por, rop, fp);
     } else {

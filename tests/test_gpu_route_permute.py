@@ -142,6 +142,24 @@ def test_reroute_permute_shapes_with_duplicates(ew, T, k, E, N, P):
     _check_permutation(got, moe.reroute(ids, aid, emap), P)
 
 
+@pytest.mark.parametrize("T,E,k,P", [(32, 256, 16, 320), (33, 256, 4, 320), (33, 128, 12, 200), (48, 128, 12, 200), (48, 128, 13, 200), (49, 128, 4, 200),
+                                     (49, 128, 5, 200), (64, 64, 8, 384), (64, 64, 9, 384), (65, 64, 6, 384), (28, 64, 8, 1600), (29, 64, 8, 1600),
+                                     (29, 64, 9, 1600), (64, 16, 8, 2048), (64, 16, 9, 2048), (48, 64, 8, 2048), (49, 64, 8, 2048)])
+def test_route_reroute_permute_joined_or_not(ew, T, E, k, P):
+    """Both sides of every line between the selection inside the single block, in one to three rounds of its waves, and in a launch of
+    its own."""
+    rng = np.random.default_rng(T + E + k + P)
+    logits = rng.standard_normal((T, E)).astype(np.float32)
+    aid = rng.integers(0, 3, size=T).astype(np.int32)
+    emap = np.stack([rng.choice(P, E, replace=False) for _ in range(3)]).astype(np.int32)
+    d = lambda a: torch.from_numpy(a).cuda()
+    got = ew.moe_route_reroute_permute(d(logits), d(aid), d(emap), k, 2, P)
+    rids, rw = moe.route_topk(logits, k, False)
+    np.testing.assert_array_equal(got[0].cpu().numpy(), rids)
+    np.testing.assert_allclose(got[1].cpu().numpy(), rw, rtol=2e-5, atol=1e-9)
+    _check_permutation(got[2:], moe.reroute(rids, aid, emap), P)
+
+
 @pytest.mark.parametrize("T,k,E,P", [(600, 4, 32, 100), (2100, 2, 16, 128), (2100, 2, 16, 129), (5000, 3, 64, 256), (700, 7, 64, 257), (900, 5, 64, 512),
                                      (900, 5, 64, 513), (32768, 8, 64, 200), (32769, 8, 64, 200), (131072, 2, 16, 40), (131073, 2, 16, 40)])
 def test_reroute_permute_two_or_three_launches(ew, T, k, E, P):
