@@ -369,13 +369,14 @@ __device__ __forceinline__ void wave0_exscan(int32_t* v, int P) {
 // Router top-k, four waves per block.  REROUTE: with the rerouting fused in (Sec. 4.3: the lookup rides on the kernel that
 // produces the ids), over as many blocks as the batch needs: the first half of the decode-sized path, whose second half (k_small
 // with slots given) is a single block.  The grid strides over the tokens: a launch takes less than 2^32 threads in a dimension,
-// which one wave per token would pass at 2^26 tokens.
+// which one wave per token would pass at 2^26 tokens.  The stride is that of the largest grid; a smaller one ends after its first step.
+// (gridDim lies behind the 64 bytes of arguments, in a line of its own that every wave would wait for: 0.2 to 0.4 us of 4 to 7.)
 constexpr int kRouteBlocks = 1 << 20;
 template <int V, bool REROUTE>
 __global__ __launch_bounds__(256) void k_route(const float* __restrict__ logits, const int32_t* __restrict__ aid,
                                                const int32_t* __restrict__ emap, int T, int E, int k, int renorm,
                                                int32_t* __restrict__ ids, float* __restrict__ w, int32_t* __restrict__ slot_ids) {
-  for (unsigned first = (blockIdx.x * 4 + threadIdx.x / kWave) * kTokensPerWave<V>; first < (unsigned)T; first += gridDim.x * 4 * kTokensPerWave<V>)
+  for (unsigned first = (blockIdx.x * 4 + threadIdx.x / kWave) * kTokensPerWave<V>; first < (unsigned)T; first += kRouteBlocks * 4u * kTokensPerWave<V>)
     wave_select<V, REROUTE>(logits, aid, emap, (int)first, T, E, k, renorm, [&](int t, int rank, int e, int slot, float wt) {
       const size_t p = (size_t)t * k + rank;
       ids[p] = e;
