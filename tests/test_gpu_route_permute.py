@@ -78,19 +78,22 @@ def test_route_topk_selection_edges(ew, T, E, k):
         _check_permutation(fused[2:], emap[0][rids], E)
 
 
-@pytest.mark.parametrize("E,k", [(1, 1), (8, 2), (16, 16), (17, 3), (48, 8), (64, 6), (65, 16), (96, 4), (128, 8), (200, 5), (256, 16)])
-def test_route_topk_weights_do_not_depend_on_the_selection(ew, E, k):
+@pytest.mark.parametrize("T,E,k", [(501, 1, 1), (501, 8, 2), (501, 16, 16), (501, 17, 3), (501, 48, 8), (501, 64, 6), (501, 65, 16), (501, 96, 4),
+                                   (501, 128, 16), (501, 200, 5), (501, 256, 14), (1025, 129, 15), (1025, 256, 16)])
+def test_route_topk_weights_do_not_depend_on_the_selection(ew, T, E, k):
     """Sixteen lanes per token and one wave per token give a weight the same bits: behind the E experts others that weigh exactly
-    zero, up to the first number of experts that takes the wave."""
+    zero, up to the first number of experts that takes the wave; and the first tokens alone, where fewer of them take the wave."""
     rng = np.random.default_rng(E + k)
-    logits = torch.from_numpy((rng.standard_normal((501, E)) * 1.5).astype(np.float32)).cuda()
-    padded = torch.full((501, 257), -1e30, device="cuda")
+    logits = torch.from_numpy((rng.standard_normal((T, E)) * 1.5).astype(np.float32)).cuda()
+    padded = torch.full((T, 257), -1e30, device="cuda")
     padded[:, :E] = logits
     for renorm in (False, True):
         ids, w = ew.moe_route_topk(logits, k, renorm)
         ids_w, w_w = ew.moe_route_topk(padded, k, renorm)
         assert torch.equal(ids, ids_w)
         assert torch.equal(w, w_w), f"{int((w != w_w).sum())} of {w.numel()} weights differ, renorm {renorm}"
+        ids_f, w_f = ew.moe_route_topk(logits[:T - 1].contiguous(), k, renorm)
+        assert torch.equal(ids[:T - 1], ids_f) and torch.equal(w[:T - 1], w_f)
 
 
 @pytest.mark.parametrize("T,E,k", [((1 << 24) + 5, 2, 2), ((1 << 28) + 37, 1, 1), ((1 << 26) + 3, 17, 17)], ids=["second-stride", "sixteen-lanes", "wave"])
