@@ -132,15 +132,20 @@ __device__ __forceinline__ int first_slab(const FfnUnit& u, int nk) { return (u.
 // ------------------------------------------------------------------------------------------
 // A call of a few tokens has one to three units of the first product per workgroup, and the second product waits for the last
 // one: where the units beyond the last full round fit one round as halves (of their weight rows), they are split.  1 token: 96
-// units beyond 256, a pass 48.9 -> 47.9 us; 13 tokens: 62 beyond 512, 56.9 -> 54.6.  Halves keep their unit's walk over K, so no
-// result depends on the split.  Not for more rounds or more tokens, and not in the second product, where the workgroups end 7 to 26
-// us apart: a slab costs about half a microsecond of hand-overs between the waves however small it is, and the last units in
-// halves or quarters cost more than the even end gave (64 tokens 241 -> 247 us, 256 tokens 2028 -> 2046).
+// units beyond 256, a pass 48.9 -> 47.9 us; 13 tokens: 62 beyond 512, 56.9 -> 54.6.  A slab costs about half a microsecond of hand-overs
+// between the waves however small it is, so halves cost more than their unit and pay only where the last round of the whole call,
+// `second` units of the second product among it, has room for that: call alone, us, whole / halves, 2048 x 1408 with 594 + 432 units
+// (4.0 rounds) 80.9 / 81.4, 638 + 464 (4.3) 87.6 / 84.0, but 572 + 416 (3.9) 75.8 / 81.5; 1024 x 896 with 574 + 328 (3.5) 47.7 / 46.0,
+// 602 + 344 (3.7) 47.7 / 51.8.  Nor with less than one round, where nothing waits: 1280 x 512, 1 to 3 tokens, 1 to 3 us lost.
+// Halves keep their unit's walk over K, so no result depends on the split.  Not for more rounds or more tokens, and not in the second
+// product, where the workgroups end 7 to 26 us apart: the last units in halves or quarters cost more than the even end gave (64 tokens
+// 241 -> 247 us, 256 tokens 2028 -> 2046).
 template <typename C>
-__device__ __forceinline__ int whole_units(int mode, int n) {  // positions below are whole units, above there are two for each
-  if (!C::SPLIT || mode) return n;
-  const int grid = (int)gridDim.x, over = n % grid;
-  return n < 3 * grid && 2 * over <= grid ? n - over : n;
+__device__ __forceinline__ int whole_units(int first, int second) {  // positions below are whole units, above there are two for each
+  const int grid = (int)gridDim.x;
+  if (!C::SPLIT || first <= grid || first >= 3 * grid) return first;
+  const int over = first % grid, last = (first + second) % grid;
+  return 2 * over <= grid && last > 0 && 2 * last <= grid ? first - over : first;
 }
 // What a stored unit of the first product adds to its chunk's completion counter, which ends at kDone G.
 constexpr int kDone = 2;
@@ -162,19 +167,19 @@ __device__ __forceinline__ void sched_claim(const FfnArgs& a, Sched& s) {
   if ((threadIdx.x & 63) == 0 && s.mode <= a.last_mode) s.w = __hip_atomic_fetch_add(sched_counter(a, s.mode, s.list), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 template <typename C>
-__device__ __forceinline__ void sched_entry(const FfnArgs& a, int n_chunks, Sched& s) {
+__device__ __forceinline__ void sched_entry(const FfnArgs& a, int n_chunks, int whole, Sched& s) {
   const int lane = threadIdx.x & 63;
   for (;;) {
     if (s.mode > a.last_mode) {
       s.chunk = -1;
       return;
     }
-    const int G = s.mode ? a.m[1].G : a.m[0].G, units = n_chunks * G, whole = whole_units<C>(s.mode, units), n = units + (units - whole);
+    const int G = s.mode ? a.m[1].G : a.m[0].G, units = n_chunks * G, n = C::SPLIT && !s.mode ? 2 * units - whole : units;
     const int v = __builtin_amdgcn_readfirstlane(s.w) * 8 + s.list;
     if (v < n) {
       int u = v;
       s.how = 0;
-      if (C::SPLIT && v >= whole) {
+      if (C::SPLIT && !s.mode && v >= whole) {
         u = whole + ((v - whole) >> 1);
         s.how = 1 + ((v - whole) & 1);
       }
@@ -240,22 +245,27 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds)
   const uint32_t q0 = lds0 + C::Q_OFF;
 
   [[maybe_unused]] Sched sc{};
-  [[maybe_unused]] int n_chunks = 0;
+  [[maybe_unused]] int n_chunks = 0, whole = 0;  // whole: units of the first product that are not split
+  [[maybe_unused]] bool both = false;            // the first two units are looked up together
   [[maybe_unused]] int pending = -1, pending_by = 0;  // scheduler: chunk of the previous unit, counted inside the slab loop of the present one
   if constexpr (ROLE == 2) {
     // The first two units, three round trips each, the second one's a step behind: its last one alone competes with the bulk
     // loads that the first unit starts.  One after the other the second unit was known 5.8 us into the launch, and
-    // nothing can be multiplied before.
+    // nothing can be multiplied before.  With fewer units than workgroups the second claim comes after the first unit's loads:
+    // at once, the workgroups that start first would take two and the others none (1 token, 4 experts of 1024 x 896: 20.6 / 22.6 us;
+    // 2 tokens, 5 of 1280 x 512: 18.5 / 20.1).
     n_chunks = a.plan[0];
+    whole = whole_units<C>(n_chunks * a.m[0].G, n_chunks * a.m[1].G);
+    both = n_chunks * (a.first_mode ? a.m[1].G : a.m[0].G) >= (int)gridDim.x;
     Sched s0{};
     s0.home = s0.list = (int)(blockIdx.x & 7);
     s0.mode = a.first_mode;
     sched_claim(a, s0);
-    sched_entry<C>(a, n_chunks, s0);
+    sched_entry<C>(a, n_chunks, whole, s0);
     sc = s0;
-    sched_claim(a, sc);
+    if (both) sched_claim(a, sc);
     sched_rows<C::QI>(a, s0);
-    sched_entry<C>(a, n_chunks, sc);
+    if (both) sched_entry<C>(a, n_chunks, whole, sc);
     sched_publish<C::QI>(a, s0, queue);
   }
   __builtin_amdgcn_s_barrier();
@@ -365,6 +375,10 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds)
     aim(cur, 0);
     for (int i = 0; i < depth - 1; ++i) issue();
   } else if constexpr (ROLE == 2) {
+    if (!both) {
+      sched_claim(a, sc);
+      sched_entry<C>(a, n_chunks, whole, sc);
+    }
     sched_rows<C::QI>(a, sc);
     sched_publish<C::QI>(a, sc, queue + C::QI);
   }
@@ -450,7 +464,7 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds)
         }
         // the unit after the next: one round trip at a time, spread over this unit's slabs
         if (kt == 0) sched_claim(a, sc);
-        if (kt == (nk - 2) / 3) sched_entry<C>(a, n_chunks, sc);
+        if (kt == (nk - 2) / 3) sched_entry<C>(a, n_chunks, whole, sc);
         if (kt == 2 * (nk - 2) / 3) sched_rows<C::QI>(a, sc);
         if (kt == nk - 2) sched_publish<C::QI>(a, sc, queue + ((seq + 2) & 3) * C::QI);
       } else if constexpr (LOADS) {
