@@ -25,9 +25,11 @@ constexpr int kPlanPick = 31;
 //    workgroups that share an entry's weights (different chunks) or its token rows (different feature
 //    groups) thus run on the same XCD and meet in that XCD's L2; equal durations inside an entry and similar
 //    ones between neighbours in the list keep them together.
-//  * List x begins x eighths into its order and wraps around, so that at any time some XCDs work on slots of many rows
-//    (matrix cores) and some on slots of few (weights from HBM).  All of them in step from large to small: 8192 tokens with 20
-//    adapters 1381 us, now 1347; base-only, where all slots are large, 1082 and 1090.  Odd lists in the opposite order 1367.
+//  * Up to kTurnRows rows per active slot on average, list x begins x eighths into its order and wraps around, so that at any time
+//    some XCDs work on slots of many rows (matrix cores) and some on slots of few (weights from HBM).  All of them in step from large
+//    to small: 8192 tokens with 20 adapters (260 rows per slot) 1381 us, now 1347; odd lists in the opposite order 1367.  Beyond, hardly
+//    a slot has few rows, and XCDs in step share more of what they fetch: 8192 tokens base-only (990 rows per slot) 1093.1 us and 3.34
+//    GB read turned, 1089.6 and 3.0 to 3.2 in step.  At 500 rows (8192 tokens on 130 slots, 16384 on 256) turning gives 1 to 2 %.
 //   plan[x]        x < 8   entries of list x
 //   plan[8 + x]            row chunks of list x
 //   plan[kPlanCtr + kPlanCtrStride i]   claim counters, one cache line each (zeroed here, every call)
@@ -81,22 +83,24 @@ struct FfnPlanShape {
 // a launch (5 us); both bodies in one kernel did not fit the registers.
 constexpr int kPickRows = 128;
 
+constexpr int kTurnRows = 640;
+
 struct BigPlanLds {
   uint32_t sorted[kPlanMaxEnt];  // entries in processing order: slot | part << 16
-  uint32_t wtot[8][8];           // per size class and wave: entries, then the first position
-  int n_total;
+  uint32_t wtot[8][8];           // per size class and wave: entries (and slots << 16), then those before
+  int n_total, n_slots;          // entries, active slots
   int32_t cnt[kPlanMaxP], off[kPlanMaxP];
 };
 
 // Builds the plan of k_ffn_big.  rows / first: rows and first row of slots 4 tid .. 4 tid + 3 of every thread tid < 512
-// (thread order is slot order).  Called by every thread of a block of at least 512 threads (it contains barriers).
-__device__ __forceinline__ void big_plan_build(const int (&rows)[4], const int (&first)[4], const FfnPlanShape& sh, int32_t* __restrict__ plan,
+// (thread order is slot order); rows_all: all rows of the call.  Called by every thread of a block of at least 512 threads (it contains barriers).
+__device__ __forceinline__ void big_plan_build(const int (&rows)[4], const int (&first)[4], long long rows_all, const FfnPlanShape& sh, int32_t* __restrict__ plan,
                                                BigPlanLds& L) {
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const bool worker = tid < 512;
   const int bt = sh.bt, ch = sh.ch, cap = sh.cap;
   for (int i = tid; i < sh.n_done; i += blockDim.x) plan[sh.done_off + i] = 0;
-  // size class of a slot: 8 - (32-row fragments per chunk), i.e. 0 = largest chunks
+  // size class of a slot: 8 - (32-row fragments per chunk), i.e. 0 = largest chunks.  mine, wtot: entries, in the upper half slots.
   int cls[4], nent[4];
   uint32_t mine[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
   if (worker) {
@@ -114,7 +118,7 @@ __device__ __forceinline__ void big_plan_build(const int (&rows)[4], const int (
         nent[i] = (nch + ch - 1) / ch;
 #pragma unroll
         for (int k = 0; k < 8; ++k)
-          if (cls[i] == k) mine[k] += (uint32_t)nent[i];
+          if (cls[i] == k) mine[k] += (uint32_t)nent[i] | 1u << 16;
       }
     }
 #pragma unroll
@@ -128,12 +132,15 @@ __device__ __forceinline__ void big_plan_build(const int (&rows)[4], const int (
   if (tid < 64) {  // (class, wave) pairs in order: one wave scans them all
     const uint32_t v = (&L.wtot[0][0])[tid], inc = wave_incl_scan_u32(v);
     (&L.wtot[0][0])[tid] = inc - v;
-    if (tid == 63) L.n_total = (int)inc;
+    if (tid == 63) {
+      L.n_total = (int)(inc & 0xFFFFu);
+      L.n_slots = (int)(inc >> 16);
+    }
   }
   __syncthreads();
   if (worker) {
 #pragma unroll
-    for (int k = 0; k < 8; ++k) mine[k] += L.wtot[k][wave];
+    for (int k = 0; k < 8; ++k) mine[k] = (mine[k] + L.wtot[k][wave]) & 0xFFFFu;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       if (cls[i] < 0) continue;
@@ -151,7 +158,7 @@ __device__ __forceinline__ void big_plan_build(const int (&rows)[4], const int (
   const int x = wave;
   int32_t* list = plan + kPlanHdr + kEnt * x * cap;
   int n_chunks = 0, n_entries = 0;
-  const int n_list = (n_total - x + 7) / 8, turn = x * n_list / 8;
+  const int n_list = (n_total - x + 7) / 8, turn = rows_all <= (long long)kTurnRows * L.n_slots ? x * n_list / 8 : 0;
   for (int e0 = 0; e0 < n_list; e0 += 64) {
     const int e = e0 + lane;
     const bool ok = e < n_list;
@@ -263,12 +270,13 @@ union FfnPlanLds {
 __device__ __forceinline__ void ffn_plan_build(int (&rows)[4], int (&first)[4], int P, int S, int sh_rows, int sh_first, const FfnPlanShape& sh,
                                                int32_t* __restrict__ plan, FfnPlanLds& L) {
   const int tid = threadIdx.x;
+  const long long rows_all = sh_first + (long long)S * sh_rows;
   bool big = sh.big;
   if (sh.dec && sh.big) {
     int active = S;
 #pragma unroll
     for (int i = 0; i < 4; ++i) active += __syncthreads_count(tid < 512 && rows[i] > 0);
-    big = sh_first + (long long)S * sh_rows > (long long)kPickRows * active;
+    big = rows_all > (long long)kPickRows * active;
     if (tid == 0) plan[kPlanPick] = big ? 2 : 1;
   }
   if (!big) {
@@ -283,7 +291,7 @@ __device__ __forceinline__ void ffn_plan_build(int (&rows)[4], int (&first)[4], 
       first[i] = sh_first + s * sh_rows;
     }
   }
-  big_plan_build(rows, first, sh, plan, L.big);
+  big_plan_build(rows, first, rows_all, sh, plan, L.big);
 }
 
 }  // namespace ew

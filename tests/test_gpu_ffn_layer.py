@@ -120,8 +120,8 @@ def test_grouped_ffn_work_plan_edges(ew, nf):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("T,k,P,S,nf", [(37, 2, 24, 3, 2), (300, 4, 40, 2, 4), (300, 4, 40, 2, 8), (64, 6, 96, 1, 2), (1100, 2, 6, 2, 8),
-                                        (300, 4, 40, 2, 0)],
-                         ids=["ragged37", "t300-nf4", "t300-nf8", "decode64", "few-slots", "t300-auto"])
+                                        (300, 4, 40, 2, 0), (6000, 2, 14, 2, 8)],
+                         ids=["ragged37", "t300-nf4", "t300-nf8", "decode64", "few-slots", "t300-auto", "large-slots"])
 def test_grouped_ffn_with_shared(ew, T, k, P, S, nf):
     """Routed + shared experts in one launch: every row against the oracle's expert FFN, and -- when all calls are made
     with one kernel shape (nf > 0; the shapes walk the contraction in different orders) -- bit for bit against two plain
