@@ -169,11 +169,14 @@ def test_grouped_ffn_with_shared(ew, T, k, P, S, nf):
         ew.binding.moe_grouped_ffn_with_shared(x, k, I, P, dev(counts), dev(offsets), dev(por), w13, w2, s13[:0], s2[:0])
 
 
-@pytest.mark.parametrize("T,k,E,N,S", [(64, 6, 64, 4, 2), (300, 4, 32, 2, 1), (40, 2, 192, 15, 0), (3000, 2, 16, 3, 2)],
-                         ids=["decode64", "one-block-300", "plan-launch-P1632", "multi-block-3000"])
+@pytest.mark.parametrize("T,k,E,N,S", [(64, 6, 64, 4, 2), (300, 4, 32, 2, 1), (40, 2, 192, 15, 0), (3000, 2, 16, 3, 2), (3000, 1, 16, 3, 1), (300, 9, 16, 3, 2),
+                                       (400, 6, 64, 57, 1), (400, 6, 64, 117, 0), (3000, 2, 18, 3, 2), (131100, 2, 16, 3, 1)],
+                         ids=["decode64", "one-block-300", "plan-launch-P1632", "multi-block-3000", "one-choice", "nine-choices", "P520", "P1000",
+                              "P42-column-scan", "2^18-pairs-column-scan"])
 def test_permutation_call_can_write_the_ffn_plan(ew, T, k, E, N, S):
     """moe_route_reroute_permute_plan + moe_grouped_ffn_planned against the plain pair of calls: same permutation, same
-    FFN output bit for bit (the plan is the same plan, whoever writes it)."""
+    FFN output bit for bit (the plan is the same plan, whoever writes it): by the single block, by a launch of its own, and by a block
+    of each scatter kernel, with the histogram's columns summed there and with a column scan before it."""
     B = ew.binding
     rng = np.random.default_rng(T + E)
     H, I, E_max = 256, 128, 8 if E < 100 else 96
@@ -458,10 +461,26 @@ def test_gate_logits(ew, cfg_index):
     np.testing.assert_allclose(got0, moe.gate_logits(x, Wg), rtol=1e-4, atol=2e-5)
 
 
-@pytest.mark.parametrize("T,E,H", [(1, 1, 128), (17, 3, 640), (128, 64, 512), (129, 64, 512), (300, 37, 1024), (512, 64, 512), (1030, 96, 384),
-                                   (2048, 64, 512), (2100, 50, 640), (4096, 64, 512), (4100, 70, 512), (9000, 33, 128)])
+GATE_CASES = [(1, 1, 128), (17, 3, 640), (128, 64, 512), (129, 64, 512), (300, 37, 1024), (512, 64, 512), (1030, 96, 384), (2048, 64, 512),
+              (2100, 50, 640), (4096, 64, 512), (4100, 70, 512), (9000, 33, 128), (129, 64, 640), (500, 64, 640), (1000, 64, 512), (1000, 64, 640),
+              (4096, 64, 640)]
+
+
+def _gate_tile(T, E, H):
+    """(waves, token tiles, experts) of the workgroup that moe_gate_logits picks: the smallest whose grid is one per CU of 256."""
+    cdiv = lambda a, b: -(-a // b)
+    tiles = [(1, 2), (1, 4), (1, 8), (1, 16), (2, 16), (4, 16), (4, 32)]
+    return (16 if H % 512 == 0 else 4,) + next((t for t in tiles if cdiv(T, 16 * t[0]) * cdiv(E, t[1]) <= 256), tiles[-1])
+
+
+def test_gate_logits_cases_cover_every_tile():
+    tiles = {(nw,) + t for nw in (4, 16) for t in [(1, 2), (1, 4), (1, 8), (1, 16), (2, 16), (4, 16), (4, 32)]}
+    assert {_gate_tile(*c) for c in GATE_CASES} == tiles
+
+
+@pytest.mark.parametrize("T,E,H", GATE_CASES)
 def test_gate_logits_tiles(ew, T, E, H):
-    """Every tile of the matrix-core kernel, both wave counts, and sizes that fill a tile's tokens and experts only partly.  The
+    """Every tile of the matrix-core kernel with both wave counts, and sizes that fill a tile's tokens and experts only partly.  The
     bf16 head and tail of a gate weight leave 2^-17 of it; with sums of a few dozen such products that stays below the bound."""
     g = torch.Generator(device="cuda").manual_seed(T + E + H)
     x = torch.randn((T, H), generator=g, device="cuda").to(torch.bfloat16)
