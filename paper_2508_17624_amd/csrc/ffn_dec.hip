@@ -133,10 +133,12 @@ __device__ __forceinline__ int first_slab(const FfnUnit& u, int nk) { return (u.
 // A call of a few tokens has one to three units of the first product per workgroup, and the second product waits for the last
 // one: where the units beyond the last full round fit one round as halves (of their weight rows), they are split.  1 token: 96
 // units beyond 256, a pass 48.9 -> 47.9 us; 13 tokens: 62 beyond 512, 56.9 -> 54.6.  A slab costs about half a microsecond of hand-overs
-// between the waves however small it is, so halves cost more than their unit and pay only where the last round of the whole call,
-// `second` units of the second product among it, has room for that: call alone, us, whole / halves, 2048 x 1408 with 594 + 432 units
-// (4.0 rounds) 80.9 / 81.4, 638 + 464 (4.3) 87.6 / 84.0, but 572 + 416 (3.9) 75.8 / 81.5; 1024 x 896 with 574 + 328 (3.5) 47.7 / 46.0,
-// 602 + 344 (3.7) 47.7 / 51.8.  Nor with less than one round, where nothing waits: 1280 x 512, 1 to 3 tokens, 1 to 3 us lost.
+// between the waves however small it is, so halves cost more than their unit and pay only where the call, `second` units of the second
+// product among it, needs no further round for them.  Call with plan, us, whole / halves, at units of both products (rounds): 2048 x 1408
+// 572 + 416 (3.9) 75.8 / 81.5, 594 + 432 (4.0) 80.9 / 81.4, 638 + 464 (4.3) 87.6 / 84.0; 1024 x 896 574 + 328 (3.5) 47.7 / 46.0, 602 + 344 (3.7)
+// 47.7 / 51.8; 1536 x 768 336 + 336 (2.6) 45.1 / 42.7, 348 + 348 (2.7) 46.4 / 48.4.  Halves of 64-row units cost more of theirs: only where
+// the last round is at most half full (1536 x 768 336 + 336 (2.6) 31.0 / 31.8; 2048 x 1024 352 + 352 (2.75) 37.8 / 40.6).  Nor with less than one
+// round, where nothing waits: 1280 x 512, 1 to 3 tokens, 1 to 3 us lost.
 // Halves keep their unit's walk over K, so no result depends on the split.  Not for more rounds or more tokens, and not in the second
 // product, where the workgroups end 7 to 26 us apart: the last units in halves or quarters cost more than the even end gave (64 tokens
 // 241 -> 247 us, 256 tokens 2028 -> 2046).
@@ -145,7 +147,8 @@ __device__ __forceinline__ int whole_units(int first, int second) {  // position
   const int grid = (int)gridDim.x;
   if (!C::SPLIT || first <= grid || first >= 3 * grid) return first;
   const int over = first % grid, last = (first + second) % grid;
-  return 2 * over <= grid && last > 0 && 2 * last <= grid ? first - over : first;
+  const int room = C::PN == 2 ? grid / 2 : grid - over;
+  return 2 * over <= grid && last > 0 && last <= room ? first - over : first;
 }
 // What a stored unit of the first product adds to its chunk's completion counter, which ends at kDone G.
 constexpr int kDone = 2;

@@ -724,12 +724,14 @@ def test_grouped_ffn_f32_tile_edges(ew, H, I):
 @pytest.mark.parametrize("T,k,P,S,H,I", [(1, 1, 3, 0, 256, 256), (2, 6, 16, 2, 2048, 1408), (16, 4, 200, 1, 384, 256), (17, 4, 40, 2, 640, 256),
                                          (32, 3, 9, 0, 256, 384), (33, 2, 12, 2, 1280, 512), (64, 6, 100, 1, 512, 256), (65, 6, 30, 2, 256, 768),
                                          (130, 4, 24, 2, 384, 256), (513, 2, 16, 1, 512, 256), (3, 2, 48, 1, 1280, 512), (3, 4, 12, 0, 1536, 1024),
-                                         (16, 4, 20, 1, 1024, 896), (1, 6, 8, 2, 2048, 1408), (16, 4, 23, 1, 1024, 896), (16, 4, 28, 0, 640, 384)])
+                                         (16, 4, 20, 1, 1024, 896), (16, 8, 68, 0, 640, 384), (1, 6, 8, 2, 2048, 1408), (16, 4, 23, 1, 1024, 896),
+                                         (16, 4, 28, 0, 640, 384), (16, 8, 72, 0, 640, 384)])
 def test_grouped_ffn_decode_kernel_edges(ew, T, k, P, S, H, I):
     """The kernel of calls with few rows per slot at the edges of its chunks (16, 32, 64 and 128 rows), with contractions
     shorter than its rings, hidden sizes that are an odd multiple of 128, a crowded slot cut into several chunks, more
-    workgroups than units (one unit looked up at a time), more units than workgroups whose last round is too full for halves (the two
-    before the last three) and, in the last three, units of the first product in halves (64 and 128 weight rows): every row against the oracle's expert FFN, twice, the same bits both times.
+    workgroups than units (one unit looked up at a time), more units than workgroups whose last round has no room for halves (the
+    three before the last four) and, in the last four, units of the first product in halves (of 64 and 128 weight rows): every row
+    against the oracle's expert FFN, twice, the same bits both times.
     Weights of deviation 0.02 keep outputs within the range that FFN_MAX_ABS is meant for: a gate or up value has deviation
     0.02 sqrt(2048) = 0.9 at most, an activation about 0.4, an output 0.02 sqrt(1408) 0.4 = 0.3, so below 4 with certainty, where
     bf16 rounds by 2^-7 at most.  At twice the weights outputs are eight times larger and bf16 alone rounds by 2^-5 = 0.03."""
