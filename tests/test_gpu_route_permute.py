@@ -145,9 +145,10 @@ def test_reroute_permute_shapes_with_duplicates(ew, T, k, E, N, P):
     _check_permutation(got, moe.reroute(ids, aid, emap), P)
 
 
-@pytest.mark.parametrize("T,E,k,P", [(32, 256, 16, 320), (33, 256, 4, 320), (33, 128, 12, 200), (48, 128, 12, 200), (48, 128, 13, 200), (49, 128, 4, 200),
-                                     (49, 128, 5, 200), (64, 64, 8, 384), (64, 64, 9, 384), (65, 64, 6, 384), (28, 64, 8, 1600), (29, 64, 8, 1600),
-                                     (29, 64, 9, 1600), (64, 16, 8, 2048), (64, 16, 9, 2048), (48, 64, 8, 2048), (49, 64, 8, 2048)])
+@pytest.mark.parametrize("T,E,k,P", [(32, 256, 16, 320), (33, 256, 16, 320), (33, 256, 15, 320), (128, 256, 16, 320), (129, 256, 16, 320),
+                                     (33, 256, 4, 320), (33, 128, 12, 200), (48, 128, 12, 200), (48, 128, 13, 200), (49, 128, 4, 200), (49, 128, 5, 200),
+                                     (64, 64, 8, 384), (64, 64, 9, 384), (65, 64, 6, 384), (28, 64, 8, 1600), (29, 64, 8, 1600), (29, 64, 9, 1600),
+                                     (64, 16, 8, 2048), (64, 16, 9, 2048), (48, 64, 8, 2048), (49, 64, 8, 2048)])
 def test_route_reroute_permute_joined_or_not(ew, T, E, k, P):
     """Both sides of every line between the selection inside the single block, in one to three rounds of its waves, and in a launch of
     its own."""
