@@ -367,7 +367,8 @@ def tune_ffn(path: int = 0, stream_token_tiles: int = 0, stream_threads: int = 0
 
 
 def tune_route(small_pairs: int = 2048):
-    """Pairs (T*k) up to which moe_reroute_permute / moe_route_reroute_permute take the single-block permutation (with the router fused: a multi-block top-k kernel, then that block)."""
+    """Pairs (T*k) up to which moe_reroute_permute / moe_route_reroute_permute take the single-block permutation
+    (with the router fused and few tokens that block selects too, otherwise a multi-block top-k kernel runs before it)."""
     lib().ew_tune_route(small_pairs)
 
 

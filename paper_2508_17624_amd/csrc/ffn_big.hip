@@ -1,11 +1,10 @@
 // Grouped SwiGLU expert FFN for calls with many rows per slot on gfx950: 256 weight rows x up to 256 token rows per unit.
 //
-// What bounds it: the operand loads into LDS.  Whole passes of 8192 tokens, us (64 + 2 experts in use / 254 + 2): 1066 / 1330; the
-// loads alone, nothing multiplied or stored, 909 / 1213; everything but the loads (operands that stay the same, so at a higher
-// clock as well) 721 / 772; the other kernels of a pass are about 130 of these.  One token slab and up to three weight halves
-// are in flight while a slab is multiplied.  What bounds the whole pass is the chip's power limit: the complete kernel takes 1.64
-// M cycles at 1.70 GHz, its loads and LDS reads without the multiplications 1.62 M at 2.38 GHz, the multiplications on constant
-// operands beside the loads 1.76 M at 2.13 GHz.  So fewer stalls on loads turn into a lower clock for the most part.
+// What bounds it: the operand loads into LDS, at the clock that the power limit leaves.  8192 tokens, this kernel alone, base-only / 20
+// adapters: complete 989 / 1218 us, 1.70 / 2.24 M cycles at 1.72 / 1.84 GHz (MFMA busy 64 / 51 %, TD 78 / 88 %); with nothing
+// multiplied 801 / 1111 us, 1.91 / 2.60 M cycles at 2.38 / 2.34 GHz (TD 92 / 94 %).  So the loads alone are 0.81 / 0.91 of the time: the
+// multiplications hide under them and cost the rest through the clock.  One token slab and up to three weight halves are in flight while a
+// slab is multiplied.
 #include "ffn_roles.h"
 
 namespace ew {

@@ -7,8 +7,9 @@
 //  * top-k: sixteen lanes per token, so four tokens per wave (up to 256 experts and k = 16); beyond
 //    that one wave per token.  Each logit becomes an order-preserving 32-bit key (ties go to the
 //    lower index).
-//  * rerouting is a lookup in the expert map (staged in LDS), fused into whichever kernel first
-//    touches the ids: it never costs a launch or a pass over memory of its own.
+//  * rerouting is a lookup in the expert map, fused into whichever kernel first touches the ids: it never costs a launch or a pass over
+//    memory of its own.  (The histogram of given ids stages the map in LDS; where the selection is fused the token's row of it is read
+//    from L2 while the selection runs.)
 //  * permutation is a stable counting sort by slot.  Order inside a slot must be ascending
 //    pair index, so no atomic cursors: every wave ranks a contiguous run of pairs 64 at a time
 //    with a ballot-built peer mask (rank = popcount of lower peers) and a wave-private LDS
@@ -228,7 +229,7 @@ __device__ __forceinline__ float key_value(uint32_t key) { return __uint_as_floa
 // selection runs, and the slots ride in the low bits of the index that the rounds reduce, so no lookup follows.  emit(rank, expert,
 // slot, weight).  What bounds the selection is the chain of dependent instructions, and the
 // wave-wide radix select above spends it on one token at a time, through the scalar unit that all waves of a SIMD share: k_hist
-// at 8192 tokens of 64 experts, k = 6: 15.8 -> 5.0 us, at 512 tokens 8.0 -> 4.7; k_route at 64 tokens 4.5 -> 4.2.
+// at 8192 tokens of 64 experts, k = 6: 15.8 -> 5.0 us, at 512 tokens 8.0 -> 4.7; top-k alone at 64 tokens 3.8 -> 2.7.
 template <int V, bool REROUTE, typename Emit>
 __device__ __forceinline__ void group_topk(const float* __restrict__ row, const int32_t* __restrict__ maprow, int E, int k, int renorm, Emit emit) {
   const int l = threadIdx.x & 15;
@@ -416,7 +417,7 @@ __device__ __forceinline__ void plan_block(const int32_t* counts, int T, int n, 
 // launch.  V = 0: ids are given (emap == nullptr: they are slots already, written by k_route), otherwise the selection
 // (wave_select) runs here too.  What bounds it is the chain of dependent steps, each a memory round trip or a barrier; so only the
 // waves that a batch gives 64 pairs rank, the scans run on DPP instead of through LDS, and one scan over all threads makes the
-// offsets.  Selection to plan, us, as two launches before / now: 1 token 8.9 / 5.9, 64 tokens 10.0 / 8.0.
+// offsets.  Selection to plan, us, as two launches before / now: 1 token 8.9 / 5.7, 64 tokens 10.2 / 7.7.
 // run = pairs per ranking wave, a multiple of 64; nrank = ranking waves, ceil(T k / run); per = slots per thread of the scan (both
 // from the host: an integer division is a few dozen dependent instructions).  Ids given, us, with the waves' totals summed in a loop
 // and both divisions here / now: 256 tokens of k = 2 on 128 slots 4.4 / 3.6, 1024 6.6 / 5.7; 341 of k = 6 on 384 7.1 / 6.3.
@@ -1056,7 +1057,10 @@ __global__ void k_zero_counts(int32_t* counts, int32_t* offsets, int P) {
 // slot in the scatter's coalesced writes.
 // Up to kDirectPairs pairs of a call that k_scatter_tok takes there are kDirectBlocks blocks at most, few enough for the scatter
 // to do without the column scan (direct_sums).  Hist, scan and scatter of 30011 tokens, k = 8, us: 3.4 + 4.0 + 7.2, without the scan
-// 3.1 + 7.8, and the call, which takes the host about as long, 20.5 -> 18.0.  More pairs want two blocks on every CU.
+// 3.1 + 7.8, and the call, which takes the host about as long, 20.5 -> 18.0.  More pairs want two blocks on every CU: calls with / without
+// the column scan, us, at 2^18 pairs 13.4 / 13.2 (k = 8, 288 slots), 13.6 / 13.6 (4, 512), 11.8 / 10.2 (2, 128); 3 2^17 14.0 / 14.1, 14.4 / 14.5,
+// 12.1 / 10.9; 2^19 14.6 / 15.2, 15.2 / 15.2, 12.8 / 12.0; 2^20 17.2 / 22.0, 17.4 / 21.0, 14.6 / 16.5.  (Of 2048 to 4096 tokens on 288 slots and more
+// the sums cost as much as the scan did: 10.8 / 11.2.)
 inline bool direct_sums(int T, int k, int P) {
   return P <= 512 && P % 4 == 0 && k >= 2 && k <= 8 && (long long)T * k <= kDirectPairs;
 }

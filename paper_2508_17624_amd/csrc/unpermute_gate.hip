@@ -410,7 +410,7 @@ __global__ __launch_bounds__(64 * NW) void k_gate_logits_mfma(const uint16_t* __
 // experts 13.3 / 17.6; 8192 tokens as 1 / 4 token tiles of 16 / 32 experts 43.7 / 17.3.
 template <typename F>
 void gate_tile(int T, int E, F f) {
-  constexpr int kCus = 256;
+  constexpr int kCus = 256;  // of the whole gfx950; on a partition the tile is one size too small, no more
   auto one = [&](auto TT, auto EW) { return (long long)ew::ceil_div(T, 16 * decltype(TT)::value) * ew::ceil_div(E, decltype(EW)::value) <= kCus; };
   using std::integral_constant;
   const integral_constant<int, 1> n1{};
