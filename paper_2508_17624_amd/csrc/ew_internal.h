@@ -66,6 +66,36 @@ size_t ffn_plan_ints(int T, int rows, int P);
 // hook's kernel shape and cap on 32-row fragments per chunk, 0 = automatic; merge: the two products share a launch;
 // wait_polls: the tuning hook's limit on a unit's wait, 0 = automatic.
 FfnPlanShape ffn_plan_shape(int T, int rows, int slots, int frags, int chunk_frags, bool merge, int wait_polls);
+// A layer pass of few tokens routes inside the grouped FFN's launch (ffn_route.h).  What that needs, and hands out: the arguments of
+// moe_route_reroute_permute.
+constexpr int kRouteTokens = 64, kRoutePairs = 512;
+struct FfnRoute {
+  const float* logits;
+  const int32_t* aid;
+  const int32_t* emap;
+  int T, E, k, renorm, bits, S;
+  int32_t* ids;
+  float* w;
+  int32_t* slot;
+  int32_t* counts;
+  int32_t* offsets;
+  int32_t* por;
+  int32_t* rop;
+};
+// Whether a plan of this shape can be made there, for these dimensions.
+bool ffn_routes(const FfnPlanShape& sh, int T, int E, int k, int P, int S);
+// The plan's counters that such a call needs zeroed before its launch: the claim counters and n_done completion counters.
+struct FfnCounters {
+  int32_t* plan;  // nullptr: none
+  int done_off, n_done;
+};
+// unpermute_gate.hip: moe_gate_logits, whose launch also zeroes the counters (bf16, H % 128 == 0).
+int gate_logits(const void* x, int dtype, const float* Wg, int T, int H, int E, const int32_t* adapter_id, const float* bias, float* logits,
+                const FfnCounters& zero, hipStream_t st);
+// route_permute.hip: whether a call of so many pairs takes the single-block permutation (a tuning hook moves the line).
+bool single_block_permute(long long pairs);
+// ffn.hip: router scores, routing, routed and shared experts of a layer pass that routes inside the FFN's launch.
+int layer_ffn_routed(const ew_layer* L, const void* x, const int32_t* adapter_id, int T, const FfnPlanShape& sh, hipStream_t st);
 // The plan kernel alone (what launch_ffn_bf16 runs first unless plan_ready).
 int launch_ffn_plan(const int32_t* counts, const int32_t* offsets, int P, int S, int T, int rows_routed, const FfnPlanShape& sh,
                     int32_t* plan, hipStream_t st);
@@ -74,7 +104,7 @@ int launch_ffn_plan(const int32_t* counts, const int32_t* offsets, int P, int S,
 // H % 128 == 0, I % 128 == 0, rows * max(H, I) * 2 < 2^32 and H * I * 4 < 2^32 are the caller's checks.
 int launch_ffn_bf16(const void* x, int rows_routed, int k, int H, int I, int P, int S, const FfnPlanShape& sh, bool plan_ready,
                     const int32_t* counts, const int32_t* offsets, const int32_t* por, const void* w13, const void* w2, const void* w13_sh,
-                    const void* w2_sh, void* act, void* y, int32_t* plan, hipStream_t st);
+                    const void* w2_sh, void* act, void* y, int32_t* plan, hipStream_t st, const FfnRoute* route = nullptr);
 
 // Whether moe_grouped_ffn / moe_grouped_ffn_with_shared with these dimensions runs those kernels, and
 // if so with which plan shape (defined beside the tuning state it depends on).

@@ -341,6 +341,18 @@ int ew::grouped_ffn_f32(const void* x, int T, int k, int H, int I, int P, int S,
   return launch_ffn_f32(x, T, k, H, I, P, S, counts, offsets, pair_of_row, w13, w2, w13_shared, w2_shared, ws, y, (hipStream_t)stream);
 }
 
+int ew::layer_ffn_routed(const ew_layer* L, const void* x, const int32_t* adapter_id, int T, const FfnPlanShape& sh, hipStream_t st) {
+  int32_t* plan = (int32_t*)L->ws_ffn;
+  char* act = (char*)L->ws_ffn + plan_bytes(T, T * (L->k + L->S), L->P + L->S);
+  const int rc = gate_logits(x, L->dtype, L->Wg, T, L->H, L->M, L->bias ? adapter_id : nullptr, L->bias, L->logits,
+                             FfnCounters{plan, sh.done_off, sh.dec_cap}, st);
+  if (rc != EW_OK) return rc;
+  const FfnRoute route{L->logits, adapter_id, L->expert_map, T, L->M, L->k, L->renormalize, ilog2_ceil(L->P), L->S, L->ids, L->w, L->slot,
+                       L->counts, L->offsets, L->pair_of_row, L->row_of_pair};
+  return launch_ffn_bf16(x, T * L->k, L->k, L->H, L->I, L->P, L->S, sh, false, L->counts, L->offsets, L->pair_of_row, L->w13, L->w2,
+                         L->w13_shared, L->w2_shared, act, L->y, plan, st, &route);
+}
+
 extern "C" int moe_grouped_ffn(const void* x, int dtype, int T, int k, int H, int I, int P, const int32_t* counts,
                                const int32_t* offsets, const int32_t* pair_of_row, const void* w13_base,
                                const void* w2_base, void* y_sorted, void* ws, size_t ws_bytes, void* stream) {

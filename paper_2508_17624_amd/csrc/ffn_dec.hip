@@ -31,7 +31,7 @@
 // product: row m = 4 q + r of fragment i is feature 16 pair + 4 q + 2 i + (r & 1), gate for r < 2 and up for r >= 2: a lane
 // holds gate and up of four consecutive features, SwiGLU needs no exchange and 8 bytes are stored.  Second product: feature
 // 32 pair + 8 q + 4 i + r, 16 bytes.  (With one fragment per wave and half the width the stores alone cost 5 to 8 %.)
-#include "ffn_roles.h"
+#include "ffn_route.h"
 
 namespace ew {
 
@@ -65,6 +65,16 @@ struct DecCfg {
   static constexpr int FPI = NW * RPI / 16;                         // fragments per round of the weight waves' instructions
   static constexpr bool SPLIT = NTF == 1;                           // units of the first product may come in halves, see whole_units
   static_assert(!SPLIT || (PN / 2 % FPI == 0 && NWI % 2 == 0), "half a unit: whole pairs of fragments, loads for every weight wave");
+};
+
+// Where the plan of a call lies that routes itself: behind the rings and the queue.
+template <typename C>
+struct Routed {
+  static constexpr int OFF = C::LDS, LDS = C::LDS + (int)sizeof(RoutePlan);
+  static_assert(C::LDS % 8 == 0 && LDS <= 160 * 1024, "LDS budget of a CU");
+  static_assert(2 * sizeof(RouteScratch) <= C::Q_OFF, "the ranking's scratch, in the rings");
+  int claim = 0, n_chunks = 0;                                      // scheduling wave: its first claim, chunks of the plan
+  static __device__ __forceinline__ RoutePlan& plan(unsigned char* s_lds) { return *reinterpret_cast<RoutePlan*>(s_lds + OFF); }
 };
 
 // Operands of one k-step (32 elements): MFW weight fragments WS bytes apart and NB token fragments FS bytes apart, issued
@@ -143,10 +153,11 @@ __device__ __forceinline__ int first_slab(const FfnUnit& u, int nk) { return (u.
 // product, where the workgroups end 7 to 26 us apart: the last units in halves or quarters cost more than the even end gave (64 tokens
 // 241 -> 247 us, 256 tokens 2028 -> 2046).
 template <typename C>
-__device__ __forceinline__ int whole_units(int first, int second) {  // positions below are whole units, above there are two for each
-  const int grid = (int)gridDim.x;
+__device__ __forceinline__ int whole_units(int grid, int first, int second) {  // positions below are whole units, above there are two for each
   if (!C::SPLIT || first <= grid || first >= 3 * grid) return first;
-  const int over = first % grid, last = (first + second) % grid;
+  const int over = first < 2 * grid ? first - grid : first - 2 * grid;
+  int last = first + second;  // (of the remainder: few rounds, where a division is a long chain)
+  while (last >= grid) last -= grid;
   const int room = C::PN == 2 ? grid / 2 : grid - over;
   return 2 * over <= grid && last > 0 && last <= room ? first - over : first;
 }
@@ -167,10 +178,11 @@ __device__ __forceinline__ int32_t* sched_counter(const FfnArgs& a, int mode, in
   return a.plan + kDecCtr + (mode * 8 + list) * kDecCtrStride;
 }
 __device__ __forceinline__ void sched_claim(const FfnArgs& a, Sched& s) {
-  if ((threadIdx.x & 63) == 0 && s.mode <= a.last_mode) s.w = __hip_atomic_fetch_add(sched_counter(a, s.mode, s.list), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if ((threadIdx.x & 63) == 0 && s.mode <= a.last_mode) s.w = claim_next(sched_counter(a, s.mode, s.list));
 }
-template <typename C>
-__device__ __forceinline__ void sched_entry(const FfnArgs& a, int n_chunks, int whole, Sched& s) {
+// own: the plan in LDS of a call that routes itself.
+template <typename C, bool ROUTED>
+__device__ __forceinline__ void sched_entry(const FfnArgs& a, const RoutePlan* own, int n_chunks, int whole, Sched& s) {
   const int lane = threadIdx.x & 63;
   for (;;) {
     if (s.mode > a.last_mode) {
@@ -186,9 +198,22 @@ __device__ __forceinline__ void sched_entry(const FfnArgs& a, int n_chunks, int 
         u = whole + ((v - whole) >> 1);
         s.how = 1 + ((v - whole) & 1);
       }
-      s.chunk = u / G;
+      // u / G, without an integer division's chain of instructions in front of the first loads: off by one at most
+      s.chunk = (int)(((float)u + 0.5f) * (s.mode ? a.m[1].inv_g : a.m[0].inv_g));
       s.g = u - s.chunk * G;
-      s.en = *reinterpret_cast<const i32x4*>(a.plan + kDecEnt + 4 * s.chunk);
+      if (s.g < 0) {
+        --s.chunk;
+        s.g += G;
+      } else if (s.g >= G) {
+        ++s.chunk;
+        s.g -= G;
+      }
+      if constexpr (ROUTED) {
+        const uint2 en = own->entry[s.chunk];
+        s.en = (i32x4){(int)(en.x & 0xFFFFu), (int)(en.x >> 16), (int)en.y, 0};
+      } else {
+        s.en = *reinterpret_cast<const i32x4*>(a.plan + kDecEnt + 4 * s.chunk);
+      }
       return;
     }
     // this list is empty: the next one that is not, or the next product
@@ -205,15 +230,19 @@ __device__ __forceinline__ void sched_entry(const FfnArgs& a, int n_chunks, int 
     sched_claim(a, s);
   }
 }
-template <int QI>
-__device__ __forceinline__ void sched_rows(const FfnArgs& a, Sched& s) {
+template <int QI, bool ROUTED>
+__device__ __forceinline__ void sched_rows(const FfnArgs& a, const RoutePlan* own, Sched& s) {
   if (s.chunk < 0) return;
   const int slot = s.en[0], rows = s.en[1], off = s.en[2];
 #pragma unroll
   for (int h = 0; h < (QI > 72 ? 2 : 1); ++h) {
     const int r = min((int)(threadIdx.x & 63) + 64 * h, rows - 1);
     int src = off + r;
-    if (s.mode == 0) src = slot >= a.P ? off - a.rows_routed - (slot - a.P) * a.sh_rows + r : (a.por ? a.por[off + r] : off + r) / a.k;
+    if (s.mode == 0) {
+      if (slot >= a.P) src = off - a.rows_routed - (slot - a.P) * a.sh_rows + r;
+      else if constexpr (ROUTED) src = own->token[off + r];
+      else src = (a.por ? a.por[off + r] : off + r) / a.k;
+    }
     s.src[h] = (uint32_t)src * (uint32_t)(2 * (s.mode ? a.m[1].K : a.m[0].K));
   }
 }
@@ -234,9 +263,10 @@ __device__ __forceinline__ void sched_publish(const FfnArgs& a, const Sched& s, 
 }
 
 // ROLE 0: weight wave, 1: token wave, 2: scheduler, 3: multiplying wave.  All roles execute the same number of barriers.
-template <int NTF, int MR, int ROLE>
-__device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds) {
+template <int NTF, int MR, int ROLE, bool ROUTED>
+__device__ __forceinline__ void dec_body(const FfnArgs& a, const Routed<DecCfg<NTF, MR>>& rt, unsigned char* s_lds) {
   using C = DecCfg<NTF, MR>;
+  [[maybe_unused]] const RoutePlan* own = ROUTED ? &Routed<C>::plan(s_lds) : nullptr;
   constexpr int kShift = MR == 64 ? 7 : 6;                                    // log2 of a slab's contraction elements
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -256,19 +286,21 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds)
     // loads that the first unit starts.  One after the other the second unit was known 5.8 us into the launch, and
     // nothing can be multiplied before.  With fewer units than workgroups the second claim comes after the first unit's loads:
     // at once, the workgroups that start first would take two and the others none (1 token, 4 experts of 1024 x 896: 20.6 / 22.6 us;
-    // 2 tokens, 5 of 1280 x 512: 18.5 / 20.1).
-    n_chunks = a.plan[0];
-    whole = whole_units<C>(n_chunks * a.m[0].G, n_chunks * a.m[1].G);
-    both = n_chunks * (a.first_mode ? a.m[1].G : a.m[0].G) >= (int)gridDim.x;
+    // 2 tokens, 5 of 1280 x 512: 18.5 / 20.1).  With the plan in LDS only the second claim itself is a round trip, and the first
+    // unit's loads do not wait for it.
+    n_chunks = ROUTED ? rt.n_chunks : a.plan[0];
+    whole = whole_units<C>(a.grid, n_chunks * a.m[0].G, n_chunks * a.m[1].G);
+    both = n_chunks * (a.first_mode ? a.m[1].G : a.m[0].G) >= a.grid;
     Sched s0{};
     s0.home = s0.list = (int)(blockIdx.x & 7);
     s0.mode = a.first_mode;
-    sched_claim(a, s0);
-    sched_entry<C>(a, n_chunks, whole, s0);
+    if constexpr (ROUTED) s0.w = rt.claim;
+    else sched_claim(a, s0);
+    sched_entry<C, ROUTED>(a, own, n_chunks, whole, s0);
     sc = s0;
     if (both) sched_claim(a, sc);
-    sched_rows<C::QI>(a, s0);
-    if (both) sched_entry<C>(a, n_chunks, whole, sc);
+    sched_rows<C::QI, ROUTED>(a, own, s0);
+    if (both && !ROUTED) sched_entry<C, ROUTED>(a, own, n_chunks, whole, sc);
     sched_publish<C::QI>(a, s0, queue);
   }
   __builtin_amdgcn_s_barrier();
@@ -378,11 +410,9 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds)
     aim(cur, 0);
     for (int i = 0; i < depth - 1; ++i) issue();
   } else if constexpr (ROLE == 2) {
-    if (!both) {
-      sched_claim(a, sc);
-      sched_entry<C>(a, n_chunks, whole, sc);
-    }
-    sched_rows<C::QI>(a, sc);
+    if (!both) sched_claim(a, sc);
+    if (!both || ROUTED) sched_entry<C, ROUTED>(a, own, n_chunks, whole, sc);
+    sched_rows<C::QI, ROUTED>(a, own, sc);
     sched_publish<C::QI>(a, sc, queue + C::QI);
   }
   __builtin_amdgcn_s_barrier();
@@ -467,8 +497,8 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds)
         }
         // the unit after the next: one round trip at a time, spread over this unit's slabs
         if (kt == 0) sched_claim(a, sc);
-        if (kt == (nk - 2) / 3) sched_entry<C>(a, n_chunks, whole, sc);
-        if (kt == 2 * (nk - 2) / 3) sched_rows<C::QI>(a, sc);
+        if (kt == (nk - 2) / 3) sched_entry<C, ROUTED>(a, own, n_chunks, whole, sc);
+        if (kt == 2 * (nk - 2) / 3) sched_rows<C::QI, ROUTED>(a, own, sc);
         if (kt == nk - 2) sched_publish<C::QI>(a, sc, queue + ((seq + 2) & 3) * C::QI);
       } else if constexpr (LOADS) {
         if (!p_next && p_k == nk && nxt.slot >= 0 && !(ROLE == 1 && change)) {
@@ -505,23 +535,65 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, unsigned char* s_lds)
   }
 }
 
+template <int NTF, int MR, bool ROUTED>
+__device__ __forceinline__ void dec_roles(const FfnArgs& a, const Routed<DecCfg<NTF, MR>>& rt, unsigned char* s_lds) {
+  using C = DecCfg<NTF, MR>;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (wave < C::NW) dec_body<NTF, MR, 0, ROUTED>(a, rt, s_lds);
+  else if (wave < C::NW + C::NT) dec_body<NTF, MR, 1, ROUTED>(a, rt, s_lds);
+  else if (wave == C::NW + C::NT) dec_body<NTF, MR, 2, ROUTED>(a, rt, s_lds);
+  else dec_body<NTF, MR, 3, ROUTED>(a, rt, s_lds);
+}
+
 template <int NTF, int MR>
 __global__ __launch_bounds__((DecCfg<NTF, MR>::THREADS)) void k_ffn_dec(FfnArgs a) {
   __shared__ __align__(1024) unsigned char s_lds[DecCfg<NTF, MR>::LDS];
   if (a.pick && picked(a) != a.pick) return;  // the counts chose the other kernel
+  dec_roles<NTF, MR, false>(a, {}, s_lds);
+}
+
+// The same for a call that routes itself, with one wave more: it selects as the others do, in the first workgroup it then writes what
+// the call hands out, and ends.
+template <int NTF, int MR>
+__global__ __launch_bounds__((DecCfg<NTF, MR>::THREADS + 64)) void k_ffn_dec_routed(FfnArgs a, FfnRoute r) {
   using C = DecCfg<NTF, MR>;
+  constexpr int kSched = C::NW + C::NT, kWriter = C::THREADS / 64;
+  __shared__ __align__(1024) unsigned char s_lds[Routed<C>::LDS];
+  RouteScratch* sc = reinterpret_cast<RouteScratch*>(s_lds);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (wave < C::NW) dec_body<NTF, MR, 0>(a, s_lds);
-  else if (wave < C::NW + C::NT) dec_body<NTF, MR, 1>(a, s_lds);
-  else if (wave == C::NW + C::NT) dec_body<NTF, MR, 2>(a, s_lds);
-  else dec_body<NTF, MR, 3>(a, s_lds);
+  Routed<C> rt;
+  // (the first claim is made by every workgroup whatever the plan, and comes back while the experts are selected)
+  if (wave == kSched && (threadIdx.x & 63) == 0)
+    rt.claim = claim_next(sched_counter(a, 0, (int)(blockIdx.x & 7)));
+  if (wave == kSched) {
+    // The arguments take six cache lines, and each would be a round trip where it is first read, in the chain up to the first loads:
+    // this wave, which mostly has no token to select for, brings them in meanwhile.
+    const auto* args = (const __attribute__((address_space(4))) uint32_t*)__builtin_amdgcn_kernarg_segment_ptr();
+    uint32_t any = 0;
+#pragma unroll
+    for (unsigned i = 0; i < (sizeof(FfnArgs) + sizeof(FfnRoute)) / 4; i += 16) any |= args[i];
+    asm volatile("" ::"s"(any));
+  }
+  const bool writes = blockIdx.x == 0;
+  route_select<kWriter + 1, kSched + 1>(r, a.P, sc, writes ? 2 : 1);
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  if (wave == kSched) rt.n_chunks = route_rank<false>(r, a.P, 16 * NTF, sc[0], Routed<C>::plan(s_lds));
+  if (wave == kWriter) {
+    if (writes) route_rank<true>(r, a.P, 16 * NTF, sc[1], Routed<C>::plan(s_lds));
+    // the first unit is published behind this barrier, and only then is anything loaded into the rings that the scratch lies in
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    return;
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  dec_roles<NTF, MR, true>(a, rt, s_lds);
 }
 
 template <int NTF, int MR>
-int launch(FfnArgs a, const FfnPlanShape& sh, int n_cu, hipStream_t st) {
+int launch(FfnArgs a, const FfnPlanShape& sh, int n_cu, hipStream_t st, [[maybe_unused]] const FfnRoute* route = nullptr) {
   using C = DecCfg<NTF, MR>;
   a.m[0].G = a.m[0].NOUT / (MR / 2);
   a.m[1].G = a.m[1].NOUT / MR;
+  for (FfnProd& m : a.m) m.inv_g = 1.f / (float)m.G;
   const int nk = (a.m[0].K < a.m[1].K ? a.m[0].K : a.m[1].K) / C::SK;  // >= 2
   a.depth_w = C::DW < nk ? C::DW : nk;
   a.depth_t = C::DT < nk ? C::DT : nk;
@@ -530,7 +602,16 @@ int launch(FfnArgs a, const FfnPlanShape& sh, int n_cu, hipStream_t st) {
     a.first_mode = mode;
     a.last_mode = merged ? 1 : mode;
     const long long units = (long long)sh.dec_cap * (merged ? a.m[0].G + a.m[1].G : a.m[mode].G);
-    hipLaunchKernelGGL((k_ffn_dec<NTF, MR>), dim3(units < n_cu ? (int)units : n_cu), dim3(C::THREADS), 0, st, a);
+    a.grid = units < n_cu ? (int)units : n_cu;
+    const dim3 grid(a.grid);
+    if constexpr (NTF <= 4) {
+      if (route) {
+        hipLaunchKernelGGL((k_ffn_dec_routed<NTF, MR>), grid, dim3(C::THREADS + 64), 0, st, a, *route);
+        EW_LAUNCH_CHECK("k_ffn_dec_routed");
+        continue;
+      }
+    }
+    hipLaunchKernelGGL((k_ffn_dec<NTF, MR>), grid, dim3(C::THREADS), 0, st, a);
     EW_LAUNCH_CHECK("k_ffn_dec");
   }
   return EW_OK;
@@ -538,7 +619,12 @@ int launch(FfnArgs a, const FfnPlanShape& sh, int n_cu, hipStream_t st) {
 
 }  // namespace
 
-int launch_ffn_dec(FfnArgs a, const FfnPlanShape& sh, int n_cu, hipStream_t st) {
+bool ffn_routes(const FfnPlanShape& sh, int T, int E, int k, int P, int S) {
+  return sh.dec >= 1 && sh.dec <= 4 && !sh.big && sh.merged && T <= kRouteTokens && T * k <= kRoutePairs && k <= 16 && k <= E && E <= 256 &&
+         P <= kPlanMaxP && S * dec_chunks(T, 16 * sh.dec) <= kRouteShared;
+}
+
+int launch_ffn_dec(FfnArgs a, const FfnPlanShape& sh, int n_cu, hipStream_t st, const FfnRoute* route) {
   const int H = a.m[0].K, I = a.m[1].K;
   // Units of 128 weight rows read every token row half as often as units of 64: C1-shaped calls 261 -> 247 us, 48 tokens on
   // 84 small experts 111 -> 101 us.  Only where even 64-row units leave a compute unit no more than two of the first
@@ -546,9 +632,9 @@ int launch_ffn_dec(FfnArgs a, const FfnPlanShape& sh, int n_cu, hipStream_t st) 
   // which a unit must have two.)
   const bool fine = sh.dec == 1 && H >= 256 && I >= 256 && (long long)sh.dec_cap * (I / 32) <= 2 * n_cu;
   switch (sh.dec) {
-    case 1: return fine ? launch<1, 64>(a, sh, n_cu, st) : launch<1, 128>(a, sh, n_cu, st);
-    case 2: return launch<2, 128>(a, sh, n_cu, st);
-    case 4: return launch<4, 128>(a, sh, n_cu, st);
+    case 1: return fine ? launch<1, 64>(a, sh, n_cu, st, route) : launch<1, 128>(a, sh, n_cu, st, route);
+    case 2: return launch<2, 128>(a, sh, n_cu, st, route);
+    case 4: return launch<4, 128>(a, sh, n_cu, st, route);
     default: return H % 256 == 0 ? launch<8, 256>(a, sh, n_cu, st) : launch<8, 128>(a, sh, n_cu, st);
   }
 }

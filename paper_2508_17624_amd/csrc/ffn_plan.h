@@ -205,6 +205,12 @@ constexpr int kDecCtr = 32, kDecCtrStride = 32;
 constexpr int kDecEnt = kDecCtr + 16 * kDecCtrStride;
 constexpr int kDecDoneStride = 16;
 
+// Zeroes them, n_done completion counters: thread tid of n threads' share.
+__device__ __forceinline__ void dec_zero_counters(int32_t* __restrict__ plan, int done_off, int n_done, int tid, int n) {
+  for (int i = tid; i < n_done; i += n) plan[done_off + kDecDoneStride * i] = 0;
+  if (tid < 16) plan[kDecCtr + kDecCtrStride * tid] = 0;
+}
+
 __host__ __device__ inline int dec_chunks(int c, int bt) { return (c + bt - 1) / bt; }
 
 struct DecPlanLds {
@@ -254,8 +260,7 @@ __device__ __forceinline__ void dec_plan_build(const int (&rows)[4], const int (
     if (tid >= 512 - 64)  // the last wave: it has no routed slot below 1792 of them
       for (int s = tid - (512 - 64); s < S; s += 64) put(s * sh_chunks, P + s, sh_rows, sh_first + s * sh_rows);
   }
-  for (int i = tid; i < total; i += blockDim.x) plan[sh.done_off + kDecDoneStride * i] = 0;
-  if (tid < 16) plan[kDecCtr + kDecCtrStride * tid] = 0;
+  dec_zero_counters(plan, sh.done_off, total, tid, (int)blockDim.x);
   if (tid == 0) plan[0] = total;
 }
 

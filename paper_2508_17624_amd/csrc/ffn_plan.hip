@@ -104,7 +104,7 @@ int launch_ffn_plan(const int32_t* counts, const int32_t* offsets, int P, int S,
 
 int launch_ffn_bf16(const void* x, int rows_routed, int k, int H, int I, int P, int S, const FfnPlanShape& sh, bool plan_ready,
                     const int32_t* counts, const int32_t* offsets, const int32_t* por, const void* w13, const void* w2, const void* w13_sh,
-                    const void* w2_sh, void* act, void* y, int32_t* plan, hipStream_t st) {
+                    const void* w2_sh, void* act, void* y, int32_t* plan, hipStream_t st, const FfnRoute* route) {
   const int T = rows_routed / k;              // tokens = rows of each shared expert
   const int rows = rows_routed + S * T, slots = P + S;
   // persistent grids: one workgroup per CU, a multiple of the 8 XCDs; the count is kept per device
@@ -120,17 +120,18 @@ int launch_ffn_bf16(const void* x, int rows_routed, int k, int H, int I, int P, 
     n_cu = v < 8 ? 8 : v / 8 * 8;
     if (dev >= 0 && dev < kMaxDev) cu_of_dev[dev].store(n_cu, std::memory_order_relaxed);
   }
-  if (!plan_ready) {
+  if (!plan_ready && !route) {
     const int rc = launch_ffn_plan(counts, offsets, P, S, T, rows_routed, sh, plan, st);
     if (rc != EW_OK) return rc;
   }
   FfnArgs a{};
-  a.m[0] = FfnProd{(const uint16_t*)x, (const uint16_t*)w13, (const uint16_t*)w13_sh, (uint16_t*)act, (size_t)2 * I * H, H, I, 0};
-  a.m[1] = FfnProd{(const uint16_t*)act, (const uint16_t*)w2, (const uint16_t*)w2_sh, (uint16_t*)y, (size_t)H * I, I, H, 0};
+  a.m[0] = FfnProd{(const uint16_t*)x, (const uint16_t*)w13, (const uint16_t*)w13_sh, (uint16_t*)act, (size_t)2 * I * H, H, I, 0, 0.f};
+  a.m[1] = FfnProd{(const uint16_t*)act, (const uint16_t*)w2, (const uint16_t*)w2_sh, (uint16_t*)y, (size_t)H * I, I, H, 0, 0.f};
   a.por = por; a.plan = plan; a.done = plan + sh.done_off;
   a.P = P; a.rows_routed = rows_routed; a.sh_rows = T > 0 ? T : 1; a.k = k;
   a.cap = sh.cap; a.list_chunks = sh.ch * sh.cap;
   a.wait_polls = sh.wait_polls;
+  if (route) return launch_ffn_dec(a, sh, n_cu, st, route);
   const bool both = sh.dec && sh.big;
   if (sh.dec) {
     a.pick = both ? 1 : 0;

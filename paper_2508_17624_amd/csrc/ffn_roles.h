@@ -20,6 +20,7 @@ struct FfnProd {
   uint16_t* out;       // [rows, NOUT]
   size_t slot_stride;  // elements per slot
   int K, NOUT, G;      // G: units per chunk
+  float inv_g;         // k_ffn_dec: 1 / G
 };
 
 struct FfnArgs {
@@ -33,6 +34,7 @@ struct FfnArgs {
   int cap, list_chunks;       // k_ffn_big: entries and chunks per list of the plan at most
   int pick;                   // 0, or this kernel's number in plan[kPlanPick]
   int wait_polls;             // looks at a completion counter before a wait for it is given up
+  int grid;                   // k_ffn_dec: workgroups of the launch
 };
 
 // The kernel that the counts chose (wave-uniform, as the branch on it has to be).
@@ -80,6 +82,14 @@ __device__ __forceinline__ FfnUnit read_unit(uint32_t addr) {
   u.how = __builtin_amdgcn_readfirstlane(hi[3]);
   return u;
 }
+// Adds 1 to a claim counter; the value before comes back while the wave goes on (it is waited for where it is used).  The address is
+// a vector one on purpose: given a uniform one the compiler combines the lanes' additions and waits for the result at once, a round
+// trip in which the scheduling wave is missing at the slabs' barriers.
+__device__ __forceinline__ int32_t claim_next(int32_t* counter) {
+  uint32_t at = 0;
+  asm volatile("" : "+v"(at));
+  return __hip_atomic_fetch_add(reinterpret_cast<int32_t*>(reinterpret_cast<char*>(counter) + at), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 // N ints STEP bytes apart (N: 1, 2 or a multiple of 4).
 template <int N, int STEP>
 __device__ __forceinline__ void read_lds_ints(uint32_t addr, uint32_t* r) {
@@ -120,8 +130,8 @@ __device__ __forceinline__ bool wait_expired(const FfnUnit& u, uint32_t entry) {
   return (int)__builtin_amdgcn_readfirstlane(r) == kExpired;
 }
 
-// ffn_dec.hip: calls with few rows per slot.
-int launch_ffn_dec(FfnArgs a, const FfnPlanShape& sh, int n_cu, hipStream_t st);
+// ffn_dec.hip: calls with few rows per slot.  route: the launch routes too (ffn_routes), no plan is there.
+int launch_ffn_dec(FfnArgs a, const FfnPlanShape& sh, int n_cu, hipStream_t st, const FfnRoute* route = nullptr);
 // ffn_big.hip: the calls with many rows per slot; max_chunks: row chunks of the plan at most.
 int launch_ffn_big(FfnArgs a, const FfnPlanShape& sh, int max_chunks, int n_cu, hipStream_t st);
 

@@ -348,13 +348,14 @@ __device__ __forceinline__ void split_bf16(const float4& lo4, const float4& hi4,
 template <int NW, int TT, int EW>
 __global__ __launch_bounds__(64 * NW) void k_gate_logits_mfma(const uint16_t* __restrict__ x, const float* __restrict__ Wg, int T,
                                                           int H, int E, const int32_t* __restrict__ aid,
-                                                          const float* __restrict__ bias, float* __restrict__ logits) {
+                                                          const float* __restrict__ bias, float* __restrict__ logits, ew::FfnCounters zero) {
   constexpr int J = (EW + 15) / 16;  // 16-expert tiles; of a narrower one the last row repeats
   __shared__ float s_red[NW][16 * TT][16 * J + 4];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int m = lane & 15, q = lane >> 4;
   const int t0 = blockIdx.x * 16 * TT, e0 = blockIdx.y * EW;
   const int Kw = H / NW, k_lo = wave * Kw;  // H % (32 NW) == 0
+  if (zero.plan && blockIdx.x == 0 && blockIdx.y == 0) ew::dec_zero_counters(zero.plan, zero.done_off, zero.n_done, threadIdx.x, 64 * NW);
   const uint16_t* xr[TT];
 #pragma unroll
   for (int tt = 0; tt < TT; ++tt) xr[tt] = x + (size_t)min(t0 + tt * 16 + m, T - 1) * H + k_lo + q * 8;
@@ -496,25 +497,23 @@ extern "C" int moe_unpermute_rmsnorm(const void* y_sorted, const int32_t* row_of
                    eps, normed_out, stream);
 }
 
-extern "C" int moe_gate_logits(const void* x, int dtype, const float* Wg, int T, int H, int E, const int32_t* adapter_id,
-                               const float* bias, float* logits, void* stream) {
-  using ew::fail;
+int ew::gate_logits(const void* x, int dtype, const float* Wg, int T, int H, int E, const int32_t* adapter_id, const float* bias, float* logits,
+                    const FfnCounters& zero, hipStream_t st) {
   if (T < 0 || H < 1 || E < 1) return fail(EW_ERR_INVALID_ARG, "moe_gate_logits: need T>=0, H>=1, E>=1");
   if (dtype != EW_F32 && dtype != EW_BF16) return fail(EW_ERR_INVALID_ARG, "moe_gate_logits: unknown dtype %d", dtype);
   if ((adapter_id == nullptr) != (bias == nullptr)) return fail(EW_ERR_INVALID_ARG, "moe_gate_logits: adapter_id and bias go together");
   if (H % 4) return fail(EW_ERR_UNSUPPORTED, "moe_gate_logits: H=%d must be a multiple of 4", H);
   if (T == 0) return EW_OK;
   if (!x || !Wg || !logits) return fail(EW_ERR_INVALID_ARG, "moe_gate_logits: NULL device pointer");
-  hipStream_t st = (hipStream_t)stream;
   if (dtype == EW_BF16 && H % 128 == 0) {
     gate_tile(T, E, [&](auto tt, auto ew_tag) {
       constexpr int TT = decltype(tt)::value, EW = decltype(ew_tag)::value;
       const dim3 grid(ew::ceil_div(T, 16 * TT), ew::ceil_div(E, EW));
       // 16 waves where they divide the contraction: a wave then has its whole part in flight at once
       if (H % 512 == 0)
-        hipLaunchKernelGGL((k_gate_logits_mfma<16, TT, EW>), grid, dim3(1024), 0, st, (const uint16_t*)x, Wg, T, H, E, adapter_id, bias, logits);
+        hipLaunchKernelGGL((k_gate_logits_mfma<16, TT, EW>), grid, dim3(1024), 0, st, (const uint16_t*)x, Wg, T, H, E, adapter_id, bias, logits, zero);
       else
-        hipLaunchKernelGGL((k_gate_logits_mfma<4, TT, EW>), grid, dim3(256), 0, st, (const uint16_t*)x, Wg, T, H, E, adapter_id, bias, logits);
+        hipLaunchKernelGGL((k_gate_logits_mfma<4, TT, EW>), grid, dim3(256), 0, st, (const uint16_t*)x, Wg, T, H, E, adapter_id, bias, logits, zero);
     });
     EW_LAUNCH_CHECK("k_gate_logits");
     return EW_OK;
@@ -526,6 +525,11 @@ extern "C" int moe_gate_logits(const void* x, int dtype, const float* Wg, int T,
     hipLaunchKernelGGL((k_gate_logits<false>), grid, dim3(256), 0, st, x, Wg, T, H, E, adapter_id, bias, logits);
   EW_LAUNCH_CHECK("k_gate_logits");
   return EW_OK;
+}
+
+extern "C" int moe_gate_logits(const void* x, int dtype, const float* Wg, int T, int H, int E, const int32_t* adapter_id,
+                               const float* bias, float* logits, void* stream) {
+  return ew::gate_logits(x, dtype, Wg, T, H, E, adapter_id, bias, logits, ew::FfnCounters{}, (hipStream_t)stream);
 }
 
 extern "C" int moe_rmsnorm(const void* x, int dtype, int T, int H, float eps, void* out, void* stream) {

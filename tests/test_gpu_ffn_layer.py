@@ -838,3 +838,58 @@ def test_grouped_ffn_counts_choose_the_kernel(ew, T, k, P, S, H, I, used):
         for s in range(S):
             blk = got[T * k + s * T:T * k + (s + 1) * T]
             assert rel_l2(blk, moe.expert_ffn(xs, to_f64(s13[s]), to_f64(s2[s]))) <= FFN_REL_L2, f"shared expert {s}"
+
+
+@pytest.mark.parametrize("T,E,k,N,e_max,S,H,I,renorm,repeat", [
+    (1, 64, 6, 4, 16, 2, 256, 128, False, False),       # a token's pairs alone
+    (4, 8, 2, 2, 2, 0, 128, 128, True, False),          # one selecting wave, one expert per lane
+    (13, 96, 4, 20, 16, 1, 256, 128, True, False),      # a ragged wave, eight experts per lane
+    (16, 256, 16, 1, 8, 3, 128, 128, False, False),     # sixteen experts per lane, as many choices as lanes
+    (17, 16, 5, 3, 4, 2, 128, 256, True, False),        # chunks of 32 rows
+    (32, 24, 16, 2, 16, 16, 128, 128, False, False),    # most pairs, most shared chunks
+    (33, 64, 6, 4, 16, 2, 256, 128, False, False),      # chunks of 64 rows, selecting waves of the second round
+    (61, 128, 8, 124, 15, 1, 128, 128, True, False),    # more tokens than one round of the selection takes, 1988 slots
+    (64, 64, 8, 0, 1, 0, 128, 128, False, False),       # most tokens, most pairs, no adapters
+    (64, 64, 1, 5, 16, 2, 128, 128, False, False),
+    (20, 8, 6, 2, 4, 2, 256, 128, False, True),         # a map that sends two experts to one slot: slots with more rows than tokens
+    (64, 8, 8, 1, 4, 1, 128, 128, True, True),
+])
+def test_layer_that_routes_itself_equals_the_separate_launches(ew, T, E, k, N, e_max, S, H, I, renorm, repeat):
+    """A pass of few tokens routes inside the FFN's launch; with its logits given it runs permutation and FFN as launches of their
+    own.  Everything the two leave behind has the same bits, on three passes in a row over other tokens (the counters are zeroed
+    again every time), and slots that no token visits are not read."""
+    from types import SimpleNamespace
+    from paper_2508_17624_amd.layer import MoELayer
+    rng = np.random.default_rng([T, E, k, N])
+    g = torch.Generator(device="cuda").manual_seed(T + 100 * E)
+    bf = lambda *shape, scale=1.0: (torch.randn(shape, generator=g, device="cuda") * scale).bfloat16()
+    P = E + N * e_max
+    emap = np.tile(np.arange(E, dtype=np.int32), (N + 1, 1))
+    for a in range(1, N + 1):
+        ids = np.sort(rng.choice(E, size=min(E, e_max), replace=False))
+        emap[a, ids] = E + (a - 1) * e_max + np.arange(len(ids))
+    if repeat:
+        emap //= 2
+    w13, w2 = bf(P, 2 * I, H, scale=0.05), bf(P, H, I, scale=0.05)
+    backed = torch.zeros(P, dtype=torch.bool)
+    backed[torch.from_numpy(np.unique(emap)).long()] = True
+    w13[~backed.cuda()] = float("nan")
+    w2[~backed.cuda()] = float("nan")
+    emap_t = torch.from_numpy(emap).cuda()
+    pool = SimpleNamespace(M=E, N=N, P=P, view=lambda l: (w13.data_ptr(), w2.data_ptr(), emap_t.data_ptr(), P))
+    shared = (bf(S, 2 * I, H, scale=0.05), bf(S, H, I, scale=0.05)) if S else (None, None)
+    Wg = torch.randn((E, H), generator=g, device="cuda") * 0.1
+    make = lambda: MoELayer(pool, 0, Wg, shared[0], shared[1], k, I, T, torch.bfloat16, renormalize=renorm)
+    fused, apart = make(), make()
+    names = ("ids", "w", "slot", "counts", "offsets", "por", "rop", "y", "y_shared")
+    for b in (fused.buf, apart.buf):
+        b.ws_ffn.fill_(0x5A)                                                    # whatever a workspace holds before its first call
+    for turn in range(3):
+        x, aid = bf(T, H), torch.from_numpy(rng.integers(0, N + 1, T).astype(np.int32)).cuda()
+        got = fused.forward(x, aid).clone()
+        want = apart.forward(x, aid, fused.logits[:T].clone()).clone()
+        torch.testing.assert_close(fused.logits, ew.moe_gate_logits(x, Wg), rtol=0, atol=0)
+        for name in names:
+            assert torch.equal(getattr(fused, name), getattr(apart, name)), f"pass {turn}: {name}"
+        assert torch.equal(got, want) and torch.isfinite(got.float()).all(), f"pass {turn}"
+
