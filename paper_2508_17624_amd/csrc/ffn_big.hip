@@ -31,6 +31,8 @@ struct Sched {
   int n_ent, chunks;         // lane i: entries and chunks of list (home + i) % 8
   int ent[6];                // lane e: entry e of the claimed list
   int ok, slot, rows, off, g, chunk, how;
+  int pairs;                 // src are pairs, not rows yet
+  int stored;                // first-product units of the chunk that are stored
   uint32_t src[4];
 };
 
@@ -38,25 +40,20 @@ __device__ __forceinline__ int32_t* counter(const FfnArgs& a, int mode, int list
 
 __device__ __forceinline__ void sched_claim(const FfnArgs& a, Sched& s) {
   if ((threadIdx.x & 63) == 0 && s.mode <= a.last_mode)
-    s.w = __hip_atomic_fetch_add(counter(a, s.mode, (s.home + s.t) & 7), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    s.w = claim_next(counter(a, s.mode, (s.home + s.t) & 7));
 }
-__device__ __forceinline__ void load_entry(const FfnArgs& a, Sched& s, int e) {
+__device__ __forceinline__ void load_entry(const FfnArgs& a, Sched& s, int e) {  // of a list that has entries; lanes past its last take that one
   const int x = (s.home + s.t) & 7, n = __shfl(s.n_ent, s.t, 64);
-  if (e < n) {
-    const int32_t* en = a.plan + kPlanHdr + kEnt * (x * a.cap + e);
+  const int32_t* en = a.plan + kPlanHdr + kEnt * (x * a.cap + min(e, n - 1));
 #pragma unroll
-    for (int i = 0; i < kEnt; ++i) s.ent[i] = en[i];
-  } else {
-    s.ent[1] = 0;
-    s.ent[2] = 0;
-  }
+  for (int i = 0; i < kEnt; ++i) s.ent[i] = en[i];
 }
-__device__ __forceinline__ void sched_entry(const FfnArgs& a, Sched& s) {
+__device__ __forceinline__ void sched_entry(const FfnArgs& a, const SchedDims& d, Sched& s) {
   const int lane = threadIdx.x & 63;
   for (;;) {
     s.ok = s.mode <= a.last_mode;
     if (!s.ok) return;
-    const int G = s.mode ? a.m[1].G : a.m[0].G;
+    const int G = s.mode ? d.units1 : d.units0;
     s.w = __builtin_amdgcn_readfirstlane(s.w);
     if (s.w < __shfl(s.chunks, s.t, 64) * G) {
       load_entry(a, s, lane);
@@ -70,16 +67,16 @@ __device__ __forceinline__ void sched_entry(const FfnArgs& a, Sched& s) {
     sched_claim(a, s);
   }
 }
-__device__ __forceinline__ void sched_rows(const FfnArgs& a, Sched& s) {
+__device__ __forceinline__ void sched_rows(const FfnArgs& a, const SchedDims& d, Sched& s) {
   if (!s.ok) return;
-  const int lane = threadIdx.x & 63, G = s.mode ? a.m[1].G : a.m[0].G;
+  const int lane = threadIdx.x & 63, G = s.mode ? d.units1 : d.units0;
   unsigned long long m;
   for (int e0 = 0;; e0 += 64) {  // every claimed unit lies in exactly one entry
     if (e0) load_entry(a, s, e0 + lane);
     m = __ballot(s.w >= s.ent[2] * G && s.w < (s.ent[2] + s.ent[1]) * G);
     if (m || e0 > kPlanMaxEnt) break;
   }
-  const int e = __ffsll((long long)m) - 1;
+  const int e = __ffsll((long long)m) - 1;  // (the first of equal ones)
   const int nch = __shfl(s.ent[1], e, 64), base = __shfl(s.ent[2], e, 64), bts = __shfl(s.ent[3], e, 64), c = __shfl(s.ent[4], e, 64);
   const int i = s.w - base * G, j = i % nch;
   s.slot = __builtin_amdgcn_readfirstlane(__shfl(s.ent[0], e, 64));
@@ -91,24 +88,27 @@ __device__ __forceinline__ void sched_rows(const FfnArgs& a, Sched& s) {
   s.rows = min(bts, c - j * bts);
   s.off = __shfl(s.ent[5], e, 64) + j * bts;
   s.chunk = ((s.home + s.t) & 7) * a.list_chunks + base + j;
+  const bool shared = s.slot >= a.P;
+  s.pairs = s.mode == 0 && !shared;
+  const int first = s.mode == 0 && shared ? s.off - a.rows_routed - (s.slot - a.P) * a.sh_rows : s.off;
 #pragma unroll
   for (int h = 0; h < 4; ++h) {
     const int r = min(lane + 64 * h, s.rows - 1);
-    int src = s.off + r;
-    if (s.mode == 0) src = s.slot >= a.P ? s.off - a.rows_routed - (s.slot - a.P) * a.sh_rows + r : (a.por ? a.por[s.off + r] : s.off + r) / a.k;
-    s.src[h] = (uint32_t)src * (uint32_t)(2 * (s.mode ? a.m[1].K : a.m[0].K));
+    s.src[h] = s.pairs && a.por ? a.por[s.off + r] : first + r;
   }
+  s.stored = s.mode == 0 ? 0 : __hip_atomic_load(a.done + s.chunk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ void sched_publish(const FfnArgs& a, const Sched& s, int32_t* q) {
+__device__ __forceinline__ void sched_publish(const FfnArgs& a, const SchedDims& d, const Sched& s, int32_t* q) {
   const int lane = threadIdx.x & 63;
   if (!s.ok) {
     if (lane == 0) q[0] = -1;
   } else {
+    const uint32_t pitch = (uint32_t)(s.mode ? d.pitch1 : d.pitch0);
 #pragma unroll
-    for (int h = 0; h < 4; ++h) q[8 + 64 * h + lane] = (int32_t)s.src[h];
+    for (int h = 0; h < 4; ++h) q[8 + 64 * h + lane] = (int32_t)((s.pairs ? s.src[h] / (uint32_t)a.k : s.src[h]) * pitch);
     if (lane == 0) {
       q[0] = s.slot; q[1] = s.off; q[2] = s.rows; q[3] = s.g; q[4] = s.mode; q[5] = s.chunk; q[7] = s.how;
-      q[6] = s.mode == 0 || __hip_atomic_load(a.done + s.chunk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= a.m[0].G;
+      q[6] = s.mode == 0 || s.stored >= d.units0;
     }
   }
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -240,6 +240,7 @@ __device__ __forceinline__ void big_body(const FfnArgs& a, unsigned char* s_lds)
   const uint32_t q0 = lds0 + kQOff;
 
   [[maybe_unused]] Sched sc{};
+  [[maybe_unused]] const SchedDims sd = ROLE == 2 ? sched_dims(a) : SchedDims{};
   [[maybe_unused]] int pending = -1;  // scheduler: chunk of the previous unit, counted in the last slab of the present one
   if constexpr (ROLE == 2) {
     sc.home = (int)(blockIdx.x & 7);
@@ -250,9 +251,9 @@ __device__ __forceinline__ void big_body(const FfnArgs& a, unsigned char* s_lds)
       sc.chunks = a.plan[8 + x];
     }
     sched_claim(a, sc);
-    sched_entry(a, sc);
-    sched_rows(a, sc);
-    sched_publish(a, sc, queue);
+    sched_entry(a, sd, sc);
+    sched_rows(a, sd, sc);
+    sched_publish(a, sd, sc, queue);
   }
   __builtin_amdgcn_s_barrier();
   FfnUnit cur = read_unit(q0);
@@ -347,9 +348,9 @@ __device__ __forceinline__ void big_body(const FfnArgs& a, unsigned char* s_lds)
     issue();
   } else if constexpr (ROLE == 2) {
     sched_claim(a, sc);
-    sched_entry(a, sc);
-    sched_rows(a, sc);
-    sched_publish(a, sc, queue + kQI);
+    sched_entry(a, sd, sc);
+    sched_rows(a, sd, sc);
+    sched_publish(a, sd, sc, queue + kQI);
   }
   __builtin_amdgcn_s_barrier();
   nxt = read_unit(q0 + kQI * 4);
@@ -490,10 +491,11 @@ __device__ __forceinline__ void big_body(const FfnArgs& a, unsigned char* s_lds)
             if (lane == 0) __hip_atomic_fetch_add(a.done + pending, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             pending = -1;
           }
+          // One round trip at a time, each used steps after it was started: a wait here is a wait for everyone at the barrier.
           if (kt == 0) sched_claim(a, sc);
-          if (kt == (nk - 2) / 3) sched_entry(a, sc);
-          if (kt == 2 * (nk - 2) / 3) sched_rows(a, sc);
-          if (kt == nk - 2) sched_publish(a, sc, queue + ((seq + 2) & 3) * kQI);
+          if (kt == (nk - 2) / 3) sched_entry(a, sd, sc);
+          if (kt == 2 * (nk - 2) / 3) sched_rows(a, sd, sc);
+          if (kt == nk - 2) sched_publish(a, sd, sc, queue + ((seq + 2) & 3) * kQI);
         } else {
 #pragma unroll
           for (int i = 0; i < (ROLE == 0 ? 2 : 1); ++i) {

@@ -171,7 +171,9 @@ struct Sched {
   int mode, list, home;
   int chunk, g, how;
   i32x4 en;
-  uint32_t src[2];       // byte offsets of the source rows lane, lane + 64 of the chunk
+  int pairs;             // src are pairs, not rows yet
+  int stored;            // what its chunk's completion counter holds
+  uint32_t src[2];       // the source rows lane, lane + 64 of the chunk
 };
 
 __device__ __forceinline__ int32_t* sched_counter(const FfnArgs& a, int mode, int list) {
@@ -182,14 +184,14 @@ __device__ __forceinline__ void sched_claim(const FfnArgs& a, Sched& s) {
 }
 // own: the plan in LDS of a call that routes itself.
 template <typename C, bool ROUTED>
-__device__ __forceinline__ void sched_entry(const FfnArgs& a, const RoutePlan* own, int n_chunks, int whole, Sched& s) {
+__device__ __forceinline__ void sched_entry(const FfnArgs& a, const SchedDims& d, const RoutePlan* own, int n_chunks, int whole, Sched& s) {
   const int lane = threadIdx.x & 63;
   for (;;) {
     if (s.mode > a.last_mode) {
       s.chunk = -1;
       return;
     }
-    const int G = s.mode ? a.m[1].G : a.m[0].G, units = n_chunks * G, n = C::SPLIT && !s.mode ? 2 * units - whole : units;
+    const int G = s.mode ? d.units1 : d.units0, units = n_chunks * G, n = C::SPLIT && !s.mode ? 2 * units - whole : units;
     const int v = __builtin_amdgcn_readfirstlane(s.w) * 8 + s.list;
     if (v < n) {
       int u = v;
@@ -199,7 +201,7 @@ __device__ __forceinline__ void sched_entry(const FfnArgs& a, const RoutePlan* o
         s.how = 1 + ((v - whole) & 1);
       }
       // u / G, without an integer division's chain of instructions in front of the first loads: off by one at most
-      s.chunk = (int)(((float)u + 0.5f) * (s.mode ? a.m[1].inv_g : a.m[0].inv_g));
+      s.chunk = (int)(((float)u + 0.5f) * __builtin_amdgcn_rcpf((float)G));
       s.g = u - s.chunk * G;
       if (s.g < 0) {
         --s.chunk;
@@ -234,29 +236,33 @@ template <int QI, bool ROUTED>
 __device__ __forceinline__ void sched_rows(const FfnArgs& a, const RoutePlan* own, Sched& s) {
   if (s.chunk < 0) return;
   const int slot = s.en[0], rows = s.en[1], off = s.en[2];
+  const bool shared = slot >= a.P;
+  s.pairs = !ROUTED && s.mode == 0 && !shared;
+  const int first = s.mode == 0 && shared ? off - a.rows_routed - (slot - a.P) * a.sh_rows : off;
 #pragma unroll
   for (int h = 0; h < (QI > 72 ? 2 : 1); ++h) {
     const int r = min((int)(threadIdx.x & 63) + 64 * h, rows - 1);
-    int src = off + r;
-    if (s.mode == 0) {
-      if (slot >= a.P) src = off - a.rows_routed - (slot - a.P) * a.sh_rows + r;
-      else if constexpr (ROUTED) src = own->token[off + r];
-      else src = (a.por ? a.por[off + r] : off + r) / a.k;
+    s.src[h] = first + r;
+    if (ROUTED) {
+      if (s.mode == 0 && !shared) s.src[h] = own->token[off + r];
+    } else if (s.pairs && a.por) {
+      s.src[h] = a.por[off + r];
     }
-    s.src[h] = (uint32_t)src * (uint32_t)(2 * (s.mode ? a.m[1].K : a.m[0].K));
   }
+  s.stored = s.mode == 0 ? 0 : __hip_atomic_load(a.done + s.chunk * kDecDoneStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 template <int QI>
-__device__ __forceinline__ void sched_publish(const FfnArgs& a, const Sched& s, int32_t* q) {
+__device__ __forceinline__ void sched_publish(const FfnArgs& a, const SchedDims& d, const Sched& s, int32_t* q) {
   const int lane = threadIdx.x & 63;
   if (s.chunk < 0) {
     if (lane == 0) q[0] = -1;
   } else {
-    q[8 + lane] = (int32_t)s.src[0];
-    if (QI > 72) q[8 + 64 + lane] = (int32_t)s.src[1];
+    const uint32_t pitch = (uint32_t)(s.mode ? d.pitch1 : d.pitch0);
+#pragma unroll
+    for (int h = 0; h < (QI > 72 ? 2 : 1); ++h) q[8 + 64 * h + lane] = (int32_t)((s.pairs ? s.src[h] / (uint32_t)a.k : s.src[h]) * pitch);
     if (lane == 0) {
       q[0] = s.en[0]; q[1] = s.en[2]; q[2] = s.en[1]; q[3] = s.g; q[4] = s.mode; q[5] = s.chunk; q[7] = s.how;
-      q[6] = s.mode == 0 || __hip_atomic_load(a.done + s.chunk * kDecDoneStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= kDone * a.m[0].G;
+      q[6] = s.mode == 0 || s.stored >= kDone * d.units0;
     }
   }
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -278,6 +284,7 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, const Routed<DecCfg<N
   const uint32_t q0 = lds0 + C::Q_OFF;
 
   [[maybe_unused]] Sched sc{};
+  [[maybe_unused]] const SchedDims sd = ROLE == 2 ? sched_dims(a) : SchedDims{};
   [[maybe_unused]] int n_chunks = 0, whole = 0;  // whole: units of the first product that are not split
   [[maybe_unused]] bool both = false;            // the first two units are looked up together
   [[maybe_unused]] int pending = -1, pending_by = 0;  // scheduler: chunk of the previous unit, counted inside the slab loop of the present one
@@ -296,12 +303,12 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, const Routed<DecCfg<N
     s0.mode = a.first_mode;
     if constexpr (ROUTED) s0.w = rt.claim;
     else sched_claim(a, s0);
-    sched_entry<C, ROUTED>(a, own, n_chunks, whole, s0);
+    sched_entry<C, ROUTED>(a, sd, own, n_chunks, whole, s0);
     sc = s0;
     if (both) sched_claim(a, sc);
     sched_rows<C::QI, ROUTED>(a, own, s0);
-    if (both && !ROUTED) sched_entry<C, ROUTED>(a, own, n_chunks, whole, sc);
-    sched_publish<C::QI>(a, s0, queue);
+    if (both && !ROUTED) sched_entry<C, ROUTED>(a, sd, own, n_chunks, whole, sc);
+    sched_publish<C::QI>(a, sd, s0, queue);
   }
   __builtin_amdgcn_s_barrier();
   FfnUnit cur = read_unit(q0);
@@ -411,9 +418,9 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, const Routed<DecCfg<N
     for (int i = 0; i < depth - 1; ++i) issue();
   } else if constexpr (ROLE == 2) {
     if (!both) sched_claim(a, sc);
-    if (!both || ROUTED) sched_entry<C, ROUTED>(a, own, n_chunks, whole, sc);
+    if (!both || ROUTED) sched_entry<C, ROUTED>(a, sd, own, n_chunks, whole, sc);
     sched_rows<C::QI, ROUTED>(a, own, sc);
-    sched_publish<C::QI>(a, sc, queue + C::QI);
+    sched_publish<C::QI>(a, sd, sc, queue + C::QI);
   }
   __builtin_amdgcn_s_barrier();
   nxt = read_unit(q0 + C::QI * 4);
@@ -495,11 +502,12 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, const Routed<DecCfg<N
           if (lane == 0) __hip_atomic_fetch_add(a.done + pending * kDecDoneStride, pending_by, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           pending = -1;
         }
-        // the unit after the next: one round trip at a time, spread over this unit's slabs
+        // the unit after the next: one round trip at a time, each used steps after it was started (a wait here is a wait for everyone at
+        // the barrier)
         if (kt == 0) sched_claim(a, sc);
-        if (kt == (nk - 2) / 3) sched_entry<C, ROUTED>(a, own, n_chunks, whole, sc);
+        if (kt == (nk - 2) / 3) sched_entry<C, ROUTED>(a, sd, own, n_chunks, whole, sc);
         if (kt == 2 * (nk - 2) / 3) sched_rows<C::QI, ROUTED>(a, own, sc);
-        if (kt == nk - 2) sched_publish<C::QI>(a, sc, queue + ((seq + 2) & 3) * C::QI);
+        if (kt == nk - 2) sched_publish<C::QI>(a, sd, sc, queue + ((seq + 2) & 3) * C::QI);
       } else if constexpr (LOADS) {
         if (!p_next && p_k == nk && nxt.slot >= 0 && !(ROLE == 1 && change)) {
           if (ROLE == 1) wait_done(nxt, (seq + 1) & 3);
@@ -593,7 +601,6 @@ int launch(FfnArgs a, const FfnPlanShape& sh, int n_cu, hipStream_t st, [[maybe_
   using C = DecCfg<NTF, MR>;
   a.m[0].G = a.m[0].NOUT / (MR / 2);
   a.m[1].G = a.m[1].NOUT / MR;
-  for (FfnProd& m : a.m) m.inv_g = 1.f / (float)m.G;
   const int nk = (a.m[0].K < a.m[1].K ? a.m[0].K : a.m[1].K) / C::SK;  // >= 2
   a.depth_w = C::DW < nk ? C::DW : nk;
   a.depth_t = C::DT < nk ? C::DT : nk;

@@ -125,8 +125,8 @@ int launch_ffn_bf16(const void* x, int rows_routed, int k, int H, int I, int P, 
     if (rc != EW_OK) return rc;
   }
   FfnArgs a{};
-  a.m[0] = FfnProd{(const uint16_t*)x, (const uint16_t*)w13, (const uint16_t*)w13_sh, (uint16_t*)act, (size_t)2 * I * H, H, I, 0, 0.f};
-  a.m[1] = FfnProd{(const uint16_t*)act, (const uint16_t*)w2, (const uint16_t*)w2_sh, (uint16_t*)y, (size_t)H * I, I, H, 0, 0.f};
+  a.m[0] = FfnProd{(const uint16_t*)x, (const uint16_t*)w13, (const uint16_t*)w13_sh, (uint16_t*)act, (size_t)2 * I * H, H, I, 0};
+  a.m[1] = FfnProd{(const uint16_t*)act, (const uint16_t*)w2, (const uint16_t*)w2_sh, (uint16_t*)y, (size_t)H * I, I, H, 0};
   a.por = por; a.plan = plan; a.done = plan + sh.done_off;
   a.P = P; a.rows_routed = rows_routed; a.sh_rows = T > 0 ? T : 1; a.k = k;
   a.cap = sh.cap; a.list_chunks = sh.ch * sh.cap;

@@ -20,7 +20,6 @@ struct FfnProd {
   uint16_t* out;       // [rows, NOUT]
   size_t slot_stride;  // elements per slot
   int K, NOUT, G;      // G: units per chunk
-  float inv_g;         // k_ffn_dec: 1 / G
 };
 
 struct FfnArgs {
@@ -89,6 +88,19 @@ __device__ __forceinline__ int32_t claim_next(int32_t* counter) {
   uint32_t at = 0;
   asm volatile("" : "+v"(at));
   return __hip_atomic_fetch_add(reinterpret_cast<int32_t*>(reinterpret_cast<char*>(counter) + at), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// What a scheduling wave needs of the two products, in registers: selected by product out of the arguments it would be a load each
+// time, from memory and waited for.
+struct SchedDims {
+  int units0, units1;  // per chunk
+  int pitch0, pitch1;  // bytes of a source row
+};
+__device__ __forceinline__ int in_sgpr(int v) {
+  asm volatile("" : "+s"(v));
+  return v;
+}
+__device__ __forceinline__ SchedDims sched_dims(const FfnArgs& a) {
+  return {in_sgpr(a.m[0].G), in_sgpr(a.m[1].G), in_sgpr(2 * a.m[0].K), in_sgpr(2 * a.m[1].K)};
 }
 // N ints STEP bytes apart (N: 1, 2 or a multiple of 4).
 template <int N, int STEP>
