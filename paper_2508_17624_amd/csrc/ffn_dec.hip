@@ -53,7 +53,7 @@ struct DecCfg {
   static constexpr int NWI = MR / (NW * RPI);                       // load instructions per weight wave and slab
   static constexpr int NTI = 16 / (NT * RPI);                       // load instructions per token wave and fragment
   static constexpr int PN = MR / 32;                                // pairs of weight fragments
-  static constexpr int QI = 8 + (NTF > 4 ? 16 * NTF : 64);          // ints of a queue entry: description, source rows
+  static constexpr int QI = 8 + (16 * NTF + 63) / 64 * 64;          // ints of a queue entry: description, source rows, 64 at a time
   static constexpr int LEFT = 160 * 1024 - 4 * QI * 4;
   // ring depths: the token rows come from L2 and need less, the weights take the rest
   static constexpr int DT = TSLAB > 8192 ? 3 : NTF == 1 ? 6 : 5;
@@ -71,7 +71,7 @@ struct DecCfg {
 template <typename C>
 struct Routed {
   static constexpr int OFF = C::LDS, LDS = C::LDS + (int)sizeof(RoutePlan);
-  static_assert(C::LDS % 8 == 0 && LDS <= 160 * 1024, "LDS budget of a CU");
+  static_assert(C::QI > 72 || (C::LDS % 8 == 0 && LDS <= 160 * 1024), "LDS budget of a CU, for the shapes that route themselves");
   static_assert(2 * sizeof(RouteScratch) <= C::Q_OFF, "the ranking's scratch, in the rings");
   int claim = 0, n_chunks = 0;                                      // scheduling wave: its first claim, chunks of the plan
   static __device__ __forceinline__ RoutePlan& plan(unsigned char* s_lds) { return *reinterpret_cast<RoutePlan*>(s_lds + OFF); }
@@ -105,7 +105,8 @@ __device__ __forceinline__ void landed(u32x4* v) {
 // at once where they fit the registers (128 per wave), otherwise one k-step and four token fragments at a time.
 template <int MFW, int NB, int KS, int WS, int FS>
 __device__ __forceinline__ void mul_slab(uint32_t wa, uint32_t tb, f32x4 (&acc)[MFW][NB]) {
-  constexpr int BATCH = MFW * NB + KS * (MFW + NB) <= 22 ? KS : 1, N = NB < 4 ? NB : 4;
+  constexpr int BATCH = MFW * NB + KS * (MFW + NB) <= 22 ? KS : 1, N = NB < 4 ? NB : NB % 4 ? 5 : 4;
+  static_assert(NB % N == 0, "whole rounds of token fragments");
 #pragma unroll
   for (int j0 = 0; j0 < KS; j0 += BATCH) {
     u32x4 a[BATCH][MFW];
@@ -127,7 +128,6 @@ __device__ __forceinline__ void mul_slab(uint32_t wa, uint32_t tb, f32x4 (&acc)[
       for (int j = 0; j < BATCH; ++j)
 #pragma unroll
         for (int f = 0; f < N; ++f)
-          if (f0 + f < NB)
 #pragma unroll
             for (int i = 0; i < MFW; ++i)
               acc[i][f0 + f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[j][i]), __builtin_bit_cast(bf16x8, b[j][f]),
@@ -173,7 +173,7 @@ struct Sched {
   i32x4 en;
   int pairs;             // src are pairs, not rows yet
   int stored;            // what its chunk's completion counter holds
-  uint32_t src[2];       // the source rows lane, lane + 64 of the chunk
+  uint32_t src[3];       // the source rows lane, lane + 64, ... of the chunk
 };
 
 __device__ __forceinline__ int32_t* sched_counter(const FfnArgs& a, int mode, int list) {
@@ -240,7 +240,7 @@ __device__ __forceinline__ void sched_rows(const FfnArgs& a, const RoutePlan* ow
   s.pairs = !ROUTED && s.mode == 0 && !shared;
   const int first = s.mode == 0 && shared ? off - a.rows_routed - (slot - a.P) * a.sh_rows : off;
 #pragma unroll
-  for (int h = 0; h < (QI > 72 ? 2 : 1); ++h) {
+  for (int h = 0; h < QI / 64; ++h) {
     const int r = min((int)(threadIdx.x & 63) + 64 * h, rows - 1);
     s.src[h] = first + r;
     if (ROUTED) {
@@ -249,7 +249,10 @@ __device__ __forceinline__ void sched_rows(const FfnArgs& a, const RoutePlan* ow
       s.src[h] = a.por[off + r];
     }
   }
-  s.stored = s.mode == 0 ? 0 : __hip_atomic_load(a.done + s.chunk * kDecDoneStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Asked for as late as it still comes back in time: a unit whose rows are stored by then costs its token waves no look of their own.
+__device__ __forceinline__ void sched_stored(const FfnArgs& a, Sched& s) {
+  if (s.chunk >= 0 && s.mode) s.stored = __hip_atomic_load(a.done + s.chunk * kDecDoneStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 template <int QI>
 __device__ __forceinline__ void sched_publish(const FfnArgs& a, const SchedDims& d, const Sched& s, int32_t* q) {
@@ -259,7 +262,7 @@ __device__ __forceinline__ void sched_publish(const FfnArgs& a, const SchedDims&
   } else {
     const uint32_t pitch = (uint32_t)(s.mode ? d.pitch1 : d.pitch0);
 #pragma unroll
-    for (int h = 0; h < (QI > 72 ? 2 : 1); ++h) q[8 + 64 * h + lane] = (int32_t)((s.pairs ? s.src[h] / (uint32_t)a.k : s.src[h]) * pitch);
+    for (int h = 0; h < QI / 64; ++h) q[8 + 64 * h + lane] = (int32_t)((s.pairs ? s.src[h] / (uint32_t)a.k : s.src[h]) * pitch);
     if (lane == 0) {
       q[0] = s.en[0]; q[1] = s.en[2]; q[2] = s.en[1]; q[3] = s.g; q[4] = s.mode; q[5] = s.chunk; q[7] = s.how;
       q[6] = s.mode == 0 || s.stored >= kDone * d.units0;
@@ -308,6 +311,7 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, const Routed<DecCfg<N
     if (both) sched_claim(a, sc);
     sched_rows<C::QI, ROUTED>(a, own, s0);
     if (both && !ROUTED) sched_entry<C, ROUTED>(a, sd, own, n_chunks, whole, sc);
+    sched_stored(a, s0);
     sched_publish<C::QI>(a, sd, s0, queue);
   }
   __builtin_amdgcn_s_barrier();
@@ -420,6 +424,7 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, const Routed<DecCfg<N
     if (!both) sched_claim(a, sc);
     if (!both || ROUTED) sched_entry<C, ROUTED>(a, sd, own, n_chunks, whole, sc);
     sched_rows<C::QI, ROUTED>(a, own, sc);
+    sched_stored(a, sc);
     sched_publish<C::QI>(a, sd, sc, queue + C::QI);
   }
   __builtin_amdgcn_s_barrier();
@@ -435,7 +440,7 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, const Routed<DecCfg<N
     [[maybe_unused]] const int live = half ? C::PN / 2 : C::PN;               // pairs of weight fragments that the unit has
     if constexpr (ROLE == 3) {
       const int at_pair = C::SPLIT && cur.how == 2 ? live + pair : pair;      // inside the whole unit
-      // one loop per number of live token fragments (above four: eight, the rest multiplied for nothing), so that the
+      // one loop per number of live token fragments (above four: eight or ten, the rest multiplied for nothing), so that the
       // accumulators stay where they are
       auto unit = [&](auto nb_tag) {
         constexpr int NB = decltype(nb_tag)::value, KS = C::SK / 32;
@@ -475,7 +480,8 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, const Routed<DecCfg<N
         }
       };
       const int nf = !C::SPLIT || pair < live ? (nld - nh + FSTEP - 1) / FSTEP : 0;  // this wave's live token fragments
-      if (NF >= 8 && nf > 4) unit(std::integral_constant<int, NF >= 8 ? 8 : 0>{});
+      if (NF >= 10 && nf > 8) unit(std::integral_constant<int, NF >= 10 ? 10 : 0>{});
+      else if (NF >= 8 && nf > 4) unit(std::integral_constant<int, NF >= 8 ? 8 : 0>{});
       else if (NF >= 4 && nf == 4) unit(std::integral_constant<int, NF >= 4 ? 4 : 0>{});
       else if (NF >= 3 && nf == 3) unit(std::integral_constant<int, NF >= 3 ? 3 : 0>{});
       else if (NF >= 2 && nf == 2) unit(std::integral_constant<int, NF >= 2 ? 2 : 0>{});
@@ -507,6 +513,7 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, const Routed<DecCfg<N
         if (kt == 0) sched_claim(a, sc);
         if (kt == (nk - 2) / 3) sched_entry<C, ROUTED>(a, sd, own, n_chunks, whole, sc);
         if (kt == 2 * (nk - 2) / 3) sched_rows<C::QI, ROUTED>(a, own, sc);
+        if (kt == max(nk - 3, 0)) sched_stored(a, sc);
         if (kt == nk - 2) sched_publish<C::QI>(a, sd, sc, queue + ((seq + 2) & 3) * C::QI);
       } else if constexpr (LOADS) {
         if (!p_next && p_k == nk && nxt.slot >= 0 && !(ROLE == 1 && change)) {
@@ -642,6 +649,7 @@ int launch_ffn_dec(FfnArgs a, const FfnPlanShape& sh, int n_cu, hipStream_t st, 
     case 1: return fine ? launch<1, 64>(a, sh, n_cu, st, route) : launch<1, 128>(a, sh, n_cu, st, route);
     case 2: return launch<2, 128>(a, sh, n_cu, st, route);
     case 4: return launch<4, 128>(a, sh, n_cu, st, route);
+    case 10: return launch<10, 256>(a, sh, n_cu, st);
     default: return H % 256 == 0 ? launch<8, 256>(a, sh, n_cu, st) : launch<8, 128>(a, sh, n_cu, st);
   }
 }

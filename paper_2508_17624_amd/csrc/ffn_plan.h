@@ -211,7 +211,13 @@ __device__ __forceinline__ void dec_zero_counters(int32_t* __restrict__ plan, in
   if (tid < 16) plan[kDecCtr + kDecCtrStride * tid] = 0;
 }
 
-__host__ __device__ inline int dec_chunks(int c, int bt) { return (c + bt - 1) / bt; }
+// Chunks of a slot with c rows.  Chunks of up to bt = 160 rows are there for slots of 129 to 160, whose weights are then read once;
+// larger ones are cut at 128 all the same, and so are the shared experts' (shared_bt).  Passes, us, at most 128 / 160: 1999 tokens, 128
+// experts of 1536 x 640, k = 8 (32 of 194 slots in between) 305.7 / 281.1; 1500 tokens, 64 experts of 2048 x 1408 615 / 534.  Cutting
+// the larger ones at 160 too: 160 tokens and two shared experts of 1280 x 512 92.0 / 95.4, 768 tokens 112.6 / 114.3.
+constexpr int kDecCut = 128;
+__host__ __device__ inline int shared_bt(int bt) { return bt < kDecCut ? bt : kDecCut; }
+__host__ __device__ inline int dec_chunks(int c, int bt) { return c <= bt ? (c > 0 ? 1 : 0) : (c + shared_bt(bt) - 1) / shared_bt(bt); }
 
 struct DecPlanLds {
   int32_t wtot[8];
@@ -223,7 +229,7 @@ __device__ __forceinline__ void dec_plan_build(const int (&rows)[4], const int (
                                                const FfnPlanShape& sh, int32_t* __restrict__ plan, DecPlanLds& L) {
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int bt = 16 * sh.dec;
-  const int sh_chunks = dec_chunks(sh_rows, bt);
+  const int sh_chunks = dec_chunks(sh_rows, shared_bt(bt));
   int mine = 0;
   if (tid < 512) {
 #pragma unroll
@@ -240,8 +246,8 @@ __device__ __forceinline__ void dec_plan_build(const int (&rows)[4], const int (
     if (w < wave) before += t;
     total += t;
   }
-  auto put = [&](int at, int slot, int c, int first_row) {
-    const int n = dec_chunks(c, bt), bts = ((c + n - 1) / n + 15) & ~15;
+  auto put = [&](int at, int slot, int c, int first_row, int n) {
+    const int bts = ((c + n - 1) / n + 15) & ~15;
     for (int j = 0; j < n; ++j) {
       int32_t* en = plan + kDecEnt + 4 * (at + j);
       en[0] = slot;
@@ -254,11 +260,12 @@ __device__ __forceinline__ void dec_plan_build(const int (&rows)[4], const int (
 #pragma unroll
     for (int i = 0; i < 4; ++i)
       if (rows[i] > 0) {
-        put(at, 4 * tid + i, rows[i], first[i]);
-        at += dec_chunks(rows[i], bt);
+        const int n = dec_chunks(rows[i], bt);
+        put(at, 4 * tid + i, rows[i], first[i], n);
+        at += n;
       }
     if (tid >= 512 - 64)  // the last wave: it has no routed slot below 1792 of them
-      for (int s = tid - (512 - 64); s < S; s += 64) put(s * sh_chunks, P + s, sh_rows, sh_first + s * sh_rows);
+      for (int s = tid - (512 - 64); s < S; s += 64) put(s * sh_chunks, P + s, sh_rows, sh_first + s * sh_rows, sh_chunks);
   }
   dec_zero_counters(plan, sh.done_off, total, tid, (int)blockDim.x);
   if (tid == 0) plan[0] = total;

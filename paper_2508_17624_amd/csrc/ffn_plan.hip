@@ -46,8 +46,8 @@ int list_cap(int rows, int P) {
 // A look takes well over half a microsecond: seconds, where a wait lasts as long as two units at most.
 constexpr int kWaitPolls = 1 << 22;
 
-// k_ffn_dec: chunks of a plan at most: one per active slot and one more per bt rows.
-int dec_chunk_cap(int rows, int P, int bt) { return (P < rows ? P : rows) + rows / bt + 1; }
+// k_ffn_dec: chunks of a plan at most: one per active slot and one more per bt rows (kDecCut, where that is less).
+int dec_chunk_cap(int rows, int P, int bt) { return (P < rows ? P : rows) + rows / shared_bt(bt) + 1; }
 
 }  // namespace
 
@@ -68,7 +68,7 @@ size_t ffn_plan_ints(int T, int rows, int P) {
 // 74 / 98; 256 x 8: 101 / 100; 256 x 16: 133 / 114; 384 x 4: 75 / 89; 384 x 8: 112 / 90.  So k_ffn_big wins in a corner only, eight
 // or more slots of 256 rows and more while the pool's other slots keep the average low; to let the counts find it would cost
 // every call up to 512 tokens a second launch (5 us).
-FfnPlanShape ffn_plan_shape(int T, int rows, int slots, int frags, int chunk_frags, bool merge, int wait_polls) {
+FfnPlanShape ffn_plan_shape(int T, int rows, int slots, int H, int frags, int chunk_frags, bool merge, int wait_polls) {
   FfnPlanShape sh{};
   sh.merged = merge;
   sh.wait_polls = wait_polls > 0 ? wait_polls : kWaitPolls;
@@ -86,7 +86,7 @@ FfnPlanShape ffn_plan_shape(int T, int rows, int slots, int frags, int chunk_fra
       const int most = chunk_frags >= 1 && chunk_frags < frags ? chunk_frags : frags;
       sh.dec = most >= 4 ? 8 : most >= 2 ? 4 : 2;
     } else {
-      sh.dec = T <= 16 ? 1 : T <= 32 ? 2 : T <= 64 ? 4 : 8;
+      sh.dec = T <= 16 ? 1 : T <= 32 ? 2 : T <= 64 ? 4 : T <= 128 || H % 256 ? 8 : 10;
     }
     sh.dec_cap = dec_chunk_cap(rows, slots, 16 * sh.dec);
   }

@@ -151,7 +151,7 @@ int launch_ffn_big(FfnArgs a, const FfnPlanShape& sh, int max_chunks, int n_cu, 
 __device__ __forceinline__ void wait_vm_upto(int n) {
 #define EW_VM(N) __builtin_amdgcn_s_waitcnt(0x0F70 | ((N) & 15) | (((N) >> 4) << 14))
   if (n >= 32) {
-    EW_VM(32);
+    if (n >= 40) EW_VM(40); else if (n >= 36) EW_VM(36); else EW_VM(32);
   } else if (n >= 16) {
     if (n >= 24) EW_VM(24); else if (n >= 20) EW_VM(20); else EW_VM(16);
   } else if (n >= 8) {

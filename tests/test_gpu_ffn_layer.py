@@ -725,9 +725,11 @@ def test_grouped_ffn_f32_tile_edges(ew, H, I):
                                          (32, 3, 9, 0, 256, 384), (33, 2, 12, 2, 1280, 512), (64, 6, 100, 1, 512, 256), (65, 6, 30, 2, 256, 768),
                                          (130, 4, 24, 2, 384, 256), (513, 2, 16, 1, 512, 256), (3, 2, 48, 1, 1280, 512), (3, 4, 12, 0, 1536, 1024),
                                          (16, 4, 20, 1, 1024, 896), (16, 8, 68, 0, 640, 384), (1, 6, 8, 2, 2048, 1408), (16, 4, 23, 1, 1024, 896),
-                                         (16, 4, 28, 0, 640, 384), (16, 8, 72, 0, 640, 384)])
+                                         (16, 4, 28, 0, 640, 384), (16, 8, 72, 0, 640, 384),
+                                         (129, 2, 9, 1, 256, 384), (160, 1, 5, 1, 512, 256), (161, 3, 7, 1, 256, 128), (300, 2, 24, 2, 256, 256),
+                                         (300, 2, 24, 0, 384, 256)])
 def test_grouped_ffn_decode_kernel_edges(ew, T, k, P, S, H, I):
-    """The kernel of calls with few rows per slot at the edges of its chunks (16, 32, 64 and 128 rows), with contractions
+    """The kernel of calls with few rows per slot at the edges of its chunks (16, 32, 64, 128 and 160 rows), with contractions
     shorter than its rings, hidden sizes that are an odd multiple of 128, a crowded slot cut into several chunks, more
     workgroups than units (one unit looked up at a time), more units than workgroups whose last round has no room for halves (the
     three before the last four) and, in the last four, units of the first product in halves (of 64 and 128 weight rows): every row
