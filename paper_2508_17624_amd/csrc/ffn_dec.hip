@@ -2,7 +2,7 @@
 //
 // With a handful of rows per slot both products are a pure weight stream (17 MB per active expert at the 2048/1408 shape),
 // so what counts is that every CU has enough bytes in flight from the first microsecond to the last.
-//   * A unit is 64, 128 or 256 weight rows of one slot's chunk of token rows.  The units of a workgroup form ONE stream of
+//   * A unit is 64, 128 or 256 weight rows of one slot's chunk of 16 to 160 token rows.  The units of a workgroup form ONE stream of
 //     slabs (16 or 32 KB of weights): the LDS rings keep filling across unit boundaries, nothing drains between two units.
 //   * Loading and multiplying are different waves.  An LDS-direct load stalls its wave while the CU's queue of outstanding
 //     lines is full, which here is most of the time; a wave that also multiplied would multiply late, and with it everyone
@@ -20,7 +20,8 @@
 //   * Coherence of the activations: agent-scope stores, acknowledged before they are counted; for the loads see kHalfLines.
 // Measured (call with plan, one card): 1 token on 8 experts of 2048 x 1408: 76 -> 43 us (kernel alone now 37.4 -> 34.7); 13 tokens
 // on 36 of 1024 x 896: 88 -> 47 us (42.2 -> 40.2); 64 tokens on 90: 263 -> 246 us (6.3 TB/s of weights; a bare stream of the same slabs reaches 6.85); 512 tokens on
-// 242: 699 -> 682 us; 512 on 150 of 1536 x 640: 182 -> 161 us; 2000 on 217 of those: 328 -> 257 us.
+// 242: 699 -> 682 us; 512 on 150 of 1536 x 640: 182 -> 161 us; 2000 on 194 of those: 328 -> 257 us, with chunks of up to 160 rows
+// 257 -> 228.  Calls of layer passes of up to 64 tokens route themselves too (ffn_route.h).
 //
 // Waves: NW load weights, NT token rows, each into a ring of its own (the vector-memory counter retires in order, so each
 // ring is awaited at its own depth), one schedules, eight multiply (v_mfma_f32_16x16x32_bf16).

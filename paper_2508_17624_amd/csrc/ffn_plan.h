@@ -77,8 +77,8 @@ struct FfnPlanShape {
   int wait_polls;    // looks at a completion counter before a wait is given up
 };
 
-// Both candidates: k_ffn_big runs where an active slot has more rows on average than a chunk of k_ffn_dec takes (beyond that
-// it reads weights twice).  Measured (us, k_ffn_dec / k_ffn_big, at rows per active slot): 68: 819 / 846; 74: 256 / 273;
+// Both candidates: k_ffn_big runs where an active slot has more rows on average than k_ffn_dec takes at once with certainty (beyond that
+// it reads weights of more and more slots twice).  Measured, k_ffn_dec with chunks of 128 rows (us, k_ffn_dec / k_ffn_big, at rows per active slot): 68: 819 / 846; 74: 256 / 273;
 // 124: 271 / 278; 135: 1001 / 942; 148: 493 / 318; 248: 492 / 353.  The kernel that is not chosen costs
 // a launch (5 us); both bodies in one kernel did not fit the registers.
 constexpr int kPickRows = 128;

@@ -1,6 +1,6 @@
 // Grouped SwiGLU expert FFN in bf16: the choice between the two kernels that stream both operands into LDS, their work
 // plans and the call itself.
-//   k_ffn_dec (ffn_dec.hip)  few rows per slot: a stream of weights, chunks of at most 128 rows
+//   k_ffn_dec (ffn_dec.hip)  few rows per slot: a stream of weights, chunks of at most 160 rows
 //   k_ffn_big (ffn_big.hip)  many rows per slot: matrix-core bound, chunks of at most 256 rows
 // Any counts are correct with either: larger slots are cut into chunks.
 #include "ffn_roles.h"
@@ -67,7 +67,7 @@ size_t ffn_plan_ints(int T, int rows, int P) {
 // active slot x slots): 48 x 64: 203 / 290; 64 x 32: 117 / 151; 128 x 4: 66 / 94; 128 x 16: 105 / 110; 192 x 8: 92 / 89; 256 x 4:
 // 74 / 98; 256 x 8: 101 / 100; 256 x 16: 133 / 114; 384 x 4: 75 / 89; 384 x 8: 112 / 90.  So k_ffn_big wins in a corner only, eight
 // or more slots of 256 rows and more while the pool's other slots keep the average low; to let the counts find it would cost
-// every call up to 512 tokens a second launch (5 us).
+// every call up to 512 tokens a second launch (5 us).  (k_ffn_dec with chunks of 128 rows; with 160 it is the faster one a little further up.)
 FfnPlanShape ffn_plan_shape(int T, int rows, int slots, int H, int frags, int chunk_frags, bool merge, int wait_polls) {
   FfnPlanShape sh{};
   sh.merged = merge;

@@ -1,5 +1,5 @@
 // One pass of a MoE layer as one host call: router scores -> fused top-k + rerouting + permutation (+ the grouped FFN's
-// work plan) -> routed and shared experts -> combine.  The caller describes the layer once (ew_layer: dimensions, weights,
+// work plan) -> routed and shared experts -> combine; for few tokens the steps between scores and combine are one launch.  The caller describes the layer once (ew_layer: dimensions, weights,
 // work buffers); a pass then costs one crossing from the caller's language instead of four with sixteen arguments each,
 // which took longer than the GPU work of a small layer (configuration 0: 119 us of host time per pass, most of it the
 // second stream and events that the shared experts' own calls needed).

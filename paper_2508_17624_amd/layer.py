@@ -8,7 +8,8 @@ moe_layer_forward, which runs
     moe_grouped_ffn_planned (routed experts on the pool's virtual weight tensors and the shared
     experts, one launch) -> moe_unpermute (+ residual; in a stack also the next layer's norm)
 
-(fp32 layers the same steps with kernels of their own).
+(bf16 passes of up to 64 tokens: the second and third of them in one launch; fp32 layers: the same steps with kernels of
+their own).
 """
 from __future__ import annotations
 
