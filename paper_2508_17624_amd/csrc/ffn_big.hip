@@ -20,7 +20,6 @@ constexpr int kQI = 8 + 256;               // ints of a queue entry
 constexpr int kTOff = kWRing * kHalf, kQOff = kTOff + kTRing * kTSlab, kLds = kQOff + 4 * kQI * 4;
 static_assert(kLds <= 160 * 1024, "LDS budget of a CU");
 constexpr int kAlone = 1;                  // FfnUnit::how: no other chunk reads this unit's weights
-constexpr int kGap = 2;                    // slabs between two steps of the scheduler's look at a unit
 constexpr int kThreads = 768;              // waves 0-1 load weights, 2 token rows, 3 schedules, 4-11 multiply
 
 __device__ __forceinline__ int swz(int r) { return ((r >> 1) ^ ((r & 1) << 2)) & 7; }
@@ -497,15 +496,15 @@ __device__ __forceinline__ void big_body(const FfnArgs& a, unsigned char* s_lds)
             if (lane == 0) __hip_atomic_fetch_add(a.done + pending, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             pending = -1;
           }
-          // One round trip at a time, each used kGap slabs (2.5 to 3 us) after it was started: a wait here is a wait for everyone at the
-          // barrier.  Claimed as late as that allows: a workgroup that is behind otherwise still takes two more units at the end.  Claims in
-          // slab 0 / now, passes, us: 1700 tokens on 107 slots of 1280 x 512 151 / 136, 2200 156 / 146; 1700 on 80 of 2048 x 1408 344 / 342.
-          const int gap = min((nk - 2) / 3, kGap), at = kt - (nk - 2);
-          if (at == -3 * gap) sched_claim(a, sc);
-          if (at == -2 * gap) sched_entry(a, sd, sc);
-          if (at == -gap) sched_rows(a, sd, sc);
-          if (kt == max(nk - 3, 0)) sched_stored(a, sc);
-          if (kt == nk - 2) sched_publish(a, sd, sc, queue + ((seq + 2) & 3) * kQI);
+          // One round trip at a time, each used slabs after it was started where the unit has eight or more of them: a wait here is a wait for
+          // everyone at the barrier.  Claimed as late as that allows: a workgroup that is behind otherwise still takes two more units at the end.
+          // Claims in slab 0 / now, passes, us: 1700 tokens on 107 slots of 1280 x 512 151 / 136, 2200 156 / 146; 1700 on 80 of 2048 x 1408 344 / 342.
+          const SchedSteps at = steps_late(nk);
+          if (kt == at.claim) sched_claim(a, sc);
+          if (kt == at.entry) sched_entry(a, sd, sc);
+          if (kt == at.rows) sched_rows(a, sd, sc);
+          if (kt == at.stored) sched_stored(a, sc);
+          if (kt == at.publish) sched_publish(a, sd, sc, queue + ((seq + 2) & 3) * kQI);
         } else {
 #pragma unroll
           for (int i = 0; i < (ROLE == 0 ? 2 : 1); ++i) {

@@ -511,11 +511,12 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, const Routed<DecCfg<N
         }
         // the unit after the next: one round trip at a time, each used steps after it was started (a wait here is a wait for everyone at
         // the barrier)
-        if (kt == 0) sched_claim(a, sc);
-        if (kt == (nk - 2) / 3) sched_entry<C, ROUTED>(a, sd, own, n_chunks, whole, sc);
-        if (kt == 2 * (nk - 2) / 3) sched_rows<C::QI, ROUTED>(a, own, sc);
-        if (kt == max(nk - 3, 0)) sched_stored(a, sc);
-        if (kt == nk - 2) sched_publish<C::QI>(a, sd, sc, queue + ((seq + 2) & 3) * C::QI);
+        const SchedSteps at = steps_spread(nk);
+        if (kt == at.claim) sched_claim(a, sc);
+        if (kt == at.entry) sched_entry<C, ROUTED>(a, sd, own, n_chunks, whole, sc);
+        if (kt == at.rows) sched_rows<C::QI, ROUTED>(a, own, sc);
+        if (kt == at.stored) sched_stored(a, sc);
+        if (kt == at.publish) sched_publish<C::QI>(a, sd, sc, queue + ((seq + 2) & 3) * C::QI);
       } else if constexpr (LOADS) {
         if (!p_next && p_k == nk && nxt.slot >= 0 && !(ROLE == 1 && change)) {
           if (ROLE == 1) wait_done(nxt, (seq + 1) & 3);

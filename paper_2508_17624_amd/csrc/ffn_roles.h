@@ -2,6 +2,7 @@
 // ffn_big.hip): argument structs, LDS accesses and waits placed by hand.
 #pragma once
 #include "ew_internal.h"
+#include "ffn_steps.h"
 
 #include <type_traits>
 

@@ -312,6 +312,44 @@ def test_one_launch_of_the_many_rows_kernel_equals_two(ew, T, k, P, S, H, I):
         assert rel_l2(got[r0:r1], want) <= FFN_REL_L2 and max_abs(got[r0:r1], want) <= FFN_MAX_ABS, f"slot {s}"
 
 
+@pytest.mark.parametrize("T,k,P,H,I", [(1200, 2, 270, 2048, 128), (1200, 2, 135, 2048, 256), (1200, 2, 90, 2048, 384), (1200, 2, 67, 2048, 512),
+                                       (1500, 2, 6, 2048, 256), (1500, 2, 6, 256, 1408)],
+                         ids=["2-slabs", "4-slabs", "6-slabs", "8-slabs", "4-slabs-crowded", "4-slabs-first-crowded"])
+def test_many_rows_kernel_waits_for_rows_of_short_contractions(ew, T, k, P, H, I):
+    """k_ffn_big where one product's units are much shorter than the other's, one test for each way its scheduling steps share the slabs
+    of a short unit: slightly more units of the long first product than workgroups, so that those with one unit less run through many
+    units of the second one while others still store (and crowded slots with fewer units than workgroups).  The activations are NaN
+    before each call: a row read before it is stored shows.  One launch gives the bits of two, and some slots agree with the oracle."""
+    rng = np.random.default_rng(H * 3 + I + P)
+    flat = np.concatenate([np.arange(P), rng.integers(0, P, T * k - P)]).astype(np.int32)[rng.permutation(T * k)]  # (a repeat inside a token is fine)
+    por = np.argsort(flat, kind="stable").astype(np.int32)
+    counts = np.bincount(flat, minlength=P).astype(np.int32)
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    dev = lambda a: torch.from_numpy(a).cuda()
+    g = torch.Generator(device="cuda").manual_seed(H + I)
+    bf = lambda *shape, scale=1.0: torch.randn(shape, generator=g, device="cuda", dtype=torch.bfloat16) * scale
+    x, w13, w2 = bf(T, H), bf(P, 2 * I, H, scale=0.02), bf(P, H, I, scale=0.02)
+    args = (x, k, I, P, dev(counts), dev(offsets), dev(por), w13, w2)
+    ws = ew.binding._workspace(ew.lib().moe_grouped_ffn_workspace_bytes(T, k, H, I, P, ew.EW_BF16), "cuda")
+
+    def run(two_launches):
+        ws.fill_(0xFF)
+        ew.binding.tune_ffn(path=3, ws_frags=8, ws_two_launches=two_launches)
+        try:
+            return ew.moe_grouped_ffn(*args, ws=ws)
+        finally:
+            ew.binding.tune_ffn()
+
+    ref = run(True)
+    for _ in range(4):
+        assert torch.equal(run(False), ref)
+    got, xs = to_f64(ref), to_f64(x)
+    for s in (0, int(np.argmax(counts)), P - 1):
+        r0, r1 = offsets[s], offsets[s + 1]
+        want = moe.expert_ffn(xs[por[r0:r1] // k], to_f64(w13[s]), to_f64(w2[s]))
+        assert rel_l2(got[r0:r1], want) <= FFN_REL_L2 and max_abs(got[r0:r1], want) <= FFN_MAX_ABS, f"slot {s}"
+
+
 @pytest.mark.parametrize("T", [16, 256], ids=["few-rows", "many-rows"])
 def test_a_wait_given_up_writes_nan(ew, T):
     """One slot with fewer first-product units than workgroups: those left over start with units of the second product, whose
