@@ -65,7 +65,7 @@ size_t ffn_plan_ints(int T, int rows, int P);
 // Plan shape of a call with `rows` rows in all and `slots` slots (shared experts included).  frags, chunk_frags: the tuning
 // hook's kernel shape and cap on 32-row fragments per chunk, 0 = automatic; merge: the two products share a launch;
 // wait_polls: the tuning hook's limit on a unit's wait, 0 = automatic.
-FfnPlanShape ffn_plan_shape(int T, int rows, int slots, int H, int frags, int chunk_frags, bool merge, int wait_polls);
+FfnPlanShape ffn_plan_shape(int T, int rows, int slots, int H, int I, int frags, int chunk_frags, bool merge, int wait_polls);
 // A layer pass of few tokens routes inside the grouped FFN's launch (ffn_route.h).  What that needs, and hands out: the arguments of
 // moe_route_reroute_permute.
 constexpr int kRouteTokens = 64, kRoutePairs = 512;

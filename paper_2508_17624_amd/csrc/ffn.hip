@@ -243,7 +243,7 @@ bool ffn_shape_of_call(int dtype, int T, int k, int H, int I, int P, int S, FfnP
   if (rows >= (1ll << 31) || slots > 2048 || (unsigned long long)rows * (unsigned long long)Kmax * 2ull >= (1ull << 32)) return false;
   // lane offsets of 32 bits into a slot's gate and up rows
   if ((unsigned long long)H * (unsigned long long)I * 4ull >= (1ull << 32)) return false;
-  *sh = ffn_plan_shape(T, (int)rows, slots, H, g_ws_frags, g_ws_chunk_frags, g_ws_merge != 1, g_ws_wait);
+  *sh = ffn_plan_shape(T, (int)rows, slots, H, I, g_ws_frags, g_ws_chunk_frags, g_ws_merge != 1, g_ws_wait);
   return true;
 }
 

@@ -67,6 +67,7 @@ __device__ __forceinline__ void chunking(int c, int bt, int& nch, int& bts) {
 struct FfnPlanShape {
   int dec;           // > 0: k_ffn_dec is a candidate, with chunks of 16 * dec rows
   int dec_cap;       // its chunks at most
+  int dec_round;     // its chunks whose units of both products fit one round of workgroups (chunks of more than kDecCut rows only)
   int big;           // k_ffn_big is a candidate
   int bt;            // its rows per chunk at most
   int ch;            // its chunks per entry at most
@@ -215,12 +216,16 @@ __device__ __forceinline__ void dec_zero_counters(int32_t* __restrict__ plan, in
 // larger ones are cut at 128 all the same, and so are the shared experts' (shared_bt).  Passes, us, at most 128 / 160: 1999 tokens, 128
 // experts of 1536 x 640, k = 8 (32 of 194 slots in between) 305.7 / 281.1; 1500 tokens, 64 experts of 2048 x 1408 615 / 534.  Cutting
 // the larger ones at 160 too: 160 tokens and two shared experts of 1280 x 512 92.0 / 95.4, 768 tokens 112.6 / 114.3.
+// Calls whose units, cut at 128, all have a workgroup of their own (dec_round) keep that cut: their time is that of one unit of each
+// product, which a chunk of half the rows shortens, and workgroups would stay idle.  Calls with plan, us, at most 128 / 160, slots of 144 rows (units cut
+// at 128): 2048 x 1408 1 slot (38) 55.8 / 65.3, 4 (152) 60.8 to 65.8 / 68.5, 6 (228) 68.6 / 77.2, 7 (266) 82.5 / 72.5; 1024 x 896 4 (88) 40.3 / 45.3, 10 (220)
+// 44.9 / 48.1, 13 (286) 58.6 / 51.3; 1280 x 512 8 (144) 41.9 / 45.7, 15 (270) 52.3 / 50.0; 1536 x 768 10 (240) 52.5 / 54.8, 11 (264) 62.6 / 55.0.
 constexpr int kDecCut = 128;
 __host__ __device__ inline int shared_bt(int bt) { return bt < kDecCut ? bt : kDecCut; }
 __host__ __device__ inline int dec_chunks(int c, int bt) { return c <= bt ? (c > 0 ? 1 : 0) : (c + shared_bt(bt) - 1) / shared_bt(bt); }
 
 struct DecPlanLds {
-  int32_t wtot[8];
+  uint32_t wtot[8];
 };
 
 // Builds the plan of k_ffn_dec; rows / first as for big_plan_build, without the shared experts' slots: S of them follow the
@@ -228,24 +233,39 @@ struct DecPlanLds {
 __device__ __forceinline__ void dec_plan_build(const int (&rows)[4], const int (&first)[4], int P, int S, int sh_rows, int sh_first,
                                                const FfnPlanShape& sh, int32_t* __restrict__ plan, DecPlanLds& L) {
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int bt = 16 * sh.dec;
+  int bt = 16 * sh.dec, round = sh.dec_round;
+  asm volatile("" : "+s"(round));  // (loaded here, with the others, and not as a round trip of its own where it is needed)
   const int sh_chunks = dec_chunks(sh_rows, shared_bt(bt));
-  int mine = 0;
+  // Sums are chunks and, where chunks may be longer than kDecCut, above bit 16 the slots that kDecCut would cut (there are fewer than
+  // 2^16 chunks then: at most kPickRows rows per slot, and kPlanMaxP slots).
+  const bool longer = bt > kDecCut;
+  uint32_t mine = 0, before = 0, total = 0;
   if (tid < 512) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) mine += dec_chunks(rows[i], bt);
-    const int inc = (int)wave_incl_scan_u32((uint32_t)mine);
+    for (int i = 0; i < 4; ++i) mine += (uint32_t)dec_chunks(rows[i], bt) + (longer && rows[i] > kDecCut && rows[i] <= bt ? 1u << 16 : 0u);
+    const uint32_t inc = wave_incl_scan_u32(mine);
     if (lane == 63) L.wtot[wave] = inc;
     mine = inc - mine;
   }
   __syncthreads();
-  int before = S * sh_chunks, total = before;
 #pragma unroll
   for (int w = 0; w < 8; ++w) {
-    const int t = L.wtot[w];
+    const uint32_t t = L.wtot[w];
     if (w < wave) before += t;
     total += t;
   }
+  before += mine;
+  if (longer) {
+    const uint32_t more = total >> 16;
+    total &= 0xFFFFu;
+    const bool cut = S * sh_chunks + (int)(total + more) <= round;
+    before = (before & 0xFFFFu) + (cut ? before >> 16 : 0u);
+    if (cut) {
+      total += more;
+      bt = kDecCut;
+    }
+  }
+  const int chunks = S * sh_chunks + (int)total;
   auto put = [&](int at, int slot, int c, int first_row, int n) {
     const int bts = ((c + n - 1) / n + 15) & ~15;
     for (int j = 0; j < n; ++j) {
@@ -256,7 +276,7 @@ __device__ __forceinline__ void dec_plan_build(const int (&rows)[4], const int (
     }
   };
   if (tid < 512) {
-    int at = before + mine;
+    int at = S * sh_chunks + (int)before;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
       if (rows[i] > 0) {
@@ -267,8 +287,8 @@ __device__ __forceinline__ void dec_plan_build(const int (&rows)[4], const int (
     if (tid >= 512 - 64)  // the last wave: it has no routed slot below 1792 of them
       for (int s = tid - (512 - 64); s < S; s += 64) put(s * sh_chunks, P + s, sh_rows, sh_first + s * sh_rows, sh_chunks);
   }
-  dec_zero_counters(plan, sh.done_off, total, tid, (int)blockDim.x);
-  if (tid == 0) plan[0] = total;
+  dec_zero_counters(plan, sh.done_off, chunks, tid, (int)blockDim.x);
+  if (tid == 0) plan[0] = chunks;
 }
 
 union FfnPlanLds {

@@ -43,6 +43,8 @@ int list_cap(int rows, int P) {
   return ceil_div((int)(worst < kPlanMaxEnt ? worst : kPlanMaxEnt), 8) + 1;
 }
 
+constexpr int kCus = 256;  // of an MI355X, a workgroup of k_ffn_dec on each
+
 // A look takes well over half a microsecond: seconds, where a wait lasts as long as two units at most.
 constexpr int kWaitPolls = 1 << 22;
 
@@ -68,7 +70,7 @@ size_t ffn_plan_ints(int T, int rows, int P) {
 // 74 / 98; 256 x 8: 101 / 100; 256 x 16: 133 / 114; 384 x 4: 75 / 89; 384 x 8: 112 / 90.  So k_ffn_big wins in a corner only, eight
 // or more slots of 256 rows and more while the pool's other slots keep the average low; to let the counts find it would cost
 // every call up to 512 tokens a second launch (5 us).  (k_ffn_dec with chunks of 128 rows; with 160 it is the faster one a little further up.)
-FfnPlanShape ffn_plan_shape(int T, int rows, int slots, int H, int frags, int chunk_frags, bool merge, int wait_polls) {
+FfnPlanShape ffn_plan_shape(int T, int rows, int slots, int H, int I, int frags, int chunk_frags, bool merge, int wait_polls) {
   FfnPlanShape sh{};
   sh.merged = merge;
   sh.wait_polls = wait_polls > 0 ? wait_polls : kWaitPolls;
@@ -89,6 +91,7 @@ FfnPlanShape ffn_plan_shape(int T, int rows, int slots, int H, int frags, int ch
       sh.dec = T <= 16 ? 1 : T <= 32 ? 2 : T <= 64 ? 4 : T <= 128 || H % 256 ? 8 : 10;
     }
     sh.dec_cap = dec_chunk_cap(rows, slots, 16 * sh.dec);
+    if (16 * sh.dec > kDecCut) sh.dec_round = kCus / (I / 128 + H / 256);
   }
   const int big_end = kPlanHdr + 8 * kEnt * sh.cap, dec_end = kDecEnt + 4 * sh.dec_cap;  // (of a kernel that is no candidate: headers alone)
   sh.done_off = big_end > dec_end ? big_end : dec_end;

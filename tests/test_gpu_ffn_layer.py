@@ -804,6 +804,50 @@ def test_grouped_ffn_decode_kernel_edges(ew, T, k, P, S, H, I):
         assert rel_l2(blk, ref) <= FFN_REL_L2 and max_abs(blk, ref) <= FFN_MAX_ABS, f"shared expert {s}"
 
 
+@pytest.mark.parametrize("T,k,S,n", [(432, 3, 0, 9), (480, 3, 0, 10), (396, 4, 0, 11), (384, 3, 1, 8), (432, 3, 1, 9)],
+                         ids=["one-round", "a-full-round", "more-than-one", "shared-one-round", "shared-more-than-one"])
+def test_grouped_ffn_cuts_slots_of_129_to_160_rows_where_one_round_takes_them(ew, T, k, S, n):
+    """Slots of 129 to 160 rows, among them slots at the edges, a thin one and idle ones.  Cut at 128 rows where the units of all chunks
+    then fit one round of the 256 workgroups (11 and 2 units per chunk here, so 19 chunks), one chunk each where they do not: the plan says which
+    (its first word is the number of chunks).  Both give the bits of the kernel whose chunks end at 128, and two slots agree with the oracle."""
+    P, H, I = 64, 512, 1408
+    rng = np.random.default_rng(T + n)
+    rows = np.full(n, 144)
+    rows[[0, 1, 2, 3]] = 129, 160, 161, 126                               # 576 rows, as four of 144
+    counts = np.zeros(P, np.int32)
+    counts[rng.permutation(P - 1)[:n]] = rows
+    assert counts.sum() == T * k
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    por = rng.permutation(T * k).astype(np.int32)
+    dev = lambda a: torch.from_numpy(a).cuda()
+    g = torch.Generator(device="cuda").manual_seed(T)
+    bf = lambda *shape, scale=1.0: torch.randn(shape, generator=g, device="cuda", dtype=torch.bfloat16) * scale
+    x, w13, w2 = bf(T, H), bf(P, 2 * I, H, scale=0.02), bf(P, H, I, scale=0.02)
+    s13, s2 = (bf(S, 2 * I, H, scale=0.02), bf(S, H, I, scale=0.02)) if S else (None, None)
+    args = (x, k, I, P, dev(counts), dev(offsets), dev(por), w13, w2)
+    ws = ew.binding._workspace(ew.lib().moe_grouped_ffn_workspace_bytes(T, k + S, H, I, P + S, ew.EW_BF16), "cuda")
+
+    def run(**tune):
+        ew.binding.tune_ffn(**tune)
+        try:
+            y = ew.moe_grouped_ffn_with_shared(*args, s13, s2, ws=ws) if S else ew.moe_grouped_ffn(*args, ws=ws)
+        finally:
+            ew.binding.tune_ffn()
+        return y, int(ws[:4].view(torch.int32))
+
+    y, chunks = run()
+    ref, cut = run(path=3, ws_frags=4)
+    shared = S * -(-T // 128)
+    assert cut == shared + int(sum(-(-c // 128) for c in rows))
+    assert chunks == (cut if cut <= 256 // (I // 128 + H // 256) else cut - int(((rows > 128) & (rows <= 160)).sum()))
+    assert torch.equal(y, ref)
+    got, xs = to_f64(y), to_f64(x)
+    for s in (int(np.nonzero(counts == 160)[0][0]), int(np.nonzero(counts == 161)[0][0])):
+        r0, r1 = offsets[s], offsets[s + 1]
+        want = moe.expert_ffn(xs[por[r0:r1] // k], to_f64(w13[s]), to_f64(w2[s]))
+        assert rel_l2(got[r0:r1], want) <= FFN_REL_L2 and max_abs(got[r0:r1], want) <= FFN_MAX_ABS, f"slot {s}"
+
+
 @pytest.mark.parametrize("frags", [4, 8], ids=["few-rows", "many-rows"])
 def test_grouped_ffn_rows_do_not_depend_on_their_place(ew, frags):
     """A token's rows have the same bits wherever it stands in the batch: slots of one to three chunks, crowded and thin ones, and a
