@@ -931,8 +931,8 @@ def test_grouped_ffn_counts_choose_the_kernel(ew, T, k, P, S, H, I, used):
     (16, 256, 16, 1, 8, 3, 128, 128, False, False),     # sixteen experts per lane, as many choices as lanes
     (17, 16, 5, 3, 4, 2, 128, 256, True, False),        # chunks of 32 rows
     (32, 24, 16, 2, 16, 16, 128, 128, False, False),    # most pairs, most shared chunks
-    (33, 64, 6, 4, 16, 2, 256, 128, False, False),      # chunks of 64 rows, selecting waves of the second round
-    (61, 128, 8, 124, 15, 1, 128, 128, True, False),    # more tokens than one round of the selection takes, 1988 slots
+    (33, 64, 6, 4, 16, 2, 256, 128, False, False),      # chunks of 64 rows, the ninth of the selecting waves with one token
+    (61, 128, 8, 124, 15, 1, 128, 128, True, False),    # the last selecting wave ragged, 1988 slots
     (64, 64, 8, 0, 1, 0, 128, 128, False, False),       # most tokens, most pairs, no adapters
     (64, 64, 1, 5, 16, 2, 128, 128, False, False),
     (20, 8, 6, 2, 4, 2, 256, 128, False, True),         # a map that sends two experts to one slot: slots with more rows than tokens
@@ -963,17 +963,64 @@ def test_layer_that_routes_itself_equals_the_separate_launches(ew, T, E, k, N, e
     pool = SimpleNamespace(M=E, N=N, P=P, view=lambda l: (w13.data_ptr(), w2.data_ptr(), emap_t.data_ptr(), P))
     shared = (bf(S, 2 * I, H, scale=0.05), bf(S, H, I, scale=0.05)) if S else (None, None)
     Wg = torch.randn((E, H), generator=g, device="cuda") * 0.1
-    make = lambda: MoELayer(pool, 0, Wg, shared[0], shared[1], k, I, T, torch.bfloat16, renormalize=renorm)
+    # (the adapters' gate bias, in every second case: such a pass has its scores from the same launch)
+    bias = torch.randn((N + 1, E), generator=g, device="cuda") if T % 2 == 0 else None
+    make = lambda: MoELayer(pool, 0, Wg, shared[0], shared[1], k, I, T, torch.bfloat16, bias=bias, renormalize=renorm)
     fused, apart = make(), make()
     names = ("ids", "w", "slot", "counts", "offsets", "por", "rop", "y", "y_shared")
+    first_word = lambda layer: int(layer.ws_ffn[:4].view(torch.int32))          # of the plan: its size, which no pass that routes itself writes
     for b in (fused.buf, apart.buf):
         b.ws_ffn.fill_(0x5A)                                                    # whatever a workspace holds before its first call
     for turn in range(3):
         x, aid = bf(T, H), torch.from_numpy(rng.integers(0, N + 1, T).astype(np.int32)).cuda()
-        got = fused.forward(x, aid).clone()
-        want = apart.forward(x, aid, fused.logits[:T].clone()).clone()
-        torch.testing.assert_close(fused.logits, ew.moe_gate_logits(x, Wg), rtol=0, atol=0)
+        last = dict(residual=bf(T, H), eps=1e-6) if turn else {}                # (a residual and the next layer's norm, as in a stack)
+        norms = [torch.empty_like(x) if turn else None for _ in range(2)]
+        got = fused.forward(x, aid, normed_out=norms[0], **last).clone()
+        want = apart.forward(x, aid, fused.logits[:T].clone(), normed_out=norms[1], **last).clone()
+        assert first_word(fused) == 0x5A5A5A5A and 0 < first_word(apart) <= T * k + S * T, "which of the two ways the passes took"
+        torch.testing.assert_close(fused.logits, ew.moe_gate_logits(x, Wg, None if bias is None else aid, bias), rtol=0, atol=0)
+        assert not turn or (torch.equal(*norms) and torch.isfinite(norms[0].float()).all()), f"pass {turn}: norm"
         for name in names:
             assert torch.equal(getattr(fused, name), getattr(apart, name)), f"pass {turn}: {name}"
         assert torch.equal(got, want) and torch.isfinite(got.float()).all(), f"pass {turn}"
 
+
+
+def test_what_keeps_a_pass_from_routing_itself_is_reported(ew):
+    """Arguments that a pass of few tokens cannot route itself with take the separate calls, which refuse them with their own
+    message: the same one as for a pass whose logits are given.  Nothing is left behind that the next pass would see."""
+    import ctypes
+    from types import SimpleNamespace
+    from paper_2508_17624_amd.layer import MoELayer
+    B = ew.binding
+    T, E, k, N, P, S, H, I = 20, 16, 2, 1, 24, 1, 128, 128
+    g = torch.Generator(device="cuda").manual_seed(5)
+    bf = lambda *shape, scale=1.0: (torch.randn(shape, generator=g, device="cuda") * scale).bfloat16()
+    w13, w2, emap = bf(P, 2 * I, H, scale=0.05), bf(P, H, I, scale=0.05), torch.arange(E, dtype=torch.int32, device="cuda").repeat(N + 1, 1)
+    pool = SimpleNamespace(M=E, N=N, P=P, view=lambda l: (w13.data_ptr(), w2.data_ptr(), emap.data_ptr(), P))
+    layer = MoELayer(pool, 0, torch.randn((E, H), generator=g, device="cuda"), bf(S, 2 * I, H, scale=0.05), bf(S, H, I, scale=0.05), k, I, T, torch.bfloat16)
+    x, aid = bf(T, H), torch.zeros(T, dtype=torch.int32, device="cuda")
+    want = layer.forward(x, aid).clone()
+    given = layer.logits.clone()
+
+    def call(scores, adapter=aid, **broken):
+        layer._current()
+        d = B.LayerDesc.from_buffer_copy(layer._desc)
+        for name, v in broken.items():
+            setattr(d, name, v)
+        rc = B.lib().moe_layer_forward(ctypes.byref(d), x.data_ptr(), None if adapter is None else adapter.data_ptr(), T,
+                                       None if scores is None else scores.data_ptr(), None, layer.out.data_ptr(), None, 0.0, B._stream())
+        return rc, B.lib().ew_last_error().decode() if rc else ""
+
+    layer._current()
+    d = layer._desc
+    cases = [{n: None} for n in ("expert_map", "w13", "w2", "w13_shared", "w2_shared", "ids", "w", "slot", "counts", "offsets", "pair_of_row",
+                                 "row_of_pair", "y", "ws_perm", "ws_ffn")]
+    cases += [dict(ws_ffn=d.ws_ffn + 128), dict(ws_ffn_bytes=d.ws_ffn_bytes - 256), dict(ws_perm=d.ws_perm + 128), dict(ws_perm_bytes=1),
+              dict(k=E + 1), dict(N=-1), dict(P=4096), dict(I=192), dict(adapter=None)]
+    for broken in cases:
+        rc, why = call(None, **broken)
+        assert rc < 0 and (rc, why) == call(given, **broken), f"{broken}: {rc} {why}"
+        assert call(None) == (0, "") and torch.equal(layer.out[:T], want), f"the pass after {broken}"
+    for name in ("Wg", "logits"):
+        assert call(None, **{name: None})[0] == -1 and call(given, **{name: None}) == (0, ""), name
