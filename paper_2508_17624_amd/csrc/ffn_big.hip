@@ -1,10 +1,11 @@
 // Grouped SwiGLU expert FFN for calls with many rows per slot on gfx950: 256 weight rows x up to 256 token rows per unit.
 //
-// What bounds it: the operand loads into LDS, at the clock that the power limit leaves.  8192 tokens, this kernel alone, base-only / 20
-// adapters: complete 989 / 1218 us, 1.70 / 2.24 M cycles at 1.72 / 1.84 GHz (MFMA busy 64 / 51 %, TD 78 / 88 %); with nothing
-// multiplied 801 / 1111 us, 1.91 / 2.60 M cycles at 2.38 / 2.34 GHz (TD 92 / 94 %).  So the loads alone are 0.81 / 0.91 of the time: the
-// multiplications hide under them and cost the rest through the clock.  One token slab and up to three weight halves are in flight while a
-// slab is multiplied.
+// What bounds it is not known: loads and MFMAs together, more than either.  8192 tokens, this kernel alone, base-only / 20 adapters: complete
+// 989 / 1218 us, 1.70 / 2.24 M cycles at 1.72 / 1.84 GHz (MFMA busy 64 / 51 %, TD 78 / 88 %); with nothing multiplied 801 / 1111 us, 1.91 / 2.60 M
+// cycles at 2.38 / 2.34 GHz (TD 92 / 94 %).  So the loads alone take 0.81 / 0.91 of the time, and the power limit lowers the clock once there are
+// MFMAs beside them.  But a walk that makes the loads alone 11 / 7 % shorter makes the pass 0.6 to 1.3 % shorter (sched_rows), so they do not hold it by
+// themselves; what the MFMAs' idle cycles wait for is not measured.  One token slab and up to three weight halves are in flight while a slab is
+// multiplied.
 #include "ffn_roles.h"
 
 namespace ew {

@@ -509,8 +509,8 @@ __device__ __forceinline__ void dec_body(const FfnArgs& a, const Routed<DecCfg<N
           if (lane == 0) __hip_atomic_fetch_add(a.done + pending * kDecDoneStride, pending_by, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           pending = -1;
         }
-        // the unit after the next: one round trip at a time, each used steps after it was started (a wait here is a wait for everyone at
-        // the barrier)
+        // the unit after the next: one round trip at a time, each used slabs after it was started where the unit has enough of them, from about
+        // eight on (a wait here is a wait for everyone at the barrier)
         const SchedSteps at = steps_spread(nk);
         if (kt == at.claim) sched_claim(a, sc);
         if (kt == at.entry) sched_entry<C, ROUTED>(a, sd, own, n_chunks, whole, sc);
@@ -583,8 +583,8 @@ __global__ __launch_bounds__((DecCfg<NTF, MR>::THREADS + 64)) void k_ffn_dec_rou
   if (wave == kSched && (threadIdx.x & 63) == 0)
     rt.claim = claim_next(sched_counter(a, 0, (int)(blockIdx.x & 7)));
   if (wave == kSched) {
-    // The arguments take six cache lines, and each would be a round trip where it is first read, in the chain up to the first loads:
-    // this wave, which mostly has no token to select for, brings them in meanwhile.
+    // Each of the arguments' cache lines (of 64 bytes) would be a round trip where it is first read, in the chain up to the first loads: this
+    // wave, which mostly has no token to select for, brings them in meanwhile.
     const auto* args = (const __attribute__((address_space(4))) uint32_t*)__builtin_amdgcn_kernarg_segment_ptr();
     uint32_t any = 0;
 #pragma unroll

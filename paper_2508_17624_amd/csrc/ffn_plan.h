@@ -79,9 +79,13 @@ struct FfnPlanShape {
 };
 
 // Both candidates: k_ffn_big runs where an active slot has more rows on average than k_ffn_dec takes at once with certainty (beyond that
-// it reads weights of more and more slots twice).  Measured, k_ffn_dec with chunks of 128 rows (us, k_ffn_dec / k_ffn_big, at rows per active slot): 68: 819 / 846; 74: 256 / 273;
-// 124: 271 / 278; 135: 1001 / 942; 148: 493 / 318; 248: 492 / 353.  The kernel that is not chosen costs
-// a launch (5 us); both bodies in one kernel did not fit the registers.
+// it reads weights of more and more slots twice).  The line lies below the place where the two cross for hidden sizes that 256 divides, whose chunks
+// reach 160 rows (call with plan, us, k_ffn_dec / k_ffn_big, at rows per active slot, 96 such slots): 2048 x 1408 112: 322 / 334, 128: 326 / 337, 136: 333 / 339,
+// 144: 347 / 345, 152: 397 / 352; 1536 x 640 128: 129 / 135, 136: 133 / 139, 144: 150 / 142; 1024 x 896 128: 125 / 134, 144: 130 / 140, 152: 145 / 140; 1280 x 512
+// 128: 99 / 101, 144: 104 / 105, 152: 111 / 108; 32 slots of 2048 x 1408 152: 143 / 164, 160: 172 / 168.  For other hidden sizes, with chunks of at
+// most 128 rows, it lies above it with many slots (96 slots: 1152 x 640 100: 115 / 99, 128: 145 / 104; 640 x 896 100: 97 / 86, 128: 121 / 93) and at it with
+// fewer (32: 1152 x 640 128: 63 / 65, 144: 68 / 68; 640 x 896 128: 57 / 64).  The kernel that is not chosen costs a launch (3 to 5 us); both bodies in
+// one kernel did not fit the registers.
 constexpr int kPickRows = 128;
 
 constexpr int kTurnRows = 640;

@@ -65,11 +65,11 @@ size_t ffn_plan_ints(int T, int rows, int P) {
 
 // The host knows totals only: no slot has more rows than the call has tokens, and rows / slots is the least that an active
 // slot has on average.  Above kPickRows rows per slot k_ffn_big runs; at or below it k_ffn_dec does up to 512 tokens, and above
-// 512 the counts decide.  Measured at 192 to 512 tokens (call with plan, us, k_ffn_dec / k_ffn_big; 2048 x 1408 experts, rows per
-// active slot x slots): 48 x 64: 203 / 290; 64 x 32: 117 / 151; 128 x 4: 66 / 94; 128 x 16: 105 / 110; 192 x 8: 92 / 89; 256 x 4:
-// 74 / 98; 256 x 8: 101 / 100; 256 x 16: 133 / 114; 384 x 4: 75 / 89; 384 x 8: 112 / 90.  So k_ffn_big wins in a corner only, eight
-// or more slots of 256 rows and more while the pool's other slots keep the average low; to let the counts find it would cost
-// every call up to 512 tokens a second launch (5 us).  (k_ffn_dec with chunks of 128 rows; with 160 it is the faster one a little further up.)
+// 512 the counts decide.  Measured up to 512 tokens in a pool whose other slots are idle (call with plan, us, k_ffn_dec / k_ffn_big; 2048 x
+// 1408 experts, rows per active slot x slots): 128 x 4: 68 / 70; 200 x 4: 67 / 82; 128 x 8: 80 / 77; 144 x 8: 74 / 78; 160 x 8: 77 / 84; 176 x 8:
+// 91 / 82; 200 x 8: 92 / 86; 128 x 32: 131 / 154; 152 x 32: 143 / 164; 160 x 32: 172 / 168; 176 x 32: 198 / 178.  (1024 x 896: 200 x 8: 47 / 57;
+// 160 x 32: 77 / 76; 200 x 32: 81 / 87.)  So k_ffn_big wins in a corner only, eight or more slots of more than 160 rows while the pool's other slots keep
+// the average low; to let the counts find it would cost every call up to 512 tokens a second launch (3 to 5 us).
 FfnPlanShape ffn_plan_shape(int T, int rows, int slots, int H, int I, int frags, int chunk_frags, bool merge, int wait_polls) {
   FfnPlanShape sh{};
   sh.merged = merge;
